@@ -320,20 +320,24 @@ int bfs_graph_create(bfs_graph** out, int32_t V, int64_t nnz, const int64_t* d_r
         // the rows grouped by XCD slice, in col_tmp's space (free from here on)
         if (e == hipSuccess)
             e = build_slice_rows(s, V, g->s_off, g->s_col, g->col_x, g->xo, g->num_cus * 8);
-        // internal ids run in non-increasing degree class, so the vertices
-        // with a neighbour are exactly the ids below their count
+        // internal ids run in non-increasing degree class (cut at every power
+        // of two), so the vertices of at least each degree are exactly the
+        // ids below their count
         uint32_t* d_cnt = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(g->scratch) + 128);
-        uint32_t h_cnt = 0;
-        if (e == hipSuccess) e = hipMemcpyAsync(d_cnt, &h_cnt, 4, hipMemcpyHostToDevice, s);
-        if (e == hipSuccess)
-            e = launch_count_nonzero_degree(s, g->num_cus * 8, V, g->s_off, d_cnt);
-        if (e == hipSuccess) e = hipMemcpyAsync(&h_cnt, d_cnt, 4, hipMemcpyDeviceToHost, s);
+        uint32_t h_cnt[4] = {0, 0, 0, 0};
+        if (e == hipSuccess) e = hipMemcpyAsync(d_cnt, h_cnt, sizeof(h_cnt), hipMemcpyHostToDevice, s);
+        if (e == hipSuccess) e = launch_count_degrees(s, g->num_cus * 8, V, g->s_off, d_cnt);
+        if (e == hipSuccess) e = hipMemcpyAsync(h_cnt, d_cnt, sizeof(h_cnt), hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) {
             (void)hipSetDevice(prev);
             return cleanup(hip_fail(e, "degree ordering"));
         }
-        g->v_active = (int32_t)h_cnt;
+        g->v_active = (int32_t)h_cnt[0];
+        // a pull level reads the rows as in-edges
+        if (g->symmetric)
+            g->pull = PullRows{(int32_t)h_cnt[3], (int32_t)h_cnt[2], (int32_t)h_cnt[1],
+                               (int32_t)h_cnt[0], nnz};
     }
     (void)hipSetDevice(prev);
     *out = g;

@@ -54,7 +54,7 @@ static hipError_t enqueue_level(bfs_graph* g, hipStream_t s, const BatchGrids& b
                            nullptr, g->q[parity], g->q[parity ^ 1], g->deg, g->rowstart, g->suid,
                            g->bsum, g->cumul,
                            g->tile_k, g->ms_sn, g->ms_front, g->ms_touched, nullptr,
-                           nullptr, g->ms_ctrl, skip ? g->skip : nullptr,
+                           nullptr, g->ms_ctrl, g->pull, skip ? g->skip : nullptr,
                            skip ? g->num_cus * 2 : 0);
 }
 

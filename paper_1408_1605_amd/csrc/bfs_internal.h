@@ -65,7 +65,9 @@ struct alignas(64) Ctrl {
     int32_t pad5;
     int64_t bu_deg;      // their degree sum
     int64_t bu_edges;    // neighbours the step probed
-    int64_t next_deg;    // degree sum of the next frontier, when the bitmap compaction is asked for it
+    int64_t next_deg;    // degree sum of the next frontier, when the compaction is asked for it
+    // batch: lanes this level searches from the unseen side (k_ms_pull)
+    uint64_t pull;
 };
 
 
@@ -91,11 +93,14 @@ hipError_t launch_scan(hipStream_t s, const int32_t* Q, int32_t qlen, const int6
                        const int32_t* skip = nullptr, int32_t V = 0);
 
 // Same scan with the frontier size taken from ctrl->qlen (fixed grid,
-// grid-stride); every kernel returns at once when ctrl->done is set.
+// grid-stride); every kernel returns at once when ctrl->done is set.  With
+// front (the batch's lane masks) an entry all of whose lanes are in ctrl->pull
+// gets no edges; they are added to ctrl->skipped.
 hipError_t launch_scan_dev(hipStream_t s, int grid, const int32_t* Q, const int64_t* off,
                            const int32_t* uid_map, int32_t* deg, int64_t* rowstart, int32_t* uidv,
                            int64_t* bsum, int64_t* cumul, int32_t* tile_k, int64_t tile_cap,
-                           int tile, Ctrl* ctrl, const int32_t* skip = nullptr, int32_t V = 0);
+                           int tile, Ctrl* ctrl, const int32_t* skip = nullptr, int32_t V = 0,
+                           const uint64_t* front = nullptr);
 
 // Expansion of one level (Algorithm 3); level / parent by search id, the
 // level only in list mode (bitmap mode: launch_bitmap_to_queue writes it).
@@ -190,9 +195,10 @@ hipError_t launch_bottom_up(hipStream_t s, int grid, int32_t V, int32_t V_scan, 
                             uint32_t* vis, uint32_t* vis_old, int32_t* level, int32_t* parent,
                             int32_t lvl, Ctrl* ctrl, int summary_grid, int32_t summary_shift,
                             int32_t summary_blocks, uint32_t* summary);
-// Adds the number of vertices with a neighbour to *out.
-hipError_t launch_count_nonzero_degree(hipStream_t s, int grid, int32_t V, const int64_t* off,
-                                       uint32_t* out);
+// Adds the number of vertices of degree >= 1, kPullLow, kPullMid and kPullHub to
+// out[0..3] (the caller zeroes them).
+hipError_t launch_count_degrees(hipStream_t s, int grid, int32_t V, const int64_t* off,
+                                uint32_t* out);
 // Wrapping sums of two hashes of every (u, v) and of every (v, u) into
 // sums[0..1] and sums[2..3] (the caller zeroes them).
 hipError_t launch_symmetry_sums(hipStream_t s, int grid, int32_t V, const int64_t* off,
@@ -218,6 +224,14 @@ hipError_t launch_ms_init(hipStream_t s, int grid, int32_t V, const int32_t* h_r
 hipError_t launch_ms_reorder(hipStream_t s, int grid, int32_t V, int32_t n_roots,
                              const int32_t* rank, const SeenNext* sn, const int8_t* out_int,
                              int8_t* out8);
+// Id ranges of the pull levels (degree order: ids below n_hub have degree >=
+// kPullHub, below n_wave >= kPullMid, below n_mid >= kPullLow, below n_act >= 1).
+// n_act = 0: no pull levels.
+constexpr int kPullHub = 4096, kPullMid = 256, kPullLow = 32;
+struct PullRows {
+    int32_t n_hub, n_wave, n_mid, n_act;
+    int64_t nnz;
+};
 // skip non-null (batch on a degree-ordered graph): after each level the
 // longest id prefix that every live lane has seen is found (ctrl->full_prefix)
 // and the next level's scan drops each row's block below the largest cut
@@ -230,7 +244,7 @@ hipError_t launch_ms_level(hipStream_t s, int scan_grid, int expand_grid, int fi
                            int64_t* bsum, int64_t* cumul,
                            int32_t* tile_k, SeenNext* sn, uint64_t* front,
                            uint32_t* touched, int16_t* const* lane_out,
-                           const int32_t* lane_start, Ctrl* ctrl,
+                           const int32_t* lane_start, Ctrl* ctrl, const PullRows& pull,
                            const int32_t* skip = nullptr, int prefix_grid = 0);
 int ms_expand_blocks_per_cu(int ept);
 

@@ -118,26 +118,33 @@ __global__ __launch_bounds__(kWG) void k_bottom_up(int32_t V, int32_t V_scan, in
     }
 }
 
-// Vertices with at least one neighbour (creation time: under degree order
-// they are exactly the internal ids below the count, so a bottom-up step
-// need not look at the rest, which no search can reach).
-__global__ __launch_bounds__(kWG) void k_count_nonzero_degree(int32_t V,
-                                                              const int64_t* __restrict__ off,
-                                                              uint32_t* __restrict__ out)
+// Vertices of at least each of four degrees (creation time: under degree
+// order they are exactly the internal ids below each count; a bottom-up step
+// need not look at ids without a neighbour, which no search can reach).
+__global__ __launch_bounds__(kWG) void k_count_degrees(int32_t V, const int64_t* __restrict__ off,
+                                                       uint32_t* __restrict__ out)
 {
-    uint32_t n = 0;
+    uint32_t n[4] = {0, 0, 0, 0};
     const int64_t stride = (int64_t)gridDim.x * kWG;
-    for (int64_t v = (int64_t)blockIdx.x * kWG + threadIdx.x; v < V; v += stride)
-        n += off[v + 1] > off[v] ? 1u : 0u;
-    for (int d = 32; d >= 1; d >>= 1) n += __shfl_xor(n, d, 64);
-    if (__lane_id() == 0 && n) atomicAdd(out, n);
+    for (int64_t v = (int64_t)blockIdx.x * kWG + threadIdx.x; v < V; v += stride) {
+        const int64_t d = off[v + 1] - off[v];
+        n[0] += d >= 1 ? 1u : 0u;
+        n[1] += d >= kPullLow ? 1u : 0u;
+        n[2] += d >= kPullMid ? 1u : 0u;
+        n[3] += d >= kPullHub ? 1u : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        for (int d = 32; d >= 1; d >>= 1) n[i] += __shfl_xor(n[i], d, 64);
+        if (__lane_id() == 0 && n[i]) atomicAdd(&out[i], n[i]);
+    }
 }
 
-hipError_t launch_count_nonzero_degree(hipStream_t s, int grid, int32_t V, const int64_t* off,
-                                       uint32_t* out)
+hipError_t launch_count_degrees(hipStream_t s, int grid, int32_t V, const int64_t* off,
+                                uint32_t* out)
 {
     if (grid < 1) grid = 1;
-    hipLaunchKernelGGL(k_count_nonzero_degree, dim3(grid), dim3(kWG), 0, s, V, off, out);
+    hipLaunchKernelGGL(k_count_degrees, dim3(grid), dim3(kWG), 0, s, V, off, out);
     return hipGetLastError();
 }
 

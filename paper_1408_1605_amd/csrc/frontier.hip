@@ -133,7 +133,8 @@ __global__ __launch_bounds__(kWG) void k_scan_reduce(const int32_t* __restrict__
                                                      int32_t* __restrict__ uidv,
                                                      int64_t* __restrict__ bsum,
                                                      Ctrl* __restrict__ ctrl, int dev,
-                                                     const int32_t* __restrict__ skip, int32_t V)
+                                                     const int32_t* __restrict__ skip, int32_t V,
+                                                     const uint64_t* __restrict__ front)
 {
     __shared__ int64_t s_wave[kWG / 64];
     if (dev && ctrl->done) return;
@@ -150,6 +151,8 @@ __global__ __launch_bounds__(kWG) void k_scan_reduce(const int32_t* __restrict__
             if (fp >= (1 << (kSkipLow + i))) lv = i;
         if (lv >= 0) sk = skip + (int64_t)lv * V;
     }
+    // batch: lanes searched from the unseen side at this level (0: none)
+    const uint64_t pull = front ? ctrl->pull : 0ull;
     for (int64_t blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
         const int64_t base = blk * kScanChunk;
         int64_t sum = 0, dropped = 0;
@@ -168,6 +171,10 @@ __global__ __launch_bounds__(kWG) void k_scan_reduce(const int32_t* __restrict__
                     d -= n;
                     dropped += n;
                 }
+                if (pull && !(front[u] & ~pull)) {
+                    dropped += d;
+                    d = 0;
+                }
                 deg[k] = (int32_t)d;
                 rowstart[k] = a;
                 uidv[k] = uid_map ? uid_map[u] : u;
@@ -177,7 +184,7 @@ __global__ __launch_bounds__(kWG) void k_scan_reduce(const int32_t* __restrict__
         int64_t tot;
         wg_exclusive_scan<int64_t>(sum, &tot, s_wave);
         if (threadIdx.x == 0) bsum[blk] = tot;
-        if (sk) {
+        if (sk || pull) {
             int64_t dtot;
             wg_exclusive_scan<int64_t>(dropped, &dtot, s_wave);
             if (threadIdx.x == 0 && dtot) atomicAdd((unsigned long long*)&ctrl->skipped,
@@ -377,7 +384,7 @@ hipError_t launch_scan(hipStream_t s, const int32_t* Q, int32_t qlen, const int6
     const int32_t nblk = (int32_t)(((int64_t)qlen + kScanChunk - 1) / kScanChunk);
     if (nblk > 0) {
         hipLaunchKernelGGL(k_scan_reduce, dim3(nblk), dim3(kWG), 0, s, Q, qlen, off, uid_map, deg,
-                           rowstart, uidv, bsum, ctrl, 0, skip, V);
+                           rowstart, uidv, bsum, ctrl, 0, skip, V, nullptr);
     }
     hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kWG), 0, s, bsum, qlen, tile_cap, tile,
                        bitmap_threshold, allow_bitmap, cumul, tile_k, ctrl, 0);
@@ -391,11 +398,12 @@ hipError_t launch_scan(hipStream_t s, const int32_t* Q, int32_t qlen, const int6
 hipError_t launch_scan_dev(hipStream_t s, int grid, const int32_t* Q, const int64_t* off,
                            const int32_t* uid_map, int32_t* deg, int64_t* rowstart, int32_t* uidv,
                            int64_t* bsum, int64_t* cumul, int32_t* tile_k, int64_t tile_cap,
-                           int tile, Ctrl* ctrl, const int32_t* skip, int32_t V)
+                           int tile, Ctrl* ctrl, const int32_t* skip, int32_t V,
+                           const uint64_t* front)
 {
     if (grid < 1) grid = 1;
     hipLaunchKernelGGL(k_scan_reduce, dim3(grid), dim3(kWG), 0, s, Q, 0, off, uid_map, deg,
-                       rowstart, uidv, bsum, ctrl, 1, skip, V);
+                       rowstart, uidv, bsum, ctrl, 1, skip, V, front);
     hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kWG), 0, s, bsum, 0, tile_cap, tile,
                        (int64_t)1 << 62, 0, cumul, tile_k, ctrl, 1);
     hipLaunchKernelGGL(k_scan_down, dim3(grid), dim3(kWG), 0, s, deg, 0, bsum, tile_cap, tile,

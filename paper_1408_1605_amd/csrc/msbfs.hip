@@ -110,6 +110,8 @@ __global__ __launch_bounds__(kWG) void k_ms_roots(int32_t V, int32_t n_roots,
         ctrl->full_prefix = 0;
         ctrl->fp_cand = 0x7fffffff;
         ctrl->skipped = 0;
+        ctrl->next_deg = 0;
+        ctrl->pull = 0;
         ctrl->sparse_limit = V / 64;
         ctrl->sparse = s_n <= V / 64;
     }
@@ -185,6 +187,7 @@ __global__ __launch_bounds__(kWG) void k_ms_expand(const int64_t* __restrict__ r
     __shared__ TileLds<EPT> L;
     if (ctrl->done) return;
     const bool sparse = ctrl->sparse != 0;
+    const uint64_t push = ~ctrl->pull;
     const int64_t r = ctrl->r;
     const int32_t ntiles = ctrl->ntiles;
     StageRegs<EPT> cur = fetch_stage<EPT>(blockIdx.x, ntiles, cumul, rowstart, uidv, tile_k);
@@ -199,7 +202,7 @@ __global__ __launch_bounds__(kWG) void k_ms_expand(const int64_t* __restrict__ r
         // pair only lets more threads issue the atomic)
         uint64_t f[EPT], have[EPT];
 #pragma unroll
-        for (int j = 0; j < EPT; ++j) f[j] = ok[j] ? front[uu[j]] : 0ull;
+        for (int j = 0; j < EPT; ++j) f[j] = ok[j] ? front[uu[j]] & push : 0ull;
 #pragma unroll
         for (int j = 0; j < EPT; ++j) {
             have[j] = ~0ull;
@@ -242,7 +245,8 @@ __global__ __launch_bounds__(kWG) void k_ms_finalize(int32_t V, const int32_t* _
                                                      int32_t* __restrict__ Qn,
                                                      int16_t* const* __restrict__ lane_out,
                                                      const int32_t* __restrict__ lane_start,
-                                                     Ctrl* __restrict__ ctrl)
+                                                     Ctrl* __restrict__ ctrl,
+                                                     const int64_t* __restrict__ deg_off)
 {
     constexpr int IT = kFinItems;
     __shared__ int16_t* s_out[64];
@@ -250,6 +254,7 @@ __global__ __launch_bounds__(kWG) void k_ms_finalize(int32_t V, const int32_t* _
     __shared__ uint32_t s_wave[kWG / 64];
     __shared__ uint32_t s_base;
     __shared__ uint64_t s_alive[kWG / 64];
+    __shared__ int64_t s_dsum[kWG / 64];
     if (ctrl->done) return;
     const int32_t lvl = ctrl->level;
     const bool sparse = ctrl->sparse != 0;
@@ -267,6 +272,7 @@ __global__ __launch_bounds__(kWG) void k_ms_finalize(int32_t V, const int32_t* _
     // would serialise tens of thousands of atomics per level).
     constexpr int64_t chunk = (int64_t)kWG * IT;
     uint64_t alive = 0;
+    int64_t dsum = 0;  // degrees of this thread's new union frontier entries
     for (int64_t c0 = (int64_t)blockIdx.x * chunk; c0 < V; c0 += (int64_t)gridDim.x * chunk) {
         uint64_t nw[IT];
         uint32_t cnt = 0;
@@ -304,6 +310,7 @@ __global__ __launch_bounds__(kWG) void k_ms_finalize(int32_t V, const int32_t* _
             if (pos < (uint32_t)V) Qn[pos] = (int32_t)v;
             else ctrl->err = 4;
             ++pos;
+            if (deg_off) dsum += deg_off[v + 1] - deg_off[v];
             // each vertex writes only the lanes that reached it now
             const int64_t vo = orig ? orig[v] : v;
             if (OUT16) {
@@ -335,27 +342,175 @@ __global__ __launch_bounds__(kWG) void k_ms_finalize(int32_t V, const int32_t* _
         }
         __syncthreads();  // s_base is rewritten by the next chunk
     }
-    // one alive update per workgroup
+    // one update of the level's lanes and degree sum per workgroup
     alive = wave_or64(alive);
-    if (__lane_id() == 0) s_alive[threadIdx.x >> 6] = alive;
+    if (deg_off)
+        for (int d = 32; d >= 1; d >>= 1) dsum += __shfl_xor(dsum, d, 64);
+    if (__lane_id() == 0) {
+        s_alive[threadIdx.x >> 6] = alive;
+        s_dsum[threadIdx.x >> 6] = dsum;
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
         uint64_t a = 0;
-        for (int w = 0; w < kWG / 64; ++w) a |= s_alive[w];
+        int64_t ds = 0;
+        for (int w = 0; w < kWG / 64; ++w) {
+            a |= s_alive[w];
+            ds += s_dsum[w];
+        }
         if (a) atomicOr((unsigned long long*)&ctrl->alive, (unsigned long long)a);
+        if (ds) atomicAdd((unsigned long long*)&ctrl->next_deg, (unsigned long long)ds);
     }
 }
 
-// Sparse levels: the old frontier's masks are cleared through the queue
-// (after the expansion has read them, before the finalize writes new ones).
-__global__ __launch_bounds__(kWG) void k_ms_clear_front(const int32_t* __restrict__ Q,
-                                                        uint64_t* __restrict__ front,
-                                                        const Ctrl* __restrict__ ctrl)
+// Pull levels (symmetric, degree-ordered graphs).  At the dense levels of a
+// small-world graph the expansion above is bound by its 64-bit atomics and
+// 16-byte probes.  A lane of ctrl->pull is searched the other way round: a
+// vertex that has not seen it ORs the frontier masks of its own row and
+// takes the lanes it wants (the CSR equals its transpose, so the row lists
+// the in-edges), stopping once every wanted lane is found.  The only writes
+// are one mask per vertex that found something, without atomics (hub rows
+// aside), and the rows of vertices that have seen every such lane are not
+// read.  The lanes taken and the level's result are the expansion's.
+//
+// Rows are split by id range, which under degree order is by degree: rows of
+// kPullHub edges or more are cut into kPullUnit-edge pieces, one wave each
+// (their finds meet in sn[].next with an atomic OR); a wave takes one row of
+// kPullMid edges or more, four rows of kPullLow or more, sixteen shorter ones.
+constexpr int kPullUnit = 2048;
+
+template <int CTRL>
+__device__ __forceinline__ uint64_t dpp_or64(uint64_t x)
 {
-    if (ctrl->done || !ctrl->sparse) return;
-    const int32_t qlen = ctrl->qlen;
-    const int64_t stride = (int64_t)gridDim.x * kWG;
-    for (int64_t k = (int64_t)blockIdx.x * kWG + threadIdx.x; k < qlen; k += stride) front[Q[k]] = 0;
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(x >> 32), CTRL, 0xf, 0xf, true);
+    return x | ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo;
+}
+
+// OR over aligned groups of G lanes (whole groups are active).
+template <int G>
+__device__ __forceinline__ uint64_t group_or64(uint64_t x)
+{
+    if (G >= 16) {
+        x = dpp_or64<0x128>(x);  // row_ror:8
+        x = dpp_or64<0x124>(x);  // row_ror:4
+    }
+    x = dpp_or64<0x4e>(x);  // quad_perm [2,3,0,1]
+    x = dpp_or64<0xb1>(x);  // quad_perm [1,0,3,2]
+    if (G == 64) {
+        uint64_t y = 0;
+#pragma unroll
+        for (int r = 0; r < 64; r += 16) {
+            const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)x, r);
+            const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(x >> 32), r);
+            y |= ((uint64_t)hi << 32) | lo;
+        }
+        x = y;
+    }
+    return x;
+}
+
+// The frontier lanes of edges [e, b) that want still lacks, read by a group
+// of G lanes (lane l of it), 4 edges per lane and step, until none is left.
+template <int G>
+__device__ __forceinline__ uint64_t pull_edges(int64_t e, int64_t b, int l, uint64_t want,
+                                               const int32_t* __restrict__ col,
+                                               const uint64_t* __restrict__ front)
+{
+    uint64_t acc = 0;
+    for (; e < b && (want & ~acc); e += 4 * G) {
+        int32_t u[4];
+        uint64_t f[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int64_t i = e + k * G + l;
+            u[k] = i < b ? col[i] : -1;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) f[k] = u[k] >= 0 ? front[u[k]] : 0ull;
+        acc = group_or64<G>(acc | f[0] | f[1] | f[2] | f[3]);
+    }
+    return acc & want;
+}
+
+// One group of G lanes per row of [v0, v1), 64 / G rows per wave.
+template <int G>
+__device__ __forceinline__ void pull_rows(int64_t v0, int64_t v1, uint64_t pull,
+                                          const int64_t* __restrict__ off,
+                                          const int32_t* __restrict__ col,
+                                          const uint64_t* __restrict__ front,
+                                          SeenNext* __restrict__ sn)
+{
+    const int lane = __lane_id();
+    const int64_t v = v0 + lane / G;
+    if (v >= v1) return;  // whole groups
+    const SeenNext p = sn[v];
+    const uint64_t want = pull & ~p.seen;
+    if (!want) return;
+    const uint64_t got = pull_edges<G>(off[v], off[v + 1], lane % G, want, col, front);
+    if (got && lane % G == 0) sn[v].next = p.next | got;
+}
+
+// After a level's expansion: the pull lanes, or at a sparse level (which has
+// none) the old frontier's masks are cleared through the queue (after the
+// expansion has read them, before the finalize writes new ones).
+__global__ __launch_bounds__(kWG) void k_ms_pull(const int32_t* __restrict__ Q, PullRows R,
+                                                 const int64_t* __restrict__ off,
+                                                 const int32_t* __restrict__ col,
+                                                 uint64_t* __restrict__ front,
+                                                 SeenNext* __restrict__ sn,
+                                                 const Ctrl* __restrict__ ctrl)
+{
+    if (ctrl->done) return;
+    if (ctrl->sparse) {
+        const int32_t qlen = ctrl->qlen;
+        const int64_t stride = (int64_t)gridDim.x * kWG;
+        for (int64_t k = (int64_t)blockIdx.x * kWG + threadIdx.x; k < qlen; k += stride)
+            front[Q[k]] = 0;
+        return;
+    }
+    const uint64_t pull = ctrl->pull;
+    if (!pull) return;
+    const int64_t e_hub = off[R.n_hub];
+    const int64_t u0 = (e_hub + kPullUnit - 1) / kPullUnit;      // hub pieces
+    const int64_t u1 = u0 + (R.n_wave - R.n_hub);                // one row each
+    const int64_t u2 = u1 + ((int64_t)R.n_mid - R.n_wave + 3) / 4;
+    const int64_t u3 = u2 + ((int64_t)R.n_act - R.n_mid + 15) / 16;
+    const int64_t nwaves = (int64_t)gridDim.x * (kWG / 64);
+    for (int64_t unit = (int64_t)(threadIdx.x >> 6) * gridDim.x + blockIdx.x; unit < u3;
+         unit += nwaves) {
+        if (unit >= u2) {
+            const int64_t v = R.n_mid + (unit - u2) * 16;
+            pull_rows<4>(v, R.n_act, pull, off, col, front, sn);
+        } else if (unit >= u1) {
+            const int64_t v = R.n_wave + (unit - u1) * 4;
+            pull_rows<16>(v, R.n_mid, pull, off, col, front, sn);
+        } else if (unit >= u0) {
+            const int64_t v = R.n_hub + (unit - u0);
+            pull_rows<64>(v, v + 1, pull, off, col, front, sn);
+        } else {
+            int64_t e = unit * kPullUnit;
+            const int64_t end = e + kPullUnit < e_hub ? e + kPullUnit : e_hub;
+            int32_t lo = 0, hi = R.n_hub - 1;  // the row holding edge e
+            while (lo < hi) {
+                const int32_t mid = (lo + hi + 1) >> 1;
+                if (off[mid] <= e) lo = mid;
+                else hi = mid - 1;
+            }
+            for (int32_t v = lo; e < end; ++v) {
+                const int64_t b = off[v + 1] < end ? off[v + 1] : end;
+                const SeenNext p = sn[v];
+                const uint64_t want = pull & ~(p.seen | p.next);
+                if (want) {
+                    const uint64_t got = pull_edges<64>(e, b, __lane_id(), want, col, front);
+                    if (got && __lane_id() == 0)
+                        (void)__hip_atomic_fetch_or(&sn[v].next, got, __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_AGENT);
+                }
+                e = b;
+            }
+        }
+    }
 }
 
 // After a level's finalize: the first id, from the current prefix on, that
@@ -396,9 +551,31 @@ __global__ __launch_bounds__(kWG) void k_ms_prefix(int32_t V, const SeenNext* __
     }
 }
 
-__global__ void k_ms_advance(Ctrl* __restrict__ ctrl, int32_t V, int prefix)
+// One wave.  nnz > 0: the next level may search lanes from the unseen side.
+// It does when its union frontier points at more than 1/kPullShare of the
+// edges (below that the push costs less than reading the rows: the levels of
+// R-MAT 22 on either side of the line push in 25 and 840 us and pull in 50 and
+// 350 us); the lanes are those that have seen at least kPullHubsSeen of the 64
+// highest-degree vertices.  A lane that has not is still on its way to them:
+// its frontier is cheap to expand, while searched the other way it would keep
+// every vertex reading its whole row.  R-MAT 22, 64 roots, per batch: 1 of 64
+// 3.34-3.42 ms, 8 3.20-3.26, 32 3.46, all 64 4.07, no pull levels 4.85-4.88.
+constexpr int64_t kPullShare = 8;
+constexpr int kPullHubsSeen = 8;
+
+__global__ __launch_bounds__(64) void k_ms_advance(Ctrl* __restrict__ ctrl, int32_t V, int prefix,
+                                                   const SeenNext* __restrict__ sn, int64_t nnz)
 {
     if (ctrl->done) return;
+    uint64_t core = 0;
+    if (nnz > 0 && ctrl->next_deg * kPullShare > nnz) {
+        // thread b: how many of those vertices lane b has seen
+        const uint64_t s = threadIdx.x < V ? sn[threadIdx.x].seen : 0ull;
+        int n = 0;
+        for (int x = 0; x < 64; ++x) n += (int)((__shfl(s, x, 64) >> threadIdx.x) & 1ull);
+        core = __ballot(n >= kPullHubsSeen);
+    }
+    if (threadIdx.x != 0) return;
     if (prefix) {
         // no candidate: every id from the old prefix on is seen by all live lanes
         const int32_t c = ctrl->fp_cand;
@@ -408,6 +585,8 @@ __global__ void k_ms_advance(Ctrl* __restrict__ ctrl, int32_t V, int prefix)
     const uint32_t q = ctrl->qn_count;
     ctrl->sparse = (int32_t)q <= ctrl->sparse_limit;
     ctrl->last_alive = ctrl->alive;  // lanes that found vertices this level
+    ctrl->pull = ctrl->sparse ? 0ull : core & ctrl->alive;
+    ctrl->next_deg = 0;
     ctrl->alive = 0;
     ctrl->reached += q;
     ctrl->qlen = (int32_t)q;
@@ -448,11 +627,13 @@ hipError_t launch_ms_level(hipStream_t s, int scan_grid, int expand_grid, int fi
                            int64_t* rowstart, int32_t* uidv, int64_t* bsum, int64_t* cumul,
                            int32_t* tile_k, SeenNext* sn, uint64_t* front, uint32_t* touched,
                            int16_t* const* lane_out, const int32_t* lane_start, Ctrl* ctrl,
-                           const int32_t* skip, int prefix_grid)
+                           const PullRows& pull, const int32_t* skip, int prefix_grid)
 {
     const bool prefix = skip != nullptr && prefix_grid > 0;
+    const int64_t pull_nnz = pull.n_act > 0 ? pull.nnz : 0;
     hipError_t e = launch_scan_dev(s, scan_grid, Q, off, nullptr, deg, rowstart, uidv, bsum, cumul,
-                                   tile_k, tile_cap, kWG * ept, ctrl, prefix ? skip : nullptr, V);
+                                   tile_k, tile_cap, kWG * ept, ctrl, prefix ? skip : nullptr, V,
+                                   pull_nnz > 0 ? front : nullptr);
     if (e != hipSuccess) return e;
     if (expand_grid < 1) expand_grid = 1;
     switch (ept) {
@@ -463,17 +644,20 @@ hipError_t launch_ms_level(hipStream_t s, int scan_grid, int expand_grid, int fi
     default: return hipErrorInvalidValue;
     }
     if (fin_grid < 1) fin_grid = 1;
-    hipLaunchKernelGGL(k_ms_clear_front, dim3(scan_grid), dim3(kWG), 0, s, Q, front, ctrl);
+    hipLaunchKernelGGL(k_ms_pull, dim3(pull_nnz > 0 ? expand_grid : scan_grid), dim3(kWG), 0, s, Q,
+                       pull, off, col, front, sn, ctrl);
     if (lane_out) {
         hipLaunchKernelGGL(k_ms_finalize<true>, dim3(fin_grid), dim3(kWG), 0, s, V, orig, sn,
-                           front, touched, Qn, lane_out, lane_start, ctrl);
+                           front, touched, Qn, lane_out, lane_start, ctrl,
+                           pull_nnz > 0 ? off : nullptr);
     } else {
         hipLaunchKernelGGL(k_ms_finalize<false>, dim3(fin_grid), dim3(kWG), 0, s, V, orig, sn,
-                           front, touched, Qn, lane_out, lane_start, ctrl);
+                           front, touched, Qn, lane_out, lane_start, ctrl,
+                           pull_nnz > 0 ? off : nullptr);
     }
     if (prefix)
         hipLaunchKernelGGL(k_ms_prefix, dim3(prefix_grid), dim3(kWG), 0, s, V, sn, ctrl);
-    hipLaunchKernelGGL(k_ms_advance, dim3(1), dim3(1), 0, s, ctrl, V, prefix ? 1 : 0);
+    hipLaunchKernelGGL(k_ms_advance, dim3(1), dim3(64), 0, s, ctrl, V, prefix ? 1 : 0, sn, pull_nnz);
     return hipGetLastError();
 }
 
@@ -508,6 +692,8 @@ __global__ __launch_bounds__(kWG) void k_srv_reset(int32_t V, SeenNext* __restri
         ctrl->alive = 0;
         ctrl->last_alive = 0;
         ctrl->out8 = nullptr;
+        ctrl->next_deg = 0;
+        ctrl->pull = 0;
         ctrl->sparse_limit = V / 64;
         ctrl->sparse = 1;
     }

@@ -483,6 +483,7 @@ __device__ __forceinline__ void ms_levels_body(
             ctrl->qlen = qlen;
             ctrl->qn_count = 0;
             ctrl->sparse = qlen <= ctrl->sparse_limit;
+            ctrl->pull = 0;  // chosen for a frontier that is gone
             ctrl->done = done ? 1 : 0;
         }
     }

@@ -106,6 +106,8 @@ struct bfs_graph {
     int do_beta = 24;       // bottom-up -> top-down when frontier * beta < V and shrinking
     int symmetric = 0;      // the CSR equals its transpose (checked at creation)
     int32_t v_active = 0;   // degree order: internal ids below it have a neighbour (else V)
+    bfsmi::PullRows pull{};  // batch levels searched from the unseen side (degree order,
+                             // symmetric CSR; n_act = 0: none)
     int xcd_slices = 1;     // 0 off, 1 auto, 2 whenever the frontier fits (8 * qlen <= V)
     int claim_mode = 1;     // bitmap levels: 0 atomic claims, 1 flag claims up to
                             // kFlagAutoMaxV vertices, 2 flag claims
