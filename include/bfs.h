@@ -200,7 +200,7 @@ int bfs_version(void);
  * the device.
  *   V    : 1 .. 2^31 - 1;  nnz : 0 .. 2^62
  *   flags: BFS_WS_BATCH adds the batch arrays (3 * 8 * V bytes, and 64 * V
- *   more with BFS_DEGREE_ORDER: the batch rows by internal id).
+ *   more with BFS_DEGREE_ORDER: the lanes' levels by internal id).
  * Errors: BFS_ERR_INVALID for out-of-range sizes or a null bytes pointer.
  */
 int bfs_workspace_bytes(int32_t V, int64_t nnz, uint32_t flags, size_t *bytes);

@@ -91,7 +91,7 @@ WsLayout ws_layout(int32_t V, int64_t nnz, uint32_t flags)
         L.skip = take((size_t)kSkipLevels * V * 4);
         L.lvl_int = take((size_t)V * 4);
         L.par_int = take((size_t)V * 4);
-        if (flags & BFS_WS_BATCH) L.ms_out = take((size_t)64 * V);  // batch rows by internal id
+        if (flags & BFS_WS_BATCH) L.ms_planes = take((size_t)64 * V);  // level planes (7 of 8 V bytes)
         L.found = take(W * 32);  // flag claims: one byte per id, padded to whole words
         L.xo = take((size_t)V * kXcdSlices * 4);  // XCD slices: group offsets per row
         // (the slice-grouped rows reuse col_tmp, free once creation is done)
@@ -154,7 +154,7 @@ void bind_workspace(bfs_graph* g, char* ws, const WsLayout& L, uint32_t flags)
         g->skip = reinterpret_cast<int32_t*>(ws + L.skip);
         g->lvl_int = reinterpret_cast<int32_t*>(ws + L.lvl_int);
         g->par_int = reinterpret_cast<int32_t*>(ws + L.par_int);
-        if (flags & BFS_WS_BATCH) g->ms_out = reinterpret_cast<int8_t*>(ws + L.ms_out);
+        if (flags & BFS_WS_BATCH) g->ms_planes = reinterpret_cast<uint64_t*>(ws + L.ms_planes);
         g->found = reinterpret_cast<uint8_t*>(ws + L.found);
         g->xo = reinterpret_cast<uint32_t*>(ws + L.xo);
         g->col_x = reinterpret_cast<int32_t*>(ws + L.col_tmp);

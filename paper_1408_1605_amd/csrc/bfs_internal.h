@@ -214,16 +214,16 @@ struct alignas(16) SeenNext {
 // Lanes are bits of a 64-bit mask per vertex: seen (reached), front (this
 // level's frontier), next (found during this level).  All launches read
 // their sizes from ctrl and return at once when ctrl->done is set.
-// out_int non-null: the levels write int8 rows by internal id into out_int
-// (no fill) and launch_ms_reorder produces the caller's rows out8 at the end;
-// else they write out8 directly (filled with -1 here).
+// out8 null: the levels record level planes, kMsPlanes masks of V vertices,
+// and launch_ms_rows writes the caller's rows from them at the end (max_level:
+// the last level run); else they write out8 directly (filled with -1 here).
+constexpr int kMsPlanes = 7;  // levels up to 127
 hipError_t launch_ms_init(hipStream_t s, int grid, int32_t V, const int32_t* h_roots_dev,
                           int32_t n_roots, const int32_t* rank, SeenNext* sn, uint64_t* front,
-                          uint32_t* touched, int8_t* out8, int8_t* out_int, int32_t* Q,
-                          Ctrl* ctrl);
-hipError_t launch_ms_reorder(hipStream_t s, int grid, int32_t V, int32_t n_roots,
-                             const int32_t* rank, const SeenNext* sn, const int8_t* out_int,
-                             int8_t* out8);
+                          uint32_t* touched, int8_t* out8, int32_t* Q, Ctrl* ctrl);
+hipError_t launch_ms_rows(hipStream_t s, int grid, int32_t V, int32_t n_roots, int32_t max_level,
+                          const int32_t* rank, const SeenNext* sn, const uint64_t* planes,
+                          int8_t* out8);
 // Id ranges of the pull levels (degree order: ids below n_hub have degree >=
 // kPullHub, below n_wave >= kPullMid, below n_mid >= kPullLow, below n_act >= 1).
 // n_act = 0: no pull levels.
@@ -245,7 +245,7 @@ hipError_t launch_ms_level(hipStream_t s, int scan_grid, int expand_grid, int fi
                            int32_t* tile_k, SeenNext* sn, uint64_t* front,
                            uint32_t* touched, int16_t* const* lane_out,
                            const int32_t* lane_start, Ctrl* ctrl, const PullRows& pull,
-                           const int32_t* skip = nullptr, int prefix_grid = 0);
+                           uint64_t* planes = nullptr, const int32_t* skip = nullptr, int prefix_grid = 0);
 int ms_expand_blocks_per_cu(int ept);
 
 // Serving lanes (msbfs.hip).  lane_out: device table of 64 int16 result

@@ -53,15 +53,14 @@ __global__ __launch_bounds__(kWG) void k_ms_clear(int32_t V, int32_t n_roots,
     for (int64_t i = done + tid; i < nbytes; i += stride) out8[i] = -1;
 }
 
-// out8: the rows the level kernels write (ctrl->out8): the caller's rows,
-// or with internal_rows the internal-id rows that k_ms_reorder turns into
-// the caller's at the end.
+// out8: the rows the level kernels write (ctrl->out8); null when they record
+// the levels as planes instead.
 __global__ __launch_bounds__(kWG) void k_ms_roots(int32_t V, int32_t n_roots,
                                                   const int32_t* __restrict__ roots,
                                                   const int32_t* __restrict__ rank,
                                                   SeenNext* __restrict__ sn,
                                                   uint64_t* __restrict__ front,
-                                                  int8_t* __restrict__ out8, int internal_rows,
+                                                  int8_t* __restrict__ out8,
                                                   int32_t* __restrict__ Q,
                                                   Ctrl* __restrict__ ctrl)
 {
@@ -72,7 +71,7 @@ __global__ __launch_bounds__(kWG) void k_ms_roots(int32_t V, int32_t n_roots,
     if (b < n_roots) {
         const int32_t r = roots[b];
         s_x[b] = rank ? rank[r] : r;
-        out8[(int64_t)b * V + (internal_rows ? s_x[b] : r)] = 0;
+        if (out8) out8[(int64_t)b * V + r] = 0;
     }
     __syncthreads();
     if (b < n_roots) {
@@ -119,57 +118,148 @@ __global__ __launch_bounds__(kWG) void k_ms_roots(int32_t V, int32_t n_roots,
 
 hipError_t launch_ms_init(hipStream_t s, int grid, int32_t V, const int32_t* roots_dev,
                           int32_t n_roots, const int32_t* rank, SeenNext* sn, uint64_t* front,
-                          uint32_t* touched, int8_t* out8, int8_t* out_int, int32_t* Q,
-                          Ctrl* ctrl)
+                          uint32_t* touched, int8_t* out8, int32_t* Q, Ctrl* ctrl)
 {
     if (grid < 1) grid = 1;
-    // internal rows need no fill: the reorder reads only the lanes a vertex has seen
-    int8_t* fill = out_int ? nullptr : out8;
     const int vec = ((uintptr_t)out8 % 16) == 0;
-    hipLaunchKernelGGL(k_ms_clear, dim3(grid), dim3(kWG), 0, s, V, fill ? n_roots : 0, sn, front,
-                       touched, fill, vec);
+    hipLaunchKernelGGL(k_ms_clear, dim3(grid), dim3(kWG), 0, s, V, out8 ? n_roots : 0, sn, front,
+                       touched, out8, vec);
     hipLaunchKernelGGL(k_ms_roots, dim3(1), dim3(64), 0, s, V, n_roots, roots_dev, rank, sn, front,
-                       out_int ? out_int : out8, out_int ? 1 : 0, Q, ctrl);
+                       out8, Q, ctrl);
     return hipGetLastError();
 }
 
-// Batch with degree order: out8[b][c] = out_int[b][rank[c]] where lane b has
-// seen c, else -1.  A workgroup takes runs of 4096 caller ids (the
-// relabelling's unit, one contiguous internal range per degree class), so
-// the gathers reuse lines; for a fixed lane the stores of a wave are
-// contiguous.
+// Level planes (degree order).  The levels of a batch are at most 127 and
+// usually below 8, so the level kernels record a level by its binary digits:
+// plane k holds, per vertex, the lanes whose level has bit k set, and a level
+// costs one 8-byte OR per set bit and vertex that got new lanes instead of
+// one byte store per lane.  The finalize of level 2^k writes plane k for
+// every vertex, so the planes need no clearing.
+//
+// At the end the caller's rows are written once from the planes: out8[b][c] =
+// the bits of lane b in the planes of x = rank[c] where lane b has seen x,
+// else -1.  A thread takes four caller ids; after a 4 x 4 byte transpose of
+// their masks, one shift and one mask give a bit of all four ids for a lane,
+// so a lane's four bytes cost a dozen instructions and one 4-byte store (256
+// contiguous bytes per wave and row).  The kernel is bound by those stores:
+// R-MAT 22, 64 roots (268 MB of rows) 117 us; rows stored by
+// internal id level by level and reordered byte by byte took 670 us, and
+// 384 us of finalize against 268.  Ids go to workgroups in runs of
+// 4096 (the relabelling's unit, one contiguous internal range per degree
+// class), so the gathers reuse lines.
 constexpr int kReorderChunk = 4096;
 
-__global__ __launch_bounds__(kWG) void k_ms_reorder(int32_t V, int32_t n_roots,
-                                                    const int32_t* __restrict__ rank,
-                                                    const SeenNext* __restrict__ sn,
-                                                    const int8_t* __restrict__ out_int,
-                                                    int8_t* __restrict__ out8)
+// T[g] byte i = byte g of w[i].
+__device__ __forceinline__ void transpose_bytes(const uint32_t (&w)[4], uint32_t* T)
+{
+    const uint32_t a0 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u);
+    const uint32_t a1 = __builtin_amdgcn_perm(w[1], w[0], 0x07030602u);
+    const uint32_t b0 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u);
+    const uint32_t b1 = __builtin_amdgcn_perm(w[3], w[2], 0x07030602u);
+    T[0] = __builtin_amdgcn_perm(b0, a0, 0x05040100u);
+    T[1] = __builtin_amdgcn_perm(b0, a0, 0x07060302u);
+    T[2] = __builtin_amdgcn_perm(b1, a1, 0x05040100u);
+    T[3] = __builtin_amdgcn_perm(b1, a1, 0x07060302u);
+}
+
+__device__ __forceinline__ void transpose_masks(const uint64_t (&m)[4], uint32_t (&T)[8])
+{
+    const uint32_t lo[4] = {(uint32_t)m[0], (uint32_t)m[1], (uint32_t)m[2], (uint32_t)m[3]};
+    const uint32_t hi[4] = {(uint32_t)(m[0] >> 32), (uint32_t)(m[1] >> 32), (uint32_t)(m[2] >> 32),
+                            (uint32_t)(m[3] >> 32)};
+    transpose_bytes(lo, T);
+    transpose_bytes(hi, T + 4);
+}
+
+// VEC: the thread's ids are four consecutive ones (4-byte stores; V and out8
+// multiples of 4), else they are kWG apart (byte stores).
+template <int NP, bool VEC>
+__global__ __launch_bounds__(kWG) void k_ms_rows(int32_t V, int32_t n_roots,
+                                                 const int32_t* __restrict__ rank,
+                                                 const SeenNext* __restrict__ sn,
+                                                 const uint64_t* __restrict__ planes,
+                                                 int8_t* __restrict__ out8)
 {
     const int64_t nchunks = ((int64_t)V + kReorderChunk - 1) / kReorderChunk;
     for (int64_t ch = blockIdx.x; ch < nchunks; ch += gridDim.x) {
-        for (int j = 0; j < kReorderChunk / kWG; ++j) {
-            const int64_t c = ch * kReorderChunk + j * kWG + threadIdx.x;
-            if (c >= V) continue;
-            const int32_t x = rank[c];
-            const uint64_t seen = sn[x].seen;
-            for (int b = 0; b < n_roots; ++b) {
-                const int8_t lv = ((seen >> b) & 1ull) ? out_int[(int64_t)b * V + x] : (int8_t)-1;
-                out8[(int64_t)b * V + c] = lv;
+        for (int j = 0; j < kReorderChunk / (4 * kWG); ++j) {
+            const int64_t c0 = ch * kReorderChunk + j * 4 * kWG + (VEC ? 4 : 1) * threadIdx.x;
+            constexpr int step = VEC ? 1 : kWG;
+            if (c0 >= V) continue;
+            int32_t x[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int64_t c = c0 + i * step;
+                x[i] = rank[c < V ? c : c0];
+            }
+            uint64_t m[4];
+            uint32_t S[8], P[NP][8];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) m[i] = sn[x[i]].seen;
+            transpose_masks(m, S);
+#pragma unroll
+            for (int k = 0; k < NP; ++k) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) m[i] = planes[(int64_t)k * V + x[i]];
+                transpose_masks(m, P[k]);
+            }
+            int8_t* o = out8 + c0;
+#pragma unroll
+            for (int g = 0; g < 8; ++g) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    if (8 * g + i < n_roots) {  // uniform
+                        const uint32_t not_seen = ~(S[g] >> i) & 0x01010101u;
+                        uint32_t lv = (not_seen << 8) - not_seen;  // 0xff where not seen
+#pragma unroll
+                        for (int k = 0; k < NP; ++k) lv |= ((P[k][g] >> i) & 0x01010101u) << k;
+                        if (VEC) {
+                            *reinterpret_cast<uint32_t*>(o) = lv;
+                        } else {
+#pragma unroll
+                            for (int q = 0; q < 4; ++q)
+                                if (c0 + q * step < V) o[q * step] = (int8_t)(lv >> (8 * q));
+                        }
+                        o += V;
+                    }
+                }
             }
         }
     }
 }
 
-hipError_t launch_ms_reorder(hipStream_t s, int grid, int32_t V, int32_t n_roots,
-                             const int32_t* rank, const SeenNext* sn, const int8_t* out_int,
-                             int8_t* out8)
+hipError_t launch_ms_rows(hipStream_t s, int grid, int32_t V, int32_t n_roots, int32_t max_level,
+                          const int32_t* rank, const SeenNext* sn, const uint64_t* planes,
+                          int8_t* out8)
 {
     const int64_t nchunks = ((int64_t)V + kReorderChunk - 1) / kReorderChunk;
     if (grid > nchunks) grid = (int)nchunks;
     if (grid < 1) grid = 1;
-    hipLaunchKernelGGL(k_ms_reorder, dim3(grid), dim3(kWG), 0, s, V, n_roots, rank, sn, out_int,
-                       out8);
+    // planes written: those of the powers of two up to the last level run
+    int np = 1;
+    while (np < kMsPlanes && (2 << (np - 1)) <= max_level) ++np;
+    const bool vec = V % 4 == 0 && (uintptr_t)out8 % 4 == 0;
+#define BFS_ROWS_CASE(N)                                                                          \
+    case N:                                                                                      \
+        if (vec)                                                                                 \
+            hipLaunchKernelGGL((k_ms_rows<N, true>), dim3(grid), dim3(kWG), 0, s, V, n_roots, rank, \
+                               sn, planes, out8);                                                \
+        else                                                                                     \
+            hipLaunchKernelGGL((k_ms_rows<N, false>), dim3(grid), dim3(kWG), 0, s, V, n_roots,     \
+                               rank, sn, planes, out8);                                          \
+        break;
+    switch (np) {
+        BFS_ROWS_CASE(1)
+        BFS_ROWS_CASE(2)
+        BFS_ROWS_CASE(3)
+        BFS_ROWS_CASE(4)
+        BFS_ROWS_CASE(5)
+        BFS_ROWS_CASE(6)
+        BFS_ROWS_CASE(7)
+    default:
+        return hipErrorInvalidValue;
+    }
+#undef BFS_ROWS_CASE
     return hipGetLastError();
 }
 
@@ -234,7 +324,8 @@ __device__ __forceinline__ uint64_t wave_or64(uint64_t x)
     return x;
 }
 
-// OUT16 = false: batch output, int8 rows ctrl->out8[b][v] = level.
+// OUT16 = false: batch output, the level planes (degree order), or without
+//                them int8 rows ctrl->out8[b][v] = level.
 // OUT16 = true : serving output, lane b writes level - lane_start[b] into
 //                its own int16 buffer lane_out[b] (caller ids).
 template <bool OUT16>
@@ -246,7 +337,8 @@ __global__ __launch_bounds__(kWG) void k_ms_finalize(int32_t V, const int32_t* _
                                                      int16_t* const* __restrict__ lane_out,
                                                      const int32_t* __restrict__ lane_start,
                                                      Ctrl* __restrict__ ctrl,
-                                                     const int64_t* __restrict__ deg_off)
+                                                     const int64_t* __restrict__ deg_off,
+                                                     uint64_t* __restrict__ planes)
 {
     constexpr int IT = kFinItems;
     __shared__ int16_t* s_out[64];
@@ -271,6 +363,10 @@ __global__ __launch_bounds__(kWG) void k_ms_finalize(int32_t V, const int32_t* _
     // queue slots with one atomicAdd (a per-wave add on the one counter
     // would serialise tens of thousands of atomics per level).
     constexpr int64_t chunk = (int64_t)kWG * IT;
+    // level planes: the new lanes go to the planes of the level's set bits;
+    // level 2^k writes plane k whole
+    const bool plane_out = !OUT16 && planes && lvl <= 127;
+    const bool whole = (lvl & (lvl - 1)) == 0;
     uint64_t alive = 0;
     int64_t dsum = 0;  // degrees of this thread's new union frontier entries
     for (int64_t c0 = (int64_t)blockIdx.x * chunk; c0 < V; c0 += (int64_t)gridDim.x * chunk) {
@@ -295,6 +391,12 @@ __global__ __launch_bounds__(kWG) void k_ms_finalize(int32_t V, const int32_t* _
                 }
                 front[v] = nw[j];
             }
+            if (plane_out && v < V && (whole || nw[j])) {
+                for (int32_t bits = lvl; bits; bits &= bits - 1) {
+                    uint64_t* pl = planes + (int64_t)__builtin_ctz(bits) * V + v;
+                    *pl = whole ? nw[j] : (*pl | nw[j]);
+                }
+            }
             cnt += nw[j] ? 1u : 0u;
         }
         uint32_t tot;
@@ -312,8 +414,8 @@ __global__ __launch_bounds__(kWG) void k_ms_finalize(int32_t V, const int32_t* _
             ++pos;
             if (deg_off) dsum += deg_off[v + 1] - deg_off[v];
             // each vertex writes only the lanes that reached it now
-            const int64_t vo = orig ? orig[v] : v;
             if (OUT16) {
+                const int64_t vo = orig ? orig[v] : v;
                 for (uint64_t m = nw[j]; m; m &= m - 1) {
                     const int b = __builtin_ctzll(m);
                     const int32_t d = lvl - s_start[b];
@@ -322,14 +424,11 @@ __global__ __launch_bounds__(kWG) void k_ms_finalize(int32_t V, const int32_t* _
                 }
             } else if (lvl > 127) {
                 ctrl->overflow = 1;
-            } else if (orig) {
-                for (uint64_t m = nw[j]; m; m &= m - 1)
-                    out8[(int64_t)__builtin_ctzll(m) * V + vo] = (int8_t)lvl;
             }
             alive |= nw[j];
         }
-        if (!OUT16 && !orig && lvl <= 127) {
-            // rows by search id: lane b of a wave's vertices is one contiguous
+        if (!OUT16 && !planes && lvl <= 127) {
+            // lane b of a wave's vertices is one contiguous
             // (masked) store, lanes taken in the same order by every thread
 #pragma unroll
             for (int j = 0; j < IT; ++j) {
@@ -627,7 +726,8 @@ hipError_t launch_ms_level(hipStream_t s, int scan_grid, int expand_grid, int fi
                            int64_t* rowstart, int32_t* uidv, int64_t* bsum, int64_t* cumul,
                            int32_t* tile_k, SeenNext* sn, uint64_t* front, uint32_t* touched,
                            int16_t* const* lane_out, const int32_t* lane_start, Ctrl* ctrl,
-                           const PullRows& pull, const int32_t* skip, int prefix_grid)
+                           const PullRows& pull, uint64_t* planes, const int32_t* skip,
+                           int prefix_grid)
 {
     const bool prefix = skip != nullptr && prefix_grid > 0;
     const int64_t pull_nnz = pull.n_act > 0 ? pull.nnz : 0;
@@ -649,11 +749,11 @@ hipError_t launch_ms_level(hipStream_t s, int scan_grid, int expand_grid, int fi
     if (lane_out) {
         hipLaunchKernelGGL(k_ms_finalize<true>, dim3(fin_grid), dim3(kWG), 0, s, V, orig, sn,
                            front, touched, Qn, lane_out, lane_start, ctrl,
-                           pull_nnz > 0 ? off : nullptr);
+                           pull_nnz > 0 ? off : nullptr, planes);
     } else {
         hipLaunchKernelGGL(k_ms_finalize<false>, dim3(fin_grid), dim3(kWG), 0, s, V, orig, sn,
                            front, touched, Qn, lane_out, lane_start, ctrl,
-                           pull_nnz > 0 ? off : nullptr);
+                           pull_nnz > 0 ? off : nullptr, planes);
     }
     if (prefix)
         hipLaunchKernelGGL(k_ms_prefix, dim3(prefix_grid), dim3(kWG), 0, s, V, sn, ctrl);

@@ -24,7 +24,7 @@ int ok();
 struct WsLayout {
     size_t vis, vis_old, q0, q1, deg, rowstart, suid, cumul, bsum, tile_k, ctrl, scratch, sync, sside, summary;
     size_t ms_sn, ms_front, ms_ctrl, ms_roots, ms_touched;
-    size_t rank, orig, off_r, col_r, hist, col_tmp, skip, lvl_int, par_int, ms_out;
+    size_t rank, orig, off_r, col_r, hist, col_tmp, skip, lvl_int, par_int, ms_planes;
     size_t found, xo;
     size_t total;
 };
@@ -73,7 +73,7 @@ struct bfs_graph {
     int32_t* skip = nullptr;  // row prefix skip counts [kSkipLevels][V] (degree order only)
     int32_t* lvl_int = nullptr;  // level by internal id during a search (degree order only)
     int32_t* par_int = nullptr;  // parent (caller id) by internal id (degree order only)
-    int8_t* ms_out = nullptr;    // batch: int8 rows by internal id (degree order + batch)
+    uint64_t* ms_planes = nullptr;  // batch: level planes by internal id (degree order + batch)
     uint8_t* found = nullptr;    // flag claims: one byte per id (degree order only)
     uint32_t* xo = nullptr;      // XCD slices: per row, the offset of each slice's group
     int32_t* col_x = nullptr;    // XCD slices: rows grouped by slice (degree order only)
