@@ -42,11 +42,6 @@ int ok()
 
 static size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-// Entries per set of the persistent loop's frontier row data: a frontier
-// that continues in the loop holds at most kSmallQ vertices, and never more
-// than V.
-static int32_t small_side_cap(int32_t V) { return V < kSmallQ ? V : kSmallQ; }
-
 WsLayout ws_layout(int32_t V, int64_t nnz, uint32_t flags)
 {
     WsLayout L{};
@@ -72,7 +67,8 @@ WsLayout ws_layout(int32_t V, int64_t nnz, uint32_t flags)
     L.ctrl = take(sizeof(Ctrl));
     L.scratch = take(256);
     L.sync = take(sizeof(SmallSync));
-    L.sside = take((size_t)small_side_cap(V) * 32);
+    // not used: kept so that the sizes callers were told stay what they were
+    (void)take((size_t)std::min(V, kSmallQ) * 32);
     L.summary = take(kSummaryMaxWords * 4);
     if (flags & BFS_WS_BATCH) {
         L.ms_sn = take((size_t)V * 16);
@@ -124,17 +120,6 @@ void bind_workspace(bfs_graph* g, char* ws, const WsLayout& L, uint32_t flags)
     g->ctrl = reinterpret_cast<Ctrl*>(ws + L.ctrl);
     g->scratch = reinterpret_cast<int32_t*>(ws + L.scratch);
     g->small_sync = reinterpret_cast<SmallSync*>(ws + L.sync);
-    {
-        const int32_t cap = small_side_cap(g->V);
-        char* b = ws + L.sside;
-        g->small_side.off[0] = reinterpret_cast<int64_t*>(b);
-        g->small_side.off[1] = reinterpret_cast<int64_t*>(b + (size_t)cap * 8);
-        g->small_side.deg[0] = reinterpret_cast<int32_t*>(b + (size_t)cap * 16);
-        g->small_side.deg[1] = reinterpret_cast<int32_t*>(b + (size_t)cap * 20);
-        g->small_side.id[0] = reinterpret_cast<int32_t*>(b + (size_t)cap * 24);
-        g->small_side.id[1] = reinterpret_cast<int32_t*>(b + (size_t)cap * 28);
-        g->small_side.cap = cap;
-    }
     g->summary = reinterpret_cast<uint32_t*>(ws + L.summary);
     {
         // blocks of 2^shift ids, at most kSummaryMaxWords * 32 of them
@@ -244,6 +229,12 @@ int bfs_graph_create(bfs_graph** out, int32_t V, int64_t nnz, const int64_t* d_r
     }
     g->num_cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
     g->small_grid = small_loop_grid(g->num_cus);
+    {
+        // handles take the XCDs in turn, so that concurrent searches on
+        // different graphs spread over them
+        static std::atomic<uint32_t> next_cls{0};
+        g->small_cls = (int)(next_cls.fetch_add(1) % kXcdSlices);
+    }
 
     // pinned host block: [Ctrl][Ctrl for the batch][64 batch roots]
     hipError_t e = hipHostMalloc((void**)&g->h_ctrl, 2 * sizeof(Ctrl) + 64 * sizeof(int32_t),
@@ -539,6 +530,7 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
     // leaves it zero; the workspace's contents before the search are unknown)
     if (dev_ok) BFS_HIP_TRY(hipMemsetAsync(g->small_sync, 0, sizeof(SmallSync), s));
     bool dev_left = false;  // the persistent loop just handed a heavy level back
+    bool old_left = false;  // ... after levels of its own: vis_old is behind vis
     // direction-optimizing mode: the degree sum of the frontier a bottom-up
     // step searches from, and the size of the frontier before it
     const bool dir_opt = g->direction != 0 && g->symmetric;
@@ -585,11 +577,12 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
             continue;
         }
         if (dev_ok && !dev_left && qlen <= g->small_limit) {
-            BFS_HIP_TRY(launch_small_levels(s, g->small_grid, g->V, g->s_off, g->s_col, g->orig,
-                                            g->vis, g->vis_old, g->q[cur], g->q[cur ^ 1], lv_s,
-                                            pa_s, g->small_sync, g->small_side, g->ctrl, qlen,
+            BFS_HIP_TRY(launch_small_levels(s, g->small_grid, g->small_cls, g->V, g->s_off, g->s_col,
+                                            g->orig, g->vis, g->q[cur], g->q[cur ^ 1], lv_s, pa_s,
+                                            g->small_sync, g->summary, g->ctrl, qlen,
                                             lvl, g->small_limit,
-                                            (int64_t)g->small_grid * kSmallDeg, kSmallDeg));
+                                            (int64_t)g->small_grid * kSmallDeg, kSmallDeg,
+                                            g->maxdeg));
             BFS_HIP_TRY(hipMemcpyAsync(g->h_ctrl, g->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
             BFS_HIP_TRY(hipStreamSynchronize(s));
             const Ctrl& c = *g->h_ctrl;
@@ -604,6 +597,7 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
             qlen = c.qlen;
             if (c.done == 1) break;  // the frontier ran empty
             dev_left = true;         // done == 2: the next level is the host's
+            old_left |= c.steps > 0;
             continue;
         }
         dev_left = false;
@@ -634,8 +628,12 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
         if (use_sum) {
             const int gs = std::max(1, std::min(grid_cap, (g->summary_blocks + 31) / 32));
             BFS_HIP_TRY(launch_visited_summary(s, gs, g->V, g->W, g->vis, g->summary_shift,
-                                               g->summary_blocks, g->summary, g->ctrl));
+                                               g->summary_blocks, g->summary, g->ctrl,
+                                               old_left ? g->vis_old : nullptr));
+        } else if (old_left) {
+            BFS_HIP_TRY(launch_sync_old(s, grid_cap, g->W, g->vis, g->vis_old));
         }
+        old_left = false;
         if (sliced)
             BFS_HIP_TRY(launch_slice_scan(s, std::max(1, std::min(grid_cap, (qlen + kWG - 1) / kWG)),
                                           Q, qlen, g->s_off, g->xo, g->orig, g->deg, g->rowstart,
@@ -703,11 +701,11 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
         // levels after a heavy one costs no extra host round trip
         const bool spec = dev_ok && !dir_opt;
         if (spec) {
-            BFS_HIP_TRY(launch_small_levels(s, g->small_grid, g->V, g->s_off, g->s_col, g->orig,
-                                            g->vis, g->vis_old, Qn, g->q[cur], lv_s, pa_s,
-                                            g->small_sync, g->small_side, g->ctrl, -1, lvl + 1,
+            BFS_HIP_TRY(launch_small_levels(s, g->small_grid, g->small_cls, g->V, g->s_off, g->s_col,
+                                            g->orig, g->vis, Qn, g->q[cur], lv_s, pa_s,
+                                            g->small_sync, g->summary, g->ctrl, -1, lvl + 1,
                                             g->small_limit, (int64_t)g->small_grid * kSmallDeg,
-                                            kSmallDeg));
+                                            kSmallDeg, g->maxdeg));
         }
         BFS_HIP_TRY(hipMemcpyAsync(g->h_ctrl, g->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
         BFS_HIP_TRY(hipStreamSynchronize(s));
@@ -748,6 +746,7 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
                 lvl = c.level;
                 qlen = c.qlen;
                 if (c.done == 1) break;  // the frontier ran empty
+                old_left = true;
             }
             continue;
         }

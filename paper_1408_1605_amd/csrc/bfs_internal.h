@@ -122,49 +122,41 @@ hipError_t launch_slice_scan(hipStream_t s, int grid, const int32_t* Q, int32_t 
                              int64_t bitmap_threshold, int allow_bitmap, Ctrl* ctrl);
 
 // Single-root persistent loop for runs of small levels (smallloop.hip).
-// Zeroed by the host before each launch.
-// The grid barrier's counter and the per-level counters sit on separate
-// 128-byte lines, so the barrier's polling does not queue behind the
-// counters' atomics.
 // Zero before a search's first launch; each launch leaves it zero again.
+constexpr int kSmallMaxWGs = 64;  // fits the 7-bit counts below
 struct SmallSync {
-    uint32_t arrive;   // grid barrier: arrivals (only grows within a launch)
+    uint64_t arrive;   // workgroups that have arrived, 7 bits per XCC; bit 63: called off
     uint32_t leave;    // workgroups that have finished (the last one re-zeroes the block)
-    uint32_t pad0[30];
-    uint32_t qn[3];    // next-frontier size, by level mod 3
-    uint32_t pad1[29];
-    int32_t md[3];     // largest degree in the next frontier
-    int32_t pad2[29];
-    int64_t rn[3];     // edges of the next frontier
+    uint32_t pad0[29]; // the word below sits on another line
+    uint32_t spill;    // queue positions reserved by shares that overflowed
+    uint32_t pad1[31];
     int64_t edges;     // edges the launch expanded (to ctrl->r_total at the end)
-    int64_t pad3[12];
-};
-// Row start, degree and caller id of each frontier entry, one set per
-// queue (cap entries each), written by the workgroup that claims the vertex
-// so the next level need not look them up.
-struct SmallSide {
-    int64_t* off[2];
-    int32_t* deg[2];
-    int32_t* id[2];
-    int32_t cap;
+    int64_t pad2[31];
 };
 int small_loop_blocks();
-// qlen < 0: the frontier size is read from ctrl->qn_count (the previous
-// host-driven level's output); the loop then runs no level when it is 0 or
-// above qlimit.
-hipError_t launch_small_levels(hipStream_t s, int grid, int32_t V, const int64_t* off,
+// wgs workgroups (at most kSmallMaxWGs) on the XCD that workgroups cls, cls + 8,
+// .. of a launch run on; slot_words: kSummaryMaxWords words of scratch, any
+// contents.  qlen < 0: the frontier size is read from ctrl->qn_count (the
+// previous host-driven level's output); the loop then runs no level when it
+// is 0 or above qlimit.  The loop does not keep vis_old.  rlimit is at most 8192 * wgs; maxdeg: the graph's
+// largest degree.
+hipError_t launch_small_levels(hipStream_t s, int wgs, int cls, int32_t V, const int64_t* off,
                                const int32_t* col, const int32_t* orig, uint32_t* vis,
-                               uint32_t* vis_old, int32_t* Qa, int32_t* Qb, int32_t* level,
-                               int32_t* parent, SmallSync* sy, SmallSide side, Ctrl* ctrl,
+                               int32_t* Qa, int32_t* Qb, int32_t* level,
+                               int32_t* parent, SmallSync* sy, uint32_t* slot_words, Ctrl* ctrl,
                                int32_t qlen, int32_t lvl, int32_t qlimit, int64_t rlimit,
-                               int32_t dlimit);
+                               int32_t dlimit, int32_t maxdeg);
 
 // Visited summary before a heavy level: ctrl->full_prefix and one bit per
 // block of 2^shift ids (set when the whole block is visited); clears
-// ctrl->skipped for the level's degree scan.
+// ctrl->skipped for the level's degree scan.  vis_old non-null: also brought
+// up to date (vis_old := vis).
 hipError_t launch_visited_summary(hipStream_t s, int grid, int32_t V, int32_t W,
                                   const uint32_t* vis, int32_t shift, int32_t nblocks,
-                                  uint32_t* summary, Ctrl* ctrl);
+                                  uint32_t* summary, Ctrl* ctrl, uint32_t* vis_old = nullptr);
+// vis_old := vis
+hipError_t launch_sync_old(hipStream_t s, int grid, int32_t W, const uint32_t* vis,
+                           uint32_t* vis_old);
 
 // Resident expansion workgroups per CU for this configuration.
 int expand_blocks_per_cu(int ept, int summary_words);

@@ -429,7 +429,8 @@ hipError_t launch_scan_dev(hipStream_t s, int grid, const int32_t* Q, const int6
 __global__ __launch_bounds__(kWG) void k_visited_summary(int32_t V, int32_t W,
                                                          const uint32_t* __restrict__ vis,
                                                          int32_t shift, int32_t nwords,
-                                                         uint32_t* __restrict__ summary)
+                                                         uint32_t* __restrict__ summary,
+                                                         uint32_t* __restrict__ vis_old)
 {
     __shared__ uint32_t s_bits[kWG / 64];
     const int32_t P = 1 << (shift - 8);
@@ -441,6 +442,7 @@ __global__ __launch_bounds__(kWG) void k_visited_summary(int32_t V, int32_t W,
         for (int32_t j = 0; j < P; ++j) {
             const int64_t w = w0 + j;
             const uint32_t x = w < W ? vis[w] : 0u;
+            if (vis_old && w < W) vis_old[w] = x;
             const int64_t lo = w * 32;
             uint32_t valid = 0xffffffffu;  // ids at or beyond V count as visited
             if (lo + 32 > V) valid = lo >= V ? 0u : ((1u << (V - lo)) - 1u);
@@ -506,15 +508,30 @@ __global__ __launch_bounds__(kWG) void k_visited_prefix(int32_t V, int32_t W,
 
 hipError_t launch_visited_summary(hipStream_t s, int grid, int32_t V, int32_t W,
                                   const uint32_t* vis, int32_t shift, int32_t nblocks,
-                                  uint32_t* summary, Ctrl* ctrl)
+                                  uint32_t* summary, Ctrl* ctrl, uint32_t* vis_old)
 {
     const int32_t nwords = (nblocks + 31) / 32;
     if (grid < 1) grid = 1;
     if (grid > nwords) grid = nwords;
     hipLaunchKernelGGL(k_visited_summary, dim3(grid), dim3(kWG), 0, s, V, W, vis, shift, nwords,
-                       summary);
+                       summary, vis_old);
     hipLaunchKernelGGL(k_visited_prefix, dim3(1), dim3(kWG), 0, s, V, W, vis, shift, nwords,
                        summary, ctrl);
+    return hipGetLastError();
+}
+
+__global__ __launch_bounds__(kWG) void k_sync_old(int32_t W, const uint32_t* __restrict__ vis,
+                                                  uint32_t* __restrict__ vis_old)
+{
+    const int64_t stride = (int64_t)gridDim.x * kWG;
+    for (int64_t i = (int64_t)blockIdx.x * kWG + threadIdx.x; i < W; i += stride) vis_old[i] = vis[i];
+}
+
+hipError_t launch_sync_old(hipStream_t s, int grid, int32_t W, const uint32_t* vis,
+                           uint32_t* vis_old)
+{
+    if (grid > (W + kWG - 1) / kWG) grid = (W + kWG - 1) / kWG;
+    hipLaunchKernelGGL(k_sync_old, dim3(grid < 1 ? 1 : grid), dim3(kWG), 0, s, W, vis, vis_old);
     return hipGetLastError();
 }
 

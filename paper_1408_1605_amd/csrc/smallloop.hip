@@ -4,378 +4,702 @@
 // but launching its kernels (degree scan, expansion, bookkeeping) costs a
 // dispatch gap of several microseconds each; a 4096 x 4096 grid has
 // thousands of such levels.  One persistent kernel of a few dozen
-// workgroups (at most one per CU, so all are resident together) runs them
-// back to back instead:
-//   - each workgroup takes an equal slice of the frontier, stages the
-//     slice's degrees, row starts and caller ids in LDS with a prefix sum,
-//     and maps the slice's edges to threads by binary search in it
-//     (Section 3.4, within the slice, so no grid-wide scan is needed);
-//   - on levels of at most 64K edges claims go straight to the atomicOr of
-//     Algorithm 3 (the plain-read probe would add one dependent memory round
-//     trip per level, and such levels are bound by round trips, not by
-//     atomic throughput); levels with more edges probe first, since hub rows
-//     would queue their claims on a few bitmap lines; winners write level
-//     and parent, and append to the next queue with one reservation per
-//     workgroup and tile;
-//   - a winner also stores its row start, degree and caller id beside its
-//     queue slot, so the next level stages its frontier without looking
-//     them up in the CSR;
-//   - one grid-wide barrier ends each level.
+// workgroups runs them back to back instead.
+//
+// Such levels are bound by the chain of dependent memory round trips, so the
+// loop is built around that chain:
+//   - one XCD: of the launch's workgroups only every eighth takes part, and
+//     workgroups are dealt to the eight XCDs in turn, so the ones that do
+//     share one L2.  They compare their XCC ids when they start: when all are
+//     equal, claims and barrier words are atomics and stores of that L2
+//     (workgroup scope), a fraction of the latency of the device-scope ones,
+//     and no barrier writes back or invalidates the L2; otherwise the same
+//     loop runs at device scope;
+//   - the frontier stays in the LDS of the workgroup that found it.  The next
+//     queue in memory is written only when the frontier is dealt out anew (a
+//     workgroup's share overflowed or became a multiple of the mean) and when
+//     the kernel hands the search back;
+//   - one barrier per level, which orders nothing but the claims: a workgroup
+//     arrives as soon as its claims have returned, then loads the row starts
+//     and the first neighbours of the vertices it found, and only then waits.
+//     Each workgroup arrives with one store to its own slot, which also holds
+//     its share of the new frontier, and reads all slots with one load per
+//     lane, so the sizes arrive with the barrier;
+//   - graphs whose largest degree is at most kRowEdges (lattices) take one lane
+//     per edge; others map edges to threads by binary search in the
+//     share's degree prefix sum (Section 3.4), and check the level's edge
+//     count and largest degree in a second set of slots.
+// One search, against one device-scope counter barrier and queue reservation
+// per level: 256 x 256 grid (378 levels) 2.1-2.7 -> 0.69 ms, 4096 x 4096 grid
+// (5799 levels) 46.8 -> 22.8 ms; the loop's launches of an R-MAT 16 search
+// 82 -> 43 us.
+//
+// On levels of few edges claims go straight to the atomicOr of Algorithm 3
+// (a plain-read probe would add one dependent round trip).  Levels with more
+// probe first, and collect the ids below kHotIds (under degree order the ones
+// most edges point at) in LDS, to be claimed a bitmap word at a time.  Winners
+// write level and parent; the bitmap of the level before (vis_old) is left
+// behind, the host brings it up to date before it next drives a level itself.
+//
 // The kernel hands the search back to the host when the next frontier, its
 // edge count or its largest degree exceeds the limits the host passes, and
-// ends the search when a frontier is empty.  Every barrier wait is bounded:
-// a wait that does not end sets ctrl->err and every workgroup leaves.
+// ends the search when a frontier is empty.  Every wait is bounded.  The
+// workgroups start together or not at all: one that has waited too long for
+// the others (the GPU is held by other work) calls the launch off, and the
+// host runs the level itself.  A wait inside the loop that does not end sets
+// ctrl->err and every workgroup leaves.
 #include "bfs_internal.h"
 #include "wave_ops.h"
 
 namespace bfsmi {
 
-constexpr int kSmallEPT = 4;
-constexpr int kSmallTile = kWG * kSmallEPT;
-constexpr int kSmallStage = 1024;  // frontier entries staged per pass (4 per thread)
-constexpr uint32_t kSpinCap = 1u << 24;
-constexpr int64_t kSmallProbeEdges = 1 << 16;  // levels with more edges probe before claiming
-static_assert(kWG == 256, "per-wave partials below assume four waves");
+constexpr int kSW = 512;           // threads per workgroup (8 waves)
+constexpr int kSmallEPT = 2;
+constexpr int kSmallTile = kSW * kSmallEPT;
+constexpr int kSmallStage = 1024;  // frontier entries per workgroup and pass
+constexpr int kStagePer = kSmallStage / kSW;
+constexpr int kRowEdges = 4;       // rows of at most this many edges: one lane per edge
+constexpr int kRowStep = kSmallTile / kRowEdges;  // such rows per step
+constexpr uint32_t kStartCap = 1u << 14;  // polls before a launch is called off
+constexpr uint32_t kSpinCap = 1u << 23;
+constexpr int64_t kMergeEdges = 1 << 11;   // levels with more edges merge the hot ids' claims
+constexpr int kHotIds = 1 << 16;           // ... those below this
+// Edge counts saturate, per thread and per share, above every limit the host
+// passes (at most 8192 edges per workgroup).
+constexpr int64_t kDegSat = 1 << 22, kEdgeSat = 1 << 24;
+static_assert((int64_t)kSmallMaxWGs * 8192 < kDegSat, "a saturated count is over the limit");
 
-// Grid-wide barrier on a counter that only grows (reset to zero before the
-// launch): barrier number k is passed once it reaches k * nwg.  Thread 0 of
-// each workgroup arrives with a release add and waits with relaxed loads
-// followed by an acquire fence.
-__device__ __forceinline__ bool grid_sync(SmallSync* sy, uint32_t nwg, uint32_t* s_ep)
+// Barrier words, one per workgroup, in two sets used in turn: a workgroup
+// writes set k mod 2 again only after every other has arrived at barrier
+// k + 1, which they do after reading set k mod 2.
+struct SmallSlots {
+    uint64_t cnt[2][kSmallMaxWGs];  // epoch << 32 | overflow << 31 | vertices found
+    uint64_t deg[2][kSmallMaxWGs];  // epoch << 32 | a degree is over the limit << 31 | edges
+};
+static_assert(sizeof(SmallSlots) <= kSummaryMaxWords * 4, "the slots lie in the summary's words");
+
+struct SmallLds {
+    int32_t cum[kSmallStage + 1];
+    int32_t uid[kSmallStage];
+    int64_t base[kSmallStage];
+    uint16_t map[kSmallTile];
+    uint32_t hot[kHotIds / 32];  // merge levels: hot ids this workgroup's edges point at
+    int32_t nv[2][kSmallStage];  // vertices found, this level's and the last one's
+    int32_t wave[kSW / 64];
+    int32_t dmax[kSW / 64];
+    uint32_t cnt[2];   // vertices found at the level, by level mod 2
+    // of the last barrier: total, bits (some flag bit set; some share above
+    // twice the mean; the wait ended), sum before this workgroup
+    int32_t sum, bits, pre;
+};
+constexpr int kBarAny = 1, kBarSkew = 2, kBarOk = 4;
+
+template <bool L>
+__device__ __forceinline__ uint32_t claim_or(uint32_t* p, uint32_t m)
 {
-    __shared__ int s_ok;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const uint32_t target = (*s_ep + 1u) * nwg;
-        uint32_t a = __hip_atomic_fetch_add(&sy->arrive, 1u, __ATOMIC_RELEASE,
-                                            __HIP_MEMORY_SCOPE_AGENT) + 1u;
-        int ok = 1;
+    if constexpr (L)
+        return __hip_atomic_fetch_or(p, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    else
+        return __hip_atomic_fetch_or(p, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <bool L, typename T>
+__device__ __forceinline__ void scoped_store(T* p, T x)
+{
+    if constexpr (L)
+        __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    else
+        __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Queue entries are read past the L1: other workgroups write them during the
+// launch, and no barrier invalidates it.  (Also applied to shares in LDS.)
+__device__ __forceinline__ int32_t queue_load(const int32_t* p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Waits until all N slots carry the epoch, then sums their low 31 bits into
+// S.sum and S.pre; S.bits as above (skew: a share of more than skew_min that
+// is more than twice the mean).  Returns {sum, bits}, uniform.  Every thread
+// calls it; the last wave, which has the least to load, polls.
+__device__ __forceinline__ int2 wait_slots(const uint64_t* slots, uint32_t epoch, int N, int w,
+                                           int32_t skew_min, SmallLds& S)
+{
+    if (threadIdx.x >= kSW - 64) {
+        const int lane = __lane_id();
+        uint64_t x = (uint64_t)epoch << 32;
         uint32_t spins = 0;
-        while ((int32_t)(a - target) < 0) {
-            __builtin_amdgcn_s_sleep(2);
-            a = __hip_atomic_load(&sy->arrive, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        bool ok = true;
+        while (true) {
+            // agent scope: read past the L1
+            if (lane < N) x = __hip_atomic_load(slots + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (__all((uint32_t)(x >> 32) == epoch)) break;
             if (++spins > kSpinCap) {
-                ok = 0;
+                ok = false;
                 break;
             }
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        *s_ep += 1u;
-        s_ok = ok;
+        const int32_t c = (int32_t)((uint32_t)x & 0x7fffffffu);
+        const int32_t inc = wave_inclusive_scan_dpp(c);
+        const int32_t sum = __builtin_amdgcn_readlane(inc, 63);
+        const uint64_t any = __ballot(((uint32_t)x >> 31) != 0);
+        const uint64_t skew = __ballot(c > skew_min && (int64_t)c * N > 2 * (int64_t)sum);
+        if (lane == w) S.pre = inc - c;
+        if (lane == 0) {
+            S.sum = sum;
+            S.bits = (any ? kBarAny : 0) | (skew ? kBarSkew : 0) | (ok ? kBarOk : 0);
+        }
     }
     __syncthreads();
-    return s_ok != 0;
+    return make_int2(__builtin_amdgcn_readfirstlane(S.sum), __builtin_amdgcn_readfirstlane(S.bits));
 }
 
-// The levels; every workgroup returns from it exactly once.
-__device__ __forceinline__ void small_levels_body(
-    int32_t V, const int64_t* __restrict__ off, const int32_t* __restrict__ col,
-    const int32_t* __restrict__ orig, uint32_t* __restrict__ vis, uint32_t* __restrict__ vis_old,
-    int32_t* __restrict__ Qa, int32_t* __restrict__ Qb, int32_t* __restrict__ level,
-    int32_t* __restrict__ parent, SmallSync* __restrict__ sy, SmallSide side,
-    Ctrl* __restrict__ ctrl, int32_t qlen0, int32_t lvl0, int32_t qlimit, int64_t rlimit, int32_t dlimit)
+// Appends the winners among a wave's NE edges per lane to the workgroup's
+// share; those that do not fit go to the queue in memory, behind one
+// reservation per wave.
+template <bool L, int NE>
+__device__ __forceinline__ void keep_winners(const int32_t (&vv)[NE], const bool (&win)[NE],
+                                             int32_t V, int32_t* nv, uint32_t* cnt, int32_t* __restrict__ Qn,
+                                             uint32_t* __restrict__ spill, uint32_t spill0,
+                                             Ctrl* __restrict__ ctrl)
 {
-    __shared__ int32_t s_cum[kSmallStage + 1];
-    __shared__ int32_t s_uid[kSmallStage];
-    __shared__ int64_t s_base[kSmallStage];
-    __shared__ uint16_t s_map[kSmallTile];
-    __shared__ int32_t s_wave[kWG / 64];
-    __shared__ uint32_t s_wq[kWG / 64];
-    __shared__ int64_t s_rs[kWG / 64];
-    __shared__ int32_t s_rm[kWG / 64];
-    __shared__ uint32_t s_qbase;
-    __shared__ uint32_t s_epoch;
-    const uint32_t N = gridDim.x;
-    const uint32_t w = blockIdx.x;
-    const int t = threadIdx.x;
-    const int wave = t >> 6;
-    if (t == 0) s_epoch = 0;
-    // qlen0 < 0: launched right behind a host-driven level, whose next
-    // frontier size is in ctrl->qn_count; an empty frontier ends the search
-    // and one above the limits goes back to the host, both before any level
-    if (qlen0 < 0) {
-        qlen0 = (int32_t)ctrl->qn_count;
-        if (qlen0 == 0 || qlen0 > qlimit || qlen0 > side.cap) {
-            if (w == 0 && t == 0) {
-                ctrl->done = qlen0 == 0 ? 1 : 2;
-                ctrl->qlen = qlen0;
-                ctrl->level = lvl0;
-                ctrl->steps = 0;
-                ctrl->reached = 0;
-                ctrl->levels = 0;
+    uint64_t mask[NE];
+    uint32_t total = 0;
+#pragma unroll
+    for (int j = 0; j < NE; ++j) {
+        mask[j] = __ballot(win[j]);
+        total += (uint32_t)__popcll(mask[j]);
+    }
+    if (!total) return;  // uniform over the wave
+    uint32_t pos0 = 0;
+    if (__lane_id() == 0) pos0 = atomicAdd(cnt, total);
+    pos0 = __builtin_amdgcn_readfirstlane(pos0);
+    const uint32_t over0 = pos0 > kSmallStage ? pos0 : kSmallStage;  // first position that spills
+    uint32_t q0 = 0;
+    if (pos0 + total > over0) {
+        if (__lane_id() == 0) q0 = atomicAdd(spill, pos0 + total - over0);
+        q0 = __builtin_amdgcn_readfirstlane(q0) - spill0;
+    }
+    uint32_t base = pos0;
+#pragma unroll
+    for (int j = 0; j < NE; ++j) {
+        if (win[j]) {
+            const int32_t v = vv[j];
+            const uint32_t pos = base + lanes_below(mask[j]);
+            if (pos < kSmallStage) {
+                nv[pos] = v;
+            } else {
+                const uint32_t q = q0 + (pos - over0);
+                if (q < (uint32_t)V) scoped_store<L>(Qn + q, v);
+                else ctrl->err = 5;
             }
-            return;
+        }
+        base += (uint32_t)__popcll(mask[j]);
+    }
+}
+
+// Claims of one step: the atomicOr on every edge.  At a merge level an edge
+// first reads the bitmap; one to an unvisited hot id is noted in hot (the
+// first of the workgroup stores the parent: whichever store remains, it names
+// a frontier neighbour) and claimed by merge_hot.
+// (Loads are unconditional, of valid ids, here and below: behind a branch
+// the compiler waits for each before it issues the next.)
+template <bool L, int NE>
+__device__ __forceinline__ void claim_edges(const int32_t (&vv)[NE], const int32_t (&uu)[NE],
+                                            const bool (&ok)[NE], bool merge,
+                                            uint32_t* __restrict__ vis,
+                                            int32_t* __restrict__ parent, uint32_t* hot,
+                                            bool (&win)[NE])
+{
+    uint32_t old[NE];
+#pragma unroll
+    for (int j = 0; j < NE; ++j) old[j] = ok[j] ? 0u : ~0u;
+    if (merge) {
+#pragma unroll
+        for (int j = 0; j < NE; ++j)  // past the L1, which no barrier here invalidates
+            old[j] |= __hip_atomic_load(vis + (vv[j] >> 5), __ATOMIC_RELAXED,
+                                        __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int j = 0; j < NE; ++j) {
+            const uint32_t bit = 1u << (vv[j] & 31);
+            if (!(old[j] & bit) && vv[j] < kHotIds) {
+                old[j] = ~0u;
+                if (!(atomicOr(&hot[vv[j] >> 5], bit) & bit) && parent) parent[vv[j]] = uu[j];
+            }
         }
     }
+#pragma unroll
+    for (int j = 0; j < NE; ++j)
+        if (!(old[j] & (1u << (vv[j] & 31))))
+            old[j] = claim_or<L>(vis + (vv[j] >> 5), 1u << (vv[j] & 31));
+#pragma unroll
+    for (int j = 0; j < NE; ++j) win[j] = !(old[j] & (1u << (vv[j] & 31)));
+}
 
-    // The first frontier's size limits are checked before any level runs.
-    {
-        const int64_t k0 = (int64_t)qlen0 * w / N, k1 = (int64_t)qlen0 * (w + 1) / N;
-        int64_t sum = 0;
-        int32_t mx = 0;
-        for (int64_t k = k0 + t; k < k1; k += kWG) {
-            const int32_t u = Qa[k];
-            const int64_t d = off[u + 1] - off[u];
-            sum += d;
-            mx = d > mx ? (int32_t)d : mx;
+// End of a merge level: the noted ids are claimed a bitmap word at a time,
+// consecutive words by consecutive lanes.  Hub rows point at the same few
+// lines of the bitmap, whose atomics an L2 takes one after the other: a level
+// of R-MAT 12 with 32K edges (4 lines) took 58 us of single-bit claims.
+template <bool L>
+__device__ __forceinline__ void merge_hot(uint32_t* hot, int32_t lvl, int32_t V,
+                                          uint32_t* __restrict__ vis, int32_t* __restrict__ level,
+                                          int32_t* nv, uint32_t* cnt, int32_t* __restrict__ Qn,
+                                          uint32_t* __restrict__ spill, uint32_t spill0,
+                                          Ctrl* __restrict__ ctrl)
+{
+    constexpr int PER = kHotIds / 32 / kSW;
+    uint32_t x[PER], old[PER];
+#pragma unroll
+    for (int m = 0; m < PER; ++m) {
+        x[m] = hot[m * kSW + threadIdx.x];
+        old[m] = 0;
+        if (x[m]) old[m] = claim_or<L>(vis + m * kSW + threadIdx.x, x[m]);
+    }
+#pragma unroll
+    for (int m = 0; m < PER; ++m) x[m] &= ~old[m];
+#pragma unroll
+    for (int m = 0; m < PER; ++m) {
+        const int32_t c = __popc(x[m]);
+        const int32_t inc = wave_inclusive_scan_dpp(c);
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane(inc, 63);
+        if (!total) continue;  // uniform over the wave
+        uint32_t pos0 = 0, q0 = 0;
+        if (__lane_id() == 0) pos0 = atomicAdd(cnt, total);
+        pos0 = __builtin_amdgcn_readfirstlane(pos0);
+        const uint32_t over0 = pos0 > kSmallStage ? pos0 : kSmallStage;
+        if (pos0 + total > over0) {
+            if (__lane_id() == 0) q0 = atomicAdd(spill, pos0 + total - over0);
+            q0 = __builtin_amdgcn_readfirstlane(q0) - spill0;
         }
+        uint32_t pos = pos0 + (uint32_t)(inc - c);
+        for (uint32_t b = x[m]; b; b &= b - 1, ++pos) {
+            const int32_t v = (m * kSW + (int32_t)threadIdx.x) * 32 + __builtin_ctz(b);
+            if (pos < kSmallStage) {
+                nv[pos] = v;
+            } else {
+                const uint32_t q = q0 + (pos - over0);
+                if (q < (uint32_t)V) scoped_store<L>(Qn + q, v);
+                else ctrl->err = 5;
+            }
+            level[v] = lvl;
+        }
+    }
+}
+
+// Maps the tile's slots of the staged share (n entries, R edges) to entries
+// and loads their neighbours.
+__device__ __forceinline__ void map_small_tile(SmallLds& S, int32_t n, int32_t R, int32_t e0,
+                                               const int32_t* __restrict__ col,
+                                               int32_t (&vv)[kSmallEPT], int32_t (&uu)[kSmallEPT],
+                                               bool (&ok)[kSmallEPT])
+{
+    const int t = threadIdx.x;
+    const int32_t n_e = R - e0 < kSmallTile ? R - e0 : kSmallTile;
+    // slots sl0, sl0 + 1 of this thread: entry = max{i : cum[i] <= slot}
+    const int32_t sl0 = e0 + t * kSmallEPT;
+    if (t * kSmallEPT < n_e) {
+        int32_t lo = 0;
+        for (int32_t st = 1 << (31 - __builtin_clz(n)); st > 0; st >>= 1) {
+            const int32_t x = lo + st;
+            if (x < n && S.cum[x] <= sl0) lo = x;
+        }
+        int32_t i = lo;
+#pragma unroll
+        for (int j = 0; j < kSmallEPT; ++j) {
+            const int32_t sl = sl0 + j;
+            if (sl - e0 < n_e) {
+                while (i + 1 < n && S.cum[i + 1] <= sl) ++i;
+                S.map[sl - e0] = (uint16_t)i;
+            }
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kSmallEPT; ++j) {
+        const int32_t sl = t + j * kSW;
+        ok[j] = sl < n_e;
+        const int32_t sc = ok[j] ? sl : n_e - 1;
+        const int32_t i = S.map[sc];
+        uu[j] = S.uid[i];
+        vv[j] = col[S.base[i] + e0 + sc];
+    }
+}
+
+// Stages entries ids[0..n), n <= kSmallStage, kStagePer consecutive ones per thread:
+// row starts, caller ids and the prefix sum of the degrees.  Returns the
+// share's edges (saturated: over the limits the prefix sums mean nothing);
+// S.dmax gets the largest degree of each wave.
+__device__ __forceinline__ int32_t stage_share(SmallLds& S, const int32_t* __restrict__ ids, int32_t n,
+                                               const int64_t* __restrict__ off,
+                                               const int32_t* __restrict__ orig)
+{
+    const int t = threadIdx.x;
+    if (n == 0) {  // uniform
+        if (t < kSW / 64) S.dmax[t] = 0;
+        __syncthreads();
+        return 0;
+    }
+    int64_t a[kStagePer], sum = 0;
+    int32_t d[kStagePer], id[kStagePer];
+    int32_t mx = 0;
+#pragma unroll
+    for (int m = 0; m < kStagePer; ++m) {
+        const int32_t i = t * kStagePer + m;
+        const int32_t u = queue_load(ids + (i < n ? i : n - 1));
+        a[m] = off[u];
+        const int64_t dd = off[u + 1] - a[m];
+        d[m] = i < n ? (int32_t)(dd < kDegSat ? dd : kDegSat) : 0;
+        id[m] = orig ? orig[u] : u;
+    }
+#pragma unroll
+    for (int m = 0; m < kStagePer; ++m) {
+        sum += d[m];
+        mx = d[m] > mx ? d[m] : mx;
+    }
+    const int32_t tot = (int32_t)(sum < kDegSat ? sum : kDegSat);
+    const int32_t inc = wave_inclusive_scan_dpp(tot);
+    const uint64_t big = __ballot(mx > 0);
+    if (big)  // uniform over the wave
         for (int o = 32; o >= 1; o >>= 1) {
-            sum += __shfl_xor(sum, o, 64);
             const int32_t m2 = __shfl_xor(mx, o, 64);
             mx = m2 > mx ? m2 : mx;
         }
-        if ((t & 63) == 0) {
-            if (sum) atomicAdd(reinterpret_cast<unsigned long long*>(&sy->rn[2]),
-                               (unsigned long long)sum);
-            if (mx) atomicMax(&sy->md[2], mx);
-        }
+    if ((t & 63) == 63) S.wave[t >> 6] = inc;
+    if ((t & 63) == 0) S.dmax[t >> 6] = mx;
+    __syncthreads();
+    int32_t c = inc - tot, R = 0;
+#pragma unroll
+    for (int k = 0; k < kSW / 64; ++k) {
+        const int32_t x = S.wave[k];
+        if (k < (t >> 6)) c += x;
+        R += x;
     }
-    if (!grid_sync(sy, N, &s_epoch)) {
+#pragma unroll
+    for (int m = 0; m < kStagePer; ++m) {
+        const int32_t i = t * kStagePer + m;
+        if (i < n) {
+            S.cum[i] = c;
+            S.uid[i] = id[m];
+            S.base[i] = a[m] - c;
+        }
+        c += d[m];
+    }
+    if (t == 0) S.cum[n] = R;
+    __syncthreads();
+    return R;
+}
+
+// Edges and largest degree of this workgroup's slice of Q, as a deg slot's
+// low half (every thread gets it).
+__device__ __forceinline__ uint32_t slice_limits(SmallLds& S, const int32_t* __restrict__ Q,
+                                                 int64_t k0, int64_t k1,
+                                                 const int64_t* __restrict__ off, int32_t dlimit)
+{
+    const int t = threadIdx.x;
+    int64_t sum = 0;
+    int32_t over = 0;
+    for (int64_t k = k0 + t; k < k1; k += kSW) {
+        const int32_t u = queue_load(Q + k);
+        const int64_t d = off[u + 1] - off[u];
+        sum += d;
+        over |= d > dlimit;
+    }
+    int32_t s = (int32_t)(sum < kDegSat ? sum : kDegSat);
+    s = __builtin_amdgcn_readlane(wave_inclusive_scan_dpp(s), 63);
+    const uint64_t any = __ballot(over);
+    if ((t & 63) == 0) {
+        S.wave[t >> 6] = s;
+        S.dmax[t >> 6] = any != 0;
+    }
+    __syncthreads();
+    int64_t tot = 0;
+    uint32_t o = 0;
+#pragma unroll
+    for (int k = 0; k < kSW / 64; ++k) {
+        tot += S.wave[k];
+        o |= (uint32_t)S.dmax[k];
+    }
+    __syncthreads();
+    return (uint32_t)(tot < kEdgeSat ? tot : kEdgeSat) | (o << 31);
+}
+
+// The levels; every workgroup returns from it exactly once.  deg slot set 1
+// holds epoch 1, the limits of the first frontier (Qa[0 .. qlen0)).
+template <bool L>
+__device__ __forceinline__ void small_levels_body(
+    SmallLds& S, int32_t V, const int64_t* __restrict__ off, const int32_t* __restrict__ col,
+    const int32_t* __restrict__ orig, uint32_t* __restrict__ vis,
+    int32_t* __restrict__ Qa, int32_t* __restrict__ Qb, int32_t* __restrict__ level,
+    int32_t* __restrict__ parent, SmallSync* __restrict__ sy, SmallSlots* __restrict__ slots,
+    Ctrl* __restrict__ ctrl, int N, int w, int32_t qlen0, int32_t lvl0, int32_t qlimit,
+    int64_t rlimit, int32_t dlimit, int32_t maxdeg)
+{
+    const int t = threadIdx.x;
+    // one lane per edge: the limits on edges and degrees cannot be exceeded
+    // by a frontier that fits the workgroups' shares
+    const bool rows = maxdeg <= kRowEdges && maxdeg <= dlimit &&
+                      (int64_t)N * kSmallStage * maxdeg <= rlimit;
+    uint32_t ep_cnt = 0, ep_deg = 1;
+    int32_t qlen = qlen0, lvl = lvl0, step = 0, par = 0, code = 0;
+    int64_t my_edges = 0, reached = 0;
+
+    int2 bar = wait_slots(slots->deg[1], 1, N, w, 0, S);
+    if (!(bar.y & kBarOk)) {
         if (t == 0) ctrl->err = 4;
         return;
     }
-    int64_t cur_rn;  // edges of the frontier being expanded
-    {
-        // slot 2 is next reset during level 1, after every workgroup read it
-        const int64_t rn = __hip_atomic_load(&sy->rn[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        cur_rn = rn;
-        const int32_t md = __hip_atomic_load(&sy->md[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (rn > rlimit || md > dlimit) {
-            if (w == 0 && t == 0) {
-                ctrl->done = 2;
-                ctrl->qlen = qlen0;
-                ctrl->level = lvl0;
-                ctrl->steps = 0;
-                ctrl->reached = 0;
-                ctrl->levels = 0;
-            }
-            return;
-        }
-    }
-
-    int32_t qlen = qlen0, lvl = lvl0, step = 0, par = 0, code = 0;
-    int64_t my_edges = 0, reached = 0;
-    while (true) {
-        const int32_t* __restrict__ Q = par ? Qb : Qa;
-        int32_t* __restrict__ Qn = par ? Qa : Qb;
-        // from the second level on, every frontier entry carries its row start,
-        // degree and caller id, written by the workgroup that claimed it
-        const bool from_side = step > 0;
-        const int64_t* __restrict__ in_off = side.off[par];
-        const int32_t* __restrict__ in_deg = side.deg[par];
-        const int32_t* __restrict__ in_id = side.id[par];
-        int64_t* __restrict__ out_off = side.off[par ^ 1];
-        int32_t* __restrict__ out_deg = side.deg[par ^ 1];
-        int32_t* __restrict__ out_id = side.id[par ^ 1];
-        const int cs = step % 3;  // counters of this level
-        // a level with many edges reads the target's bitmap word first and
-        // claims only unset bits: on hub rows the claims of a bare atomicOr
-        // would queue on a few bitmap lines
-        const bool probe = cur_rn > kSmallProbeEdges;
+    if (bar.x > rlimit || (bar.y & kBarAny)) {
         if (w == 0 && t == 0) {
-            // the next level's counters were last read two barriers ago
-            const int nx = (step + 1) % 3;
-            sy->qn[nx] = 0;
-            sy->rn[nx] = 0;
-            sy->md[nx] = 0;
+            ctrl->done = 2;
+            ctrl->qlen = qlen0;
+            ctrl->level = lvl0;
+            ctrl->steps = 0;
+            ctrl->reached = 0;
+            ctrl->levels = 0;
         }
-        int64_t dsum = 0;
-        int32_t dmax = 0;
-        const int64_t k0 = (int64_t)qlen * w / N, k1 = (int64_t)qlen * (w + 1) / N;
-        for (int64_t s0 = k0; s0 < k1; s0 += kSmallStage) {
-            const int32_t n = (int32_t)(k1 - s0 < kSmallStage ? k1 - s0 : kSmallStage);
-            // stage 4 consecutive entries per thread, prefix sum of degrees
-            int64_t a[4];
-            int32_t d[4], id[4];
-            int32_t tot = 0;
+        return;
+    }
+    bool merge = bar.x > kMergeEdges;
+    if (t < 2) S.cnt[t] = 0;
+    __syncthreads();
+    uint32_t spill0 = 0; // sy->spill before this level: it only grows within a launch
+    bool local = false;  // the frontier lies in the shares, else in the queue
+    int32_t n = 0;       // this workgroup's share
+    int buf = 0;         // nv[buf]: this level's share
+    // a step's edges; the share's first step is loaded ahead of the barrier
+    int32_t tv[kSmallEPT] = {}, tu[kSmallEPT] = {};
+    bool tok[kSmallEPT] = {};
+    int32_t R = 0;
+    // the last step's winners, whose outputs are stored behind the next loads
+    int32_t ov[kSmallEPT], ou[kSmallEPT];
+    bool own[kSmallEPT] = {};
+    auto store_outputs = [&](int32_t depth) {
 #pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                const int32_t i = t * 4 + m;
-                a[m] = 0;
-                d[m] = 0;
-                id[m] = 0;
-                if (i < n) {
-                    if (from_side) {
-                        a[m] = in_off[s0 + i];
-                        d[m] = in_deg[s0 + i];
-                        id[m] = in_id[s0 + i];
-                    } else
-                    {
-                        const int32_t u = Q[s0 + i];
-                        a[m] = off[u];
-                        d[m] = (int32_t)(off[u + 1] - a[m]);
-                        id[m] = orig ? orig[u] : u;
-                    }
-                }
-                tot += d[m];
+        for (int j = 0; j < kSmallEPT; ++j) {
+            if (own[j]) {
+                level[ov[j]] = depth;
+                if (parent) parent[ov[j]] = ou[j];
             }
-            int32_t R;
-            int32_t c = wg_exclusive_scan<int32_t>(tot, &R, s_wave);
+            own[j] = false;
+        }
+    };
+
+    // rows i0 .. i0 + kRowStep - 1 of the share nv, one lane per edge
+    auto load_rows = [&](const int32_t* nv, int32_t i0) {
+        const int32_t e = t % kRowEdges;
+        int64_t a[kSmallEPT], b[kSmallEPT];
+        bool any = false;
 #pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                const int32_t i = t * 4 + m;
-                if (i < n) {
-                    s_cum[i] = c;
-                    s_uid[i] = id[m];
-                    s_base[i] = a[m] - c;
-                }
-                c += d[m];
-            }
-            if (t == 0) s_cum[n] = R;
+        for (int j = 0; j < kSmallEPT; ++j) {
+            const int32_t i = i0 + j * (kSW / kRowEdges) + t / kRowEdges;
+            tok[j] = i < n;
+            tv[j] = tok[j] ? nv[i] : 0;
+            any |= tok[j];
+        }
+        if (!__any(any)) return;
+#pragma unroll
+        for (int j = 0; j < kSmallEPT; ++j) {
+            a[j] = off[tv[j]];
+            b[j] = off[tv[j] + 1];
+            tu[j] = orig && parent ? orig[tv[j]] : tv[j];
+        }
+        any = false;
+#pragma unroll
+        for (int j = 0; j < kSmallEPT; ++j) {
+            tok[j] = tok[j] && a[j] + e < b[j];
+            any |= tok[j];
+        }
+        if (!__any(any)) return;  // (some edge exists: col[0] is one)
+#pragma unroll
+        for (int j = 0; j < kSmallEPT; ++j) tv[j] = col[tok[j] ? a[j] + e : 0];
+    };
+
+    while (true) {
+        int32_t* __restrict__ Qn = par ? Qa : Qb;
+        uint32_t* cnt = &S.cnt[step & 1];
+        if (merge) {
+            for (int i = t; i < kHotIds / 32; i += kSW) S.hot[i] = 0;
             __syncthreads();
-            my_edges += R;
+        }
+        int32_t* nv_in = S.nv[buf];
+        int32_t* nv_out = S.nv[buf ^ 1];
+        auto tile_step = [&]() {
+            store_outputs(lvl);
+            claim_edges<L, kSmallEPT>(tv, tu, tok, merge, vis, parent, S.hot, own);
+            keep_winners<L, kSmallEPT>(tv, own, V, nv_out, cnt, Qn, &sy->spill, spill0, ctrl);
+#pragma unroll
+            for (int j = 0; j < kSmallEPT; ++j) {
+                ov[j] = tv[j];
+                ou[j] = tu[j];
+            }
+        };
+        if (local && rows) {
+            for (int32_t i0 = 0; i0 < n; i0 += kRowStep) {
+                if (i0 > 0) load_rows(nv_in, i0);
+#pragma unroll
+                for (int j = 0; j < kSmallEPT; ++j) my_edges += tok[j] ? 1 : 0;
+                tile_step();
+            }
+        } else if (local) {
+            if (t == 0) my_edges += R;
             for (int32_t e0 = 0; e0 < R; e0 += kSmallTile) {
-                const int32_t n_e = R - e0 < kSmallTile ? R - e0 : kSmallTile;
-                // slots s0 .. s0+3 of this thread: entry = max{i : cum[i] <= slot}
-                const int32_t sl0 = e0 + t * kSmallEPT;
-                if (t * kSmallEPT < n_e) {
-                    int32_t lo = 0;
-                    for (int32_t st = 1 << (31 - __builtin_clz(n)); st > 0; st >>= 1) {
-                        const int32_t x = lo + st;
-                        if (x < n && s_cum[x] <= sl0) lo = x;
-                    }
-                    int32_t i = lo;
-#pragma unroll
-                    for (int j = 0; j < kSmallEPT; ++j) {
-                        const int32_t sl = sl0 + j;
-                        if (sl - e0 < n_e) {
-                            while (i + 1 < n && s_cum[i + 1] <= sl) ++i;
-                            s_map[sl - e0] = (uint16_t)i;
-                        }
-                    }
+                if (e0 > 0) {
+                    __syncthreads();  // the map is reused
+                    map_small_tile(S, n, R, e0, col, tv, tu, tok);
                 }
-                __syncthreads();
-                int32_t vv[kSmallEPT], uu[kSmallEPT];
-                bool ok[kSmallEPT];
-#pragma unroll
-                for (int j = 0; j < kSmallEPT; ++j) {
-                    const int32_t sl = t + j * kWG;
-                    ok[j] = sl < n_e;
-                    const int32_t sc = ok[j] ? sl : n_e - 1;
-                    const int32_t i = s_map[sc];
-                    uu[j] = s_uid[i];
-                    vv[j] = col[s_base[i] + e0 + sc];
+                tile_step();
+            }
+        } else {
+            const int32_t* __restrict__ Q = par ? Qb : Qa;
+            // a frontier that one stage holds is split by edges (every
+            // workgroup stages all of it), a larger one by entries
+            const bool split = qlen <= kSmallStage;
+            const int64_t k0 = split ? 0 : (int64_t)qlen * w / N;
+            const int64_t k1 = split ? qlen : (int64_t)qlen * (w + 1) / N;
+            for (int64_t s0 = k0; s0 < k1; s0 += kSmallStage) {
+                const int32_t ns = (int32_t)(k1 - s0 < kSmallStage ? k1 - s0 : kSmallStage);
+                const int32_t Rs = stage_share(S, Q + s0, ns, off, orig);
+                const int32_t e_lo = split ? (int32_t)((int64_t)Rs * w / N) : 0;
+                const int32_t e_hi = split ? (int32_t)((int64_t)Rs * (w + 1) / N) : Rs;
+                if (t == 0) my_edges += e_hi - e_lo;
+                for (int32_t e0 = e_lo; e0 < e_hi; e0 += kSmallTile) {
+                    map_small_tile(S, ns, e_hi, e0, col, tv, tu, tok);
+                    tile_step();
+                    __syncthreads();  // the map and the stage are reused
                 }
-                uint32_t old[kSmallEPT];
-                if (probe) {
-#pragma unroll
-                    for (int j = 0; j < kSmallEPT; ++j) old[j] = ok[j] ? vis[vv[j] >> 5] : ~0u;
-#pragma unroll
-                    for (int j = 0; j < kSmallEPT; ++j)
-                        if (!(old[j] & (1u << (vv[j] & 31))))
-                            old[j] = atomicOr(vis + (vv[j] >> 5), 1u << (vv[j] & 31));
-                } else {
-#pragma unroll
-                    for (int j = 0; j < kSmallEPT; ++j) {
-                        old[j] = ~0u;
-                        if (ok[j]) old[j] = atomicOr(vis + (vv[j] >> 5), 1u << (vv[j] & 31));
-                    }
-                }
-                bool win[kSmallEPT];
-                uint64_t mask[kSmallEPT];
-                uint32_t total = 0;
-#pragma unroll
-                for (int j = 0; j < kSmallEPT; ++j) {
-                    win[j] = ok[j] && !(old[j] & (1u << (vv[j] & 31)));
-                    mask[j] = __ballot(win[j]);
-                    total += (uint32_t)__popcll(mask[j]);
-                }
-                int64_t va[kSmallEPT];
-                int32_t vd[kSmallEPT], vi[kSmallEPT];
-#pragma unroll
-                for (int j = 0; j < kSmallEPT; ++j) {
-                    va[j] = 0;
-                    vd[j] = 0;
-                    vi[j] = 0;
-                    if (win[j]) {
-                        const int32_t v = vv[j];
-                        level[v] = lvl;
-                        if (parent) parent[v] = uu[j];
-                        va[j] = off[v];
-                        vd[j] = (int32_t)(off[v + 1] - va[j]);
-                        vi[j] = orig ? orig[v] : v;
-                        atomicOr(vis_old + (v >> 5), 1u << (v & 31));
-                    }
-                    dsum += vd[j];
-                    dmax = vd[j] > dmax ? vd[j] : dmax;
-                }
-                // one queue reservation per workgroup and tile
-                if (__lane_id() == 0) s_wq[wave] = total;
-                __syncthreads();
-                if (t == 0) {
-                    const uint32_t all = s_wq[0] + s_wq[1] + s_wq[2] + s_wq[3];
-                    s_qbase = all ? atomicAdd(&sy->qn[cs], all) : 0u;
-                }
-                __syncthreads();
-                if (total) {
-                    uint32_t base = s_qbase;
-                    for (int k = 0; k < wave; ++k) base += s_wq[k];
-#pragma unroll
-                    for (int j = 0; j < kSmallEPT; ++j) {
-                        if (win[j]) {
-                            const uint32_t pos = base + lanes_below(mask[j]);
-                            if (pos < (uint32_t)V) {
-                                Qn[pos] = vv[j];
-                                if (pos < (uint32_t)side.cap) {
-                                    out_off[pos] = va[j];
-                                    out_deg[pos] = vd[j];
-                                    out_id[pos] = vi[j];
-                                }
-                            } else {
-                                ctrl->err = 5;
-                            }
-                        }
-                        base += (uint32_t)__popcll(mask[j]);
-                    }
-                }
-                __syncthreads();
             }
         }
-        // the next frontier's edges and largest degree: one update per workgroup
-        for (int o = 32; o >= 1; o >>= 1) {
-            dsum += __shfl_xor(dsum, o, 64);
-            const int32_t m2 = __shfl_xor(dmax, o, 64);
-            dmax = m2 > dmax ? m2 : dmax;
-        }
-        if (__lane_id() == 0) {
-            s_rs[wave] = dsum;
-            s_rm[wave] = dmax;
+        if (merge) {
+            __syncthreads();
+            merge_hot<L>(S.hot, lvl, V, vis, level, nv_out, cnt, Qn, &sy->spill, spill0, ctrl);
         }
         __syncthreads();
-        if (t == 0) {
-            const int64_t rs = s_rs[0] + s_rs[1] + s_rs[2] + s_rs[3];
-            int32_t rm = s_rm[0];
-            for (int k = 1; k < kWG / 64; ++k) rm = s_rm[k] > rm ? s_rm[k] : rm;
-            if (rs) atomicAdd(reinterpret_cast<unsigned long long*>(&sy->rn[cs]),
-                              (unsigned long long)rs);
-            if (rm) atomicMax(&sy->md[cs], rm);
+        // arrive: every claim of this workgroup has returned
+        const uint32_t c = __builtin_amdgcn_readfirstlane(*cnt);
+        const uint32_t flag = c > (uint32_t)kSmallStage ? 1u : 0u;
+        n = flag ? kSmallStage : (int32_t)c;
+        buf ^= 1;
+        ++ep_cnt;
+        if (t == 0)
+            scoped_store<L>(&slots->cnt[ep_cnt & 1][w],
+                          ((uint64_t)ep_cnt << 32) | (flag << 31) | (uint32_t)n);
+        if (t == kSW - 1) S.cnt[(step & 1) ^ 1] = 0;  // the next level's, behind a barrier
+        // the share's rows and first neighbours, while the others arrive
+        if (rows) {
+            load_rows(S.nv[buf], 0);
+        } else {
+            R = stage_share(S, S.nv[buf], n, off, orig);
+            ++ep_deg;
+            if (t == 0) {
+                int32_t mx = S.dmax[0];
+                for (int k = 1; k < kSW / 64; ++k) mx = S.dmax[k] > mx ? S.dmax[k] : mx;
+                const uint32_t sat = R > kEdgeSat ? (uint32_t)kEdgeSat : (uint32_t)R;
+                scoped_store<L>(&slots->deg[ep_deg & 1][w],
+                              ((uint64_t)ep_deg << 32) | (mx > dlimit ? 1u << 31 : 0u) | sat);
+            }
+            if (R > 0 && R <= rlimit) map_small_tile(S, n, R, 0, col, tv, tu, tok);
         }
-        if (!grid_sync(sy, N, &s_epoch)) {
-            if (t == 0) ctrl->err = 4;
+        store_outputs(lvl);
+        bar = wait_slots(slots->cnt[ep_cnt & 1], ep_cnt, N, w, kRowStep, S);
+        if (!(bar.y & kBarOk)) {
             code = 3;
             break;
         }
-        const uint32_t qn = __hip_atomic_load(&sy->qn[cs], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int64_t rn = __hip_atomic_load(&sy->rn[cs], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int32_t md = __hip_atomic_load(&sy->md[cs], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        cur_rn = rn;
+        const bool over = (bar.y & kBarAny) != 0;
+        bool deal = over || (rows && (bar.y & kBarSkew));
+        int32_t qn = bar.x, spilled = 0;
+        if (over) {
+            // (the next spill is behind the barrier of the dealing below)
+            const uint32_t s1 = __builtin_amdgcn_readfirstlane(
+                __hip_atomic_load(&sy->spill, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+            spilled = (int32_t)(s1 - spill0);
+            spill0 = s1;
+            qn += spilled;  // at most V
+        }
         ++step;
         ++lvl;
+        par ^= 1;
         reached += qn;
+        qlen = qn;
         if (qn == 0) {
             code = 1;
             break;
         }
-        qlen = (int32_t)qn;
-        par ^= 1;
-        if ((int32_t)qn > qlimit || (int32_t)qn > side.cap || rn > rlimit || md > dlimit) {
-            code = 2;
-            break;
+        bool back = qn > qlimit;
+        int32_t pre = -1;
+        if (!back && !over) {
+            if (rows) {
+                merge = (int64_t)qn * maxdeg > kMergeEdges * 32;
+            } else {
+                pre = S.pre;
+                __syncthreads();  // S.pre has been read
+                bar = wait_slots(slots->deg[ep_deg & 1], ep_deg, N, w, kSmallTile, S);
+                if (!(bar.y & kBarOk)) {
+                    code = 3;
+                    break;
+                }
+                back = bar.x > rlimit || (bar.y & kBarAny);
+                deal = (bar.y & kBarSkew) != 0;
+                merge = bar.x > kMergeEdges;
+            }
+        }
+        if (back || deal) {
+            // the whole frontier to the queue: the spilled entries are there
+            int32_t* __restrict__ Qx = par ? Qb : Qa;
+            if (pre < 0) pre = S.pre;
+            for (int32_t i = t; i < n; i += kSW) {
+                const int64_t q = (int64_t)spilled + pre + i;
+                if (q < V) scoped_store<L>(Qx + q, S.nv[buf][i]);
+                else ctrl->err = 5;
+            }
+            if (back) {
+                code = 2;
+                break;
+            }
+            // the stores (the spilled entries' too) have reached the L2, or
+            // with device scope the other XCDs: no cache is written back
+            __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+            __syncthreads();
+            ++ep_cnt;
+            if (t == 0) scoped_store<L>(&slots->cnt[ep_cnt & 1][w], (uint64_t)ep_cnt << 32);
+            bar = wait_slots(slots->cnt[ep_cnt & 1], ep_cnt, N, w, 0, S);
+            if (!(bar.y & kBarOk)) {
+                code = 3;
+                break;
+            }
+            if (over) {
+                // the spilled entries' degrees have not been looked at
+                const int64_t k0 = (int64_t)qlen * w / N, k1 = (int64_t)qlen * (w + 1) / N;
+                const uint32_t lim = slice_limits(S, Qx, k0, k1, off, dlimit);
+                ++ep_deg;
+                if (t == 0)
+                    scoped_store<L>(&slots->deg[ep_deg & 1][w], ((uint64_t)ep_deg << 32) | lim);
+                bar = wait_slots(slots->deg[ep_deg & 1], ep_deg, N, w, 0, S);
+                if (!(bar.y & kBarOk)) {
+                    code = 3;
+                    break;
+                }
+                if (bar.x > rlimit || (bar.y & kBarAny)) {
+                    code = 2;
+                    break;
+                }
+                merge = bar.x > kMergeEdges;
+            }
+            local = false;
+        } else {
+            local = true;
         }
     }
-    if (t == 0 && my_edges)
-        atomicAdd(reinterpret_cast<unsigned long long*>(&sy->edges), (unsigned long long)my_edges);
-    if (w == 0 && t == 0 && code != 3) {
+    if (code == 3) {
+        if (t == 0) ctrl->err = 4;
+        return;
+    }
+    int64_t e = my_edges;
+    for (int o = 32; o >= 1; o >>= 1) e += __shfl_xor(e, o, 64);
+    if ((t & 63) == 0 && e)
+        atomicAdd(reinterpret_cast<unsigned long long*>(&sy->edges), (unsigned long long)e);
+    if (w == 0 && t == 0) {
         ctrl->done = code;
         ctrl->qlen = qlen;
         ctrl->level = lvl;
@@ -385,30 +709,94 @@ __device__ __forceinline__ void small_levels_body(
     }
 }
 
-// The launch leaves its sync block as it found it (zero), so it needs no
-// clearing of its own: the workgroup that leaves last (after every other has
-// stopped reading the block) publishes the edge total and clears the block.
-__global__ __launch_bounds__(kWG) void k_small_levels(
-    int32_t V, const int64_t* __restrict__ off, const int32_t* __restrict__ col,
-    const int32_t* __restrict__ orig, uint32_t* __restrict__ vis, uint32_t* __restrict__ vis_old,
-    int32_t* __restrict__ Qa, int32_t* __restrict__ Qb, int32_t* __restrict__ level,
-    int32_t* __restrict__ parent, SmallSync* __restrict__ sy, SmallSide side,
-    Ctrl* __restrict__ ctrl, int32_t qlen0, int32_t lvl0, int32_t qlimit, int64_t rlimit, int32_t dlimit)
+__device__ __forceinline__ int arrivals(uint64_t a)
 {
-    small_levels_body(V, off, col, orig, vis, vis_old, Qa, Qb, level, parent, sy, side, ctrl, qlen0,
-                      lvl0, qlimit, rlimit, dlimit);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const uint32_t k =
-            __hip_atomic_fetch_add(&sy->leave, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        if (k == gridDim.x - 1) {
-            ctrl->r_total = sy->edges;
-            sy->arrive = 0;
-            for (int i = 0; i < 3; ++i) {
-                sy->qn[i] = 0;
-                sy->md[i] = 0;
-                sy->rn[i] = 0;
+    int n = 0;
+#pragma unroll
+    for (int x = 0; x < kXcdSlices; ++x) n += (int)((a >> (7 * x)) & 127u);
+    return n;
+}
+
+// Workgroups b with b mod 8 == cls take part; the launch leaves its sync
+// block as it found it (zero): the workgroup that leaves last publishes the
+// edge total and clears the block.
+__global__ __launch_bounds__(kSW) void k_small_levels(
+    int32_t V, const int64_t* __restrict__ off, const int32_t* __restrict__ col,
+    const int32_t* __restrict__ orig, uint32_t* __restrict__ vis,
+    int32_t* __restrict__ Qa, int32_t* __restrict__ Qb, int32_t* __restrict__ level,
+    int32_t* __restrict__ parent, SmallSync* __restrict__ sy, SmallSlots* __restrict__ slots,
+    Ctrl* __restrict__ ctrl, int32_t cls, int32_t qlen0, int32_t lvl0, int32_t qlimit,
+    int64_t rlimit, int32_t dlimit, int32_t maxdeg)
+{
+    if ((int)(blockIdx.x & (kXcdSlices - 1)) != cls) return;
+    __shared__ SmallLds S;
+    __shared__ int s_go;  // 0 called off, 1 device scope, 2 one XCD
+    const int N = (int)(gridDim.x / kXcdSlices);
+    const int w = (int)(blockIdx.x / kXcdSlices);
+    const int t = threadIdx.x;
+    // qlen0 < 0: launched right behind a host-driven level, whose next
+    // frontier size is in ctrl->qn_count; an empty frontier ends the search
+    // and one above the limit goes back to the host, both before any level
+    bool run = true;
+    if (qlen0 < 0) {
+        qlen0 = (int32_t)ctrl->qn_count;
+        if (qlen0 == 0 || qlen0 > qlimit) run = false;
+    }
+    auto not_run = [&]() {
+        ctrl->done = qlen0 == 0 ? 1 : 2;
+        ctrl->qlen = qlen0;
+        ctrl->level = lvl0;
+        ctrl->steps = 0;
+        ctrl->reached = 0;
+        ctrl->levels = 0;
+    };
+    if (run) {
+        const uint32_t lim = slice_limits(S, Qa, (int64_t)qlen0 * w / N, (int64_t)qlen0 * (w + 1) / N,
+                                          off, dlimit);
+        if (t == 0) {
+            scoped_store<false>(&slots->cnt[0][w], (uint64_t)0);
+            scoped_store<false>(&slots->cnt[1][w], (uint64_t)0);
+            scoped_store<false>(&slots->deg[0][w], (uint64_t)0);
+            scoped_store<false>(&slots->deg[1][w], ((uint64_t)1 << 32) | lim);
+            // the slots have reached the other XCDs before this arrival does
+            __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+            // one 7-bit count of arrivals per XCC; the sign bit calls off
+            const uint32_t xcc = __builtin_amdgcn_s_getreg((2 << 11) | 20);  // XCC_ID[2:0]
+            const uint64_t one = 1ull << (7 * xcc);
+            uint64_t a = __hip_atomic_fetch_add(&sy->arrive, one, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT) + one;
+            uint32_t spins = 0;
+            while (!(a >> 63) && arrivals(a) < N) {
+                if (++spins > kStartCap) {
+                    uint64_t seen = a;
+                    if (__hip_atomic_compare_exchange_strong(&sy->arrive, &seen, a | (1ull << 63),
+                                                             __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                             __HIP_MEMORY_SCOPE_AGENT))
+                        not_run();
+                }
+                a = __hip_atomic_load(&sy->arrive, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
+            s_go = (a >> 63) ? 0 : (a == one * (uint64_t)N ? 2 : 1);
+        }
+        __syncthreads();
+        if (s_go == 2)
+            small_levels_body<true>(S, V, off, col, orig, vis, Qa, Qb, level, parent, sy,
+                                    slots, ctrl, N, w, qlen0, lvl0, qlimit, rlimit, dlimit, maxdeg);
+        else if (s_go == 1)
+            small_levels_body<false>(S, V, off, col, orig, vis, Qa, Qb, level, parent, sy,
+                                     slots, ctrl, N, w, qlen0, lvl0, qlimit, rlimit, dlimit, maxdeg);
+    } else if (w == 0 && t == 0) {
+        not_run();
+    }
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): the edge counts have been added
+    __syncthreads();
+    if (t == 0) {
+        const uint32_t k =
+            __hip_atomic_fetch_add(&sy->leave, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((int)k == N - 1) {
+            ctrl->r_total = __hip_atomic_load(&sy->edges, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            sy->arrive = 0;
+            sy->spill = 0;
             sy->edges = 0;
             sy->leave = 0;
         }
@@ -418,23 +806,26 @@ __global__ __launch_bounds__(kWG) void k_small_levels(
 int small_loop_blocks()
 {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_small_levels, kWG, 0) != hipSuccess)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_small_levels, kSW, 0) != hipSuccess)
         return 0;
     return n;
 }
 
-hipError_t launch_small_levels(hipStream_t s, int grid, int32_t V, const int64_t* off,
+hipError_t launch_small_levels(hipStream_t s, int wgs, int cls, int32_t V, const int64_t* off,
                                const int32_t* col, const int32_t* orig, uint32_t* vis,
-                               uint32_t* vis_old, int32_t* Qa, int32_t* Qb, int32_t* level,
-                               int32_t* parent, SmallSync* sy, SmallSide side, Ctrl* ctrl,
+                               int32_t* Qa, int32_t* Qb, int32_t* level,
+                               int32_t* parent, SmallSync* sy, uint32_t* slot_words, Ctrl* ctrl,
                                int32_t qlen, int32_t lvl, int32_t qlimit, int64_t rlimit,
-                               int32_t dlimit)
+                               int32_t dlimit, int32_t maxdeg)
 {
-    // An ordinary launch: the grid (at most one workgroup per CU) is small
-    // enough to be resident at once, and a cooperative launch would make
-    // the runtime stop overlapping later kernels of other streams.
-    hipLaunchKernelGGL(k_small_levels, dim3(grid), dim3(kWG), 0, s, V, off, col, orig, vis, vis_old,
-                       Qa, Qb, level, parent, sy, side, ctrl, qlen, lvl, qlimit, rlimit, dlimit);
+    // An ordinary launch: the workgroups that take part are few enough to be
+    // resident at once, and a cooperative launch would make the runtime stop
+    // overlapping later kernels of other streams.
+    if (wgs < 1 || wgs > kSmallMaxWGs) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_small_levels, dim3(wgs * kXcdSlices), dim3(kSW), 0, s, V, off, col, orig,
+                       vis, Qa, Qb, level, parent, sy,
+                       reinterpret_cast<SmallSlots*>(slot_words), ctrl, cls, qlen, lvl, qlimit,
+                       rlimit, dlimit, maxdeg);
     return hipGetLastError();
 }
 

@@ -24,6 +24,20 @@ __device__ __forceinline__ T wave_inclusive_scan(T x)
     return x;
 }
 
+// Inclusive scan of a 32-bit value over the wave by DPP row shifts and
+// broadcasts (a few cycles a step, where a shuffle goes through the LDS).
+// Every lane of the wave must be active.
+__device__ __forceinline__ int32_t wave_inclusive_scan_dpp(int32_t x)
+{
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);  // row_shr:2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);  // row_shr:4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);  // row_shr:8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31
+    return x;
+}
+
 // Exclusive scan over the 256 threads of a workgroup; *total receives the
 // sum.  s_wave must hold kWG / 64 elements.  Contains two barriers: every
 // thread of the workgroup must call it.
