@@ -243,7 +243,9 @@ int bfs_graph_create(bfs_graph** out, int32_t V, int64_t nnz, const int64_t* d_r
         (void)hipSetDevice(prev);
         return cleanup(hip_fail(e, "hipHostMalloc"));
     }
+    g->h_ctrl->seq = 0;
     g->h_ms_ctrl = g->h_ctrl + 1;
+    g->h_ms_ctrl->seq = 0;
     g->h_roots = reinterpret_cast<int32_t*>(g->h_ctrl + 2);
     if ((e = hipEventCreate(&g->ev0)) != hipSuccess || (e = hipEventCreate(&g->ev1)) != hipSuccess) {
         (void)hipSetDevice(prev);
@@ -513,7 +515,7 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
     // clears the flags of a search that may use them
     uint8_t* const flags = g->claim_mode != 0 ? g->found : nullptr;
     BFS_HIP_TRY(launch_init(s, g->V, g->W, root, g->rank, lv_s, pa_s, g->vis, g->vis_old,
-                            g->q[0], g->ctrl, grid_cap, g->rank ? 0 : 1, flags));
+                            g->q[0], g->ctrl, g->small_sync, grid_cap, g->rank ? 0 : 1, flags));
     const int32_t sum_words = g->summary_words;
     const int xgrid_full = g->num_cus * std::min(g->grid_wgs, expand_blocks_per_cu(g->ept, 0));
     const int xgrid_sum = g->num_cus * std::min(g->grid_wgs, expand_blocks_per_cu(g->ept, sum_words));
@@ -526,9 +528,25 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
     int64_t reached = 1, edges = 0, xbytes = 0, xalg = 0;
     int32_t nlevels = 1, bitmap_levels = 0, xlaunches = 0, dev_levels = 0;
     const bool dev_ok = g->loop_driver != 1 && g->small_grid > 0;
-    // the persistent loop's sync block: zero once per search (each launch
-    // leaves it zero; the workspace's contents before the search are unknown)
-    if (dev_ok) BFS_HIP_TRY(hipMemsetAsync(g->small_sync, 0, sizeof(SmallSync), s));
+    // read-backs of the control block: the persistent loop publishes it itself
+    // at its end, other points have a launch of their own for it
+    Ctrl* const mirror = g->pinned ? g->h_ctrl : nullptr;
+    auto read_back = [&](bool published) -> int {
+        if (!mirror) {
+            BFS_HIP_TRY(hipMemcpyAsync(g->h_ctrl, g->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
+            BFS_HIP_TRY(hipStreamSynchronize(s));
+        } else {
+            if (!published)
+                BFS_HIP_TRY(launch_publish(s, g->ctrl, offsetof(Ctrl, seq), mirror, &mirror->seq,
+                                           ++g->seq));
+            const int rc = wait_published(&mirror->seq, g->seq, s);
+            if (rc != BFS_OK) return rc;
+        }
+        if (g->h_ctrl->err)
+            return fail(BFS_ERR_HIP, "internal guard tripped (code %d)", g->h_ctrl->err);
+        return BFS_OK;
+    };
+    int rc = BFS_OK;
     bool dev_left = false;  // the persistent loop just handed a heavy level back
     bool old_left = false;  // ... after levels of its own: vis_old is behind vis
     // direction-optimizing mode: the degree sum of the frontier a bottom-up
@@ -548,10 +566,8 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
                                          g->s_off, g->s_col, g->orig, g->vis, g->vis_old, lv_s,
                                          pa_s, lvl, g->ctrl, sum_grid, g->summary_shift,
                                          g->summary_blocks, g->summary));
-            BFS_HIP_TRY(hipMemcpyAsync(g->h_ctrl, g->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
-            BFS_HIP_TRY(hipStreamSynchronize(s));
+            if ((rc = read_back(false)) != BFS_OK) return rc;
             const Ctrl& c = *g->h_ctrl;
-            if (c.err) return fail(BFS_ERR_HIP, "internal guard tripped (code %d)", c.err);
             const int64_t found = c.bu_found;
             edges += bu_front_deg;  // the searched frontier's vertices are reached ones
             examined += c.bu_edges;
@@ -579,14 +595,13 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
         if (dev_ok && !dev_left && qlen <= g->small_limit) {
             BFS_HIP_TRY(launch_small_levels(s, g->small_grid, g->small_cls, g->V, g->s_off, g->s_col,
                                             g->orig, g->vis, g->q[cur], g->q[cur ^ 1], lv_s, pa_s,
-                                            g->small_sync, g->summary, g->ctrl, qlen,
+                                            g->small_sync, g->summary, g->ctrl, mirror,
+                                            mirror ? ++g->seq : 0, qlen,
                                             lvl, g->small_limit,
                                             (int64_t)g->small_grid * kSmallDeg, kSmallDeg,
                                             g->maxdeg));
-            BFS_HIP_TRY(hipMemcpyAsync(g->h_ctrl, g->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
-            BFS_HIP_TRY(hipStreamSynchronize(s));
+            if ((rc = read_back(true)) != BFS_OK) return rc;
             const Ctrl& c = *g->h_ctrl;
-            if (c.err) return fail(BFS_ERR_HIP, "internal guard tripped (code %d)", c.err);
             reached += c.reached;
             nlevels += c.levels;
             edges += c.r_total;
@@ -647,10 +662,7 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
             // the frontier's edge count decides the direction (Beamer et
             // al.): bottom-up when it exceeds the unvisited vertices' edges
             // divided by alpha; the scan is then not used
-            BFS_HIP_TRY(hipMemcpyAsync(g->h_ctrl, g->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
-            BFS_HIP_TRY(hipStreamSynchronize(s));
-            if (g->h_ctrl->err)
-                return fail(BFS_ERR_HIP, "internal guard tripped (code %d)", g->h_ctrl->err);
+            if ((rc = read_back(false)) != BFS_OK) return rc;
             const int64_t mf = g->h_ctrl->r + (skip_rows ? g->h_ctrl->skipped : 0);
             const int64_t mu = g->nnz - edges - mf;
             if (mf * g->do_alpha > mu) {
@@ -703,15 +715,14 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
         if (spec) {
             BFS_HIP_TRY(launch_small_levels(s, g->small_grid, g->small_cls, g->V, g->s_off, g->s_col,
                                             g->orig, g->vis, Qn, g->q[cur], lv_s, pa_s,
-                                            g->small_sync, g->summary, g->ctrl, -1, lvl + 1,
+                                            g->small_sync, g->summary, g->ctrl, mirror,
+                                            mirror ? ++g->seq : 0, -1, lvl + 1,
                                             g->small_limit, (int64_t)g->small_grid * kSmallDeg,
                                             kSmallDeg, g->maxdeg));
         }
-        BFS_HIP_TRY(hipMemcpyAsync(g->h_ctrl, g->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
-        BFS_HIP_TRY(hipStreamSynchronize(s));
-        if (g->h_ctrl->err)
-            return fail(BFS_ERR_HIP, "internal guard tripped (code %d)", g->h_ctrl->err);
+        if ((rc = read_back(spec)) != BFS_OK) return rc;
         if (prof) {
+            BFS_HIP_TRY(hipEventSynchronize(g->pev[3]));
             acc.scan_ms += event_ms(g->pev[0], g->pev[1]);
             acc.expand_ms += event_ms(g->pev[1], g->pev[2]);
             acc.compact_ms += event_ms(g->pev[2], g->pev[3]);

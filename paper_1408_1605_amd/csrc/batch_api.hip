@@ -167,8 +167,9 @@ extern "C" int bfs_run_batch(bfs_graph* g, const int32_t* h_roots, int32_t n_roo
             BFS_HIP_TRY(enqueue_level(g, s, b, parity));
             parity ^= 1;
         }
-        BFS_HIP_TRY(hipMemcpyAsync(g->h_ms_ctrl, g->ms_ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
-        BFS_HIP_TRY(hipStreamSynchronize(s));
+        BFS_HIP_TRY(launch_publish(s, g->ms_ctrl, offsetof(Ctrl, seq), g->h_ms_ctrl,
+                                   &g->h_ms_ctrl->seq, ++g->seq));
+        if ((rc = wait_published(&g->h_ms_ctrl->seq, g->seq, s)) != BFS_OK) return rc;
         if (g->h_ms_ctrl->done) break;
         if (++rounds > max_rounds) return fail(BFS_ERR_HIP, "batch level loop did not terminate");
     }

@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 namespace bfsmi {
@@ -68,15 +69,21 @@ struct alignas(64) Ctrl {
     int64_t next_deg;    // degree sum of the next frontier, when the compaction is asked for it
     // batch: lanes this level searches from the unseen side (k_ms_pull)
     uint64_t pull;
+    // only in the pinned host mirror: stored last, counts the read-backs
+    alignas(16) uint64_t seq;
+    uint64_t pad6;
 };
 
 
+struct SmallSync;  // below
+
 // ---- single-root kernels (frontier.hip) ----
+// Also clears the persistent loop's sync block.
 // fill == 0: only the root's level / parent entries (degree order; the
 // finish pass masks unvisited vertices).
 hipError_t launch_init(hipStream_t s, int32_t V, int32_t W, int32_t root,
                        const int32_t* rank, int32_t* level, int32_t* parent,
-                       uint32_t* vis, uint32_t* vis_old, int32_t* Q, Ctrl* ctrl,
+                       uint32_t* vis, uint32_t* vis_old, int32_t* Q, Ctrl* ctrl, SmallSync* sy,
                        int grid_cap, int fill, uint8_t* found = nullptr);
 
 // Degree scan of the frontier Q: deg, cumul (exclusive, cumul[qlen] = r),
@@ -138,12 +145,14 @@ int small_loop_blocks();
 // .. of a launch run on; slot_words: kSummaryMaxWords words of scratch, any
 // contents.  qlen < 0: the frontier size is read from ctrl->qn_count (the
 // previous host-driven level's output); the loop then runs no level when it
-// is 0 or above qlimit.  The loop does not keep vis_old.  rlimit is at most 8192 * wgs; maxdeg: the graph's
+// is 0 or above qlimit.  h_ctrl non-null: pinned host mirror of ctrl, published
+// at the end with sequence number seq.  The loop does not keep vis_old.  rlimit is at most 8192 * wgs; maxdeg: the graph's
 // largest degree.
 hipError_t launch_small_levels(hipStream_t s, int wgs, int cls, int32_t V, const int64_t* off,
                                const int32_t* col, const int32_t* orig, uint32_t* vis,
                                int32_t* Qa, int32_t* Qb, int32_t* level,
                                int32_t* parent, SmallSync* sy, uint32_t* slot_words, Ctrl* ctrl,
+                               Ctrl* h_ctrl, uint64_t seq,
                                int32_t qlen, int32_t lvl, int32_t qlimit, int64_t rlimit,
                                int32_t dlimit, int32_t maxdeg);
 

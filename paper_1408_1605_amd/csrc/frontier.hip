@@ -34,7 +34,7 @@ __global__ __launch_bounds__(kWG) void k_init(int32_t V, int32_t W, int32_t root
                                               uint32_t* __restrict__ vis,
                                               uint32_t* __restrict__ vis_old,
                                               int32_t* __restrict__ Q, Ctrl* __restrict__ ctrl,
-                                              int vec, int fill, uint4* __restrict__ found16,
+                                              SmallSync* __restrict__ sy, int vec, int fill, uint4* __restrict__ found16,
                                               int64_t n_found16)
 {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -78,6 +78,9 @@ __global__ __launch_bounds__(kWG) void k_init(int32_t V, int32_t W, int32_t root
         vis[i] = w;
         vis_old[i] = w;
     }
+    constexpr int kSyncWords = sizeof(SmallSync) / 4;
+    static_assert(kSyncWords <= kWG, "one word per thread");
+    if (blockIdx.x == 0 && threadIdx.x < kSyncWords) reinterpret_cast<uint32_t*>(sy)[threadIdx.x] = 0;
     if (tid == 0) {
         Q[0] = rin;
         ctrl->r = 0;
@@ -98,7 +101,8 @@ __global__ __launch_bounds__(kWG) void k_init(int32_t V, int32_t W, int32_t root
 
 hipError_t launch_init(hipStream_t s, int32_t V, int32_t W, int32_t root, const int32_t* rank,
                        int32_t* level, int32_t* parent, uint32_t* vis, uint32_t* vis_old,
-                       int32_t* Q, Ctrl* ctrl, int grid_cap, int fill, uint8_t* found)
+                       int32_t* Q, Ctrl* ctrl, SmallSync* sy, int grid_cap, int fill,
+                       uint8_t* found)
 {
     const bool vec = ((uintptr_t)level % 16 == 0) &&
                      (parent == nullptr || (uintptr_t)parent % 16 == 0);
@@ -111,7 +115,7 @@ hipError_t launch_init(hipStream_t s, int32_t V, int32_t W, int32_t root, const 
     if (grid > grid_cap) grid = grid_cap;
     if (grid < 1) grid = 1;
     hipLaunchKernelGGL(k_init, dim3((unsigned)grid), dim3(kWG), 0, s, V, W, root, rank, level,
-                       parent, vis, vis_old, Q, ctrl, vec ? 1 : 0, fill,
+                       parent, vis, vis_old, Q, ctrl, sy, vec ? 1 : 0, fill,
                        reinterpret_cast<uint4*>(found), n_found16);
     return hipGetLastError();
 }

@@ -93,8 +93,18 @@ struct Ctl {
     uint32_t dcnt[kMaxP * kMaxP];    // list lengths by (sender p, destination column m)
 };
 constexpr size_t kCtlHead = offsetof(Ctl, tstart);
+static_assert(kCtlHead % 16 == 0, "published in 16-byte words");
+static_assert(sizeof(Plan) % 4 == 0 && sizeof(Plan) <= 4000, "the plan travels as a kernel argument");
 
 constexpr int kMsgAuto = 0, kMsgList = 1, kMsgBitmap = 2;
+
+// The level's plan into device memory (a kernel argument instead of a copy).
+__global__ __launch_bounds__(kWG) void k2_plan(Plan p, Plan* __restrict__ out)
+{
+    const uint32_t* a = reinterpret_cast<const uint32_t*>(&p);
+    for (int i = threadIdx.x; i < (int)(sizeof(Plan) / 4); i += kWG)
+        reinterpret_cast<uint32_t*>(out)[i] = a[i];
+}
 
 // Which processors workgroup blockIdx.x serves (see the file comment): the
 // porder positions [first, end) and its index among the nw workgroups that
@@ -781,8 +791,10 @@ struct bfs_grid2d {
     int32_t* tile_k = nullptr;
     Ctl* ctl = nullptr;
     Plan* plan = nullptr;    // device copy
-    Plan* h_plan = nullptr;  // pinned host
+    Plan* h_plan = nullptr;  // host
     Ctl* h_ctl = nullptr;    // pinned host (head only is read back)
+    uint64_t* h_seq = nullptr;  // pinned host: number of the last read-back
+    uint64_t seq = 0;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     std::atomic<int> busy{0};
 };
@@ -945,7 +957,7 @@ int run2d(bfs_grid2d* g, int32_t root, int32_t msg_mode, int32_t* levels, int32_
             }
         }
         P.lvl = lvl;
-        BFS_HIP_TRY(hipMemcpyAsync(g->plan, g->h_plan, sizeof(Plan), hipMemcpyHostToDevice, s));
+        hipLaunchKernelGGL(k2_plan, dim3(1), dim3(kWG), 0, s, P, g->plan);
         if (P.ub[RC] > 0)
             hipLaunchKernelGGL(k2_gather, dim3(std::min(P.ub[RC], cap)), dim3(kWG), 0, s, g->plan,
                                g->dst, g->fbm, g->af, g->ctl);
@@ -967,8 +979,11 @@ int run2d(bfs_grid2d* g, int32_t root, int32_t msg_mode, int32_t* levels, int32_
         hipLaunchKernelGGL(k2_front, dim3(g->slot_grid), dim3(kWG), 0, s, g->plan, g->ctl, g->bm,
                            g->bm_old, g->fbm);
         BFS_HIP_TRY(hipGetLastError());
-        BFS_HIP_TRY(hipMemcpyAsync(g->h_ctl, g->ctl, kCtlHead, hipMemcpyDeviceToHost, s));
-        BFS_HIP_TRY(hipStreamSynchronize(s));
+        BFS_HIP_TRY(launch_publish(s, g->ctl, kCtlHead, g->h_ctl, g->h_seq, ++g->seq));
+        {
+            const int rc = wait_published(g->h_seq, g->seq, s);
+            if (rc != BFS_OK) return rc;
+        }
         const Ctl& c = *g->h_ctl;
         if (c.err) return fail(BFS_ERR_HIP, "internal guard tripped in the 2D search (code %d)", c.err);
         int64_t found = 0;
@@ -1093,9 +1108,13 @@ int bfs_grid2d_create(bfs_grid2d** out, int32_t V, int64_t nnz, const int64_t* d
         g->expand_grid = grid;
         g->slot_grid = std::max(kSlots, cus * 4 / kSlots * kSlots);
     }
-    hipError_t e = hipHostMalloc((void**)&g->h_plan, sizeof(Plan) + sizeof(Ctl), hipHostMallocDefault);
+    constexpr size_t kPlanBytes = (sizeof(Plan) + 15) / 16 * 16;
+    hipError_t e = hipHostMalloc((void**)&g->h_plan, kPlanBytes + sizeof(Ctl) + sizeof(uint64_t),
+                                 hipHostMallocDefault);
     if (e != hipSuccess) return bail(hip_fail(e, "hipHostMalloc"));
-    g->h_ctl = reinterpret_cast<Ctl*>(reinterpret_cast<char*>(g->h_plan) + sizeof(Plan));
+    g->h_ctl = reinterpret_cast<Ctl*>(reinterpret_cast<char*>(g->h_plan) + kPlanBytes);
+    g->h_seq = reinterpret_cast<uint64_t*>(g->h_ctl + 1);
+    *g->h_seq = 0;
     if ((e = hipEventCreate(&g->ev0)) != hipSuccess || (e = hipEventCreate(&g->ev1)) != hipSuccess)
         return bail(hip_fail(e, "hipEventCreate"));
 

@@ -110,6 +110,7 @@ extern "C" int bfs_run_noalloc(int32_t V, int64_t nnz, const int64_t* d_row_offs
     g.num_cus = d->num_cus;
     g.small_grid = d->small_grid;
     g.h_ctrl = &d->h_ctrl;
+    g.pinned = false;
     bind_workspace(&g, d->base, L, 0);
 
     const auto t0 = std::chrono::steady_clock::now();

@@ -80,6 +80,8 @@ struct bfs_graph {
 
     bfsmi::Ctrl* h_ctrl = nullptr;      // pinned host mirror
     bfsmi::Ctrl* h_ms_ctrl = nullptr;   // pinned host mirror
+    bool pinned = true;                 // (false: h_ctrl is ordinary host memory)
+    uint64_t seq = 0;                   // read-backs so far, both mirrors
     hipStream_t cap_stream = nullptr;   // private stream for graph capture
     hipGraphExec_t ms_graph = nullptr;  // captured batch levels
     int ms_graph_ept = 0;
@@ -124,6 +126,13 @@ void bind_workspace(bfs_graph* g, char* ws, const WsLayout& L, uint32_t flags);
 // has made its device current.
 int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
                   hipStream_t s, bfs_stats* st);
+
+// Read-backs (mirror.hip): the stream copies bytes (a multiple of 16) from
+// device memory to pinned host memory and then stores seq to *flag (pinned
+// too); wait_published returns once it has.  Both words belong to one reader.
+hipError_t launch_publish(hipStream_t s, const void* src, size_t bytes, void* dst, uint64_t* flag,
+                          uint64_t seq);
+int wait_published(const uint64_t* flag, uint64_t seq, hipStream_t s);
 
 // Workgroups of the persistent small-level loop on a device with num_cus
 // compute units (0: the loop is not available).

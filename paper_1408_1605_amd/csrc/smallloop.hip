@@ -112,6 +112,18 @@ __device__ __forceinline__ void scoped_store(T* p, T x)
         __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The launch's result, visible to the workgroup that leaves last.
+__device__ __forceinline__ void report(Ctrl* ctrl, int32_t done, int32_t qlen, int32_t level,
+                                       int32_t steps, int64_t reached, int32_t levels)
+{
+    scoped_store<false>(&ctrl->done, done);
+    scoped_store<false>(&ctrl->qlen, qlen);
+    scoped_store<false>(&ctrl->level, level);
+    scoped_store<false>(&ctrl->steps, steps);
+    scoped_store<false>(&ctrl->reached, reached);
+    scoped_store<false>(&ctrl->levels, levels);
+}
+
 // Queue entries are read past the L1: other workgroups write them during the
 // launch, and no barrier invalidates it.  (Also applied to shares in LDS.)
 __device__ __forceinline__ int32_t queue_load(const int32_t* p)
@@ -192,7 +204,7 @@ __device__ __forceinline__ void keep_winners(const int32_t (&vv)[NE], const bool
             } else {
                 const uint32_t q = q0 + (pos - over0);
                 if (q < (uint32_t)V) scoped_store<L>(Qn + q, v);
-                else ctrl->err = 5;
+                else scoped_store<false>(&ctrl->err, 5);
             }
         }
         base += (uint32_t)__popcll(mask[j]);
@@ -280,7 +292,7 @@ __device__ __forceinline__ void merge_hot(uint32_t* hot, int32_t lvl, int32_t V,
             } else {
                 const uint32_t q = q0 + (pos - over0);
                 if (q < (uint32_t)V) scoped_store<L>(Qn + q, v);
-                else ctrl->err = 5;
+                else scoped_store<false>(&ctrl->err, 5);
             }
             level[v] = lvl;
         }
@@ -446,18 +458,11 @@ __device__ __forceinline__ void small_levels_body(
 
     int2 bar = wait_slots(slots->deg[1], 1, N, w, 0, S);
     if (!(bar.y & kBarOk)) {
-        if (t == 0) ctrl->err = 4;
+        if (t == 0) scoped_store<false>(&ctrl->err, 4);
         return;
     }
     if (bar.x > rlimit || (bar.y & kBarAny)) {
-        if (w == 0 && t == 0) {
-            ctrl->done = 2;
-            ctrl->qlen = qlen0;
-            ctrl->level = lvl0;
-            ctrl->steps = 0;
-            ctrl->reached = 0;
-            ctrl->levels = 0;
-        }
+        if (w == 0 && t == 0) report(ctrl, 2, qlen0, lvl0, 0, 0, 0);
         return;
     }
     bool merge = bar.x > kMergeEdges;
@@ -651,7 +656,7 @@ __device__ __forceinline__ void small_levels_body(
             for (int32_t i = t; i < n; i += kSW) {
                 const int64_t q = (int64_t)spilled + pre + i;
                 if (q < V) scoped_store<L>(Qx + q, S.nv[buf][i]);
-                else ctrl->err = 5;
+                else scoped_store<false>(&ctrl->err, 5);
             }
             if (back) {
                 code = 2;
@@ -692,21 +697,15 @@ __device__ __forceinline__ void small_levels_body(
         }
     }
     if (code == 3) {
-        if (t == 0) ctrl->err = 4;
+        if (t == 0) scoped_store<false>(&ctrl->err, 4);
         return;
     }
     int64_t e = my_edges;
     for (int o = 32; o >= 1; o >>= 1) e += __shfl_xor(e, o, 64);
     if ((t & 63) == 0 && e)
         atomicAdd(reinterpret_cast<unsigned long long*>(&sy->edges), (unsigned long long)e);
-    if (w == 0 && t == 0) {
-        ctrl->done = code;
-        ctrl->qlen = qlen;
-        ctrl->level = lvl;
-        ctrl->steps = step;
-        ctrl->reached = reached;
-        ctrl->levels = code == 1 ? step - 1 : step;
-    }
+    if (w == 0 && t == 0)
+        report(ctrl, code, qlen, lvl, step, reached, code == 1 ? step - 1 : step);
 }
 
 __device__ __forceinline__ int arrivals(uint64_t a)
@@ -718,14 +717,14 @@ __device__ __forceinline__ int arrivals(uint64_t a)
 }
 
 // Workgroups b with b mod 8 == cls take part; the launch leaves its sync
-// block as it found it (zero): the workgroup that leaves last publishes the
-// edge total and clears the block.
+// block as it found it (zero): the workgroup that leaves last stores the edge
+// total, clears the block and publishes the control block to the host.
 __global__ __launch_bounds__(kSW) void k_small_levels(
     int32_t V, const int64_t* __restrict__ off, const int32_t* __restrict__ col,
     const int32_t* __restrict__ orig, uint32_t* __restrict__ vis,
     int32_t* __restrict__ Qa, int32_t* __restrict__ Qb, int32_t* __restrict__ level,
     int32_t* __restrict__ parent, SmallSync* __restrict__ sy, SmallSlots* __restrict__ slots,
-    Ctrl* __restrict__ ctrl, int32_t cls, int32_t qlen0, int32_t lvl0, int32_t qlimit,
+    Ctrl* __restrict__ ctrl, Ctrl* __restrict__ h_ctrl, uint64_t seq, int32_t cls, int32_t qlen0, int32_t lvl0, int32_t qlimit,
     int64_t rlimit, int32_t dlimit, int32_t maxdeg)
 {
     if ((int)(blockIdx.x & (kXcdSlices - 1)) != cls) return;
@@ -742,14 +741,7 @@ __global__ __launch_bounds__(kSW) void k_small_levels(
         qlen0 = (int32_t)ctrl->qn_count;
         if (qlen0 == 0 || qlen0 > qlimit) run = false;
     }
-    auto not_run = [&]() {
-        ctrl->done = qlen0 == 0 ? 1 : 2;
-        ctrl->qlen = qlen0;
-        ctrl->level = lvl0;
-        ctrl->steps = 0;
-        ctrl->reached = 0;
-        ctrl->levels = 0;
-    };
+    auto not_run = [&]() { report(ctrl, qlen0 == 0 ? 1 : 2, qlen0, lvl0, 0, 0, 0); };
     if (run) {
         const uint32_t lim = slice_limits(S, Qa, (int64_t)qlen0 * w / N, (int64_t)qlen0 * (w + 1) / N,
                                           off, dlimit);
@@ -788,17 +780,36 @@ __global__ __launch_bounds__(kSW) void k_small_levels(
     } else if (w == 0 && t == 0) {
         not_run();
     }
-    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): the edge counts have been added
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): edge counts and result are stored
     __syncthreads();
-    if (t == 0) {
-        const uint32_t k =
-            __hip_atomic_fetch_add(&sy->leave, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if ((int)k == N - 1) {
-            ctrl->r_total = __hip_atomic_load(&sy->edges, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (t < 64) {
+        uint32_t k = 0;
+        if (t == 0)
+            k = __hip_atomic_fetch_add(&sy->leave, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        k = __builtin_amdgcn_readfirstlane(k);
+        if ((int)k != N - 1) return;
+        const int64_t edges =
+            __hip_atomic_load(&sy->edges, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (t == 0) {
+            ctrl->r_total = edges;
             sy->arrive = 0;
             sy->spill = 0;
             sy->edges = 0;
             sy->leave = 0;
+        }
+        if (h_ctrl) {
+            // the mirror: a lane per 8 bytes, then the sequence number
+            constexpr int n8 = offsetof(Ctrl, seq) / 8;
+            static_assert(n8 <= 64, "one lane per word");
+            if (t < n8) {
+                uint64_t x = __hip_atomic_load(reinterpret_cast<const uint64_t*>(ctrl) + t,
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (t == offsetof(Ctrl, r_total) / 8) x = (uint64_t)edges;
+                reinterpret_cast<uint64_t*>(h_ctrl)[t] = x;
+            }
+            __threadfence_system();
+            if (t == 0)
+                __hip_atomic_store(&h_ctrl->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
         }
     }
 }
@@ -815,7 +826,7 @@ hipError_t launch_small_levels(hipStream_t s, int wgs, int cls, int32_t V, const
                                const int32_t* col, const int32_t* orig, uint32_t* vis,
                                int32_t* Qa, int32_t* Qb, int32_t* level,
                                int32_t* parent, SmallSync* sy, uint32_t* slot_words, Ctrl* ctrl,
-                               int32_t qlen, int32_t lvl, int32_t qlimit, int64_t rlimit,
+                               Ctrl* h_ctrl, uint64_t seq, int32_t qlen, int32_t lvl, int32_t qlimit, int64_t rlimit,
                                int32_t dlimit, int32_t maxdeg)
 {
     // An ordinary launch: the workgroups that take part are few enough to be
@@ -824,8 +835,8 @@ hipError_t launch_small_levels(hipStream_t s, int wgs, int cls, int32_t V, const
     if (wgs < 1 || wgs > kSmallMaxWGs) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_small_levels, dim3(wgs * kXcdSlices), dim3(kSW), 0, s, V, off, col, orig,
                        vis, Qa, Qb, level, parent, sy,
-                       reinterpret_cast<SmallSlots*>(slot_words), ctrl, cls, qlen, lvl, qlimit,
-                       rlimit, dlimit, maxdeg);
+                       reinterpret_cast<SmallSlots*>(slot_words), ctrl, h_ctrl, seq, cls, qlen,
+                       lvl, qlimit, rlimit, dlimit, maxdeg);
     return hipGetLastError();
 }
 
