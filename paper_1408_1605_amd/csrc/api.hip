@@ -16,6 +16,9 @@ namespace bfsmi {
 constexpr int32_t kSmallQ = 1 << 16;  // frontiers up to this size may run in the persistent loop
 constexpr int32_t kSmallDeg = 8192;   // ... if no frontier vertex has a larger degree
 constexpr int kSmallWGs = 32;         // workgroups of the persistent loop
+// levels whose scan came with the compaction take the summary's block bits from
+// this size on (R-MAT 26 4% faster with them, R-MAT 22 and 24 unchanged)
+constexpr int32_t kLdsSummaryMinV = 1 << 25;
 
 
 static thread_local char g_err[512] = "";
@@ -556,6 +559,13 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
     bool bu_done = false;  // the search has switched back from bottom-up
     int64_t bu_front_deg = 0, bu_prev = 0, examined = 0;
     int32_t bu_levels = 0;
+    // one-launch scans (not with the direction-optimizing mode, which looks at
+    // a level's edges before it decides how to search it)
+    const bool fuse = !dir_opt && g->nnz < kPackMaxEdges;
+    int pk = 0;             // ctrl->pack[pk]: this host-driven level's size
+    bool scanned = false;   // the current frontier's scan is there
+    bool prefixed = false;  // ... and ctrl->full_prefix is its level's prefix
+    int64_t r_next = 0;     // its edges
     const int nb_grid = (int)std::max<int64_t>(
         1, std::min<int64_t>(((int64_t)g->W + kBitmapWordsPerWG - 1) / kBitmapWordsPerWG, grid_cap));
     const int sum_grid = std::max(1, std::min(grid_cap, (g->summary_blocks + 31) / 32));
@@ -618,14 +628,6 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
         dev_left = false;
         const int32_t* Q = g->q[cur];
         int32_t* Qn = g->q[cur ^ 1];
-        int64_t rmax = (int64_t)qlen * (int64_t)g->maxdeg;
-        if (rmax > g->nnz) rmax = g->nnz;
-        const int64_t tiles_ub = (rmax + tile - 1) / tile;
-        // heavy levels get the visited summary (a cheap pass over the bitmap):
-        // the fully visited prefix always, the LDS block bits in mode 2; it
-        // runs before the degree scan so the scan can drop row prefixes
-        const bool use_sum = g->use_summary > 0 && rmax > T;
-        const bool lds_sum = use_sum && g->use_summary == 2;
         // XCD-sliced level: each XCD probes its eighth of the bitmap (for
         // early levels with few, high-degree frontier vertices: the level
         // after the hubs on large graphs); the row prefix skip is not used
@@ -633,23 +635,49 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
             g->xo && g->xcd_slices != 0 && !dir_opt && (int64_t)qlen * kXcdSlices <= g->V &&
             (g->xcd_slices == 2 ||
              (g->V >= kSliceMinV && reached * kXcdSlices <= (int64_t)g->V));
-        const bool skip_rows = use_sum && g->skip && g->row_skip && !sliced;
+        const bool have = scanned && !sliced;  // the level before left the scan
+        int64_t rmax = (int64_t)qlen * (int64_t)g->maxdeg;
+        if (rmax > g->nnz) rmax = g->nnz;
+        if (have) rmax = r_next;
+        const int64_t tiles_ub = (rmax + tile - 1) / tile;
+        // heavy levels get the visited summary (a cheap pass over the bitmap):
+        // the fully visited prefix always, the LDS block bits in mode 2; it
+        // runs before the degree scan so the scan can drop row prefixes
+        // (no prefix below the smallest skip threshold pays for its launches:
+        // R-MAT 16 and a plain graph of 10^6 vertices are 10 to 15 us faster
+        // without any, R-MAT 22 and 26 a quarter and a half slower)
+        const bool use_sum = g->use_summary > 0 && rmax > T &&
+                             (!fuse || (g->rank && reached >= (1 << kSkipLow)));
+        const bool lds_sum = use_sum && g->use_summary == 2 && (!have || g->V >= kLdsSummaryMinV);
+        const bool skip_rows =
+            have ? prefixed : use_sum && g->skip && g->row_skip && !sliced;
         const int grid_cap_x = lds_sum ? xgrid_sum : xgrid_full;
         const int grid = sliced
             ? (int)std::max<int64_t>(kXcdSlices, std::min<int64_t>(
                   (tiles_ub + 2 * kXcdSlices) / kXcdSlices * kXcdSlices, grid_cap_x))
             : (int)std::max<int64_t>(1, std::min<int64_t>(tiles_ub, grid_cap_x));
         if (prof) BFS_HIP_TRY(hipEventRecord(g->pev[0], s));
-        if (use_sum) {
+        if (have) {
+            if (lds_sum)
+                BFS_HIP_TRY(launch_summary_bits(s, sum_grid, g->V, g->W, g->vis, g->summary_shift,
+                                                g->summary_blocks, g->summary));
+        } else if (use_sum) {
             const int gs = std::max(1, std::min(grid_cap, (g->summary_blocks + 31) / 32));
             BFS_HIP_TRY(launch_visited_summary(s, gs, g->V, g->W, g->vis, g->summary_shift,
                                                g->summary_blocks, g->summary, g->ctrl,
                                                old_left ? g->vis_old : nullptr));
-        } else if (old_left) {
-            BFS_HIP_TRY(launch_sync_old(s, grid_cap, g->W, g->vis, g->vis_old));
+            old_left = false;
         }
-        old_left = false;
-        if (sliced)
+        const bool packed = have || (fuse && !sliced && !skip_rows);
+        if (old_left && (sliced || !packed))
+            BFS_HIP_TRY(launch_sync_old(s, grid_cap, g->W, g->vis, g->vis_old));
+        if (have) {
+            // the compaction has scanned this frontier
+        } else if (packed)
+            BFS_HIP_TRY(launch_list_scan(s, Q, qlen, g->s_off, g->orig, g->rowstart, g->suid,
+                                         g->cumul, g->tile_k, tile, g->ctrl, pk, g->W, g->vis,
+                                         old_left ? g->vis_old : nullptr));
+        else if (sliced)
             BFS_HIP_TRY(launch_slice_scan(s, std::max(1, std::min(grid_cap, (qlen + kWG - 1) / kWG)),
                                           Q, qlen, g->s_off, g->xo, g->orig, g->deg, g->rowstart,
                                           g->suid, g->bsum, g->cumul, g->tile_k, tile_cap, tile, T,
@@ -658,6 +686,7 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
             BFS_HIP_TRY(launch_scan(s, Q, qlen, g->s_off, g->orig, g->deg, g->rowstart, g->suid,
                                     g->bsum, g->cumul, g->tile_k, tile_cap, tile, T, allow_bitmap,
                                     g->ctrl, skip_rows ? g->skip : nullptr, g->V));
+        old_left = false;
         if (dir_opt && !bu_done) {
             // the frontier's edge count decides the direction (Beamer et
             // al.): bottom-up when it exceeds the unvisited vertices' edges
@@ -692,8 +721,10 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
                 ? flags : nullptr;
         BFS_HIP_TRY(launch_expand(s, g->ept, grid, g->V, g->rowstart, g->suid, g->cumul,
                                   g->tile_k, sliced ? g->col_x : g->s_col, g->summary,
-                                  lds_sum ? sum_words : 0, g->summary_shift, use_sum ? 1 : 0,
-                                  g->vis, g->vis_old, lv_s, pa_s, lvl, Qn, g->ctrl, lflags,
+                                  lds_sum ? sum_words : 0, g->summary_shift,
+                                  (have ? prefixed : use_sum) ? 1 : 0, g->vis, g->vis_old, lv_s,
+                                  pa_s, lvl, Qn, g->ctrl,
+                                  LevelSize{packed ? pk : -1, allow_bitmap, T}, lflags,
                                   sliced ? qlen : 0));
         xlaunches++;
         if (prof) BFS_HIP_TRY(hipEventRecord(g->pev[2], s));
@@ -701,10 +732,23 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
         if (maybe_bitmap) {
             const int64_t nb = ((int64_t)g->W + kBitmapWordsPerWG - 1) / kBitmapWordsPerWG;
             const int grid2 = (int)std::max<int64_t>(1, std::min<int64_t>(nb, grid_cap));
-            // the direction-optimizing mode also sums the next frontier's
-            // degrees, so the next level's direction is known without a scan
-            BFS_HIP_TRY(launch_bitmap_to_queue(s, grid2, g->V, g->W, g->vis, g->vis_old, Qn, lv_s,
-                                               lvl, g->ctrl, dir_opt ? g->s_off : nullptr, lflags));
+            if (fuse) {
+                // the next level's prefix, where its rows may skip one
+                prefixed = g->skip && g->row_skip && g->use_summary > 0 && g->V > (1 << kSkipLow);
+                if (prefixed)
+                    BFS_HIP_TRY(launch_found_prefix(s, g->num_cus, g->V, g->W, g->vis, lflags,
+                                                    g->ctrl));
+                BFS_HIP_TRY(launch_front_scan(s, g->num_cus, g->V, g->vis, g->vis_old, Qn, lv_s, lvl,
+                                              lflags, g->s_off, g->orig,
+                                              prefixed ? g->skip : nullptr, g->rowstart, g->suid,
+                                              g->cumul, g->tile_k, tile, g->ctrl, pk ^ 1));
+            } else {
+                // the direction-optimizing mode also sums the next frontier's
+                // degrees, so the next level's direction is known without a scan
+                BFS_HIP_TRY(launch_bitmap_to_queue(s, grid2, g->V, g->W, g->vis, g->vis_old, Qn,
+                                                   lv_s, lvl, g->ctrl,
+                                                   dir_opt ? g->s_off : nullptr, lflags));
+            }
         }
         if (prof) BFS_HIP_TRY(hipEventRecord(g->pev[3], s));
         // the persistent loop is queued right behind the level, before the
@@ -716,7 +760,7 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
             BFS_HIP_TRY(launch_small_levels(s, g->small_grid, g->small_cls, g->V, g->s_off, g->s_col,
                                             g->orig, g->vis, Qn, g->q[cur], lv_s, pa_s,
                                             g->small_sync, g->summary, g->ctrl, mirror,
-                                            mirror ? ++g->seq : 0, -1, lvl + 1,
+                                            mirror ? ++g->seq : 0, -1 - (pk ^ 1), lvl + 1,
                                             g->small_limit, (int64_t)g->small_grid * kSmallDeg,
                                             kSmallDeg, g->maxdeg));
         }
@@ -728,8 +772,13 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
             acc.compact_ms += event_ms(g->pev[2], g->pev[3]);
         }
         const int64_t r = g->h_ctrl->r;
-        const uint32_t qn = g->h_ctrl->qn_count;
+        const uint64_t pnext = g->h_ctrl->pack[pk ^ 1];
+        const uint32_t qn = spec ? g->h_ctrl->front_n
+                                 : g->h_ctrl->qn_count + (uint32_t)(pnext & kPackMask);
         const bool bm = g->h_ctrl->bitmap_out != 0;
+        pk ^= 1;
+        scanned = fuse && bm;
+        r_next = (int64_t)(pnext >> kPackBits);
         edges += r + (skip_rows ? g->h_ctrl->skipped : 0);
         examined += r;
         xbytes += 4 * r + 20 * (sliced ? kXcdSlices : 1) * (int64_t)qlen + (parents ? 4 : 0) * (int64_t)qn +
@@ -758,6 +807,7 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
                 qlen = c.qlen;
                 if (c.done == 1) break;  // the frontier ran empty
                 old_left = true;
+                scanned = false;  // the loop has moved on
             }
             continue;
         }

@@ -36,6 +36,7 @@ constexpr int32_t kFlagAutoMaxV = 1 << 25;
 // per level; the kernels read the fields they need directly.
 struct alignas(64) Ctrl {
     int64_t r;           // edges of the current frontier (sum of degrees)
+    int64_t dropped[2];  // edges those scans dropped (not on the packs' line)
     int32_t ntiles;      // ceil(r / tile)
     int32_t bitmap_out;  // 1: next frontier produced in bitmap form
     uint32_t qn_count;   // size of the next frontier
@@ -69,10 +70,18 @@ struct alignas(64) Ctrl {
     int64_t next_deg;    // degree sum of the next frontier, when the compaction is asked for it
     // batch: lanes this level searches from the unseen side (k_ms_pull)
     uint64_t pull;
+    // single-root levels scanned in one launch (launch_list_scan,
+    // launch_front_scan): edges << kPackBits | entries of the level, for
+    // host-driven levels in turn
+    uint64_t pack[2];
+    uint32_t front_n;    // size of the frontier the persistent loop was queued with
+    uint32_t pad7;
     // only in the pinned host mirror: stored last, counts the read-backs
     alignas(16) uint64_t seq;
     uint64_t pad6;
 };
+static_assert(sizeof(Ctrl) <= 256, "the workspace's control blocks are 256 bytes apart");
+static_assert(offsetof(Ctrl, pack) / 128 != offsetof(Ctrl, dropped) / 128, "two lines");
 
 
 struct SmallSync;  // below
@@ -86,7 +95,7 @@ hipError_t launch_init(hipStream_t s, int32_t V, int32_t W, int32_t root,
                        uint32_t* vis, uint32_t* vis_old, int32_t* Q, Ctrl* ctrl, SmallSync* sy,
                        int grid_cap, int fill, uint8_t* found = nullptr);
 
-// Degree scan of the frontier Q: deg, cumul (exclusive, cumul[qlen] = r),
+// Degree scan of the frontier Q (three launches, entries in Q's order): deg, cumul (exclusive, cumul[qlen] = r),
 // rowstart[k] = off[Q[k]], uidv[k] = uid_map ? uid_map[Q[k]] : Q[k], and
 // tile_k (the entry holding each tile's first edge).  With skip (the row
 // prefix skip counts, [kSkipLevels][V]) each entry drops the leading block
@@ -109,6 +118,44 @@ hipError_t launch_scan_dev(hipStream_t s, int grid, const int32_t* Q, const int6
                            int tile, Ctrl* ctrl, const int32_t* skip = nullptr, int32_t V = 0,
                            const uint64_t* front = nullptr);
 
+// The same scan in one launch, for graphs of fewer than 2^32 edges.  The
+// entries' order is free, so a workgroup scans its own chunk and reserves the
+// chunk's places in the entry arrays and in the edge numbering with one atomic
+// on ctrl->pack[par] (zero before).  ctrl->r, skipped and bitmap_out are left
+// to the expansion.  Clears ctrl->qn_count; vis_old non-null: vis_old := vis.
+constexpr int kPackBits = 31;
+constexpr uint64_t kPackMask = (1ull << kPackBits) - 1;
+constexpr int64_t kPackMaxEdges = (int64_t)1 << 32;
+hipError_t launch_list_scan(hipStream_t s, const int32_t* Q, int32_t qlen, const int64_t* off,
+                            const int32_t* uid_map, int64_t* rowstart, int32_t* uidv,
+                            int64_t* cumul, int32_t* tile_k, int tile, Ctrl* ctrl, int par,
+                            int32_t W, const uint32_t* vis, uint32_t* vis_old);
+// launch_bitmap_to_queue and the scan of the frontier it finds, in one launch
+// (into ctrl->pack[par]).  skip: the row prefix skip counts, applied to the
+// prefix launch_found_prefix has found (ctrl->full_prefix is set to it), or null.
+hipError_t launch_front_scan(hipStream_t s, int num_cus, int32_t V, uint32_t* vis,
+                             uint32_t* vis_old, int32_t* Qn, int32_t* level, int32_t lvl,
+                             uint8_t* found, const int64_t* off, const int32_t* uid_map,
+                             const int32_t* skip, int64_t* rowstart, int32_t* uidv,
+                             int64_t* cumul, int32_t* tile_k, int tile, Ctrl* ctrl, int par);
+// First id that is neither visited nor flagged, to ctrl->fp_cand (reset by the
+// expansion).
+hipError_t launch_found_prefix(hipStream_t s, int grid, int32_t V, int32_t W, const uint32_t* vis,
+                               const uint8_t* found, Ctrl* ctrl);
+// The visited summary's block bits alone.
+hipError_t launch_summary_bits(hipStream_t s, int grid, int32_t V, int32_t W, const uint32_t* vis,
+                               int32_t shift, int32_t nblocks, uint32_t* summary);
+
+// Where the expansion finds the level's size: par >= 0: ctrl->pack[par] (the
+// other pack is cleared, and ctrl->r, skipped and bitmap_out are set);
+// par < 0: ctrl->r and bitmap_out as launch_scan leaves them (both packs are
+// cleared).
+struct LevelSize {
+    int par;
+    int allow_bitmap;
+    int64_t bitmap_threshold;
+};
+
 // Expansion of one level (Algorithm 3); level / parent by search id, the
 // level only in list mode (bitmap mode: launch_bitmap_to_queue writes it).
 hipError_t launch_expand(hipStream_t s, int ept, int grid, int32_t V, const int64_t* rowstart,
@@ -116,7 +163,7 @@ hipError_t launch_expand(hipStream_t s, int ept, int grid, int32_t V, const int6
                          const int32_t* col,
                          const uint32_t* summary, int32_t summary_words, int32_t shift,
                          int use_prefix, uint32_t* vis, uint32_t* vis_old, int32_t* level,
-                         int32_t* parent, int32_t lvl, int32_t* Qn, Ctrl* ctrl,
+                         int32_t* parent, int32_t lvl, int32_t* Qn, Ctrl* ctrl, LevelSize size,
                          uint8_t* found = nullptr, int32_t slice_q = 0);
 // XCD-sliced level: the scan of launch_scan over 8 * qlen entries, entry
 // s * qlen + k being slice s's group of frontier entry k's row in the
@@ -143,9 +190,10 @@ struct SmallSync {
 int small_loop_blocks();
 // wgs workgroups (at most kSmallMaxWGs) on the XCD that workgroups cls, cls + 8,
 // .. of a launch run on; slot_words: kSummaryMaxWords words of scratch, any
-// contents.  qlen < 0: the frontier size is read from ctrl->qn_count (the
-// previous host-driven level's output); the loop then runs no level when it
-// is 0 or above qlimit.  h_ctrl non-null: pinned host mirror of ctrl, published
+// contents.  qlen < 0: the frontier size is that of the previous host-driven
+// level's output, ctrl->qn_count + the entries in ctrl->pack[-1 - qlen] (one of
+// them is 0), also stored to ctrl->front_n; the loop then runs no level when it
+// is 0 or above qlimit.  Levels run here leave both packs zero.  h_ctrl non-null: pinned host mirror of ctrl, published
 // at the end with sequence number seq.  The loop does not keep vis_old.  rlimit is at most 8192 * wgs; maxdeg: the graph's
 // largest degree.
 hipError_t launch_small_levels(hipStream_t s, int wgs, int cls, int32_t V, const int64_t* off,

@@ -96,6 +96,9 @@ __global__ __launch_bounds__(kWG) void k_init(int32_t V, int32_t W, int32_t root
         ctrl->bitmap_levels = 0;
         ctrl->err = 0;
         ctrl->skipped = 0;
+        ctrl->pack[0] = ctrl->pack[1] = 0;
+        ctrl->dropped[0] = ctrl->dropped[1] = 0;
+        ctrl->fp_cand = 0x7fffffff;
     }
 }
 
@@ -524,6 +527,16 @@ hipError_t launch_visited_summary(hipStream_t s, int grid, int32_t V, int32_t W,
     return hipGetLastError();
 }
 
+hipError_t launch_summary_bits(hipStream_t s, int grid, int32_t V, int32_t W, const uint32_t* vis,
+                               int32_t shift, int32_t nblocks, uint32_t* summary)
+{
+    const int32_t nwords = (nblocks + 31) / 32;
+    if (grid > nwords) grid = nwords;
+    hipLaunchKernelGGL(k_visited_summary, dim3(grid < 1 ? 1 : grid), dim3(kWG), 0, s, V, W, vis,
+                       shift, nwords, summary, nullptr);
+    return hipGetLastError();
+}
+
 __global__ __launch_bounds__(kWG) void k_sync_old(int32_t W, const uint32_t* __restrict__ vis,
                                                   uint32_t* __restrict__ vis_old)
 {
@@ -563,15 +576,41 @@ __global__ __launch_bounds__(kWG) void k_expand(int32_t V, const int64_t* __rest
                                                 int32_t* __restrict__ level,
                                                 int32_t* __restrict__ parent, int32_t lvl,
                                                 int32_t* __restrict__ Qn,
-                                                Ctrl* __restrict__ ctrl,
+                                                Ctrl* __restrict__ ctrl, LevelSize size,
                                                 uint8_t* __restrict__ found, int32_t slice_q)
 {
     __shared__ TileLds<EPT> L;
     extern __shared__ uint32_t s_sum[];
 
-    const int64_t r = ctrl->r;
-    const int32_t ntiles = ctrl->ntiles;
-    const bool list_out = ctrl->bitmap_out == 0;
+    int64_t r;
+    int32_t ntiles, k_last = -1;
+    bool list_out;
+    if (size.par >= 0) {
+        const uint64_t pk = ctrl->pack[size.par];
+        r = (int64_t)(pk >> kPackBits);
+        ntiles = (int32_t)((r + TileLds<EPT>::TILE - 1) / TileLds<EPT>::TILE);
+        k_last = (int32_t)(pk & kPackMask) - 1;
+        list_out = !((size.allow_bitmap == 2 && r > 0) ||
+                     (size.allow_bitmap == 1 && r > size.bitmap_threshold));
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            ctrl->r = r;
+            ctrl->skipped = ctrl->dropped[size.par];
+            ctrl->bitmap_out = list_out ? 0 : 1;
+            // for the scan at this level's end
+            ctrl->pack[size.par ^ 1] = 0;
+            ctrl->dropped[size.par ^ 1] = 0;
+            ctrl->fp_cand = 0x7fffffff;
+        }
+    } else {
+        r = ctrl->r;
+        ntiles = ctrl->ntiles;
+        list_out = ctrl->bitmap_out == 0;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            ctrl->pack[0] = ctrl->pack[1] = 0;
+            ctrl->dropped[0] = ctrl->dropped[1] = 0;
+            ctrl->fp_cand = 0x7fffffff;
+        }
+    }
     // flag claims: a bitmap level marks its vertices with byte stores
     // instead of claiming bits (below)
     const bool flags = found != nullptr && !list_out;
@@ -595,7 +634,7 @@ __global__ __launch_bounds__(kWG) void k_expand(int32_t V, const int64_t* __rest
     }
     if (t_first >= t_end) return;  // whole workgroup: uniform
 
-    StageRegs<EPT> cur = fetch_stage<EPT>(t_first, t_end, cumul, rowstart, uidv, tile_k);
+    StageRegs<EPT> cur = fetch_stage<EPT>(t_first, t_end, cumul, rowstart, uidv, tile_k, k_last);
     for (int32_t w = threadIdx.x; w < summary_words; w += kWG) s_sum[w] = summary[w];
     __syncthreads();
 
@@ -624,7 +663,7 @@ __global__ __launch_bounds__(kWG) void k_expand(int32_t V, const int64_t* __rest
             if (!known[j]) wd[j] = vis[v >> 5];
         }
         // the next tile's staging loads overlap this tile's probes and claims
-        cur = fetch_stage<EPT>(tile + t_step, t_end, cumul, rowstart, uidv, tile_k);
+        cur = fetch_stage<EPT>(tile + t_step, t_end, cumul, rowstart, uidv, tile_k, k_last);
         bool need[EPT];
 #pragma unroll
         for (int j = 0; j < EPT; ++j) need[j] = !known[j] && !(wd[j] & (1u << (vv[j] & 31)));
@@ -712,7 +751,7 @@ hipError_t launch_expand(hipStream_t s, int ept, int grid, int32_t V, const int6
                          const int32_t* col, const uint32_t* summary,
                          int32_t summary_words, int32_t shift, int use_prefix, uint32_t* vis,
                          uint32_t* vis_old, int32_t* level, int32_t* parent, int32_t lvl,
-                         int32_t* Qn, Ctrl* ctrl, uint8_t* found, int32_t slice_q)
+                         int32_t* Qn, Ctrl* ctrl, LevelSize size, uint8_t* found, int32_t slice_q)
 {
     if (slice_q > 0) grid = grid / kXcdSlices * kXcdSlices;  // every slice the same workgroups
     if (grid < 1) grid = slice_q > 0 ? kXcdSlices : 1;
@@ -724,7 +763,7 @@ hipError_t launch_expand(hipStream_t s, int ept, int grid, int32_t V, const int6
                            tile_k, col, summary, summary_words, shift, use_prefix, vis,           \
                            vis_old,                                                              \
                            level, parent,                                                        \
-                           lvl, Qn, ctrl, found, slice_q);                                       \
+                           lvl, Qn, ctrl, size, found, slice_q);                                       \
         break;
     switch (ept) {
         BFS_EXPAND_CASE(1)
@@ -761,6 +800,41 @@ int expand_blocks_per_cu(int ept, int summary_words)
 // 256 words (8192 vertices); thread j of pass p looks at vertex p * 256 + j
 // of the block, so level stores and queue stores of a wave are contiguous.
 
+// The 32 flag bytes (0 or 1) of word w's ids as bits.
+__device__ __forceinline__ uint32_t flag_bits(const uint4* found16, int64_t w)
+{
+    const uint4 x = found16[2 * w], y = found16[2 * w + 1];
+    const uint32_t q[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+    uint32_t pf = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const uint32_t z = q[k];
+        pf |= ((z & 1u) | ((z >> 7) & 2u) | ((z >> 14) & 4u) | ((z >> 21) & 8u)) << (4 * k);
+    }
+    return pf;
+}
+
+// Word i's bits that turned on during the level: its flags become bits (and
+// are cleared for the next level), and vis_old catches up.
+__device__ __forceinline__ uint32_t new_bits(int64_t i, uint32_t* __restrict__ vis,
+                                             uint32_t* __restrict__ vis_old,
+                                             uint4* __restrict__ found16)
+{
+    uint32_t a = vis[i];
+    if (found16) {
+        const uint32_t pf = flag_bits(found16, i);
+        if (pf) {
+            a |= pf;
+            vis[i] = a;
+            found16[2 * i] = make_uint4(0u, 0u, 0u, 0u);
+            found16[2 * i + 1] = make_uint4(0u, 0u, 0u, 0u);
+        }
+    }
+    const uint32_t f = a & ~vis_old[i];
+    if (f) vis_old[i] = a;
+    return f;
+}
+
 __global__ __launch_bounds__(kWG) void k_bitmap_to_queue(int32_t V, int32_t W,
                                                          uint32_t* __restrict__ vis,
                                                          uint32_t* __restrict__ vis_old,
@@ -780,30 +854,7 @@ __global__ __launch_bounds__(kWG) void k_bitmap_to_queue(int32_t V, int32_t W,
     for (int64_t blk = blockIdx.x; blk < nblocks; blk += gridDim.x) {
         const int64_t i = blk * kBitmapWordsPerWG + threadIdx.x;
         uint32_t f = 0;
-        if (i < W) {
-            uint32_t a = vis[i];
-            if (found16) {
-                // the level's flag bytes (0 or 1) of this word's 32 ids
-                // become bits; the flags are cleared for the next level
-                const uint4 x = found16[2 * i], y = found16[2 * i + 1];
-                const uint32_t q[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
-                uint32_t pf = 0;
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const uint32_t z = q[k];
-                    pf |= ((z & 1u) | ((z >> 7) & 2u) | ((z >> 14) & 4u) | ((z >> 21) & 8u)) << (4 * k);
-                }
-                if (pf) {
-                    a |= pf;
-                    vis[i] = a;
-                    found16[2 * i] = make_uint4(0u, 0u, 0u, 0u);
-                    found16[2 * i + 1] = make_uint4(0u, 0u, 0u, 0u);
-                }
-            }
-            const uint32_t b = vis_old[i];
-            f = a & ~b;
-            if (f) vis_old[i] = a;
-        }
+        if (i < W) f = new_bits(i, vis, vis_old, found16);
         uint32_t tot;
         const uint32_t ex = wg_exclusive_scan<uint32_t>((uint32_t)__popc(f), &tot, s_wave);
         s_f[threadIdx.x] = f;
@@ -844,6 +895,361 @@ hipError_t launch_bitmap_to_queue(hipStream_t s, int grid, int32_t V, int32_t W,
     if (grid < 1) grid = 1;
     hipLaunchKernelGGL(k_bitmap_to_queue, dim3(grid), dim3(kWG), 0, s, V, W, vis, vis_old, Qn,
                        level, lvl, ctrl, deg_off, reinterpret_cast<uint4*>(found));
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// Scan in one launch.  The expansion needs cumul to be increasing over the
+// entries, not a particular order of the entries, so no workgroup has to know
+// what the ones before it hold: each scans its own chunk and takes the
+// chunk's places in the entry arrays and in the edge numbering together, with
+// one atomic on a word that holds both counts.  The frontier of a bitmap
+// level is scanned where the bitmap is compacted, which has its ids and reads
+// its row offsets in id order.  One search, against compaction, reduce, top
+// and down as four launches and two for the visited summary: R-MAT 16 202 ->
+// 152 us, plain graph of 777777 vertices 547 -> 489, R-MAT 22 660 -> 656,
+// R-MAT 26 7.72 -> 7.55 ms (its two dense levels: 830 -> 550 us).
+
+// The heads of the tiles that start inside a chunk: n entries from place p0 on,
+// edges [c0, c0 + total), s_c[i] the edges before entry i within the chunk.
+// One search per tile, so hub entries that cover many tiles need no care.
+__device__ __forceinline__ void write_tile_heads(const uint32_t* s_c, int32_t n, uint32_t total,
+                                                 int32_t p0, int64_t c0, int tile_sh,
+                                                 int32_t* __restrict__ tile_k)
+{
+    if (total == 0) return;
+    const int64_t x1 = (c0 + total - 1) >> tile_sh;
+    for (int64_t x = ((c0 + ((int64_t)1 << tile_sh) - 1) >> tile_sh) + threadIdx.x; x <= x1;
+         x += blockDim.x) {
+        const uint32_t e = (uint32_t)((x << tile_sh) - c0);
+        int32_t lo = 0, hi = n - 1;  // max{i : s_c[i] <= e}
+        while (lo < hi) {
+            const int32_t mid = (lo + hi + 1) >> 1;
+            if (s_c[mid] <= e) lo = mid;
+            else hi = mid - 1;
+        }
+        tile_k[x] = p0 + lo;
+    }
+}
+
+// A list of any order: NI entries per thread.  (The degrees of a chunk add up
+// to less than 2^32: distinct vertices of a graph of fewer than 2^32 edges.)
+template <int NI>
+__global__ __launch_bounds__(kWG) void k_list_scan(const int32_t* __restrict__ Q, int32_t qlen,
+                                                   const int64_t* __restrict__ off,
+                                                   const int32_t* __restrict__ uid_map,
+                                                   int64_t* __restrict__ rowstart,
+                                                   int32_t* __restrict__ uidv,
+                                                   int64_t* __restrict__ cumul,
+                                                   int32_t* __restrict__ tile_k, int tile_sh,
+                                                   Ctrl* __restrict__ ctrl, int par, int32_t W,
+                                                   const uint32_t* __restrict__ vis,
+                                                   uint32_t* __restrict__ vis_old)
+{
+    __shared__ uint32_t s_wave[kWG / 64];
+    __shared__ uint32_t s_c[kWG * NI];
+    __shared__ uint64_t s_base;
+    const int t = threadIdx.x;
+    const int64_t q0 = (int64_t)blockIdx.x * kWG * NI;
+    const int32_t n = (int32_t)(qlen - q0 < kWG * NI ? qlen - q0 : kWG * NI);
+    if (blockIdx.x == 0 && t == 0) ctrl->qn_count = 0;
+    int32_t u[NI], id[NI];
+    int64_t a[NI];
+    uint32_t d[NI], sum = 0;
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+        const int32_t i = t * NI + j;
+        u[j] = Q[q0 + (i < n ? i : n - 1)];
+    }
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+        a[j] = off[u[j]];
+        d[j] = t * NI + j < n ? (uint32_t)(off[u[j] + 1] - a[j]) : 0u;
+        id[j] = uid_map ? uid_map[u[j]] : u[j];
+    }
+#pragma unroll
+    for (int j = 0; j < NI; ++j) sum += d[j];
+    if (vis_old) {
+        const int64_t stride = (int64_t)gridDim.x * kWG;
+        for (int64_t i = (int64_t)blockIdx.x * kWG + t; i < W; i += stride) vis_old[i] = vis[i];
+    }
+    uint32_t tot;
+    uint32_t c = wg_exclusive_scan_dpp(sum, &tot, s_wave);
+    if (t == 0)
+        s_base = atomicAdd(reinterpret_cast<unsigned long long*>(&ctrl->pack[par]),
+                           ((unsigned long long)tot << kPackBits) | (unsigned long long)n);
+    __syncthreads();
+    const int32_t p0 = (int32_t)(s_base & kPackMask);
+    const int64_t c0 = (int64_t)(s_base >> kPackBits);
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+        const int32_t i = t * NI + j;
+        if (i < n) {
+            s_c[i] = c;
+            cumul[p0 + i] = c0 + c;
+            rowstart[p0 + i] = a[j];
+            uidv[p0 + i] = id[j];
+        }
+        c += d[j];
+    }
+    __syncthreads();
+    write_tile_heads(s_c, n, tot, p0, c0, tile_sh, tile_k);
+}
+
+constexpr int32_t kFrontWideV = 1 << 24;
+
+static int log2_tile(int tile)
+{
+    int sh = 0;
+    while ((1 << sh) < tile) ++sh;
+    return sh;
+}
+
+hipError_t launch_list_scan(hipStream_t s, const int32_t* Q, int32_t qlen, const int64_t* off,
+                            const int32_t* uid_map, int64_t* rowstart, int32_t* uidv,
+                            int64_t* cumul, int32_t* tile_k, int tile, Ctrl* ctrl, int par,
+                            int32_t W, const uint32_t* vis, uint32_t* vis_old)
+{
+    if (qlen < 1) return hipErrorInvalidValue;
+    // short lists one entry per thread, so that they spread over the chip
+    const int items = qlen <= (1 << 16) ? 1 : 8;
+    const unsigned grid = (unsigned)(((int64_t)qlen + kWG * items - 1) / (kWG * items));
+    if (items == 1)
+        hipLaunchKernelGGL(k_list_scan<1>, dim3(grid), dim3(kWG), 0, s, Q, qlen, off, uid_map,
+                           rowstart, uidv, cumul, tile_k, log2_tile(tile), ctrl, par, W, vis,
+                           vis_old);
+    else
+        hipLaunchKernelGGL(k_list_scan<8>, dim3(grid), dim3(kWG), 0, s, Q, qlen, off,
+                           uid_map, rowstart, uidv, cumul, tile_k, log2_tile(tile), ctrl, par, W,
+                           vis, vis_old);
+    return hipGetLastError();
+}
+
+// The bitmap level's compaction and scan.  A thread looks at eight ids: their
+// flag bytes, one byte of each bitmap, and (where its wave has a new vertex at
+// all) their row offsets and skip counts, read in id order with wide loads
+// where the arrays' alignment allows (vec).  The new vertices and their edge
+// numbers are listed in LDS and written out from there, so that the entry
+// arrays' stores are contiguous.  A workgroup of NT threads reserves its
+// places with one atomic; these take 12 ns each, one after the other, so
+// graphs above kFrontWideV take NT = 1024.
+template <int NT>
+__global__ __launch_bounds__(NT) void k_front_scan(
+    int32_t V, uint8_t* __restrict__ vis8, uint8_t* __restrict__ old8, int32_t* __restrict__ Qn,
+    int32_t* __restrict__ level, int32_t lvl, uint8_t* __restrict__ found,
+    const int64_t* __restrict__ off, const int32_t* __restrict__ uid_map,
+    const int32_t* __restrict__ skip, int64_t* __restrict__ rowstart, int32_t* __restrict__ uidv,
+    int64_t* __restrict__ cumul, int32_t* __restrict__ tile_k, int tile_sh,
+    Ctrl* __restrict__ ctrl, int par, int vec)
+{
+    if (!ctrl->bitmap_out) return;
+    __shared__ uint32_t s_cnt[NT / 64], s_deg[NT / 64];
+    __shared__ uint64_t s_base;
+    __shared__ int64_t s_drop[NT / 64];
+    __shared__ uint32_t s_c[NT * 8];
+    __shared__ uint16_t s_id[NT * 8];
+    const int t = threadIdx.x;
+    const int32_t* sk = nullptr;  // row prefix skip, see k_scan_reduce
+    if (skip) {
+        const int32_t cand = ctrl->fp_cand;
+        const int32_t fp = cand < V ? cand : V;
+        if (blockIdx.x == 0 && t == 0) ctrl->full_prefix = fp;
+        int lv = -1;
+#pragma unroll
+        for (int i = 0; i < kSkipLevels; ++i)
+            if (fp >= (1 << (kSkipLow + i))) lv = i;
+        if (lv >= 0) sk = skip + (int64_t)lv * V;
+    }
+    int64_t dropped = 0;
+    const int64_t nblocks = ((int64_t)V + 8 * NT - 1) / (8 * NT);
+    for (int64_t blk = blockIdx.x; blk < nblocks; blk += gridDim.x) {
+        const int64_t b0 = blk * NT * 8, v0 = b0 + t * 8;
+        uint32_t f = 0;
+        if (v0 < V) {  // (flags and bitmaps are padded to whole words)
+            uint32_t x = vis8[v0 >> 3];
+            const uint32_t y = old8[v0 >> 3];
+            if (found) {
+                const uint2 z = *reinterpret_cast<const uint2*>(found + v0);
+                const uint32_t pf =
+                    ((z.x & 1u) | ((z.x >> 7) & 2u) | ((z.x >> 14) & 4u) | ((z.x >> 21) & 8u)) |
+                    (((z.y & 1u) | ((z.y >> 7) & 2u) | ((z.y >> 14) & 4u) | ((z.y >> 21) & 8u)) << 4);
+                if (pf) {
+                    x |= pf;
+                    vis8[v0 >> 3] = (uint8_t)x;
+                    *reinterpret_cast<uint2*>(found + v0) = make_uint2(0u, 0u);
+                }
+            }
+            f = x & ~y;
+            if (f) old8[v0 >> 3] = (uint8_t)x;
+        }
+        uint32_t d[8], dsum = 0;
+        if (__ballot(f != 0)) {  // uniform over the wave
+            int64_t o[9];
+            int32_t m[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+            if (vec && v0 + 8 <= V) {
+                const longlong2* p = reinterpret_cast<const longlong2*>(off + v0);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const longlong2 q = p[k];
+                    o[2 * k] = q.x;
+                    o[2 * k + 1] = q.y;
+                }
+                o[8] = off[v0 + 8];
+                if (sk) {
+                    const int4 m0 = *reinterpret_cast<const int4*>(sk + v0);
+                    const int4 m1 = *reinterpret_cast<const int4*>(sk + v0 + 4);
+                    m[0] = m0.x; m[1] = m0.y; m[2] = m0.z; m[3] = m0.w;
+                    m[4] = m1.x; m[5] = m1.y; m[6] = m1.z; m[7] = m1.w;
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < 9; ++k) o[k] = off[v0 + k < V ? v0 + k : V];
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    if (sk) m[k] = sk[v0 + k < V ? v0 + k : V - 1];
+            }
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const bool on = (f >> k) & 1u;
+                d[k] = on ? (uint32_t)(o[k + 1] - o[k] - m[k]) : 0u;
+                dsum += d[k];
+                if (on) dropped += m[k];
+            }
+        }
+        // places and edge numbers: both scans with one exchange
+        const uint32_t cnt = (uint32_t)__popc(f);
+        const uint32_t ci = (uint32_t)wave_inclusive_scan_dpp((int32_t)cnt);
+        const uint32_t di = (uint32_t)wave_inclusive_scan_dpp((int32_t)dsum);
+        if ((t & 63) == 63) {
+            s_cnt[t >> 6] = ci;
+            s_deg[t >> 6] = di;
+        }
+        __syncthreads();
+        uint32_t cb = 0, db = 0, n = 0, tot = 0;
+#pragma unroll
+        for (int w = 0; w < NT / 64; ++w) {
+            if (w == (t >> 6)) {
+                cb = n;
+                db = tot;
+            }
+            n += s_cnt[w];
+            tot += s_deg[w];
+        }
+        if (n == 0) {  // uniform
+            __syncthreads();
+            continue;
+        }
+        if (t == 0)
+            s_base = atomicAdd(reinterpret_cast<unsigned long long*>(&ctrl->pack[par]),
+                               ((unsigned long long)tot << kPackBits) | (unsigned long long)n);
+        if (f) {
+            uint32_t i = cb + ci - cnt, c = db + di - dsum;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                if ((f >> k) & 1u) {
+                    s_id[i] = (uint16_t)(t * 8 + k);
+                    s_c[i] = c;
+                    ++i;
+                    c += d[k];
+                }
+            }
+        }
+        __syncthreads();
+        const int32_t p0 = (int32_t)(s_base & kPackMask);
+        const int64_t c0 = (int64_t)(s_base >> kPackBits);
+        for (int32_t i = t; i < (int32_t)n; i += NT) {
+            const int32_t v = (int32_t)b0 + s_id[i];
+            const int64_t a = off[v] + (sk ? sk[v] : 0);
+            const int32_t id = uid_map ? uid_map[v] : v;
+            Qn[p0 + i] = v;
+            level[v] = lvl;
+            cumul[p0 + i] = c0 + s_c[i];
+            rowstart[p0 + i] = a;
+            uidv[p0 + i] = id;
+        }
+        write_tile_heads(s_c, (int32_t)n, tot, p0, c0, tile_sh, tile_k);
+        __syncthreads();
+    }
+    if (sk) {  // one atomic per workgroup
+        for (int d = 32; d >= 1; d >>= 1) dropped += __shfl_xor(dropped, d, 64);
+        if (__lane_id() == 0) s_drop[t >> 6] = dropped;
+        __syncthreads();
+        if (t == 0) {
+            for (int w = 1; w < NT / 64; ++w) dropped += s_drop[w];
+            if (dropped)
+                atomicAdd(reinterpret_cast<unsigned long long*>(&ctrl->dropped[par]),
+                          (unsigned long long)dropped);
+        }
+    }
+}
+
+hipError_t launch_front_scan(hipStream_t s, int num_cus, int32_t V, uint32_t* vis,
+                             uint32_t* vis_old, int32_t* Qn, int32_t* level, int32_t lvl,
+                             uint8_t* found, const int64_t* off, const int32_t* uid_map,
+                             const int32_t* skip, int64_t* rowstart, int32_t* uidv,
+                             int64_t* cumul, int32_t* tile_k, int tile, Ctrl* ctrl, int par)
+{
+    // the skip counts of one threshold start at a multiple of V entries
+    const int vec = (uintptr_t)off % 16 == 0 &&
+                    (!skip || ((uintptr_t)skip % 16 == 0 && V % 4 == 0));
+    const bool big = V > kFrontWideV;
+    const int64_t per = big ? 8 * 1024 : 8 * 256;
+    const int64_t nb = ((int64_t)V + per - 1) / per;
+    const int64_t cap = (int64_t)num_cus * (big ? 2 : 8);
+    const unsigned grid = (unsigned)(nb < cap ? nb : cap);
+    uint8_t* v8 = reinterpret_cast<uint8_t*>(vis);
+    uint8_t* o8 = reinterpret_cast<uint8_t*>(vis_old);
+    if (big)
+        hipLaunchKernelGGL(k_front_scan<1024>, dim3(grid), dim3(1024), 0, s, V, v8, o8, Qn, level,
+                           lvl, found, off, uid_map, skip, rowstart, uidv, cumul, tile_k,
+                           log2_tile(tile), ctrl, par, vec);
+    else
+        hipLaunchKernelGGL(k_front_scan<256>, dim3(grid), dim3(256), 0, s, V, v8, o8, Qn, level,
+                           lvl, found, off, uid_map, skip, rowstart, uidv, cumul, tile_k,
+                           log2_tile(tile), ctrl, par, vec);
+    return hipGetLastError();
+}
+
+// The prefix the next level's rows may skip, before the compaction has moved
+// the flags into the bitmap.  Workgroups take chunks of 8192 ids in order and
+// stop once a smaller candidate is known.
+__global__ __launch_bounds__(kWG) void k_found_prefix(int32_t V, int32_t W,
+                                                      const uint32_t* __restrict__ vis,
+                                                      const uint4* __restrict__ found16,
+                                                      Ctrl* __restrict__ ctrl)
+{
+    __shared__ int32_t s_min, s_known;
+    if (!ctrl->bitmap_out) return;
+    for (int64_t w0 = (int64_t)blockIdx.x * kWG; w0 < W; w0 += (int64_t)gridDim.x * kWG) {
+        if (threadIdx.x == 0) {
+            s_min = 0x7fffffff;
+            s_known = __hip_atomic_load(&ctrl->fp_cand, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+        if (w0 * 32 >= s_known) break;  // uniform
+        const int64_t w = w0 + threadIdx.x;
+        if (w < W) {
+            uint32_t open = ~(vis[w] | (found16 ? flag_bits(found16, w) : 0u));
+            if (w * 32 + 32 > V) open &= (1u << (V - w * 32)) - 1u;
+            if (open) atomicMin(&s_min, (int32_t)(w * 32) + __builtin_ctz(open));
+        }
+        __syncthreads();
+        const int32_t m = s_min;
+        if (m != 0x7fffffff) {
+            if (threadIdx.x == 0) atomicMin(&ctrl->fp_cand, m);
+            break;  // uniform
+        }
+        __syncthreads();  // s_min is reset for the next chunk
+    }
+}
+
+hipError_t launch_found_prefix(hipStream_t s, int grid, int32_t V, int32_t W, const uint32_t* vis,
+                               const uint8_t* found, Ctrl* ctrl)
+{
+    const int64_t n = ((int64_t)W + kWG - 1) / kWG;
+    if (grid > n) grid = (int)n;
+    hipLaunchKernelGGL(k_found_prefix, dim3(grid < 1 ? 1 : grid), dim3(kWG), 0, s, V, W, vis,
+                       reinterpret_cast<const uint4*>(found), ctrl);
     return hipGetLastError();
 }
 

@@ -734,11 +734,12 @@ __global__ __launch_bounds__(kSW) void k_small_levels(
     const int w = (int)(blockIdx.x / kXcdSlices);
     const int t = threadIdx.x;
     // qlen0 < 0: launched right behind a host-driven level, whose next
-    // frontier size is in ctrl->qn_count; an empty frontier ends the search
-    // and one above the limit goes back to the host, both before any level
+    // frontier size is in ctrl; an empty frontier ends the search and one
+    // above the limit goes back to the host, both before any level
     bool run = true;
     if (qlen0 < 0) {
-        qlen0 = (int32_t)ctrl->qn_count;
+        qlen0 = (int32_t)(ctrl->qn_count + (uint32_t)(ctrl->pack[-1 - qlen0] & kPackMask));
+        if (w == 0 && t == 0) scoped_store<false>(&ctrl->front_n, (uint32_t)qlen0);
         if (qlen0 == 0 || qlen0 > qlimit) run = false;
     }
     auto not_run = [&]() { report(ctrl, qlen0 == 0 ? 1 : 2, qlen0, lvl0, 0, 0, 0); };
@@ -792,6 +793,11 @@ __global__ __launch_bounds__(kSW) void k_small_levels(
             __hip_atomic_load(&sy->edges, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (t == 0) {
             ctrl->r_total = edges;
+            if (__hip_atomic_load(&ctrl->steps, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > 0) {
+                // a scan of the frontier these levels started from is spent
+                ctrl->pack[0] = ctrl->pack[1] = 0;
+                ctrl->dropped[0] = ctrl->dropped[1] = 0;
+            }
             sy->arrive = 0;
             sy->spill = 0;
             sy->edges = 0;

@@ -54,14 +54,17 @@ __device__ __forceinline__ StageRegs<EPT> fetch_stage(int32_t tile, int32_t ntil
                                                       const int64_t* __restrict__ cumul,
                                                       const int64_t* __restrict__ rowstart,
                                                       const int32_t* __restrict__ uidv,
-                                                      const int32_t* __restrict__ tile_k)
+                                                      const int32_t* __restrict__ tile_k,
+                                                      int32_t k_last = -1)
 {
     StageRegs<EPT> R;
     const bool valid = tile < ntiles;
     R.tile = valid ? tile : -1;
     const int32_t t = valid ? tile : 0;
     R.k_lo = valid ? tile_k[t] : 0;
-    R.k_hi = valid ? tile_k[t + 1] : 0;
+    // the last tile ends at the last entry (k_last; negative: tile_k holds it
+    // behind the last tile's head)
+    R.k_hi = valid ? (k_last >= 0 && t + 1 == ntiles ? k_last : tile_k[t + 1]) : 0;
 #pragma unroll
     for (int m = 0; m < TileLds<EPT>::PER; ++m) {
         int32_t k = R.k_lo + (int32_t)threadIdx.x + m * kWG;

@@ -38,6 +38,27 @@ __device__ __forceinline__ int32_t wave_inclusive_scan_dpp(int32_t x)
     return x;
 }
 
+// As wg_exclusive_scan below, for 32-bit values, with DPP steps in the wave.
+__device__ __forceinline__ uint32_t wg_exclusive_scan_dpp(uint32_t x, uint32_t* total,
+                                                          uint32_t* s_wave)
+{
+    const int lane = __lane_id();
+    const int wave = threadIdx.x >> 6;
+    const uint32_t incl = (uint32_t)wave_inclusive_scan_dpp((int32_t)x);
+    if (lane == 63) s_wave[wave] = incl;
+    __syncthreads();
+    uint32_t before = 0, tot = 0;
+#pragma unroll
+    for (int w = 0; w < kWG / 64; ++w) {
+        const uint32_t t = s_wave[w];
+        if (w < wave) before += t;
+        tot += t;
+    }
+    __syncthreads();
+    *total = tot;
+    return before + incl - x;
+}
+
 // Exclusive scan over the 256 threads of a workgroup; *total receives the
 // sum.  s_wave must hold kWG / 64 elements.  Contains two barriers: every
 // thread of the workgroup must call it.
