@@ -118,9 +118,9 @@ extern "C" {
 #define BFS_OPT_LOOP_LIMIT      12 /* largest frontier (vertices) the
                                       persistent small-level loop takes and
                                       keeps: 64..65536 (default 65536)     */
-#define BFS_OPT_CLAIM_MODE      13 /* degree-ordered graphs: how a level whose
-                                      next frontier takes the bitmap form
-                                      records the vertices it finds.  0: the
+#define BFS_OPT_CLAIM_MODE      13 /* how a level whose next frontier takes
+                                      the bitmap form records the vertices it
+                                      finds.  0: the
                                       atomicOr claim on the visited bitmap of
                                       Algorithm 3; 2: each vertex found gets a
                                       byte flag (a plain byte store, read

@@ -515,8 +515,22 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
     int32_t* pa_s = parents ? (g->rank ? g->par_int : parents) : nullptr;
     if (timed) BFS_HIP_TRY(hipEventRecord(g->ev0, s));
     // flag claims (bitmap levels mark vertices with byte stores): the init
-    // clears the flags of a search that may use them
-    uint8_t* const flags = g->claim_mode != 0 ? g->found : nullptr;
+    // clears the flags of a search that may use them.  Without degree order
+    // they lie in deg, which only the three-launch scans write and a plain
+    // graph's search never launches while fuse holds: V * 4 bytes, rounded
+    // up to 256, are at least the W * 32 that are cleared.  The claims of a
+    // plain graph are as scattered as an ordered one's, and an atomicOr per
+    // new vertex bound its big levels (R-MAT without order, edge factor 16:
+    // 65,536 vertices 202 -> 138 us, 777,777 at edge factor 9 499 -> 257,
+    // 2^22 1957 -> 1178, 2^24 5653 -> 5485, 2^25 10,505 -> 9,670).
+    const bool dir_opt = g->direction != 0 && g->symmetric;
+    // one-launch scans (not with the direction-optimizing mode, which looks at
+    // a level's edges before it decides how to search it)
+    const bool fuse = !dir_opt && g->nnz < kPackMaxEdges;
+    uint8_t* const flags = g->claim_mode == 0 ? nullptr
+                           : g->found         ? g->found
+                           : fuse             ? reinterpret_cast<uint8_t*>(g->deg)
+                                              : nullptr;
     BFS_HIP_TRY(launch_init(s, g->V, g->W, root, g->rank, lv_s, pa_s, g->vis, g->vis_old,
                             g->q[0], g->ctrl, g->small_sync, grid_cap, g->rank ? 0 : 1, flags));
     const int32_t sum_words = g->summary_words;
@@ -554,14 +568,10 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
     bool old_left = false;  // ... after levels of its own: vis_old is behind vis
     // direction-optimizing mode: the degree sum of the frontier a bottom-up
     // step searches from, and the size of the frontier before it
-    const bool dir_opt = g->direction != 0 && g->symmetric;
     bool bottom_up = false;
     bool bu_done = false;  // the search has switched back from bottom-up
     int64_t bu_front_deg = 0, bu_prev = 0, examined = 0;
     int32_t bu_levels = 0;
-    // one-launch scans (not with the direction-optimizing mode, which looks at
-    // a level's edges before it decides how to search it)
-    const bool fuse = !dir_opt && g->nnz < kPackMaxEdges;
     int pk = 0;             // ctrl->pack[pk]: this host-driven level's size
     bool scanned = false;   // the current frontier's scan is there
     bool prefixed = false;  // ... and ctrl->full_prefix is its level's prefix

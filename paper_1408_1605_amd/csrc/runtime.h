@@ -74,7 +74,7 @@ struct bfs_graph {
     int32_t* lvl_int = nullptr;  // level by internal id during a search (degree order only)
     int32_t* par_int = nullptr;  // parent (caller id) by internal id (degree order only)
     uint64_t* ms_planes = nullptr;  // batch: level planes by internal id (degree order + batch)
-    uint8_t* found = nullptr;    // flag claims: one byte per id (degree order only)
+    uint8_t* found = nullptr;    // flag claims: one byte per id (degree order; else in deg)
     uint32_t* xo = nullptr;      // XCD slices: per row, the offset of each slice's group
     int32_t* col_x = nullptr;    // XCD slices: rows grouped by slice (degree order only)
 
