@@ -800,20 +800,6 @@ int expand_blocks_per_cu(int ept, int summary_words)
 // 256 words (8192 vertices); thread j of pass p looks at vertex p * 256 + j
 // of the block, so level stores and queue stores of a wave are contiguous.
 
-// The 32 flag bytes (0 or 1) of word w's ids as bits.
-__device__ __forceinline__ uint32_t flag_bits(const uint4* found16, int64_t w)
-{
-    const uint4 x = found16[2 * w], y = found16[2 * w + 1];
-    const uint32_t q[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
-    uint32_t pf = 0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const uint32_t z = q[k];
-        pf |= ((z & 1u) | ((z >> 7) & 2u) | ((z >> 14) & 4u) | ((z >> 21) & 8u)) << (4 * k);
-    }
-    return pf;
-}
-
 // Word i's bits that turned on during the level: its flags become bits (and
 // are cleared for the next level), and vis_old catches up.
 __device__ __forceinline__ uint32_t new_bits(int64_t i, uint32_t* __restrict__ vis,

@@ -84,7 +84,7 @@ struct Plan {
 struct Ctl {
     int32_t err, total_tiles;
     uint32_t nfront[kMaxP];          // next front size by processor
-    int32_t listmode[kMaxP];         // this level's expansion appends lists
+    int32_t form[kMaxP];             // how this level's expansion keeps what it finds
     int64_t rp[kMaxP];               // this level's edges by processor
     unsigned long long fold_list_msgs, fold_bitmap_msgs, fold_bytes, fold_vertices, updated;
     int32_t tstart[kMaxP + 1];       // tiles of porder position t: [tstart[t], tstart[t+1])
@@ -95,6 +95,9 @@ struct Ctl {
 constexpr size_t kCtlHead = offsetof(Ctl, tstart);
 static_assert(kCtlHead % 16 == 0, "published in 16-byte words");
 static_assert(sizeof(Plan) % 4 == 0 && sizeof(Plan) <= 4000, "the plan travels as a kernel argument");
+
+// Ctl::form: claimed in the bitmap, claimed and appended to lists, flagged
+constexpr int32_t kFormBits = 0, kFormList = 1, kFormFlags = 2;
 
 constexpr int kMsgAuto = 0, kMsgList = 1, kMsgBitmap = 2;
 
@@ -356,8 +359,9 @@ __global__ __launch_bounds__(kWG) void k2_scan_top(const Plan* __restrict__ plp,
             ctl->estart[t] = start;
             ctl->tstart[t] = (int32_t)(start / kTile);
             ctl->rp[p] = rp;
-            ctl->listmode[p] = pl.msg_mode == kMsgList ? 1
-                             : pl.msg_mode == kMsgBitmap ? 0 : (rp <= list_limit ? 1 : 0);
+            const bool list = pl.msg_mode == kMsgList ||
+                              (pl.msg_mode == kMsgAuto && rp <= list_limit);
+            ctl->form[p] = list ? kFormList : rp > list_limit ? kFormFlags : kFormBits;
         }
     }
     if (threadIdx.x == 0) {
@@ -384,13 +388,26 @@ __global__ __launch_bounds__(kWG) void k2_scan_down(const Plan* __restrict__ plp
                                                     const int32_t* __restrict__ deg,
                                                     const int64_t* __restrict__ bsum,
                                                     int64_t tile_cap, int64_t* __restrict__ cumul,
-                                                    int32_t* __restrict__ tile_k)
+                                                    int32_t* __restrict__ tile_k,
+                                                    int32_t* __restrict__ dst,
+                                                    const Ctl* __restrict__ ctl)
 {
     __shared__ int64_t s_wave[kWG / 64];
     __shared__ int32_t s_deg[kChunk + kChunk / kScanItems];
     __shared__ int64_t s_cum[kChunk];
     const Plan& pl = *plp;
     const int32_t nch = pl.cb[pl.RC];
+    // clear the flags of the processors that will set some (see k2_expand)
+    const int64_t row16 = (int64_t)pl.C * pl.B / 16;
+    const int32_t lane = __lane_id();
+    uint64_t flagging = __ballot(lane < pl.RC && ctl->form[min(lane, pl.RC - 1)] == kFormFlags);
+    for (; flagging; flagging &= flagging - 1) {
+        const int32_t p = __ffsll((unsigned long long)flagging) - 1;
+        uint4* f = reinterpret_cast<uint4*>(dst + (int64_t)p * pl.C * pl.B);
+        for (int64_t x = (int64_t)blockIdx.x * kWG + threadIdx.x; x < row16;
+             x += (int64_t)gridDim.x * kWG)
+            f[x] = make_uint4(0u, 0u, 0u, 0u);
+    }
     for (int32_t cid = blockIdx.x; cid < nch; cid += gridDim.x) {
         const int32_t t = last_le<int32_t>(pl.cb, 0, pl.RC, cid);
         const int64_t k0 = pl.eb[t] + (int64_t)(cid - pl.cb[t]) * kChunk;
@@ -446,7 +463,22 @@ __global__ __launch_bounds__(kWG) void k2_scan_down(const Plan* __restrict__ plp
 // mode winners are appended to the processor's outgoing list for column
 // tgtj (own rows as ROW2COL, forming the processor's next front), one LDS
 // counter per column and one global reservation per column and tile.
+//
+// A processor that keeps no lists and has more edges than its bitmap has
+// words flags the rows it finds instead (a byte per local row, read first,
+// stored plainly; ctl->form): an atomicOr per row bound the heavy level
+// (R-MAT 20, edge factor 16, 2 x 4: 1095 -> 640 us, its
+// k2_expand there 600 -> 157; 4 x 4 at scale 22 3220 -> 1820, 8 x 8 at scale
+// 23 7180 -> 5110).  The flags lie
+// in the processor's list region, idle at such a level (C*B bytes of its
+// C*B ints), and are cleared by k2_scan_down.  k2_update reads a sender's
+// and its own flags next to their bitmap words, k2_front folds them into
+// the bitmap.  Concurrent finders of a row store the same flag and level, and
+// any of their columns is a valid predecessor.  Below that edge count the
+// extra passes over the flags (three of C*B bytes) would cost more than the
+// claims.  List-only searches never flag: kFlags = false.
 
+template <bool kFlags>
 __global__ __launch_bounds__(kWG) void k2_expand(const Plan* __restrict__ plp,
                                                  Ctl* __restrict__ ctl,
                                                  const int64_t* __restrict__ rowstart,
@@ -465,12 +497,16 @@ __global__ __launch_bounds__(kWG) void k2_expand(const Plan* __restrict__ plp,
     __shared__ int64_t s_rend[kMaxP];
     __shared__ uint32_t s_cnt[kMaxP];
     __shared__ uint32_t s_base[kMaxP];
+    __shared__ int32_t s_form[kMaxP];
     const Plan& pl = *plp;
     const int32_t R = pl.R, C = pl.C, B = pl.B, WB = pl.WB, lvl = pl.lvl;
     const SlotWork sw = slot_work(pl);
     if (threadIdx.x <= pl.RC) s_tstart[threadIdx.x] = ctl->tstart[threadIdx.x];
-    if (threadIdx.x < pl.RC)
-        s_rend[threadIdx.x] = ctl->estart[threadIdx.x] + ctl->rp[pl.porder[threadIdx.x]];
+    if (threadIdx.x < pl.RC) {
+        const int32_t p = pl.porder[threadIdx.x];
+        s_rend[threadIdx.x] = ctl->estart[threadIdx.x] + ctl->rp[p];
+        s_form[threadIdx.x] = ctl->form[p];
+    }
     __syncthreads();
     const int32_t A = s_tstart[sw.first], E = s_tstart[sw.end];
     int32_t tile = A + sw.widx;
@@ -480,7 +516,7 @@ __global__ __launch_bounds__(kWG) void k2_expand(const Plan* __restrict__ plp,
         const int32_t t = last_le<int32_t>(s_tstart, sw.first, sw.end, tile);
         const int32_t p = pl.porder[t];
         const int32_t i = p % R, j = p / R;
-        const bool list = ctl->listmode[p] != 0;
+        const bool list = s_form[t] == kFormList;
         uint32_t* bmp = bm + (int64_t)p * C * WB;
         int32_t* prp = pred + (int64_t)p * C * B;
         if (threadIdx.x < C) s_cnt[threadIdx.x] = 0;
@@ -492,6 +528,27 @@ __global__ __launch_bounds__(kWG) void k2_expand(const Plan* __restrict__ plp,
 #pragma unroll
         for (int q = 0; q < EPT; ++q) wd[q] = ok[q] ? bmp[vv[q] >> 5] : 0xffffffffu;
         cur = fetch_stage<EPT>(tile + sw.nw, E, cumul, rowstart, uidv, tile_k);
+        if (kFlags && s_form[t] == kFormFlags) {
+            uint8_t* flag = reinterpret_cast<uint8_t*>(dst + (int64_t)p * C * B);
+            uint8_t fl[EPT];
+            bool open[EPT];
+#pragma unroll
+            for (int q = 0; q < EPT; ++q) {
+                open[q] = ok[q] && !(wd[q] & (1u << (vv[q] & 31)));
+                fl[q] = flag[open[q] ? vv[q] : 0];  // unconditional: the loads overlap
+            }
+#pragma unroll
+            for (int q = 0; q < EPT; ++q) {
+                if (open[q] && fl[q] == 0) {
+                    flag[vv[q]] = 1;
+                    prp[vv[q]] = uu[q];
+                    const int32_t own = vv[q] - j * B;  // local row in the owned block
+                    if (own >= 0 && own < B) level[(int64_t)(j * R + i) * B + own] = lvl;
+                }
+            }
+            __syncthreads();
+            continue;
+        }
         bool need[EPT];
         uint32_t old[EPT];
 #pragma unroll
@@ -545,9 +602,17 @@ __global__ __launch_bounds__(kWG) void k2_expand(const Plan* __restrict__ plp,
 // (-2 - column) and, in list mode, appends it to the receiver's next front
 // (one reservation per wave).
 
+// processor p's flags, or null where it set none
+__device__ __forceinline__ const uint4* flags_of(const Plan& pl, const Ctl* ctl, const int32_t* dst,
+                                                 int32_t p)
+{
+    if (ctl->form[p] != kFormFlags) return nullptr;
+    return reinterpret_cast<const uint4*>(dst + (int64_t)p * pl.C * pl.B);
+}
+
 __device__ __forceinline__ bool fold_is_list(const Plan& pl, const Ctl* ctl, int32_t p, int32_t m)
 {
-    if (!ctl->listmode[p]) return false;  // the sender kept no lists
+    if (ctl->form[p] != kFormList) return false;  // the sender kept no lists
     if (pl.msg_mode == kMsgList) return true;
     return ctl->dcnt[p * pl.C + m] <= (uint32_t)pl.WB;
 }
@@ -571,7 +636,9 @@ __global__ __launch_bounds__(kWG) void k2_update(const Plan* __restrict__ plp,
         const int32_t i = q % R, m = q / R;
         uint32_t* bmq = bm + (int64_t)q * pw;
         int32_t* prq = pred + (int64_t)q * C * B;
-        const bool qlist = ctl->listmode[q] != 0;
+        const bool qlist = ctl->form[q] == kFormList;
+        // rows this processor found itself are flags until k2_front
+        const uint4* qflag = flags_of(pl, ctl, dst, q);
         int32_t* qfront = dst + ((int64_t)q * C + m) * B;
         uint32_t* qcnt = &ctl->dcnt[q * C + m];
         const int64_t vbase = (int64_t)(m * R + i) * B - (int64_t)m * B;  // v = vbase + r
@@ -592,7 +659,8 @@ __global__ __launch_bounds__(kWG) void k2_update(const Plan* __restrict__ plp,
                     if (e < n) {
                         r = src[e];
                         const uint32_t bit = 1u << (r & 31);
-                        if (!(bmq[r >> 5] & bit)) win = !(atomicOr(bmq + (r >> 5), bit) & bit);
+                        const bool own = qflag && reinterpret_cast<const uint8_t*>(qflag)[r] != 0;
+                        if (!own && !(bmq[r >> 5] & bit)) win = !(atomicOr(bmq + (r >> 5), bit) & bit);
                     }
                     if (win) {
                         level[vbase + r] = lvl;
@@ -618,13 +686,15 @@ __global__ __launch_bounds__(kWG) void k2_update(const Plan* __restrict__ plp,
                 const uint32_t* a = bm + (int64_t)p * pw + (int64_t)m * WB;
                 const uint32_t* b = bm_old + (int64_t)p * pw + (int64_t)m * WB;
                 uint32_t* rq = bmq + (int64_t)m * WB;
+                const uint4* pflag = flags_of(pl, ctl, dst, p);
                 for (int64_t w0 = (int64_t)sw.widx * kWG; w0 < WB; w0 += step) {
                     const int64_t w = w0 + threadIdx.x;
                     uint32_t got = 0;
                     if (w < WB) {
-                        const uint32_t f = a[w] & ~b[w];
+                        const int64_t rw = (int64_t)m * WB + w;  // word of the local rows
+                        const uint32_t f = (a[w] & ~b[w]) | (pflag ? flag_bits(pflag, rw) : 0u);
                         carried += __popc(f);
-                        const uint32_t open = f & ~rq[w];
+                        const uint32_t open = f & ~(rq[w] | (qflag ? flag_bits(qflag, rw) : 0u));
                         if (open) got = open & ~atomicOr(rq + w, open);
                     }
                     const uint32_t ng = (uint32_t)__popc(got);
@@ -674,8 +744,9 @@ __global__ __launch_bounds__(kWG) void k2_update(const Plan* __restrict__ plp,
 
 __global__ __launch_bounds__(kWG) void k2_front(const Plan* __restrict__ plp,
                                                 Ctl* __restrict__ ctl,
-                                                const uint32_t* __restrict__ bm,
+                                                uint32_t* __restrict__ bm,
                                                 uint32_t* __restrict__ bm_old,
+                                                const int32_t* __restrict__ dst,
                                                 uint32_t* __restrict__ fbm)
 {
     const Plan& pl = *plp;
@@ -685,11 +756,20 @@ __global__ __launch_bounds__(kWG) void k2_front(const Plan* __restrict__ plp,
     for (int32_t t = sw.first; t < sw.end; ++t) {
         const int32_t q = pl.porder[t];
         const int32_t m = q / R;
-        const uint32_t* a = bm + (int64_t)q * pw;
+        uint32_t* a = bm + (int64_t)q * pw;
         uint32_t* b = bm_old + (int64_t)q * pw;
+        const uint4* flag = flags_of(pl, ctl, dst, q);
         uint32_t cnt = 0;
         for (int64_t w = (int64_t)sw.widx * kWG + threadIdx.x; w < pw; w += (int64_t)sw.nw * kWG) {
-            const uint32_t x = a[w], y = b[w];
+            uint32_t x = a[w];
+            const uint32_t y = b[w];
+            if (flag) {
+                const uint32_t f = flag_bits(flag, w);
+                if (f) {
+                    x |= f;
+                    a[w] = x;
+                }
+            }
             if (w >= (int64_t)m * WB && w < (int64_t)(m + 1) * WB) {
                 const uint32_t f = x & ~y;
                 fbm[(int64_t)q * WB + (w - (int64_t)m * WB)] = f;
@@ -753,10 +833,11 @@ __global__ __launch_bounds__(kWG) void k2_finish(int32_t V, int32_t R, int32_t C
     }
 }
 
+template <bool kFlags>
 int expand_occupancy()
 {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k2_expand, kWG, 0) != hipSuccess || n < 1)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k2_expand<kFlags>, kWG, 0) != hipSuccess || n < 1)
         n = 1;
     return n;
 }
@@ -772,7 +853,8 @@ struct bfs_grid2d {
     int64_t nnz = 0;
     int device = 0;
     int num_cus = 256;
-    int expand_grid = 0, slot_grid = 0;
+    int expand_grid[2] = {0, 0};  // without and with flags
+    int slot_grid = 0;
     int64_t tile_cap = 0;
     char* ws = nullptr;
     int64_t* off2 = nullptr;
@@ -969,15 +1051,17 @@ int run2d(bfs_grid2d* g, int32_t root, int32_t msg_mode, int32_t* levels, int32_
                            g->tile_k, g->tile_cap, g->ctl);
         if (nch > 0)
             hipLaunchKernelGGL(k2_scan_down, dim3(std::min(nch, cap)), dim3(kWG), 0, s, g->plan,
-                               g->deg, g->bsum, g->tile_cap, g->cumul, g->tile_k);
-        hipLaunchKernelGGL(k2_expand, dim3(g->expand_grid), dim3(kWG), 0, s, g->plan, g->ctl,
+                               g->deg, g->bsum, g->tile_cap, g->cumul, g->tile_k, g->dst, g->ctl);
+        const bool may_flag = msg_mode != kMsgList;
+        const auto expand = may_flag ? k2_expand<true> : k2_expand<false>;
+        hipLaunchKernelGGL(expand, dim3(g->expand_grid[may_flag]), dim3(kWG), 0, s, g->plan, g->ctl,
                            g->rowstart, g->uidv, g->cumul, g->tile_k, g->lrow, g->bm, g->pred,
                            g->dst, levels);
         if (C > 1)
             hipLaunchKernelGGL(k2_update, dim3(g->slot_grid), dim3(kWG), 0, s, g->plan, g->ctl,
                                g->bm, g->bm_old, g->pred, g->dst, levels);
         hipLaunchKernelGGL(k2_front, dim3(g->slot_grid), dim3(kWG), 0, s, g->plan, g->ctl, g->bm,
-                           g->bm_old, g->fbm);
+                           g->bm_old, g->dst, g->fbm);
         BFS_HIP_TRY(hipGetLastError());
         BFS_HIP_TRY(launch_publish(s, g->ctl, kCtlHead, g->h_ctl, g->h_seq, ++g->seq));
         {
@@ -991,9 +1075,10 @@ int run2d(bfs_grid2d* g, int32_t root, int32_t msg_mode, int32_t* levels, int32_
             edges += c.rp[p];
             found += c.nfront[p];
             P.nfront[p] = (int32_t)c.nfront[p];
-            const bool keep_list = c.listmode[p] && (msg_mode == kMsgList || c.nfront[p] <= (uint32_t)WB);
+            const bool list = c.form[p] == kFormList;
+            const bool keep_list = list && (msg_mode == kMsgList || c.nfront[p] <= (uint32_t)WB);
             P.fform[p] = keep_list ? 0 : 1;
-            acc.list_levels += c.listmode[p] ? 1 : 0;
+            acc.list_levels += list ? 1 : 0;
         }
         if (found == 0) break;
         reached += found;
@@ -1103,9 +1188,10 @@ int bfs_grid2d_create(bfs_grid2d** out, int32_t V, int64_t nnz, const int64_t* d
         cus = 256;
     g->num_cus = cus;
     {
-        const int per_cu = std::min(8, expand_occupancy());
-        const int grid = std::max(kSlots, cus * per_cu / kSlots * kSlots);
-        g->expand_grid = grid;
+        const int per_cu[2] = {std::min(8, expand_occupancy<false>()),
+                               std::min(8, expand_occupancy<true>())};
+        for (int f = 0; f < 2; ++f)
+            g->expand_grid[f] = std::max(kSlots, cus * per_cu[f] / kSlots * kSlots);
         g->slot_grid = std::max(kSlots, cus * 4 / kSlots * kSlots);
     }
     constexpr size_t kPlanBytes = (sizeof(Plan) + 15) / 16 * 16;

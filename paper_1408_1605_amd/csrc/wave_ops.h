@@ -82,4 +82,18 @@ __device__ __forceinline__ T wg_exclusive_scan(T x, T* total, T* s_wave)
     return before + incl - x;
 }
 
+// The 32 flag bytes (0 or 1) of word w's ids as bits.
+__device__ __forceinline__ uint32_t flag_bits(const uint4* found16, int64_t w)
+{
+    const uint4 x = found16[2 * w], y = found16[2 * w + 1];
+    const uint32_t q[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+    uint32_t pf = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const uint32_t z = q[k];
+        pf |= ((z & 1u) | ((z >> 7) & 2u) | ((z >> 14) & 4u) | ((z >> 21) & 8u)) << (4 * k);
+    }
+    return pf;
+}
+
 }  // namespace bfsmi
