@@ -314,27 +314,33 @@ hipError_t launch_srv_join(hipStream_t s, int32_t V, int32_t n_join, const int32
 // before the first launch (the host clears it with the batch state); each
 // launch leaves it zero again.
 struct MsSync {
-    uint32_t arrive;     // grid barrier: arrivals (only grows within a launch)
+    uint64_t arrive;     // arrivals by XCC (7 bits each); sign bit: the launch is called off
     uint32_t leave;      // workgroups that have finished (the last one re-zeroes the block)
-    uint32_t pad0[30];   // the counters below sit on other lines
-    uint32_t fn[3];      // found-list size, by level mod 3
-    uint32_t qn[3];      // next-frontier size
-    int32_t md[3];       // largest degree in the next frontier
-    int32_t pad;
-    int64_t rn[3];       // edges of the next frontier
-    uint64_t alive[3];   // lanes that found vertices
+    int32_t steps;       // levels run
+    uint64_t reached;    // vertices found, all levels
+    uint64_t alive;      // lanes that found vertices in the last level
+    uint32_t qn;         // the frontier left in Qa
+    uint32_t fn[3];      // candidates in the lists in memory, by level mod 3
+    uint32_t pad[52];
 };
+static_assert(sizeof(MsSync) == 256, "a batch's state keeps its size");
+constexpr int kMsMaxWGs = 32;
+constexpr int32_t kMsMinV = 128;  // smaller graphs run on one workgroup
 int ms_small_loop_blocks();
-// Runs up to max_levels serving levels (OUT16 outputs) from ctrl's state;
-// ctrl->steps = levels run; the frontier ends in Qa; found is int32[V]
-// scratch.  h_ctrl (pinned host memory, or null) receives a copy of the
-// final control block.
-hipError_t launch_ms_small_levels(hipStream_t s, int grid, int32_t V, const int64_t* off,
+// Runs up to max_levels serving levels (OUT16 outputs) from ctrl's state on
+// wgs workgroups of one XCD (cls: which eighth of the launch's workgroups);
+// ctrl->steps = levels run (0 also when the workgroups could not start
+// together); the frontier ends in Qa; Qb and found are int32[V] scratch,
+// slots is scratch of 4 * 8 * wgs bytes (64 bytes below kMsMinV vertices).
+// h_ctrl (pinned host memory, or null) receives a copy of the final control
+// block.  maxdeg: the graph's largest degree.
+hipError_t launch_ms_small_levels(hipStream_t s, int wgs, int cls, int32_t V, const int64_t* off,
                                   const int32_t* col, const int32_t* orig, SeenNext* sn,
                                   uint64_t* front, int32_t* Qa, int32_t* Qb, int32_t* found,
                                   int16_t* const* lane_out, const int32_t* lane_start,
-                                  MsSync* sy, Ctrl* ctrl, Ctrl* h_ctrl, int32_t max_levels,
-                                  int32_t qlimit, int64_t rlimit, int32_t dlimit);
+                                  MsSync* sy, uint64_t* slots, Ctrl* ctrl, Ctrl* h_ctrl,
+                                  int32_t max_levels, int32_t qlimit, int64_t rlimit,
+                                  int32_t dlimit, int32_t maxdeg);
 
 // Degree-ordered internal relabelling (relabel.hip).  rank[v] is v's
 // internal id (vertices in non-increasing degree order, ties arbitrary),

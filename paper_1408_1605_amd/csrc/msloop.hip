@@ -5,26 +5,46 @@
 // is seven kernels (degree scan, expansion, front clear, finalize, advance),
 // and on a busy GPU every one of them waits behind other graphs' kernels in
 // the shared hardware queues.  This kernel runs up to max_levels such levels
-// in one launch of a few dozen workgroups, one grid barrier per level.
+// in one launch of a few dozen workgroups, one barrier per level.
 //
 // A level's work is the expansion of the paper's Section 3.4 on lane masks:
-// per edge u -> v the lanes new to v are f = mask(u) & ~(seen[v] | next[v]),
-// ORed into next[v] with a returning atomic, and the thread that turns
-// next[v] from zero to non-zero appends v to the level's candidate list (so
-// each vertex is listed once); then each candidate is finalized: new =
-// next & ~seen, seen |= new, next = 0, and each new lane b gets depth
-// level - lane_start[b] in its int16 result row (caller ids).
+// per edge u -> v the lanes new to v are f = mask(u) & ~seen[v], ORed into
+// v's marks with a returning atomic, and the thread that turns the marks from
+// zero to non-zero keeps v as a candidate (so each vertex is kept once); then
+// each candidate is finalized: new = marks & ~seen, seen |= new, marks = 0,
+// and each new lane b gets depth level - lane_start[b] in its int16 result
+// row (caller ids).
 //
 // The finalize of one level and the expansion of the next run in the same
-// phase: a workgroup finalizes its slice of the candidate list and expands
-// the vertices that got new lanes right away (degree prefix sum in LDS,
-// edges mapped to threads by binary search in it), so only one grid barrier
-// separates levels.  The next masks and candidate lists come in two
-// parities (sn[].next and front[]; the found and Qb lists): a phase
-// finalizes one parity while its expansion fills the other, so a thread
-// that finalizes v writes only v's own words of the parity it reads, and
-// the seen masks it updates are read elsewhere only as a filter (a stale
-// seen lets a spurious candidate through, which its finalize then drops).
+// phase, so only one barrier separates levels.  Marks and candidates come in
+// two parities (sn[].next and front[]): a phase finalizes one parity while
+// its expansion fills the other, so a thread that finalizes v writes only v's
+// own words of the parity it reads, and the seen masks it updates are read
+// elsewhere only as a filter (a stale seen lets a spurious candidate through,
+// which its finalize then drops).
+//
+// Such levels are bound by the chain of dependent memory round trips, so, as
+// in the single-root loop (smallloop.hip):
+//   - the workgroups that take part share one XCD (every eighth of the launch;
+//     they compare their XCC ids when they start): marks are ORed with atomics
+//     of that L2, shared words are read past the L1, and no barrier writes
+//     back or invalidates the L2;
+//   - candidates stay in the LDS of the workgroup that found them; the lists
+//     in memory take only those that do not fit, or all when the candidates
+//     are dealt out anew (a share overflowed or is a multiple of the mean);
+//   - a workgroup arrives at the barrier with one store to its own slot, which
+//     also holds its candidate count, and loads the rows of its candidates
+//     while it waits; it reads all slots with one load per lane;
+//   - graphs whose largest degree is at most kMsRowEdges (lattices) take one
+//     lane per row and load the neighbours before the barrier too, so the
+//     candidates' marks and the neighbours' seen masks are one round trip.
+//     Others map edges to threads by binary search in the share's degree
+//     prefix sum and put the level's edge count and largest degree in the
+//     slots.
+// A 512 x 512 grid served alone, against one agent-scope counter barrier and
+// list reservations per wave (and host rounds of 2, 8, 32 levels): 1 query
+// (836 levels) 13.2 -> 3.5 ms, 6 queries 16.4 -> 5.2, 48 queries 29.0 -> 15.0;
+// a 1000 x 1000 grid, 32 queries 62.7 -> 39.9 ms.
 //
 // The kernel starts from the state the level kernels leave (frontier in Qa,
 // lane masks in front) and leaves the same state when it stops: the round's
@@ -34,520 +54,661 @@
 // change.  The kernel stops when the batch is done, after max_levels levels,
 // or before expanding a frontier whose candidates (an upper bound on it),
 // their edges or their largest degree exceed the limits; the host then
-// runs that level with the ordinary kernels.  The grid is small enough to
-// be resident together; every barrier wait is bounded (ctrl->err on
-// expiry).
+// runs that level with the ordinary kernels.  Every wait is bounded.  The
+// workgroups start together or not at all: one that has waited too long for
+// the others, or finds them on more than one XCD, makes the launch run no
+// level, and the host runs the round.  A wait inside the loop that does not
+// end sets ctrl->err and every workgroup leaves.
 #include "bfs_internal.h"
 #include "wave_ops.h"
 
 namespace bfsmi {
 
-constexpr int kMsStage = 1024;           // frontier entries staged per pass
+constexpr int kMsW = 512;                // threads per workgroup
+constexpr int kMsShare = 1024;           // candidates a workgroup keeps in LDS
+constexpr int kMsPass = kMsW;            // candidates per pass, one per thread
 constexpr int kMsEPT = 4;                // edges per thread per pass
-constexpr int kMsTile = kWG * kMsEPT;
-constexpr uint32_t kMsSpinCap = 1u << 24;
+constexpr int kMsTile = kMsW * kMsEPT;
+constexpr int kMsRowEdges = 4;           // rows of at most this many edges: a lane per row
+constexpr int kMsSkewMin = 256;          // shares up to this size are left alone
+constexpr uint32_t kMsStartCap = 1u << 14;  // polls before a launch is called off
+constexpr uint32_t kMsSpinCap = 1u << 23;
+constexpr int32_t kMsDegSat = 1 << 14;   // degrees saturate here in the sums, above the host's limit
+constexpr uint32_t kMsEdgeSat = 1u << 25;  // ... and a share's edges in its slot
 
-// Grid-wide barrier on a counter that only grows (zeroed before each
-// launch): barrier number k is passed once it reaches k * nwg.  Thread 0 of
-// each workgroup arrives with a release add and waits with relaxed loads
-// followed by an acquire fence.
-__device__ __forceinline__ bool ms_grid_sync(MsSync* sy, uint32_t nwg, uint32_t* s_ep)
-{
-    __shared__ int s_ok;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const uint32_t target = (*s_ep + 1u) * nwg;
-        uint32_t a = __hip_atomic_fetch_add(&sy->arrive, 1u, __ATOMIC_RELEASE,
-                                            __HIP_MEMORY_SCOPE_AGENT) + 1u;
-        int ok = 1;
-        uint32_t spins = 0;
-        while ((int32_t)(a - target) < 0) {
-            __builtin_amdgcn_s_sleep(2);
-            a = __hip_atomic_load(&sy->arrive, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (++spins > kMsSpinCap) {
-                ok = 0;
-                break;
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        *s_ep += 1u;
-        s_ok = ok;
-    }
-    __syncthreads();
-    return s_ok != 0;
-}
+struct MsLds {
+    int32_t cum[kMsPass + 1];
+    uint64_t f[kMsPass];
+    int64_t base[kMsPass];
+    uint16_t map[kMsTile];
+    int32_t nv[2][kMsShare];  // candidates, by parity
+    int32_t wave[kMsW / 64];
+    int16_t* out[64];
+    int32_t start[64];
+    uint32_t cnt[2];      // candidates found (those in memory included), by parity
+    uint32_t found;       // some vertex got new lanes in this phase
+    uint32_t bad;         // a guard tripped or a depth overflowed
+    unsigned long long edges;  // of this workgroup's candidates
+    int32_t mdeg;              // their largest degree
+    uint32_t q0;          // flush: where this share goes in the list
+    // of the last barrier
+    int32_t sum, esum, bits;
+};
+constexpr int kMsDeal = 1, kMsFound = 2, kMsBad = 4, kMsOver = 8, kMsOk = 16;
+// slot word 0: epoch << 32 | share overflowed << 31 | found << 30 | bad << 29 |
+// candidates; word 1: epoch << 32 | a degree over the limit << 31 | edges
+constexpr uint32_t kMsCount = (1u << 29) - 1;
 
 template <typename T>
-__device__ __forceinline__ T ms_load(const T* p)
+__device__ __forceinline__ T ms_load(const T* p)  // past the L1
 {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-constexpr int kMsPer = kMsStage / kWG;  // staged entries per thread
-
-// Stages n frontier entries, kMsPer per thread (row start a, degree d, lane
-// mask f): the exclusive prefix of the degrees goes to s_cum (s_cum[n] = R,
-// the stage's edges), the masks to s_f and the row starts less the prefix to
-// s_base.  Returns R (uniform).
-__device__ __forceinline__ int32_t ms_stage(int32_t n, const int64_t (&a)[kMsPer],
-                                            const int32_t (&d)[kMsPer],
-                                            const uint64_t (&f)[kMsPer], int32_t* s_cum,
-                                            uint64_t* s_f, int64_t* s_base, int32_t* s_wave)
+template <typename T>
+__device__ __forceinline__ void ms_store_agent(T* p, T x)
 {
-    const int t = threadIdx.x;
-    int32_t tot = 0;
-#pragma unroll
-    for (int m = 0; m < kMsPer; ++m) tot += d[m];
-    int32_t R;
-    int32_t c = wg_exclusive_scan<int32_t>(tot, &R, s_wave);
-#pragma unroll
-    for (int m = 0; m < kMsPer; ++m) {
-        const int32_t i = t * kMsPer + m;
-        if (i < n) {
-            s_cum[i] = c;
-            s_f[i] = f[m];
-            s_base[i] = a[m] - c;
-        }
-        c += d[m];
-    }
-    if (t == 0) s_cum[n] = R;
-    __syncthreads();
-    return R;
+    __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Expands a staged set of n entries with R edges: edges go to threads by
-// binary search in s_cum, kMsTile per pass.  Per edge u -> x the lanes new
-// to x are f = mask(u) & ~(seen[x] | next[x] | front[x]), ORed into x's
-// marks of parity tp (0: sn[x].next, 1: front[x]) with a returning atomic;
-// the thread that turns those marks from zero to non-zero appends x to list
-// (so x is listed once per level) and adds x's degree to the bounds rsum,
-// rmax on the next frontier's edges.
-__device__ __forceinline__ void ms_expand_staged(
-    int32_t n, int32_t R, int32_t V, const int64_t* __restrict__ off,
-    const int32_t* __restrict__ col, SeenNext* __restrict__ sn, uint64_t* __restrict__ front,
-    int tp, int32_t* __restrict__ list, uint32_t* __restrict__ list_n, Ctrl* __restrict__ ctrl,
-    const int32_t* s_cum, const uint64_t* s_f, const int64_t* s_base, uint16_t* s_map,
-    int64_t& rsum, int32_t& rmax)
+__device__ __forceinline__ void ms_bad(MsLds& S, int32_t* flag, int32_t x)
 {
-    const int t = threadIdx.x;
-    for (int32_t e0 = 0; e0 < R; e0 += kMsTile) {
-        const int32_t n_e = R - e0 < kMsTile ? R - e0 : kMsTile;
-        const int32_t sl0 = e0 + t * kMsEPT;
-        if (t * kMsEPT < n_e) {
-            int32_t lo = 0;
-            for (int32_t st = 1 << (31 - __builtin_clz(n)); st > 0; st >>= 1) {
-                const int32_t x = lo + st;
-                if (x < n && s_cum[x] <= sl0) lo = x;
+    ms_store_agent(flag, x);
+    S.bad = 1;
+}
+
+// Slots of set epoch & 1: N words 0, then N words 1.
+__device__ __forceinline__ uint64_t* ms_slots(uint64_t* slots, uint32_t epoch, int N)
+{
+    return slots + (epoch & 1u) * 2 * N;
+}
+
+// Waits until all slots carry the epoch; sums and flags go to S.  Every
+// thread calls it; the last wave, which has the least to load, polls (word 0
+// on its lower half, word 1 on its upper).
+template <bool ROWS>
+__device__ __forceinline__ void ms_wait(uint64_t* slots, uint32_t epoch, int N, MsLds& S)
+{
+    if (threadIdx.x >= kMsW - 64) {
+        const int lane = __lane_id();
+        const int k = lane & 31;
+        const bool mine = k < N && (lane < 32 || !ROWS);
+        const uint64_t* p = ms_slots(slots, epoch, N) + (lane < 32 ? 0 : N) + (mine ? k : 0);
+        uint64_t x = (uint64_t)epoch << 32;
+        uint32_t spins = 0;
+        bool ok = true;
+        while (true) {
+            if (mine) x = ms_load(p);
+            if (__all((uint32_t)(x >> 32) == epoch)) break;
+            if (++spins > kMsSpinCap) {
+                ok = false;
+                break;
             }
-            int32_t i = lo;
+        }
+        const uint32_t lo = (uint32_t)x;
+        const int32_t c = mine && lane < 32 ? (int32_t)(lo & kMsCount) : 0;
+        const int32_t sum = __builtin_amdgcn_readlane(wave_inclusive_scan_dpp(c), 63);
+        int32_t esum = 0;
+        if (!ROWS) {
+            const int32_t e = mine && lane >= 32 ? (int32_t)(lo & 0x7fffffffu) : 0;
+            esum = __builtin_amdgcn_readlane(wave_inclusive_scan_dpp(e), 63);
+        }
+        const uint64_t top = __ballot(mine && (lo >> 31));
+        const uint64_t found = __ballot(mine && lane < 32 && ((lo >> 30) & 1u));
+        const uint64_t bad = __ballot(mine && lane < 32 && ((lo >> 29) & 1u));
+        const uint64_t skew = __ballot(c > kMsSkewMin && (int64_t)c * N > 2 * (int64_t)sum);
+        if (lane == 0) {
+            S.sum = sum;
+            S.esum = esum;
+            S.bits = ((uint32_t)top || skew ? kMsDeal : 0) | (found ? kMsFound : 0) |
+                     (bad ? kMsBad : 0) | (top >> 32 ? kMsOver : 0) | (ok ? kMsOk : 0);
+        }
+    }
+    __syncthreads();
+}
+
+// Appends the candidates among a wave's NE edges per lane to the workgroup's
+// share; those that do not fit go to the list in memory.
+template <bool ROWS, int NE>
+__device__ __forceinline__ void ms_append(MsLds& S, const int32_t (&vv)[NE], const bool (&first)[NE],
+                                          int par, int32_t V, const int64_t* __restrict__ off,
+                                          int32_t* __restrict__ list, uint32_t* list_n,
+                                          Ctrl* __restrict__ ctrl)
+{
+    uint64_t mask[NE];
+    uint32_t total = 0;
 #pragma unroll
-            for (int j = 0; j < kMsEPT; ++j) {
-                const int32_t sl = sl0 + j;
-                if (sl - e0 < n_e) {
-                    while (i + 1 < n && s_cum[i + 1] <= sl) ++i;
-                    s_map[sl - e0] = (uint16_t)i;
+    for (int j = 0; j < NE; ++j) {
+        mask[j] = __ballot(first[j]);
+        total += (uint32_t)__popcll(mask[j]);
+    }
+    if (!total) return;  // uniform over the wave
+    uint32_t pos0 = 0, q0 = 0;
+    if (__lane_id() == 0) pos0 = atomicAdd(&S.cnt[par], total);
+    pos0 = __builtin_amdgcn_readfirstlane(pos0);
+    const uint32_t over0 = pos0 > kMsShare ? pos0 : kMsShare;  // first position that spills
+    if (pos0 + total > over0) {
+        if (__lane_id() == 0)
+            q0 = __hip_atomic_fetch_add(list_n, pos0 + total - over0, __ATOMIC_RELAXED,
+                                        __HIP_MEMORY_SCOPE_WORKGROUP);
+        q0 = __builtin_amdgcn_readfirstlane(q0);
+    }
+    uint32_t base = pos0;
+#pragma unroll
+    for (int j = 0; j < NE; ++j) {
+        if (first[j]) {
+            const uint32_t pos = base + lanes_below(mask[j]);
+            if (pos < kMsShare) {
+                S.nv[par][pos] = vv[j];
+            } else {
+                const uint32_t q = q0 + (pos - over0);
+                if (q < (uint32_t)V) list[q] = vv[j];
+                else ms_bad(S, &ctrl->err, 7);
+                if (!ROWS) {
+                    const int64_t dd = off[vv[j] + 1] - off[vv[j]];
+                    const int32_t d = (int32_t)(dd < kMsDegSat ? dd : kMsDegSat);
+                    atomicAdd(&S.edges, (unsigned long long)d);
+                    atomicMax(&S.mdeg, d);
                 }
             }
         }
-        __syncthreads();
-        int32_t vv[kMsEPT];
-        uint64_t fm[kMsEPT], have[kMsEPT];
-#pragma unroll
-        for (int j = 0; j < kMsEPT; ++j) {
-            const int32_t sl = t + j * kWG;
-            const bool ok = sl < n_e;
-            const int32_t sc = ok ? sl : n_e - 1;
-            const int32_t i = s_map[sc];
-            fm[j] = ok ? s_f[i] : 0ull;
-            vv[j] = col[s_base[i] + e0 + sc];
-        }
-        // stale masks only let more threads issue the atomic
-#pragma unroll
-        for (int j = 0; j < kMsEPT; ++j) {
-            have[j] = ~0ull;
-            if (fm[j]) {
-                const SeenNext p = sn[vv[j]];
-                have[j] = p.seen | p.next | front[vv[j]];
-            }
-        }
-        bool first[kMsEPT];
-#pragma unroll
-        for (int j = 0; j < kMsEPT; ++j) {
-            const uint64_t nb = fm[j] & ~have[j];
-            first[j] = false;
-            if (nb) {
-                uint64_t* mk = tp ? front + vv[j] : &sn[vv[j]].next;
-                const uint64_t old =
-                    __hip_atomic_fetch_or(mk, nb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                first[j] = old == 0;
-            }
-        }
-        uint64_t mask[kMsEPT];
-        uint32_t total = 0;
-#pragma unroll
-        for (int j = 0; j < kMsEPT; ++j) {
-            mask[j] = __ballot(first[j]);
-            total += (uint32_t)__popcll(mask[j]);
-        }
-        if (total) {
-            uint32_t base = 0;
-            if (__lane_id() == 0) base = atomicAdd(list_n, total);
-            base = __shfl(base, 0, 64);
-#pragma unroll
-            for (int j = 0; j < kMsEPT; ++j) {
-                if (first[j]) {
-                    const uint32_t pos = base + lanes_below(mask[j]);
-                    if (pos < (uint32_t)V) list[pos] = vv[j];
-                    else ctrl->err = 7;
-                    const int32_t dv = (int32_t)(off[vv[j] + 1] - off[vv[j]]);
-                    rsum += dv;
-                    rmax = dv > rmax ? dv : rmax;
-                }
-                base += (uint32_t)__popcll(mask[j]);
-            }
-        }
-        __syncthreads();
+        base += (uint32_t)__popcll(mask[j]);
     }
 }
 
-// A phase's totals, one set of atomics per wave (alive: one per workgroup).
-__device__ __forceinline__ void ms_phase_totals(MsSync* __restrict__ sy, int cs, uint64_t alive,
-                                                uint32_t qcnt, int64_t rsum, int32_t rmax,
-                                                uint64_t* s_alive)
+// A thread's NE edges: the lanes nb new to x go into its marks of parity tp;
+// first: they were the first.  (All atomics are issued before one is waited
+// for.)
+template <int NE>
+__device__ __forceinline__ void ms_mark(const uint64_t (&nb)[NE], const int32_t (&x)[NE], int tp,
+                                        SeenNext* sn, uint64_t* front, bool (&first)[NE])
 {
-    for (int o = 32; o >= 1; o >>= 1) {
-        alive |= __shfl_xor(alive, o, 64);
-        qcnt += __shfl_xor(qcnt, o, 64);
-        rsum += __shfl_xor(rsum, o, 64);
-        const int32_t m2 = __shfl_xor(rmax, o, 64);
-        rmax = m2 > rmax ? m2 : rmax;
-    }
-    if (__lane_id() == 0) {
-        s_alive[threadIdx.x >> 6] = alive;
-        if (qcnt) atomicAdd(&sy->qn[cs], qcnt);
-        if (rsum) atomicAdd(reinterpret_cast<unsigned long long*>(&sy->rn[cs]),
-                            (unsigned long long)rsum);
-        if (rmax) atomicMax(&sy->md[cs], rmax);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint64_t a = 0;
-        for (int k = 0; k < kWG / 64; ++k) a |= s_alive[k];
-        if (a) atomicOr(reinterpret_cast<unsigned long long*>(&sy->alive[cs]),
-                        (unsigned long long)a);
-    }
+    uint64_t old[NE];
+#pragma unroll
+    for (int k = 0; k < NE; ++k) old[k] = ~0ull;
+#pragma unroll
+    for (int k = 0; k < NE; ++k)
+        if (nb[k])
+            old[k] = __hip_atomic_fetch_or(tp ? front + x[k] : &sn[x[k]].next, nb[k],
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+    for (int k = 0; k < NE; ++k) first[k] = old[k] == 0;
 }
 
 // The levels; every workgroup returns from it exactly once.
+template <bool ROWS>
 __device__ __forceinline__ void ms_levels_body(
-    int32_t V, const int64_t* __restrict__ off, const int32_t* __restrict__ col,
-    const int32_t* __restrict__ orig, SeenNext* __restrict__ sn, uint64_t* __restrict__ front,
-    int32_t* __restrict__ Qa, int32_t* __restrict__ Qb, int32_t* __restrict__ found,
-    int16_t* const* __restrict__ lane_out, const int32_t* __restrict__ lane_start,
-    MsSync* __restrict__ sy, Ctrl* __restrict__ ctrl, int32_t max_levels, int32_t qlimit,
-    int64_t rlimit, int32_t dlimit)
+    MsLds& S, int32_t V, const int64_t* __restrict__ off, const int32_t* __restrict__ col,
+    const int32_t* __restrict__ orig, SeenNext* sn, uint64_t* front, int32_t* Qa, int32_t* Qb,
+    int32_t* found, uint64_t* slots, MsSync* sy, Ctrl* ctrl, int N, int w, int32_t qlen0,
+    int32_t lvl0, int32_t max_levels, int32_t qlimit, int64_t rlimit, int32_t dlimit)
 {
-    __shared__ int32_t s_cum[kMsStage + 1];
-    __shared__ uint64_t s_f[kMsStage];
-    __shared__ int64_t s_base[kMsStage];
-    __shared__ uint16_t s_map[kMsTile];
-    __shared__ int32_t s_wave[kWG / 64];
-    __shared__ int16_t* s_out[64];
-    __shared__ int32_t s_start[64];
-    __shared__ uint64_t s_alive[kWG / 64];
-    __shared__ uint32_t s_epoch;
-    const uint32_t N = gridDim.x;
-    const uint32_t w = blockIdx.x;
     const int t = threadIdx.x;
-    if (t == 0) s_epoch = 0;
-    if (t < 64) {
-        s_out[t] = lane_out[t];
-        s_start[t] = lane_start[t];
-    }
-    if (w == 0 && t == 0) ctrl->steps = 0;  // levels run, set again at the end
-    if (ctrl->done) return;  // uniform (rewritten only after the last barrier): nothing to run
-    const int32_t qlen0 = ctrl->qlen;
-    const int32_t lvl0 = ctrl->level;
-
-    // limits of the first frontier, before anything is changed
-    {
-        const int64_t k0 = (int64_t)qlen0 * w / N, k1 = (int64_t)qlen0 * (w + 1) / N;
-        int64_t sum = 0;
-        int32_t mx = 0;
-        for (int64_t k = k0 + t; k < k1; k += kWG) {
-            const int32_t u = Qa[k];
-            const int64_t d = off[u + 1] - off[u];
-            sum += d;
-            mx = d > mx ? (int32_t)d : mx;
+    // this thread's entry of the pass: vertex (-1: none), caller id, row and
+    // its first neighbours
+    int32_t v, vo = 0, d, cv[kMsRowEdges];
+    int64_t a = 0;
+    // loads entries 0 .. n-1 of a share in LDS (list null) or in memory
+    // (loads are unconditional, of valid ids: behind a branch the compiler
+    // waits for each before it issues the next)
+    auto fetch = [&](const int32_t* share, const int32_t* list, int32_t n) {
+        v = -1;
+        if (t < n) v = list ? ms_load(list + t) : share[t];
+        if (v >= V) {
+            ms_bad(S, &ctrl->err, 9);
+            v = -1;
         }
+        d = 0;
+#pragma unroll
+        for (int k = 0; k < kMsRowEdges; ++k) cv[k] = 0;
+        if (!__any(v >= 0)) return;
+        const int32_t u = v < 0 ? 0 : v;
+        a = off[u];
+        const int64_t a1 = off[u + 1];
+        vo = orig ? orig[u] : u;
+        d = v < 0 ? 0 : (int32_t)(a1 - a);
+        if (ROWS && __any(d > 0))  // (then col[0] is a neighbour)
+#pragma unroll
+            for (int k = 0; k < kMsRowEdges; ++k) cv[k] = col[k < d ? a + k : 0];
+    };
+    // expands the pass's n entries with lane masks nw into the marks of
+    // parity tp; ROWS: seen holds the neighbours' seen masks
+    auto expand = [&](uint64_t nw, const uint64_t (&seen)[kMsRowEdges], int32_t n, int tp,
+                      int32_t* list, uint32_t* list_n) {
+        if constexpr (ROWS) {
+            if (!__any(nw != 0)) return;
+            bool first[kMsRowEdges];
+            uint64_t nb[kMsRowEdges];
+#pragma unroll
+            for (int k = 0; k < kMsRowEdges; ++k) nb[k] = k < d ? nw & ~seen[k] : 0ull;
+            ms_mark(nb, cv, tp, sn, front, first);
+            ms_append<ROWS>(S, cv, first, tp, V, off, list, list_n, ctrl);
+        } else {
+            const int32_t tot = nw ? d : 0;
+            const int32_t inc = wave_inclusive_scan_dpp(tot);
+            if ((t & 63) == 63) S.wave[t >> 6] = inc;
+            __syncthreads();
+            int32_t c = inc - tot, R = 0;
+#pragma unroll
+            for (int k = 0; k < kMsW / 64; ++k) {
+                const int32_t x = S.wave[k];
+                if (k < (t >> 6)) c += x;
+                R += x;
+            }
+            if (t < n) {
+                S.cum[t] = c;
+                S.f[t] = nw;
+                S.base[t] = a - c;
+            }
+            if (t == 0) S.cum[n] = R;
+            __syncthreads();
+            for (int32_t e0 = 0; e0 < R; e0 += kMsTile) {
+                const int32_t n_e = R - e0 < kMsTile ? R - e0 : kMsTile;
+                const int32_t sl0 = e0 + t * kMsEPT;
+                if (t * kMsEPT < n_e) {
+                    int32_t lo = 0;
+                    for (int32_t st = 1 << (31 - __builtin_clz(n)); st > 0; st >>= 1) {
+                        const int32_t x = lo + st;
+                        if (x < n && S.cum[x] <= sl0) lo = x;
+                    }
+                    int32_t i = lo;
+#pragma unroll
+                    for (int j = 0; j < kMsEPT; ++j) {
+                        const int32_t sl = sl0 + j;
+                        if (sl - e0 < n_e) {
+                            while (i + 1 < n && S.cum[i + 1] <= sl) ++i;
+                            S.map[sl - e0] = (uint16_t)i;
+                        }
+                    }
+                }
+                __syncthreads();
+                if (__any(t < n_e)) {
+                    int32_t vv[kMsEPT];
+                    uint64_t fm[kMsEPT], have[kMsEPT];
+                    bool first[kMsEPT];
+#pragma unroll
+                    for (int j = 0; j < kMsEPT; ++j) {
+                        const int32_t sl = t + j * kMsW;
+                        const bool ok = sl < n_e;
+                        const int32_t sc = ok ? sl : n_e - 1;
+                        const int32_t i = S.map[sc];
+                        fm[j] = ok ? S.f[i] : 0ull;
+                        vv[j] = col[S.base[i] + e0 + sc];
+                    }
+                    // stale masks only let more threads issue the atomic
+#pragma unroll
+                    for (int j = 0; j < kMsEPT; ++j)
+                        have[j] = ms_load(&sn[vv[j]].seen) | ms_load(&sn[vv[j]].next) |
+                                  ms_load(front + vv[j]);
+#pragma unroll
+                    for (int j = 0; j < kMsEPT; ++j) fm[j] &= ~have[j];
+                    ms_mark(fm, vv, tp, sn, front, first);
+                    ms_append<ROWS>(S, vv, first, tp, V, off, list, list_n, ctrl);
+                }
+                __syncthreads();
+            }
+        }
+    };
+
+    uint32_t epoch = 0;
+    // arrives at the next barrier; called by all threads behind a
+    // __syncthreads that follows each wave's vmcnt(0)
+    auto arrive = [&](uint32_t w0, uint32_t w1) {
+        ++epoch;
+        if (t == 0) {
+            uint64_t* p = ms_slots(slots, epoch, N) + w;
+            __hip_atomic_store(p, (uint64_t)epoch << 32 | w0, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (!ROWS)
+                __hip_atomic_store(p + N, (uint64_t)epoch << 32 | w1, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    };
+    auto settle = [&]() {
+        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's stores and atomics
+        __syncthreads();
+    };
+    auto limits = [&]() {
+        return (uint32_t)(S.edges < kMsEdgeSat ? S.edges : kMsEdgeSat) |
+               (S.mdeg > dlimit ? 1u << 31 : 0u);
+    };
+    // adds the fetched entries' degrees to S.edges, S.mdeg
+    auto add_degrees = [&]() {
+        int32_t s = d < kMsDegSat ? d : kMsDegSat, mx = d;
+        if (!__any(mx > 0)) return;
+        s = __builtin_amdgcn_readlane(wave_inclusive_scan_dpp(s), 63);
         for (int o = 32; o >= 1; o >>= 1) {
-            sum += __shfl_xor(sum, o, 64);
             const int32_t m2 = __shfl_xor(mx, o, 64);
             mx = m2 > mx ? m2 : mx;
         }
         if ((t & 63) == 0) {
-            if (sum) atomicAdd(reinterpret_cast<unsigned long long*>(&sy->rn[2]),
-                               (unsigned long long)sum);
-            if (mx) atomicMax(&sy->md[2], mx);
+            atomicAdd(&S.edges, (unsigned long long)s);
+            atomicMax(&S.mdeg, mx);
         }
+    };
+    // the last pass's new vertices, whose results are stored behind the loads
+    // for the next phase
+    uint64_t onw = 0;
+    int32_t ovo = 0;
+    auto store_results = [&](int32_t dl) {
+        for (; onw; onw &= onw - 1) {
+            const int k = __builtin_ctzll(onw);
+            const int32_t dd = dl - S.start[k];
+            if (dd > 32767) ms_bad(S, &ctrl->overflow, 1);
+            else if (S.out[k]) S.out[k][ovo] = (int16_t)dd;  // null: retired lane
+        }
+    };
+    // the end of a phase: publishes this share's size and limits, loads its
+    // rows and waits for the others
+    auto next_phase = [&](int par, int32_t dl) {
+        settle();
+        const uint32_t c = S.cnt[par];
+        const int32_t n = (int32_t)(c < (uint32_t)kMsShare ? c : (uint32_t)kMsShare);
+        const uint32_t w0 = (c & kMsCount) | (c > (uint32_t)kMsShare ? 1u << 31 : 0u) |
+                            (S.found ? 1u << 30 : 0u) | (S.bad ? 1u << 29 : 0u);
+        uint32_t w1 = 0;
+        if (ROWS) {
+            arrive(w0, 0u);
+            fetch(S.nv[par], nullptr, n);
+        } else {
+            // the first pass's entries last: the next phase starts with them
+            for (int32_t s0 = (n - 1) / kMsPass * kMsPass; s0 >= 0; s0 -= kMsPass) {
+                fetch(S.nv[par] + s0, nullptr, n - s0);
+                add_degrees();
+            }
+            __syncthreads();
+            w1 = limits();
+            arrive(w0, w1);
+        }
+        if (t == 0) {
+            S.cnt[par ^ 1] = 0;
+            S.found = 0;
+            S.edges = 0;
+            S.mdeg = 0;
+        }
+        store_results(dl);
+        ms_wait<ROWS>(slots, epoch, N, S);
+        return n;
+    };
+    auto fail = [&]() {
+        if (t == 0) ms_store_agent(&ctrl->err, 6);
+    };
+
+    // the entry frontier's limits
+    const int64_t k0 = (int64_t)qlen0 * w / N, k1 = (int64_t)qlen0 * (w + 1) / N;
+    if (!ROWS) {
+        for (int64_t s0 = k0; s0 < k1; s0 += kMsPass) {
+            const int32_t n = (int32_t)(k1 - s0 < kMsPass ? k1 - s0 : kMsPass);
+            fetch(nullptr, Qa + s0, n);
+            add_degrees();
+        }
+        __syncthreads();
+        arrive(0u, limits());
+        if (t == 0) {
+            S.edges = 0;
+            S.mdeg = 0;
+        }
+        ms_wait<ROWS>(slots, epoch, N, S);
+        if (!(S.bits & kMsOk)) return fail();
+        if (S.esum > rlimit || (S.bits & kMsOver)) return;  // no level run
     }
-    if (!ms_grid_sync(sy, N, &s_epoch)) {
-        if (t == 0) ctrl->err = 6;
-        return;
-    }
-    if (max_levels < 1 || qlen0 > qlimit || ms_load(&sy->rn[2]) > rlimit ||
-        ms_load(&sy->md[2]) > dlimit)
-        return;  // no level run: ctrl->steps stays 0, the rest of ctrl unchanged
 
     // ---- phase 0: expand the entry frontier (Qa, lane masks in front, which
-    // are cleared) into marks 0 (sn.next), candidates into list 0 (found)
-    {
-        const int64_t k0 = (int64_t)qlen0 * w / N, k1 = (int64_t)qlen0 * (w + 1) / N;
-        int64_t rsum = 0;
-        int32_t rmax = 0;
-        for (int64_t s0 = k0; s0 < k1; s0 += kMsStage) {
-            const int32_t n = (int32_t)(k1 - s0 < kMsStage ? k1 - s0 : kMsStage);
-            int64_t a[kMsPer];
-            int32_t d[kMsPer];
-            uint64_t f[kMsPer];
-#pragma unroll
-            for (int m = 0; m < kMsPer; ++m) {
-                const int32_t i = t * kMsPer + m;
-                a[m] = 0;
-                d[m] = 0;
-                f[m] = 0;
-                if (i < n) {
-                    const int32_t u = Qa[s0 + i];
-                    f[m] = front[u];
-                    front[u] = 0;  // this workgroup is the only reader of u's mask
-                    a[m] = off[u];
-                    d[m] = f[m] ? (int32_t)(off[u + 1] - a[m]) : 0;
-                }
-            }
-            const int32_t R = ms_stage(n, a, d, f, s_cum, s_f, s_base, s_wave);
-            ms_expand_staged(n, R, V, off, col, sn, front, 0, found, &sy->fn[0], ctrl, s_cum, s_f,
-                             s_base, s_map, rsum, rmax);
+    // are cleared) into marks 0 (sn.next), candidates into share 0
+    for (int64_t s0 = k0; s0 < k1; s0 += kMsPass) {
+        const int32_t n = (int32_t)(k1 - s0 < kMsPass ? k1 - s0 : kMsPass);
+        fetch(nullptr, Qa + s0, n);
+        uint64_t nw = 0, seen[kMsRowEdges];
+        if (v >= 0) {
+            nw = ms_load(front + v);
+            front[v] = 0;  // this workgroup is the only reader of v's mask
         }
-        ms_phase_totals(sy, 0, 0ull, 0u, rsum, rmax, s_alive);
+        if (ROWS)
+#pragma unroll
+            for (int k = 0; k < kMsRowEdges; ++k) seen[k] = ms_load(&sn[cv[k]].seen);
+        expand(nw, seen, n, 0, found, &sy->fn[0]);
     }
-    if (!ms_grid_sync(sy, N, &s_epoch)) {
-        if (t == 0) ctrl->err = 6;
-        return;
-    }
+    int32_t n = next_phase(0, lvl0);
+    if (!(S.bits & kMsOk)) return fail();
 
     // ---- phase j >= 1: finalize the candidates of expansion j (found at
     // depth level lvl0 + j - 1) and, unless this is the round's last phase,
-    // expand the new frontier at once (expansion j + 1).  Marks and lists
+    // expand the new frontier at once (expansion j + 1).  Marks and shares
     // alternate by parity: phase j reads those of parity (j - 1) & 1 (every
-    // candidate is listed there once, and its marks are cleared here) while
+    // candidate is kept there once, and its marks are cleared here) while
     // its expansion fills those of parity j & 1, cleared in phase j - 1.
-    uint64_t last_alive = 0;
+    int32_t steps = 0;
     int64_t reached = 0;
-    int32_t levels = 0, qlen = 0, steps = 0;
-    bool done = ms_load(&ctrl->err) != 0 || ms_load(&ctrl->overflow) != 0;
-    bool failed = false;
-    for (int32_t j = 1; !done; ++j) {
+    for (int32_t j = 1; !(S.bits & kMsBad); ++j) {
         const int pc = (j - 1) % 3, cs = j % 3;
-        uint32_t fn = ms_load(&sy->fn[pc]);
-        if (fn > (uint32_t)V) fn = (uint32_t)V;  // a vertex is listed at most once
-        const bool last = j >= max_levels || (int32_t)fn > qlimit || ms_load(&sy->rn[pc]) > rlimit ||
-                          ms_load(&sy->md[pc]) > dlimit;
-        if (w == 0 && t == 0) {
-            // slot (j + 1) % 3 was last read before the previous barrier
-            const int nx = (j + 1) % 3;
-            sy->fn[nx] = 0;
-            sy->qn[nx] = 0;
-            sy->md[nx] = 0;
-            sy->rn[nx] = 0;
-            sy->alive[nx] = 0;
-        }
         const int sp = (j - 1) & 1;
-        const int32_t* __restrict__ Lin = sp ? Qb : found;
-        int32_t* __restrict__ Lout = sp ? found : Qb;
+        int32_t* Lin = sp ? Qb : found;
+        int32_t* Lout = sp ? found : Qb;
+        const int32_t fn = S.sum;
+        const bool last = j >= max_levels || fn > qlimit ||
+                          (!ROWS && (S.esum > rlimit || (S.bits & kMsOver)));
+        const bool deal = (S.bits & kMsDeal) != 0;
+        if (w == 0 && t == 0)  // last read before the previous barrier
+            __hip_atomic_store(&sy->fn[(j + 1) % 3], 0u, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+        int64_t f0 = 0, f1 = n;
+        if (deal) {
+            // the share behind what has spilled, then equal slices for all
+            if (t == 0)
+                S.q0 = n ? __hip_atomic_fetch_add(&sy->fn[pc], (uint32_t)n, __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_WORKGROUP) : 0u;
+            __syncthreads();
+            for (int32_t i = t; i < n; i += kMsW) {
+                const uint32_t q = S.q0 + (uint32_t)i;
+                if (q < (uint32_t)V) Lin[q] = S.nv[sp][i];
+                else ms_bad(S, &ctrl->err, 8);
+            }
+            settle();
+            arrive(0u, 0u);
+            ms_wait<ROWS>(slots, epoch, N, S);
+            if (!(S.bits & kMsOk)) return fail();
+            f0 = (int64_t)fn * w / N;
+            f1 = (int64_t)fn * (w + 1) / N;
+        }
         const int32_t dl = lvl0 + j - 1;
-        uint64_t alive = 0;
-        uint32_t qcnt = 0;
-        int64_t rsum = 0;
-        int32_t rmax = 0;
-        const int64_t f0 = (int64_t)fn * w / N, f1 = (int64_t)fn * (w + 1) / N;
-        for (int64_t s0 = f0; s0 < f1; s0 += kMsStage) {
-            const int32_t n = (int32_t)(f1 - s0 < kMsStage ? f1 - s0 : kMsStage);
-            int64_t a[kMsPer];
-            int32_t d[kMsPer], vx[kMsPer];
-            uint64_t nw[kMsPer];
+        for (int64_t s0 = f0; s0 < f1; s0 += kMsPass) {
+            const int32_t ns = (int32_t)(f1 - s0 < kMsPass ? f1 - s0 : kMsPass);
+            if (deal) fetch(nullptr, Lin + s0, ns);
+            else if (s0 > 0) fetch(S.nv[sp] + s0, nullptr, ns);
+            uint64_t nw = 0, seen[kMsRowEdges];
+            if (__any(v >= 0)) {
+                const int32_t u = v < 0 ? 0 : v;
+                const uint64_t had = ms_load(&sn[u].seen);
+                const uint64_t marks = sp ? ms_load(front + u) : ms_load(&sn[u].next);
+                if (ROWS && !last)
 #pragma unroll
-            for (int m = 0; m < kMsPer; ++m) {
-                const int32_t i = t * kMsPer + m;
-                a[m] = 0;
-                d[m] = 0;
-                nw[m] = 0;
-                vx[m] = 0;
-                if (i < n) {
-                    const int32_t v = Lin[s0 + i];
-                    if ((uint32_t)v >= (uint32_t)V) {
-                        ctrl->err = 9;
-                        continue;
-                    }
-                    vx[m] = v;
-                    const SeenNext p = sn[v];
-                    const uint64_t mk = sp ? front[v] : p.next;
-                    a[m] = off[v];
-                    const int64_t a1 = off[v + 1];
-                    nw[m] = mk & ~p.seen;
+                    for (int k = 0; k < kMsRowEdges; ++k) seen[k] = ms_load(&sn[cv[k]].seen);
+                if (v >= 0) {
+                    nw = marks & ~had;
                     // v's own slot only: other threads OR into the marks of
                     // the other parity meanwhile
                     if (sp) {
-                        if (nw[m]) sn[v].seen = p.seen | nw[m];
-                        front[v] = last ? nw[m] : 0ull;
+                        if (nw) sn[v].seen = had | nw;
+                        front[v] = last ? nw : 0ull;
                     } else {
-                        sn[v] = SeenNext{p.seen | nw[m], 0ull};
-                        if (last) front[v] = nw[m];
-                    }
-                    if (nw[m]) {
-                        const int32_t vo = orig ? orig[v] : v;
-                        for (uint64_t b = nw[m]; b; b &= b - 1) {
-                            const int k = __builtin_ctzll(b);
-                            const int32_t dd = dl - s_start[k];
-                            if (dd > 32767) ctrl->overflow = 1;
-                            else if (s_out[k]) s_out[k][vo] = (int16_t)dd;  // null: retired lane
-                        }
-                        alive |= nw[m];
-                        d[m] = (int32_t)(a1 - a[m]);
+                        sn[v] = SeenNext{had | nw, 0ull};
+                        if (last) front[v] = nw;
                     }
                 }
+                if (nw) S.found = 1;
             }
+            if (!last) expand(nw, seen, ns, j & 1, Lout, &sy->fn[cs]);
+            store_results(dl);  // of the pass before
+            onw = nw;
+            ovo = vo;
+            reached += nw ? 1 : 0;
             if (last) {
+                store_results(dl);
                 // the new frontier goes to Qa, the form the level kernels take
-                uint64_t mask[kMsPer];
-                uint32_t total = 0;
-#pragma unroll
-                for (int m = 0; m < kMsPer; ++m) {
-                    mask[m] = __ballot(nw[m] != 0);
-                    total += (uint32_t)__popcll(mask[m]);
-                }
-                if (total) {
+                const uint64_t mask = __ballot(nw != 0);
+                if (mask) {
+                    uint64_t alive = nw;
+                    for (int o = 32; o >= 1; o >>= 1) alive |= __shfl_xor(alive, o, 64);
                     uint32_t base = 0;
-                    if (__lane_id() == 0) base = atomicAdd(&sy->qn[cs], total);
-                    base = __shfl(base, 0, 64);
-#pragma unroll
-                    for (int m = 0; m < kMsPer; ++m) {
-                        if (nw[m]) {
-                            const uint32_t pos = base + lanes_below(mask[m]);
-                            if (pos < (uint32_t)V) Qa[pos] = vx[m];
-                            else ctrl->err = 8;
-                        }
-                        base += (uint32_t)__popcll(mask[m]);
+                    if (__lane_id() == 0) {
+                        base = atomicAdd(&sy->qn, (uint32_t)__popcll(mask));
+                        atomicOr(reinterpret_cast<unsigned long long*>(&sy->alive),
+                                 (unsigned long long)alive);
+                    }
+                    base = __builtin_amdgcn_readfirstlane(base);
+                    if (nw) {
+                        const uint32_t pos = base + lanes_below(mask);
+                        if (pos < (uint32_t)V) Qa[pos] = v;
+                        else ms_bad(S, &ctrl->err, 8);
                     }
                 }
-            } else {
-#pragma unroll
-                for (int m = 0; m < kMsPer; ++m) qcnt += nw[m] ? 1u : 0u;
-                const int32_t R = ms_stage(n, a, d, nw, s_cum, s_f, s_base, s_wave);
-                ms_expand_staged(n, R, V, off, col, sn, front, j & 1, Lout, &sy->fn[cs], ctrl,
-                                 s_cum, s_f, s_base, s_map, rsum, rmax);
             }
         }
-        ms_phase_totals(sy, cs, alive, qcnt, rsum, rmax, s_alive);
-        if (!ms_grid_sync(sy, N, &s_epoch)) {
-            failed = true;
-            break;
-        }
-        // ---- the level's bookkeeping (as the separate advance does)
-        const uint32_t qn = ms_load(&sy->qn[cs]);
-        last_alive = ms_load(&sy->alive[cs]);
-        const int32_t ovf = ms_load(&ctrl->overflow);
-        const int32_t err = ms_load(&ctrl->err);
         steps = j;
-        reached += qn;
-        if (qn) ++levels;
-        qlen = (int32_t)qn;
-        if (qn == 0 || qn > (uint32_t)V || ovf || err) {
-            if (qn > (uint32_t)V && t == 0) ctrl->err = 8;
-            done = true;
-        } else if (last) {
-            break;
-        }
+        if (last) break;
+        n = next_phase(j & 1, dl);
+        if (!(S.bits & kMsOk)) return fail();
+        if (!(S.bits & kMsFound)) break;  // the batch has ended
     }
-    if (failed) {
-        if (t == 0) ctrl->err = 6;
-        return;
-    }
-    if (w == 0 && t == 0) {
-        ctrl->steps = steps;
-        if (steps > 0) {
-            ctrl->last_alive = last_alive;
-            ctrl->alive = 0;
-            ctrl->reached += reached;
-            ctrl->levels += levels;
-            ctrl->level = lvl0 + steps;
-            ctrl->qlen = qlen;
-            ctrl->qn_count = 0;
-            ctrl->sparse = qlen <= ctrl->sparse_limit;
-            ctrl->pull = 0;  // chosen for a frontier that is gone
-            ctrl->done = done ? 1 : 0;
-        }
-    }
+    for (int o = 32; o >= 1; o >>= 1) reached += __shfl_xor(reached, o, 64);
+    if ((t & 63) == 0 && reached)
+        atomicAdd(reinterpret_cast<unsigned long long*>(&sy->reached), (unsigned long long)reached);
+    if (w == 0 && t == 0) ms_store_agent(&sy->steps, steps);
 }
 
-// The launch leaves its sync block as it found it (zero) and mirrors the
-// control block into pinned host memory, so a round needs no clearing and
-// no copy of its own: the workgroup that leaves last (after every other
-// has stopped reading the sync block) does both.
-static_assert(sizeof(Ctrl) % sizeof(int4) == 0, "the control block is copied in 16-byte words");
+__device__ __forceinline__ int ms_arrivals(uint64_t a)
+{
+    int n = 0;
+#pragma unroll
+    for (int x = 0; x < kXcdSlices; ++x) n += (int)((a >> (7 * x)) & 127u);
+    return n;
+}
 
-__global__ __launch_bounds__(kWG) void k_ms_small_levels(
+static_assert(sizeof(Ctrl) % 8 == 0 && sizeof(Ctrl) <= 512, "mirrored by a wave, 8 bytes a lane");
+
+// Workgroups b with b mod 8 == cls take part.  The launch leaves its sync
+// block as it found it (zero) and mirrors the control block into pinned host
+// memory, so a round needs no clearing and no copy of its own: the workgroup
+// that leaves last (after every other has stopped using the sync block) does
+// both, and the level bookkeeping that the separate advance does.
+template <bool ROWS>
+__global__ __launch_bounds__(kMsW) void k_ms_small_levels(
     int32_t V, const int64_t* __restrict__ off, const int32_t* __restrict__ col,
-    const int32_t* __restrict__ orig, SeenNext* __restrict__ sn, uint64_t* __restrict__ front,
-    int32_t* __restrict__ Qa, int32_t* __restrict__ Qb, int32_t* __restrict__ found,
-    int16_t* const* __restrict__ lane_out, const int32_t* __restrict__ lane_start,
-    MsSync* __restrict__ sy, Ctrl* __restrict__ ctrl, Ctrl* __restrict__ h_ctrl,
+    const int32_t* __restrict__ orig, SeenNext* sn, uint64_t* front, int32_t* Qa, int32_t* Qb,
+    int32_t* found, int16_t* const* __restrict__ lane_out, const int32_t* __restrict__ lane_start,
+    MsSync* sy, uint64_t* slots, Ctrl* ctrl, Ctrl* __restrict__ h_ctrl, int32_t cls,
     int32_t max_levels, int32_t qlimit, int64_t rlimit, int32_t dlimit)
 {
-    ms_levels_body(V, off, col, orig, sn, front, Qa, Qb, found, lane_out, lane_start, sy, ctrl,
-                   max_levels, qlimit, rlimit, dlimit);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const uint32_t k =
-            __hip_atomic_fetch_add(&sy->leave, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        if (k == gridDim.x - 1) {
-            sy->arrive = 0;
-            for (int i = 0; i < 3; ++i) {
-                sy->fn[i] = 0;
-                sy->qn[i] = 0;
-                sy->md[i] = 0;
-                sy->rn[i] = 0;
-                sy->alive[i] = 0;
-            }
-            sy->leave = 0;
-            if (h_ctrl) {
-                const int4* src = reinterpret_cast<const int4*>(ctrl);
-                int4* dst = reinterpret_cast<int4*>(h_ctrl);
-                for (int i = 0; i < (int)(sizeof(Ctrl) / sizeof(int4)); ++i) dst[i] = src[i];
-                __threadfence_system();
-            }
+    if ((int)(blockIdx.x & (kXcdSlices - 1)) != cls) return;
+    __shared__ MsLds S;
+    __shared__ int s_go;  // the workgroups share one XCD
+    const int N = (int)(gridDim.x / kXcdSlices);
+    const int w = (int)(blockIdx.x / kXcdSlices);
+    const int t = threadIdx.x;
+    // ctrl changes only once every workgroup has left
+    const int32_t qlen0 = ctrl->qlen, lvl0 = ctrl->level;
+    if (!ctrl->done && max_levels >= 1 && qlen0 <= qlimit) {  // else no level
+        if (t < 64) {
+            S.out[t] = lane_out[t];
+            S.start[t] = lane_start[t];
         }
+        if (t == 0) {
+            S.cnt[0] = S.cnt[1] = 0;
+            S.found = S.bad = 0;
+            S.edges = 0;
+            S.mdeg = 0;
+            for (int k = 0; k < 4; ++k) ms_store_agent(slots + k * N + w, (uint64_t)0);
+            // the slots have reached the other XCDs before this arrival does
+            __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+            // one 7-bit count of arrivals per XCC; the sign bit calls off
+            const uint32_t xcc = __builtin_amdgcn_s_getreg((2 << 11) | 20);  // XCC_ID[2:0]
+            const uint64_t one = 1ull << (7 * xcc);
+            uint64_t a = __hip_atomic_fetch_add(&sy->arrive, one, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT) + one;
+            uint32_t spins = 0;
+            while (!(a >> 63) && ms_arrivals(a) < N) {
+                if (++spins > kMsStartCap) {
+                    uint64_t seen = a;
+                    (void)__hip_atomic_compare_exchange_strong(&sy->arrive, &seen,
+                                                               a | (1ull << 63), __ATOMIC_RELAXED,
+                                                               __ATOMIC_RELAXED,
+                                                               __HIP_MEMORY_SCOPE_AGENT);
+                }
+                a = __hip_atomic_load(&sy->arrive, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            s_go = a == one * (uint64_t)N;
+        }
+        __syncthreads();
+        if (s_go)
+            ms_levels_body<ROWS>(S, V, off, col, orig, sn, front, Qa, Qb, found, slots, sy, ctrl,
+                                 N, w, qlen0, lvl0, max_levels, qlimit, rlimit, dlimit);
+    }
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): what this wave reports is stored
+    __syncthreads();
+    if (t >= 64) return;
+    uint32_t k = 0;
+    if (t == 0)
+        k = __hip_atomic_fetch_add(&sy->leave, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    k = __builtin_amdgcn_readfirstlane(k);
+    if ((int)k != N - 1) return;
+    if (t == 0) {
+        const int32_t steps = ms_load(&sy->steps);
+        ctrl->steps = steps;
+        if (steps > 0) {
+            const uint32_t qn = ms_load(&sy->qn);
+            const int32_t err = ms_load(&ctrl->err), ovf = ms_load(&ctrl->overflow);
+            ctrl->last_alive = ms_load(&sy->alive);
+            ctrl->alive = 0;
+            ctrl->reached += ms_load(&sy->reached);
+            ctrl->levels += qn ? steps : steps - 1;
+            ctrl->level = lvl0 + steps;
+            ctrl->qlen = (int32_t)qn;
+            ctrl->qn_count = 0;
+            ctrl->sparse = (int32_t)qn <= ctrl->sparse_limit;
+            ctrl->pull = 0;  // chosen for a frontier that is gone
+            ctrl->done = qn == 0 || qn > (uint32_t)V || ovf || err ? 1 : 0;
+        }
+        *sy = MsSync{};
+    }
+    if (h_ctrl) {
+        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+        if (t < (int)(sizeof(Ctrl) / 8))
+            reinterpret_cast<uint64_t*>(h_ctrl)[t] =
+                ms_load(reinterpret_cast<const uint64_t*>(ctrl) + t);
+        __threadfence_system();
     }
 }
 
 int ms_small_loop_blocks()
 {
-    int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_ms_small_levels, kWG, 0) != hipSuccess)
+    int n = 0, m = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_ms_small_levels<false>, kMsW, 0) !=
+            hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&m, k_ms_small_levels<true>, kMsW, 0) !=
+            hipSuccess)
         return 0;
-    return n;
+    return n < m ? n : m;
 }
 
-hipError_t launch_ms_small_levels(hipStream_t s, int grid, int32_t V, const int64_t* off,
+hipError_t launch_ms_small_levels(hipStream_t s, int wgs, int cls, int32_t V, const int64_t* off,
                                   const int32_t* col, const int32_t* orig, SeenNext* sn,
                                   uint64_t* front, int32_t* Qa, int32_t* Qb, int32_t* found,
                                   int16_t* const* lane_out, const int32_t* lane_start,
-                                  MsSync* sy, Ctrl* ctrl, Ctrl* h_ctrl, int32_t max_levels,
-                                  int32_t qlimit, int64_t rlimit, int32_t dlimit)
+                                  MsSync* sy, uint64_t* slots, Ctrl* ctrl, Ctrl* h_ctrl,
+                                  int32_t max_levels, int32_t qlimit, int64_t rlimit,
+                                  int32_t dlimit, int32_t maxdeg)
 {
-    // an ordinary launch of a grid small enough to be resident at once
-    hipLaunchKernelGGL(k_ms_small_levels, dim3(grid), dim3(kWG), 0, s, V, off, col, orig, sn, front,
-                       Qa, Qb, found, lane_out, lane_start, sy, ctrl, h_ctrl, max_levels, qlimit,
-                       rlimit, dlimit);
+    // an ordinary launch: the workgroups that take part are few enough to be
+    // resident at once, and a cooperative launch would make the runtime stop
+    // overlapping later kernels of other streams
+    if (wgs < 1 || wgs > kMsMaxWGs) return hipErrorInvalidValue;
+    if (V < kMsMinV) wgs = 1;  // the slots fit the smallest region
+    const bool rows = maxdeg <= kMsRowEdges && maxdeg <= dlimit &&
+                      (int64_t)qlimit * kMsRowEdges <= rlimit;
+    hipLaunchKernelGGL(rows ? k_ms_small_levels<true> : k_ms_small_levels<false>,
+                       dim3(wgs * kXcdSlices), dim3(kMsW), 0, s, V, off, col, orig, sn, front, Qa,
+                       Qb, found, lane_out, lane_start, sy, slots, ctrl, h_ctrl, cls, max_levels,
+                       qlimit, rlimit, dlimit);
     return hipGetLastError();
 }
 

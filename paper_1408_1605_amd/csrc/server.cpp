@@ -155,6 +155,7 @@ struct SrvBatch {
     int parity = 0;                // stays 0: every replay runs an even number of levels
     bool in_flight = false;
     bool persist = false;          // the round in flight is the persistent kernel
+    int cls = 0;                   // ... on this eighth of the workgroups
     bool big_next = false;         // it stopped before a large level: next round uses the graphs
     int round_levels = 0;          // levels of the round in flight
     int64_t idle_since = 0;        // steady-clock ns when the batch went idle (0: busy)
@@ -162,14 +163,19 @@ struct SrvBatch {
 };
 
 constexpr int kRoundLevels[3] = {2, 8, 32};
+// ... in the persistent kernel, which runs a level in 3-7 us: a round then
+// lasts about as long as the level kernels' (a query joins at its end), and
+// the 60-100 us between rounds count less.  6 R-MAT graphs and 2 grids, 48
+// queries: 10.3 ms with 2, 8, 32 levels, 8.1 with these, 7.9 with 16, 64, 128.
+constexpr int kLoopLevels[3] = {8, 32, 64};
 constexpr int64_t kIdleKeepNs = 100 * 1000 * 1000;  // idle batches kept 100 ms
 constexpr double kDeepLife = 48.0;                  // lanes living longer: continuous joins
 constexpr int32_t kSmallV = 1 << 16;                // graphs this small: continuous joins
 // Persistent rounds on deep graphs (msloop.hip): workgroups per launch, at
-// most this many launches in flight (all their workgroups must be resident
-// together), and the level sizes they take.
-constexpr int kMsGrid = 32;
-constexpr int kMaxPersist = 8;
+// most this many launches in flight (each takes another XCD, so that its
+// workgroups find room), and the level sizes they take.
+constexpr int kMsGrid = kMsMaxWGs;
+constexpr int kMaxPersist = kXcdSlices;
 constexpr int32_t kMsQLimit = 1 << 17;
 constexpr int64_t kMsRLimit = 1 << 19;
 constexpr int32_t kMsDLimit = 8192;
@@ -243,7 +249,7 @@ struct bfs_server {
     // no batch exists and the next query's batch state plus its result does
     // not fit: only bfs_poll (which frees finished results) can make room
     bool stalled = false;
-    int persist_inflight = 0;         // worker thread only
+    uint32_t persist_busy = 0;        // XCDs of the persistent rounds in flight (worker thread only)
     int ms_grid = 0;                  // persistent round workgroups (0: not available)
     bfs_server_stats stats{};
     // result delivery (bfs_poll)
@@ -500,9 +506,9 @@ bool bfs_server::plan_step(SrvGraph& G, bool round_done, bool round_err, StepPla
     // one replay; levels after every lane has ended exit at once); deep
     // graphs start with 2 and lengthen as their oldest lane ages
     const int ri = !deep ? 1 : (oldest < 32 ? 0 : (oldest < 256 ? 1 : 2));
-    const int K = kRoundLevels[ri];
     P.round = ri;
-    P.persist = deep && ms_grid > 0 && !B->big_next && persist_inflight < kMaxPersist;
+    P.persist = deep && ms_grid > 0 && !B->big_next && persist_busy != (1u << kMaxPersist) - 1;
+    const int K = P.persist ? kLoopLevels[ri] : kRoundLevels[ri];
     stats.persistent_rounds += P.persist;
     stats.wide_rounds += deep && ms_grid > 0 && B->big_next;
     ++stats.rounds;
@@ -561,15 +567,17 @@ void bfs_server::execute(SrvGraph& G, const StepPlan& P)
     } else if (P.round >= 0) {
         bad |= hipEventRecord(G.ev0, G.stream) != hipSuccess;
         B->persist = P.persist;
-        B->round_levels = kRoundLevels[P.round];
+        B->round_levels = P.persist ? kLoopLevels[P.round] : kRoundLevels[P.round];
         if (P.persist) {
-            ++persist_inflight;
+            B->cls = __builtin_ctz(~persist_busy);
+            persist_busy |= 1u << B->cls;
             // the kernel copies the control block into G.h_ctrl itself
-            bad |= launch_ms_small_levels(G.stream, ms_grid, g->V, g->s_off, g->s_col, g->orig,
+            bad |= launch_ms_small_levels(G.stream, ms_grid, B->cls, g->V, g->s_off, g->s_col, g->orig,
                                           B->sn, B->front, B->q[0], B->q[1], B->deg, B->lane_out,
-                                          B->lane_start, B->msync, B->ctrl, G.h_ctrl,
-                                          B->round_levels, kMsQLimit, kMsRLimit,
-                                          kMsDLimit) != hipSuccess;
+                                          B->lane_start, B->msync,
+                                          reinterpret_cast<uint64_t*>(B->rowstart), B->ctrl,
+                                          G.h_ctrl, B->round_levels, kMsQLimit, kMsRLimit,
+                                          kMsDLimit, g->maxdeg) != hipSuccess;
         } else {
             bad |= !B->round[P.round] || hipGraphLaunch(B->round[P.round], G.stream) != hipSuccess;
             bad |= hipMemcpyAsync(G.h_ctrl, B->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost,
@@ -605,7 +613,7 @@ bool bfs_server::step_graph(SrvGraph& G)
         }
         B->in_flight = false;
         round_done = true;
-        if (B->persist) --persist_inflight;
+        if (B->persist) persist_busy &= ~(1u << B->cls);
     }
     StepPlan P;
     {
