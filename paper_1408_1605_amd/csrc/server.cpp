@@ -458,7 +458,9 @@ bool bfs_server::plan_step(SrvGraph& G, bool round_done, bool round_err, StepPla
     int64_t oldest = 0;
     for (int b = 0; b < 64; ++b)
         if ((B->active >> b) & 1ull) oldest = std::max(oldest, B->lane_age[b]);
-    const bool deep = G.life_n > 0 && G.life > kDeepLife;
+    // before any lane has ended, a lane alive that long tells the same (a pool's
+    // first pass, 6 R-MAT graphs and 2 grids: 44 -> 15 ms)
+    const bool deep = G.life_n > 0 ? G.life > kDeepLife : (double)oldest > kDeepLife;
     const bool continuous = deep || g->V <= kSmallV;
     const uint64_t lane_cap = cfg.max_lanes >= 64 ? ~0ull : ((1ull << cfg.max_lanes) - 1);
     if (continuous || oldest == 0) {
