@@ -16,7 +16,11 @@ using namespace bfsmi;
 
 namespace bfsmi {
 
-constexpr int kLevelsPerGraph = 4;  // even: the queue buffers alternate
+// Even: the queue buffers alternate.  A read-back costs about 45 us, a level
+// behind the last one 20: most small-world batches end within 8 levels (4
+// levels a replay: 270, 352, 968 us on degree-ordered R-MAT of 2^12, 2^16, 2^19
+// vertices; 6: 235, 384, 1,015; 8: 259, 346, 977).
+constexpr int kLevelsPerGraph = 8;
 
 int ensure_cap_stream(bfs_graph* g)
 {
@@ -47,14 +51,15 @@ static BatchGrids batch_grids(bfs_graph* g)
 // With degree order the levels also track the id prefix every searching
 // lane has seen, and each scan drops the rows' blocks below it (the row
 // prefix skip of the single-root search, over the batch's live lanes).
-static hipError_t enqueue_level(bfs_graph* g, hipStream_t s, const BatchGrids& b, int parity)
+static hipError_t enqueue_level(bfs_graph* g, hipStream_t s, const BatchGrids& b, int parity,
+                                int level, bool last)
 {
     const bool skip = g->skip && g->row_skip;
     return launch_ms_level(s, b.scan, b.expand, b.fin, b.ept, g->V, b.tile_cap, g->s_off, g->s_col,
                            nullptr, g->q[parity], g->q[parity ^ 1], g->deg, g->rowstart, g->suid,
                            g->bsum, g->cumul,
                            g->tile_k, g->ms_sn, g->ms_front, g->ms_touched, nullptr,
-                           nullptr, g->ms_ctrl, g->pull, g->ms_planes, skip ? g->skip : nullptr,
+                           nullptr, g->ms_ctrl, g->pull, level, last, g->ms_planes, skip ? g->skip : nullptr,
                            skip ? g->num_cus * 2 : 0);
 }
 
@@ -68,7 +73,8 @@ static int capture_batch_graph(bfs_graph* g, const BatchGrids& b)
     hipStream_t s = g->cap_stream;
     BFS_HIP_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
     hipError_t e = hipSuccess;
-    for (int j = 0; j < kLevelsPerGraph && e == hipSuccess; ++j) e = enqueue_level(g, s, b, j & 1);
+    for (int j = 0; j < kLevelsPerGraph && e == hipSuccess; ++j)
+        e = enqueue_level(g, s, b, j & 1, j, j == kLevelsPerGraph - 1);
     hipGraph_t graph = nullptr;
     hipError_t e2 = hipStreamEndCapture(s, &graph);
     if (e != hipSuccess) {
@@ -164,7 +170,7 @@ extern "C" int bfs_run_batch(bfs_graph* g, const int32_t* h_roots, int32_t n_roo
         if (use_graph) {
             BFS_HIP_TRY(hipGraphLaunch(g->ms_graph, s));
         } else {
-            BFS_HIP_TRY(enqueue_level(g, s, b, parity));
+            BFS_HIP_TRY(enqueue_level(g, s, b, parity, 0, true));
             parity ^= 1;
         }
         BFS_HIP_TRY(launch_publish(s, g->ms_ctrl, offsetof(Ctrl, seq), g->h_ms_ctrl,

@@ -52,7 +52,7 @@ struct alignas(64) Ctrl {
     int32_t overflow;    // batch: a level did not fit the output type
     int32_t sparse;      // batch: this level's union frontier is small (see msbfs.hip)
     int32_t sparse_limit;  // batch: frontier sizes up to this count as small
-    int32_t pad2;
+    int32_t no_push;     // batch: every searching lane is in pull, nothing to scan
     uint64_t alive;      // batch: OR of the lanes that found vertices this level
     uint64_t last_alive; // batch: alive of the last completed level
     int8_t* out8;        // batch: output rows (read by the device each launch)
@@ -286,6 +286,9 @@ struct PullRows {
 // and the next level's scan drops each row's block below the largest cut
 // 2^(16 + i) inside it (the row prefix skip); the dropped edges go to
 // ctrl->skipped.
+// level: 0 for the first of the levels queued together, whose frontier is
+// scanned from Q; last: the last of them (its next frontier is not scanned
+// here).
 hipError_t launch_ms_level(hipStream_t s, int scan_grid, int expand_grid, int fin_grid,
                            int ept, int32_t V, int64_t tile_cap, const int64_t* off,
                            const int32_t* col, const int32_t* orig, const int32_t* Q,
@@ -294,6 +297,7 @@ hipError_t launch_ms_level(hipStream_t s, int scan_grid, int expand_grid, int fi
                            int32_t* tile_k, SeenNext* sn, uint64_t* front,
                            uint32_t* touched, int16_t* const* lane_out,
                            const int32_t* lane_start, Ctrl* ctrl, const PullRows& pull,
+                           int level, bool last,
                            uint64_t* planes = nullptr, const int32_t* skip = nullptr, int prefix_grid = 0);
 int ms_expand_blocks_per_cu(int ept);
 

@@ -896,28 +896,6 @@ hipError_t launch_bitmap_to_queue(hipStream_t s, int grid, int32_t V, int32_t W,
 // 152 us, plain graph of 777777 vertices 547 -> 489, R-MAT 22 660 -> 656,
 // R-MAT 26 7.72 -> 7.55 ms (its two dense levels: 830 -> 550 us).
 
-// The heads of the tiles that start inside a chunk: n entries from place p0 on,
-// edges [c0, c0 + total), s_c[i] the edges before entry i within the chunk.
-// One search per tile, so hub entries that cover many tiles need no care.
-__device__ __forceinline__ void write_tile_heads(const uint32_t* s_c, int32_t n, uint32_t total,
-                                                 int32_t p0, int64_t c0, int tile_sh,
-                                                 int32_t* __restrict__ tile_k)
-{
-    if (total == 0) return;
-    const int64_t x1 = (c0 + total - 1) >> tile_sh;
-    for (int64_t x = ((c0 + ((int64_t)1 << tile_sh) - 1) >> tile_sh) + threadIdx.x; x <= x1;
-         x += blockDim.x) {
-        const uint32_t e = (uint32_t)((x << tile_sh) - c0);
-        int32_t lo = 0, hi = n - 1;  // max{i : s_c[i] <= e}
-        while (lo < hi) {
-            const int32_t mid = (lo + hi + 1) >> 1;
-            if (s_c[mid] <= e) lo = mid;
-            else hi = mid - 1;
-        }
-        tile_k[x] = p0 + lo;
-    }
-}
-
 // A list of any order: NI entries per thread.  (The degrees of a chunk add up
 // to less than 2^32: distinct vertices of a graph of fewer than 2^32 edges.)
 template <int NI>
@@ -983,13 +961,6 @@ __global__ __launch_bounds__(kWG) void k_list_scan(const int32_t* __restrict__ Q
 }
 
 constexpr int32_t kFrontWideV = 1 << 24;
-
-static int log2_tile(int tile)
-{
-    int sh = 0;
-    while ((1 << sh) < tile) ++sh;
-    return sh;
-}
 
 hipError_t launch_list_scan(hipStream_t s, const int32_t* Q, int32_t qlen, const int64_t* off,
                             const int32_t* uid_map, int64_t* rowstart, int32_t* uidv,

@@ -111,6 +111,9 @@ __global__ __launch_bounds__(kWG) void k_ms_roots(int32_t V, int32_t n_roots,
         ctrl->skipped = 0;
         ctrl->next_deg = 0;
         ctrl->pull = 0;
+        ctrl->no_push = 0;
+        ctrl->pack[0] = ctrl->pack[1] = 0;
+        ctrl->dropped[0] = ctrl->dropped[1] = 0;
         ctrl->sparse_limit = V / 64;
         ctrl->sparse = s_n <= V / 64;
     }
@@ -263,6 +266,149 @@ hipError_t launch_ms_rows(hipStream_t s, int grid, int32_t V, int32_t n_roots, i
     return hipGetLastError();
 }
 
+// The level's degree scan in one launch (as k_list_scan of the single-root
+// search): a workgroup reserves its entries and edges with one atomic on
+// ctrl->pack[par], so entries lie in the order in which workgroups come.  The
+// row prefix skip and the rows whose lanes are all searched from the unseen
+// side as in k_scan_reduce.  A workgroup and pass takes 256 entries, 2048 of a
+// queue that gives every workgroup more.  A level whose lanes are all searched
+// from the unseen side is not scanned at all (ctrl->no_push; 45 us at each of
+// two levels of R-MAT 22, 64 roots).
+// With FUSE, the finalize writes the entries itself, for graphs whose next
+// scan needs nothing that is known only after it (no prefix skip, no pull
+// levels): one launch less, and no second pass over the queue.
+// Against reduce, top and down as three launches a level and a read-back every
+// 4 levels instead of 8: 5 roots on a plain graph of 50,021 vertices 364 ->
+// 280 us, 64 roots on R-MAT 16 439 -> 346, R-MAT 22 2,480 -> 2,270.
+struct MsScan {
+    int64_t* rowstart;
+    int32_t* uidv;
+    int64_t* cumul;
+    int32_t* tile_k;
+    int tile_sh, par;
+    int64_t max_edges;
+};
+
+template <int NI>
+__device__ __forceinline__ void ms_scan_chunk(const int32_t* __restrict__ Q, int64_t q0, int32_t n,
+                                              const int64_t* __restrict__ off,
+                                              const int32_t* __restrict__ sk, uint64_t pull,
+                                              const uint64_t* __restrict__ front, const MsScan& o,
+                                              int32_t V, Ctrl* __restrict__ ctrl, uint32_t* s_wave,
+                                              uint32_t* s_c, uint64_t* s_base, uint32_t& dropped)
+{
+    const int t = threadIdx.x;
+    int32_t u[NI];
+    int64_t a[NI];
+    uint32_t d[NI], sum = 0;
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+        const int32_t i = t * NI + j;
+        u[j] = Q[q0 + (i < n ? i : n - 1)];
+    }
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+        a[j] = off[u[j]];
+        d[j] = (uint32_t)(off[u[j] + 1] - a[j]);
+    }
+    if (sk) {
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            const int32_t x = sk[u[j]];
+            a[j] += x;
+            d[j] -= (uint32_t)x;
+            dropped += t * NI + j < n ? (uint32_t)x : 0u;
+        }
+    }
+    if (pull) {
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            if (!(front[u[j]] & ~pull)) {
+                dropped += t * NI + j < n ? d[j] : 0u;
+                d[j] = 0;
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+        if (t * NI + j >= n) d[j] = 0;
+        sum += d[j];
+    }
+    uint32_t tot;
+    uint32_t c = wg_exclusive_scan_dpp(sum, &tot, s_wave);
+    if (t == 0)
+        *s_base = atomicAdd(reinterpret_cast<unsigned long long*>(&ctrl->pack[o.par]),
+                            ((unsigned long long)tot << kPackBits) | (unsigned long long)n);
+    __syncthreads();
+    const int32_t p0 = (int32_t)(*s_base & kPackMask);
+    const int64_t c0 = (int64_t)(*s_base >> kPackBits);
+    if ((int64_t)p0 + n > V || c0 + tot > o.max_edges) {
+        ctrl->err = 1;  // more than the graph holds: refuse
+        return;
+    }
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+        const int32_t i = t * NI + j;
+        if (i < n) {
+            s_c[i] = c;
+            o.cumul[p0 + i] = c0 + c;
+            o.rowstart[p0 + i] = a[j];
+            o.uidv[p0 + i] = u[j];
+        }
+        c += d[j];
+    }
+    __syncthreads();
+    write_tile_heads(s_c, n, tot, p0, c0, o.tile_sh, o.tile_k);
+}
+
+__global__ __launch_bounds__(kWG) void k_ms_scan(const int32_t* __restrict__ Q,
+                                                 const int64_t* __restrict__ off, MsScan out,
+                                                 Ctrl* __restrict__ ctrl,
+                                                 const int32_t* __restrict__ skip, int32_t V,
+                                                 const uint64_t* __restrict__ front)
+{
+    __shared__ uint32_t s_wave[kWG / 64];
+    __shared__ uint32_t s_c[kWG * 8];
+    __shared__ uint64_t s_base;
+    if (ctrl->done || ctrl->no_push) return;
+    const int32_t qlen = ctrl->qlen;
+    const int32_t* sk = nullptr;
+    if (skip) {
+        const int32_t fp = ctrl->full_prefix;
+        int lv = -1;
+#pragma unroll
+        for (int i = 0; i < kSkipLevels; ++i)
+            if (fp >= (1 << (kSkipLow + i))) lv = i;
+        if (lv >= 0) sk = skip + (int64_t)lv * V;
+    }
+    const uint64_t pull = front ? ctrl->pull : 0ull;
+    const bool wide = qlen > (int64_t)gridDim.x * kWG;
+    const int32_t chunk = wide ? kWG * 8 : kWG;
+    int64_t dropped = 0;
+    for (int64_t q0 = (int64_t)blockIdx.x * chunk; q0 < qlen; q0 += (int64_t)gridDim.x * chunk) {
+        const int32_t n = (int32_t)(qlen - q0 < chunk ? qlen - q0 : chunk);
+        uint32_t dr = 0;
+        if (wide)
+            ms_scan_chunk<8>(Q, q0, n, off, sk, pull, front, out, V, ctrl, s_wave, s_c, &s_base, dr);
+        else
+            ms_scan_chunk<1>(Q, q0, n, off, sk, pull, front, out, V, ctrl, s_wave, s_c, &s_base, dr);
+        dropped += dr;
+        __syncthreads();  // s_c, s_base are rewritten by the next chunk
+    }
+    if (sk || pull) {
+        for (int o = 32; o >= 1; o >>= 1) dropped += __shfl_xor(dropped, o, 64);
+        __shared__ int64_t s_drop[kWG / 64];
+        if (__lane_id() == 0) s_drop[threadIdx.x >> 6] = dropped;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            int64_t x = 0;
+            for (int w = 0; w < kWG / 64; ++w) x += s_drop[w];
+            if (x) atomicAdd(reinterpret_cast<unsigned long long*>(&ctrl->dropped[out.par]),
+                             (unsigned long long)x);
+        }
+    }
+}
+
 template <int EPT>
 __global__ __launch_bounds__(kWG) void k_ms_expand(const int64_t* __restrict__ rowstart,
                                                    const int32_t* __restrict__ uidv,
@@ -272,21 +418,24 @@ __global__ __launch_bounds__(kWG) void k_ms_expand(const int64_t* __restrict__ r
                                                    const uint64_t* __restrict__ front,
                                                    SeenNext* __restrict__ sn,
                                                    uint32_t* __restrict__ touched,
-                                                   const Ctrl* __restrict__ ctrl)
+                                                   const Ctrl* __restrict__ ctrl, int par)
 {
     __shared__ TileLds<EPT> L;
-    if (ctrl->done) return;
+    if (ctrl->done || ctrl->err) return;
     const bool sparse = ctrl->sparse != 0;
     const uint64_t push = ~ctrl->pull;
-    const int64_t r = ctrl->r;
-    const int32_t ntiles = ctrl->ntiles;
-    StageRegs<EPT> cur = fetch_stage<EPT>(blockIdx.x, ntiles, cumul, rowstart, uidv, tile_k);
+    // par >= 0: scanned in one launch, edges and entries in ctrl->pack[par]
+    const uint64_t pack = par >= 0 ? ctrl->pack[par] : 0ull;
+    const int64_t r = par >= 0 ? (int64_t)(pack >> kPackBits) : ctrl->r;
+    const int32_t ntiles = par >= 0 ? (int32_t)((r + kWG * EPT - 1) / (kWG * EPT)) : ctrl->ntiles;
+    const int32_t k_last = par >= 0 ? (int32_t)(pack & kPackMask) - 1 : -1;
+    StageRegs<EPT> cur = fetch_stage<EPT>(blockIdx.x, ntiles, cumul, rowstart, uidv, tile_k, k_last);
     for (int32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
         int32_t uu[EPT], vv[EPT];
         bool ok[EPT];
         int64_t ee[EPT];
         map_tile<EPT>(L, cur, r, cumul, rowstart, uidv, col, uu, vv, ok, ee);
-        cur = fetch_stage<EPT>(tile + gridDim.x, ntiles, cumul, rowstart, uidv, tile_k);
+        cur = fetch_stage<EPT>(tile + gridDim.x, ntiles, cumul, rowstart, uidv, tile_k, k_last);
         // one 16-byte load gives both masks of the target: lanes that have
         // seen it, and lanes already recorded for the next level (a stale
         // pair only lets more threads issue the atomic)
@@ -328,7 +477,7 @@ __device__ __forceinline__ uint64_t wave_or64(uint64_t x)
 //                them int8 rows ctrl->out8[b][v] = level.
 // OUT16 = true : serving output, lane b writes level - lane_start[b] into
 //                its own int16 buffer lane_out[b] (caller ids).
-template <bool OUT16>
+template <bool OUT16, bool FUSE>
 __global__ __launch_bounds__(kWG) void k_ms_finalize(int32_t V, const int32_t* __restrict__ orig,
                                                      SeenNext* __restrict__ sn,
                                                      uint64_t* __restrict__ front,
@@ -338,9 +487,11 @@ __global__ __launch_bounds__(kWG) void k_ms_finalize(int32_t V, const int32_t* _
                                                      const int32_t* __restrict__ lane_start,
                                                      Ctrl* __restrict__ ctrl,
                                                      const int64_t* __restrict__ deg_off,
-                                                     uint64_t* __restrict__ planes)
+                                                     uint64_t* __restrict__ planes, MsScan next)
 {
     constexpr int IT = kFinItems;
+    __shared__ uint32_t s_c[FUSE ? kWG * IT : 1];
+    __shared__ uint64_t s_wave2[kWG / 64], s_pack;
     __shared__ int16_t* s_out[64];
     __shared__ int32_t s_start[64];
     __shared__ uint32_t s_wave[kWG / 64];
@@ -399,12 +550,59 @@ __global__ __launch_bounds__(kWG) void k_ms_finalize(int32_t V, const int32_t* _
             }
             cnt += nw[j] ? 1u : 0u;
         }
-        uint32_t tot;
-        const uint32_t ex = wg_exclusive_scan<uint32_t>(cnt, &tot, s_wave);
-        if (tot == 0) continue;  // uniform: no queue slots, no outputs
-        if (threadIdx.x == 0) s_base = atomicAdd(&ctrl->qn_count, tot);
-        __syncthreads();
-        uint32_t pos = s_base + ex;
+        uint32_t tot, ex, pos;
+        if constexpr (FUSE) {
+            // the next level's scan: rows and edge numbers of the new entries
+            int64_t a[IT], a1[IT];
+            uint64_t both = cnt;
+#pragma unroll
+            for (int j = 0; j < IT; ++j) {
+                const int64_t v = c0 + j * kWG + threadIdx.x;
+                a[j] = a1[j] = 0;
+                if (nw[j]) {
+                    a[j] = deg_off[v];
+                    a1[j] = deg_off[v + 1];
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < IT; ++j) both += (uint64_t)(a1[j] - a[j]) << kPackBits;
+            uint64_t all;
+            const uint64_t before = wg_exclusive_scan<uint64_t>(both, &all, s_wave2);
+            tot = (uint32_t)(all & kPackMask);
+            if (tot == 0) continue;  // uniform: no queue slots, no outputs
+            if (threadIdx.x == 0)
+                s_pack = atomicAdd(reinterpret_cast<unsigned long long*>(&ctrl->pack[next.par]),
+                                   (unsigned long long)all);
+            __syncthreads();
+            const uint32_t p0 = (uint32_t)(s_pack & kPackMask);
+            const int64_t e0 = (int64_t)(s_pack >> kPackBits);
+            ex = (uint32_t)(before & kPackMask);
+            pos = p0 + ex;
+            if ((int64_t)p0 + tot <= V && e0 + (int64_t)(all >> kPackBits) <= next.max_edges) {
+                uint32_t c = (uint32_t)(before >> kPackBits), i = ex;
+#pragma unroll
+                for (int j = 0; j < IT; ++j) {
+                    if (!nw[j]) continue;
+                    s_c[i] = c;
+                    next.cumul[p0 + i] = e0 + c;
+                    next.rowstart[p0 + i] = a[j];
+                    next.uidv[p0 + i] = (int32_t)(c0 + j * kWG + threadIdx.x);
+                    c += (uint32_t)(a1[j] - a[j]);
+                    ++i;
+                }
+                __syncthreads();
+                write_tile_heads(s_c, (int32_t)tot, (uint32_t)(all >> kPackBits), (int32_t)p0, e0,
+                                 next.tile_sh, next.tile_k);
+            } else {
+                ctrl->err = 1;  // more than the graph holds: refuse
+            }
+        } else {
+            ex = wg_exclusive_scan<uint32_t>(cnt, &tot, s_wave);
+            if (tot == 0) continue;  // uniform: no queue slots, no outputs
+            if (threadIdx.x == 0) s_base = atomicAdd(&ctrl->qn_count, tot);
+            __syncthreads();
+            pos = s_base + ex;
+        }
 #pragma unroll
         for (int j = 0; j < IT; ++j) {
             if (!nw[j]) continue;
@@ -412,7 +610,7 @@ __global__ __launch_bounds__(kWG) void k_ms_finalize(int32_t V, const int32_t* _
             if (pos < (uint32_t)V) Qn[pos] = (int32_t)v;
             else ctrl->err = 4;
             ++pos;
-            if (deg_off) dsum += deg_off[v + 1] - deg_off[v];
+            if (!FUSE && deg_off) dsum += deg_off[v + 1] - deg_off[v];
             // each vertex writes only the lanes that reached it now
             if (OUT16) {
                 const int64_t vo = orig ? orig[v] : v;
@@ -443,7 +641,7 @@ __global__ __launch_bounds__(kWG) void k_ms_finalize(int32_t V, const int32_t* _
     }
     // one update of the level's lanes and degree sum per workgroup
     alive = wave_or64(alive);
-    if (deg_off)
+    if (!FUSE && deg_off)
         for (int d = 32; d >= 1; d >>= 1) dsum += __shfl_xor(dsum, d, 64);
     if (__lane_id() == 0) {
         s_alive[threadIdx.x >> 6] = alive;
@@ -663,7 +861,8 @@ constexpr int64_t kPullShare = 8;
 constexpr int kPullHubsSeen = 8;
 
 __global__ __launch_bounds__(64) void k_ms_advance(Ctrl* __restrict__ ctrl, int32_t V, int prefix,
-                                                   const SeenNext* __restrict__ sn, int64_t nnz)
+                                                   const SeenNext* __restrict__ sn, int64_t nnz,
+                                                   int par, int fused)
 {
     if (ctrl->done) return;
     uint64_t core = 0;
@@ -681,10 +880,20 @@ __global__ __launch_bounds__(64) void k_ms_advance(Ctrl* __restrict__ ctrl, int3
         ctrl->full_prefix = c < V ? c : V;
         ctrl->fp_cand = 0x7fffffff;
     }
-    const uint32_t q = ctrl->qn_count;
+    if (par >= 0) {  // the level's scan is spent
+        ctrl->r_total += (int64_t)(ctrl->pack[par] >> kPackBits);
+        ctrl->skipped += ctrl->dropped[par];
+        ctrl->pack[par] = 0;
+        ctrl->dropped[par] = 0;
+    }
+    const uint32_t q = fused ? (uint32_t)(ctrl->pack[par ^ 1] & kPackMask) : ctrl->qn_count;
     ctrl->sparse = (int32_t)q <= ctrl->sparse_limit;
     ctrl->last_alive = ctrl->alive;  // lanes that found vertices this level
     ctrl->pull = ctrl->sparse ? 0ull : core & ctrl->alive;
+    // the whole frontier is searched from the unseen side: its scan would only
+    // count the edges it drops, which are all of the frontier's
+    ctrl->no_push = par >= 0 && ctrl->pull != 0 && !(ctrl->alive & ~ctrl->pull);
+    if (ctrl->no_push) ctrl->skipped += ctrl->next_deg;
     ctrl->next_deg = 0;
     ctrl->alive = 0;
     ctrl->reached += q;
@@ -699,10 +908,10 @@ template <int EPT>
 static void ms_expand_launch(hipStream_t s, int grid, const int64_t* rowstart, const int32_t* uidv,
                              const int64_t* cumul, const int32_t* tile_k, const int32_t* col,
                              const uint64_t* front, SeenNext* sn, uint32_t* touched,
-                             const Ctrl* ctrl)
+                             const Ctrl* ctrl, int par)
 {
     hipLaunchKernelGGL(k_ms_expand<EPT>, dim3(grid), dim3(kWG), 0, s, rowstart, uidv, cumul, tile_k,
-                       col, front, sn, touched, ctrl);
+                       col, front, sn, touched, ctrl, par);
 }
 
 int ms_expand_blocks_per_cu(int ept)
@@ -726,38 +935,48 @@ hipError_t launch_ms_level(hipStream_t s, int scan_grid, int expand_grid, int fi
                            int64_t* rowstart, int32_t* uidv, int64_t* bsum, int64_t* cumul,
                            int32_t* tile_k, SeenNext* sn, uint64_t* front, uint32_t* touched,
                            int16_t* const* lane_out, const int32_t* lane_start, Ctrl* ctrl,
-                           const PullRows& pull, uint64_t* planes, const int32_t* skip,
-                           int prefix_grid)
+                           const PullRows& pull, int level, bool last, uint64_t* planes,
+                           const int32_t* skip, int prefix_grid)
 {
     const bool prefix = skip != nullptr && prefix_grid > 0;
     const int64_t pull_nnz = pull.n_act > 0 ? pull.nnz : 0;
-    hipError_t e = launch_scan_dev(s, scan_grid, Q, off, nullptr, deg, rowstart, uidv, bsum, cumul,
-                                   tile_k, tile_cap, kWG * ept, ctrl, prefix ? skip : nullptr, V,
-                                   pull_nnz > 0 ? front : nullptr);
-    if (e != hipSuccess) return e;
+    // scanned in one launch, or by the finalize of the level before
+    const int64_t max_edges = (tile_cap - 1) * kMinTile;
+    const bool one = max_edges < kPackMaxEdges;
+    const bool can_fuse = one && !prefix && pull_nnz == 0;
+    const int par = one ? level & 1 : -1;
+    MsScan out{rowstart, uidv, cumul, tile_k, log2_tile(kWG * ept), par, max_edges};
+    if (one && !(can_fuse && level > 0)) {
+        hipLaunchKernelGGL(k_ms_scan, dim3(scan_grid < 1 ? 1 : scan_grid), dim3(kWG), 0, s, Q, off,
+                           out, ctrl, prefix ? skip : nullptr, V, pull_nnz > 0 ? front : nullptr);
+    } else if (!one) {
+        const hipError_t e = launch_scan_dev(s, scan_grid, Q, off, nullptr, deg, rowstart, uidv, bsum,
+                                             cumul, tile_k, tile_cap, kWG * ept, ctrl,
+                                             prefix ? skip : nullptr, V,
+                                             pull_nnz > 0 ? front : nullptr);
+        if (e != hipSuccess) return e;
+    }
+    const bool fuse = can_fuse && !last;
+    out.par ^= 1;
     if (expand_grid < 1) expand_grid = 1;
     switch (ept) {
-    case 1: ms_expand_launch<1>(s, expand_grid, rowstart, uidv, cumul, tile_k, col, front, sn, touched, ctrl); break;
-    case 2: ms_expand_launch<2>(s, expand_grid, rowstart, uidv, cumul, tile_k, col, front, sn, touched, ctrl); break;
-    case 4: ms_expand_launch<4>(s, expand_grid, rowstart, uidv, cumul, tile_k, col, front, sn, touched, ctrl); break;
-    case 8: ms_expand_launch<8>(s, expand_grid, rowstart, uidv, cumul, tile_k, col, front, sn, touched, ctrl); break;
+    case 1: ms_expand_launch<1>(s, expand_grid, rowstart, uidv, cumul, tile_k, col, front, sn, touched, ctrl, par); break;
+    case 2: ms_expand_launch<2>(s, expand_grid, rowstart, uidv, cumul, tile_k, col, front, sn, touched, ctrl, par); break;
+    case 4: ms_expand_launch<4>(s, expand_grid, rowstart, uidv, cumul, tile_k, col, front, sn, touched, ctrl, par); break;
+    case 8: ms_expand_launch<8>(s, expand_grid, rowstart, uidv, cumul, tile_k, col, front, sn, touched, ctrl, par); break;
     default: return hipErrorInvalidValue;
     }
     if (fin_grid < 1) fin_grid = 1;
     hipLaunchKernelGGL(k_ms_pull, dim3(pull_nnz > 0 ? expand_grid : scan_grid), dim3(kWG), 0, s, Q,
                        pull, off, col, front, sn, ctrl);
-    if (lane_out) {
-        hipLaunchKernelGGL(k_ms_finalize<true>, dim3(fin_grid), dim3(kWG), 0, s, V, orig, sn,
-                           front, touched, Qn, lane_out, lane_start, ctrl,
-                           pull_nnz > 0 ? off : nullptr, planes);
-    } else {
-        hipLaunchKernelGGL(k_ms_finalize<false>, dim3(fin_grid), dim3(kWG), 0, s, V, orig, sn,
-                           front, touched, Qn, lane_out, lane_start, ctrl,
-                           pull_nnz > 0 ? off : nullptr, planes);
-    }
+    const auto finalize = lane_out ? (fuse ? k_ms_finalize<true, true> : k_ms_finalize<true, false>)
+                                   : (fuse ? k_ms_finalize<false, true> : k_ms_finalize<false, false>);
+    hipLaunchKernelGGL(finalize, dim3(fin_grid), dim3(kWG), 0, s, V, orig, sn, front, touched, Qn,
+                       lane_out, lane_start, ctrl, fuse || pull_nnz > 0 ? off : nullptr, planes, out);
     if (prefix)
         hipLaunchKernelGGL(k_ms_prefix, dim3(prefix_grid), dim3(kWG), 0, s, V, sn, ctrl);
-    hipLaunchKernelGGL(k_ms_advance, dim3(1), dim3(64), 0, s, ctrl, V, prefix ? 1 : 0, sn, pull_nnz);
+    hipLaunchKernelGGL(k_ms_advance, dim3(1), dim3(64), 0, s, ctrl, V, prefix ? 1 : 0, sn, pull_nnz,
+                       par, fuse ? 1 : 0);
     return hipGetLastError();
 }
 
@@ -794,6 +1013,9 @@ __global__ __launch_bounds__(kWG) void k_srv_reset(int32_t V, SeenNext* __restri
         ctrl->out8 = nullptr;
         ctrl->next_deg = 0;
         ctrl->pull = 0;
+        ctrl->no_push = 0;
+        ctrl->pack[0] = ctrl->pack[1] = 0;
+        ctrl->dropped[0] = ctrl->dropped[1] = 0;
         ctrl->sparse_limit = V / 64;
         ctrl->sparse = 1;
     }
@@ -870,6 +1092,7 @@ __global__ void k_srv_join(int32_t V, int32_t n_join, const int32_t* __restrict_
     if (i == 0) {
         ctrl->qlen = qlen + s_app;
         ctrl->sparse = ctrl->qlen <= ctrl->sparse_limit;
+        ctrl->no_push = 0;  // the new lanes push
         ctrl->done = 0;
     }
 }

@@ -666,6 +666,7 @@ __global__ __launch_bounds__(kMsW) void k_ms_small_levels(
             ctrl->qn_count = 0;
             ctrl->sparse = (int32_t)qn <= ctrl->sparse_limit;
             ctrl->pull = 0;  // chosen for a frontier that is gone
+            ctrl->no_push = 0;
             ctrl->done = qn == 0 || qn > (uint32_t)V || ovf || err ? 1 : 0;
         }
         *sy = MsSync{};

@@ -276,8 +276,9 @@ namespace {
 
 int clampi(int64_t x, int lo, int hi) { return (int)std::max<int64_t>(lo, std::min<int64_t>(x, hi)); }
 
-hipError_t enqueue_srv_level(const bfs_graph* g, SrvBatch* B, hipStream_t s, int parity)
+hipError_t enqueue_srv_level(const bfs_graph* g, SrvBatch* B, hipStream_t s, int level, bool last)
 {
+    const int parity = level & 1;
     // grids sized by the graph: every kernel is grid-stride, so this only
     // trades idle workgroups on small graphs against parallelism on big ones
     const int ept = std::max(1, g->batch_tile / kWG);
@@ -288,7 +289,7 @@ hipError_t enqueue_srv_level(const bfs_graph* g, SrvBatch* B, hipStream_t s, int
     return launch_ms_level(s, scan, expand, fin, ept, g->V, tile_cap, g->s_off, g->s_col, g->orig,
                            B->q[parity], B->q[parity ^ 1], B->deg, B->rowstart, B->suid, B->bsum,
                            B->cumul, B->tile_k, B->sn, B->front, B->touched,
-                           B->lane_out, B->lane_start, B->ctrl, g->pull);
+                           B->lane_out, B->lane_start, B->ctrl, g->pull, level, last);
 }
 
 // Capture kRoundLevels[i] levels of this batch into round[i].
@@ -297,7 +298,8 @@ int capture_rounds(const bfs_graph* g, SrvBatch* B, hipStream_t s)
     for (int i = 0; i < 3; ++i) {
         if (hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal) != hipSuccess) return BFS_ERR_HIP;
         hipError_t e = hipSuccess;
-        for (int k = 0; k < kRoundLevels[i] && e == hipSuccess; ++k) e = enqueue_srv_level(g, B, s, k & 1);
+        for (int k = 0; k < kRoundLevels[i] && e == hipSuccess; ++k)
+            e = enqueue_srv_level(g, B, s, k, k == kRoundLevels[i] - 1);
         hipGraph_t graph = nullptr;
         const hipError_t e2 = hipStreamEndCapture(s, &graph);
         if (e == hipSuccess && e2 == hipSuccess)

@@ -164,4 +164,33 @@ __device__ __forceinline__ void map_tile(TileLds<EPT>& L, const StageRegs<EPT>& 
     }
 }
 
+// The heads of the tiles that start inside a chunk: n entries from place p0 on,
+// edges [c0, c0 + total), s_c[i] the edges before entry i within the chunk.
+// One search per tile, so hub entries that cover many tiles need no care.
+__device__ __forceinline__ void write_tile_heads(const uint32_t* s_c, int32_t n, uint32_t total,
+                                                 int32_t p0, int64_t c0, int tile_sh,
+                                                 int32_t* __restrict__ tile_k)
+{
+    if (total == 0) return;
+    const int64_t x1 = (c0 + total - 1) >> tile_sh;
+    for (int64_t x = ((c0 + ((int64_t)1 << tile_sh) - 1) >> tile_sh) + threadIdx.x; x <= x1;
+         x += blockDim.x) {
+        const uint32_t e = (uint32_t)((x << tile_sh) - c0);
+        int32_t lo = 0, hi = n - 1;  // max{i : s_c[i] <= e}
+        while (lo < hi) {
+            const int32_t mid = (lo + hi + 1) >> 1;
+            if (s_c[mid] <= e) lo = mid;
+            else hi = mid - 1;
+        }
+        tile_k[x] = p0 + lo;
+    }
+}
+
+inline int log2_tile(int tile)
+{
+    int sh = 0;
+    while ((1 << sh) < tile) ++sh;
+    return sh;
+}
+
 }  // namespace bfsmi
