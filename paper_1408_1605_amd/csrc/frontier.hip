@@ -917,6 +917,11 @@ __global__ __launch_bounds__(kWG) void k_list_scan(const int32_t* __restrict__ Q
     const int64_t q0 = (int64_t)blockIdx.x * kWG * NI;
     const int32_t n = (int32_t)(qlen - q0 < kWG * NI ? qlen - q0 : kWG * NI);
     if (blockIdx.x == 0 && t == 0) ctrl->qn_count = 0;
+    if (vis_old) {
+        const int64_t stride = (int64_t)gridDim.x * kWG;
+        for (int64_t i = (int64_t)blockIdx.x * kWG + t; i < W; i += stride) vis_old[i] = vis[i];
+    }
+    if (n <= 0) return;  // uniform: a workgroup that only copies
     int32_t u[NI], id[NI];
     int64_t a[NI];
     uint32_t d[NI], sum = 0;
@@ -933,10 +938,6 @@ __global__ __launch_bounds__(kWG) void k_list_scan(const int32_t* __restrict__ Q
     }
 #pragma unroll
     for (int j = 0; j < NI; ++j) sum += d[j];
-    if (vis_old) {
-        const int64_t stride = (int64_t)gridDim.x * kWG;
-        for (int64_t i = (int64_t)blockIdx.x * kWG + t; i < W; i += stride) vis_old[i] = vis[i];
-    }
     uint32_t tot;
     uint32_t c = wg_exclusive_scan_dpp(sum, &tot, s_wave);
     if (t == 0)
@@ -970,7 +971,10 @@ hipError_t launch_list_scan(hipStream_t s, const int32_t* Q, int32_t qlen, const
     if (qlen < 1) return hipErrorInvalidValue;
     // short lists one entry per thread, so that they spread over the chip
     const int items = qlen <= (1 << 16) ? 1 : 8;
-    const unsigned grid = (unsigned)(((int64_t)qlen + kWG * items - 1) / (kWG * items));
+    unsigned grid = (unsigned)(((int64_t)qlen + kWG * items - 1) / (kWG * items));
+    // a short list of a large graph: workgroups that only copy the bitmap, 8
+    // words a thread (one workgroup alone took 480 us for 2^24 vertices)
+    if (vis_old) grid = std::max(grid, (unsigned)std::min<int64_t>(((int64_t)W + kWG * 8 - 1) / (kWG * 8), 1024));
     if (items == 1)
         hipLaunchKernelGGL(k_list_scan<1>, dim3(grid), dim3(kWG), 0, s, Q, qlen, off, uid_map,
                            rowstart, uidv, cumul, tile_k, log2_tile(tile), ctrl, par, W, vis,
