@@ -582,10 +582,10 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
     while (true) {
         if (bottom_up) {
             // one bottom-up step discovering depth lvl
-            BFS_HIP_TRY(launch_bottom_up(s, grid_cap, g->V, g->rank ? g->v_active : g->V, g->W,
+            BFS_HIP_TRY(launch_bottom_up(s, grid_cap, g->num_cus, g->V,
+                                         g->rank ? g->v_active : g->V, g->W,
                                          g->s_off, g->s_col, g->orig, g->vis, g->vis_old, lv_s,
-                                         pa_s, lvl, g->ctrl, sum_grid, g->summary_shift,
-                                         g->summary_blocks, g->summary));
+                                         pa_s, lvl, g->ctrl));
             if ((rc = read_back(false)) != BFS_OK) return rc;
             const Ctrl& c = *g->h_ctrl;
             const int64_t found = c.bu_found;
@@ -656,7 +656,12 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
         // (no prefix below the smallest skip threshold pays for its launches:
         // R-MAT 16 and a plain graph of 10^6 vertices are 10 to 15 us faster
         // without any, R-MAT 22 and 26 a quarter and a half slower)
-        const bool use_sum = g->use_summary > 0 && rmax > T &&
+        // (nor does the direction-optimizing mode before its bottom-up steps, whose
+        // top-down levels are light: it needs the frontier's edge count, from the
+        // one-launch scan)
+        const bool decide = dir_opt && !bu_done;
+        const bool quick = decide && g->nnz < kPackMaxEdges;
+        const bool use_sum = g->use_summary > 0 && rmax > T && !quick &&
                              (!fuse || (g->rank && reached >= (1 << kSkipLow)));
         const bool lds_sum = use_sum && g->use_summary == 2 && (!have || g->V >= kLdsSummaryMinV);
         const bool skip_rows =
@@ -678,7 +683,7 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
                                                old_left ? g->vis_old : nullptr));
             old_left = false;
         }
-        const bool packed = have || (fuse && !sliced && !skip_rows);
+        const bool packed = have || quick || (fuse && !sliced && !skip_rows);
         if (old_left && (sliced || !packed))
             BFS_HIP_TRY(launch_sync_old(s, grid_cap, g->W, g->vis, g->vis_old));
         if (have) {
@@ -697,12 +702,13 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
                                     g->bsum, g->cumul, g->tile_k, tile_cap, tile, T, allow_bitmap,
                                     g->ctrl, skip_rows ? g->skip : nullptr, g->V));
         old_left = false;
-        if (dir_opt && !bu_done) {
+        if (decide) {
             // the frontier's edge count decides the direction (Beamer et
             // al.): bottom-up when it exceeds the unvisited vertices' edges
             // divided by alpha; the scan is then not used
             if ((rc = read_back(false)) != BFS_OK) return rc;
-            const int64_t mf = g->h_ctrl->r + (skip_rows ? g->h_ctrl->skipped : 0);
+            const int64_t mf = quick ? (int64_t)(g->h_ctrl->pack[pk] >> kPackBits)
+                                     : g->h_ctrl->r + (skip_rows ? g->h_ctrl->skipped : 0);
             const int64_t mu = g->nnz - edges - mf;
             if (mf * g->do_alpha > mu) {
                 if (prof) {

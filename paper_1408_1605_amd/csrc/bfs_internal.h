@@ -239,11 +239,10 @@ hipError_t launch_finish(hipStream_t s, int grid, int32_t V, const int32_t* rank
 // the step's vertices into a queue.
 // Only ids below V_scan are candidates (ids at or above it have no
 // neighbour; V_scan = V when that is not known).
-hipError_t launch_bottom_up(hipStream_t s, int grid, int32_t V, int32_t V_scan, int32_t W,
-                            const int64_t* off, const int32_t* col, const int32_t* orig,
+hipError_t launch_bottom_up(hipStream_t s, int grid, int num_cus, int32_t V, int32_t V_scan,
+                            int32_t W, const int64_t* off, const int32_t* col, const int32_t* orig,
                             uint32_t* vis, uint32_t* vis_old, int32_t* level, int32_t* parent,
-                            int32_t lvl, Ctrl* ctrl, int summary_grid, int32_t summary_shift,
-                            int32_t summary_blocks, uint32_t* summary);
+                            int32_t lvl, Ctrl* ctrl);
 // Adds the number of vertices of degree >= 1, kPullLow, kPullMid and kPullHub to
 // out[0..3] (the caller zeroes them).
 hipError_t launch_count_degrees(hipStream_t s, int grid, int32_t V, const int64_t* off,
