@@ -17,7 +17,8 @@
 //       concatenation of the R fronts of its processors; a front travels as a
 //       list of local columns or, when longer than its bitmap, as the B-bit
 //       bitmap of the owner's block, unpacked by ballot/prefix compaction;
-//   expand_frontier           k2_scan_* + k2_expand: per processor, an
+//   expand_frontier           k2_scan (k2_scan_* for graphs of 2^32 edges and
+//       more) + k2_expand: per processor, an
 //       exclusive scan of the local degrees of the column frontier and the
 //       edge -> thread map of Algorithm 3 (EPT = 4, Section 3.4.1); claims in
 //       the processor's own bitmap of C*B local rows; each winner is grouped
@@ -57,7 +58,9 @@ namespace g2 {
 
 constexpr int kMaxP = 64;
 constexpr int kEPT = 4;
-constexpr int kTile = kWG * kEPT;  // edges per expansion tile
+constexpr int kTileShift = 10;
+constexpr int kTile = 1 << kTileShift;  // edges per expansion tile
+static_assert(kTile == kWG * kEPT, "a tile is kEPT edges a thread");
 constexpr int kChunk = kScanChunk; // entries per scan block
 constexpr int kListUnit = 2048;    // list entries per gather unit
 constexpr int kSlots = 8;          // XCDs
@@ -87,8 +90,8 @@ struct Ctl {
     int32_t form[kMaxP];             // how this level's expansion keeps what it finds
     int64_t rp[kMaxP];               // this level's edges by processor
     unsigned long long fold_list_msgs, fold_bitmap_msgs, fold_bytes, fold_vertices, updated;
-    int32_t tstart[kMaxP + 1];       // tiles of porder position t: [tstart[t], tstart[t+1])
-    int64_t estart[kMaxP + 1];       // edge numbering of position t starts at estart[t]
+    int32_t tstart[kMaxP + 1];       // first tile of porder position t
+    uint64_t pack[kMaxP + 1];        // position t's edges << kPackBits | entries, one-launch scan
     uint32_t segcnt[kMaxP];          // gather: reservations in front p's segment
     uint32_t dcnt[kMaxP * kMaxP];    // list lengths by (sender p, destination column m)
 };
@@ -206,6 +209,32 @@ __global__ __launch_bounds__(kWG) void k2_part_scatter(int32_t V, int32_t R, int
     }
 }
 
+// Edges of each processor (sums[p]) and the longest segment (sums[kMaxP]); the
+// caller zeroes them.
+__global__ __launch_bounds__(kWG) void k2_part_sums(int32_t V, int32_t R, int32_t B,
+                                                    const int64_t* __restrict__ off2,
+                                                    uint64_t* __restrict__ sums)
+{
+    __shared__ unsigned long long s_sum[kMaxP + 1];
+    if (threadIdx.x <= kMaxP) s_sum[threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t n = (int64_t)V * R;
+    unsigned long long mx = 0;
+    for (int64_t x = (int64_t)blockIdx.x * kWG + threadIdx.x; x < n; x += (int64_t)gridDim.x * kWG) {
+        const unsigned long long d = (unsigned long long)(off2[x + 1] - off2[x]);
+        const int32_t u = (int32_t)(x / R), i = (int32_t)(x - (int64_t)u * R);
+        const int32_t j = (int32_t)(u / ((int64_t)R * B));
+        mx = d > mx ? d : mx;
+        if (d) atomicAdd(&s_sum[j * R + i], d);
+    }
+    if (mx) atomicMax(&s_sum[kMaxP], mx);
+    __syncthreads();
+    if (threadIdx.x < kMaxP && s_sum[threadIdx.x])
+        atomicAdd(reinterpret_cast<unsigned long long*>(sums + threadIdx.x), s_sum[threadIdx.x]);
+    if (threadIdx.x == kMaxP && s_sum[kMaxP])
+        atomicMax(reinterpret_cast<unsigned long long*>(sums + kMaxP), s_sum[kMaxP]);
+}
+
 // ---------------------------------------------------------------------------
 // Initialisation (Algorithm 2 lines 1-10): level = -1, bitmaps = 0; the
 // owner of the root sets its level, predecessor and visited bit, and its
@@ -235,6 +264,7 @@ __global__ __launch_bounds__(kWG) void k2_init(int32_t V, int32_t root, int32_t*
         ctl->fold_vertices = ctl->updated = 0;
     }
     if (tid < kMaxP) ctl->segcnt[tid] = 0;
+    if (tid <= kMaxP) ctl->pack[tid] = 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -242,14 +272,12 @@ __global__ __launch_bounds__(kWG) void k2_init(int32_t V, int32_t root, int32_t*
 // front is copied; a bitmap front is unpacked (ballot/prefix compaction,
 // one reservation per workgroup in the front's segment).
 
-__global__ __launch_bounds__(kWG) void k2_gather(const Plan* __restrict__ plp,
-                                                 const int32_t* __restrict__ dst,
-                                                 const uint32_t* __restrict__ fbm,
-                                                 int32_t* __restrict__ af, Ctl* __restrict__ ctl)
+__device__ __forceinline__ void gather_units(const Plan& pl, const int32_t* __restrict__ dst,
+                                             const uint32_t* __restrict__ fbm,
+                                             int32_t* __restrict__ af, Ctl* __restrict__ ctl)
 {
     __shared__ uint32_t s_wave[kWG / 64];
     __shared__ uint32_t s_base;
-    const Plan& pl = *plp;
     const int32_t R = pl.R, C = pl.C, B = pl.B, WB = pl.WB;
     const int32_t U = pl.ub[pl.RC];
     for (int32_t u = blockIdx.x; u < U; u += gridDim.x) {
@@ -278,6 +306,138 @@ __global__ __launch_bounds__(kWG) void k2_gather(const Plan* __restrict__ plp,
             __syncthreads();
         }
     }
+}
+
+__global__ __launch_bounds__(kWG) void k2_gather(const Plan* __restrict__ plp,
+                                                 const int32_t* __restrict__ dst,
+                                                 const uint32_t* __restrict__ fbm,
+                                                 int32_t* __restrict__ af, Ctl* __restrict__ ctl)
+{
+    gather_units(*plp, dst, fbm, af, ctl);
+}
+
+// k2_plan and k2_gather in one launch, for levels of few units: every
+// workgroup reads the plan from its kernel argument.
+constexpr int kFewUnits = 16;
+constexpr int64_t kFewEntries = 1 << 16;
+__global__ __launch_bounds__(kWG) void k2_plan_gather(Plan p, Plan* __restrict__ out,
+                                                      const int32_t* __restrict__ dst,
+                                                      const uint32_t* __restrict__ fbm,
+                                                      int32_t* __restrict__ af,
+                                                      Ctl* __restrict__ ctl)
+{
+    __shared__ Plan s_plan;
+    const uint32_t* a = reinterpret_cast<const uint32_t*>(&p);
+    for (int i = threadIdx.x; i < (int)(sizeof(Plan) / 4); i += kWG) {
+        const uint32_t x = a[i];
+        reinterpret_cast<uint32_t*>(&s_plan)[i] = x;
+        if (blockIdx.x == 0) reinterpret_cast<uint32_t*>(out)[i] = x;
+    }
+    __syncthreads();
+    gather_units(s_plan, dst, fbm, af, ctl);
+}
+
+// ---------------------------------------------------------------------------
+// The degree scan (below) in one launch, for graphs of fewer than 2^32 edges:
+// each processor's tiles start where its share of the graph's tiles does
+// (ctl->tstart, fixed at creation), and a workgroup reserves its entries and
+// edges with one atomic on the processor's ctl->pack, so entries lie in the
+// order in which workgroups come.  A workgroup takes kWG * NI column entries.
+// Also clears the counters of the level and, for the processors in flagging
+// (those whose columns could reach more edges than their bitmap has words), the
+// flags k2_expand may set.  A level of a small front is a chain of launches:
+// with this, k2_plan_gather and the fold's messages spread over all
+// workgroups, R-MAT 14 on 2 x 4 299 -> 215 us, R-MAT 20 on 2 x 4 640 -> 532, on
+// 8 x 8 1,431 -> 877.
+
+template <int NI>
+__global__ __launch_bounds__(kWG) void k2_scan(const Plan* __restrict__ plp,
+                                               const int32_t* __restrict__ af,
+                                               const int64_t* __restrict__ off2,
+                                               int64_t* __restrict__ rowstart,
+                                               int32_t* __restrict__ uidv,
+                                               int64_t* __restrict__ cumul,
+                                               int32_t* __restrict__ tile_k,
+                                               int32_t* __restrict__ dst, uint64_t flagging,
+                                               Ctl* __restrict__ ctl)
+{
+    __shared__ uint32_t s_wave[kWG / 64];
+    __shared__ uint32_t s_c[kWG * NI];
+    __shared__ uint64_t s_base;
+    const Plan& pl = *plp;
+    const int t = threadIdx.x;
+    const int64_t tid = (int64_t)blockIdx.x * kWG + t, nthreads = (int64_t)gridDim.x * kWG;
+    const int64_t row16 = (int64_t)pl.C * pl.B / 16;
+    for (; flagging; flagging &= flagging - 1) {
+        const int32_t p = __builtin_ctzll(flagging);
+        uint4* f = reinterpret_cast<uint4*>(dst + (int64_t)p * pl.C * pl.B);
+        for (int64_t x = tid; x < row16; x += nthreads) f[x] = make_uint4(0u, 0u, 0u, 0u);
+    }
+    for (int64_t x = tid; x < pl.RC * pl.C; x += nthreads) ctl->dcnt[x] = 0;
+    if (tid < kMaxP) {
+        ctl->nfront[tid] = 0;
+        ctl->segcnt[tid] = 0;
+    }
+    const int32_t nch = pl.cb[pl.RC];
+    for (int32_t cid = blockIdx.x; cid < nch; cid += gridDim.x) {
+        const int32_t pos = last_le<int32_t>(pl.cb, 0, pl.RC, cid);
+        const int32_t p = pl.porder[pos];
+        const int32_t i = p % pl.R, j = p / pl.R;
+        const int64_t colbase = pl.afb[j];
+        const int64_t l0 = (int64_t)(cid - pl.cb[pos]) * (kWG * NI);
+        const int64_t left = pl.afb[j + 1] - colbase - l0;
+        const int32_t n = (int32_t)(left < kWG * NI ? left : kWG * NI);
+        int32_t u[NI];
+        int64_t a[NI];
+        uint32_t d[NI], sum = 0;
+#pragma unroll
+        for (int k = 0; k < NI; ++k) {
+            const int32_t x = t * NI + k;
+            u[k] = j * pl.R * pl.B + af[colbase + l0 + (x < n ? x : n - 1)];
+        }
+#pragma unroll
+        for (int k = 0; k < NI; ++k) {
+            const int64_t pr = (int64_t)u[k] * pl.R + i;
+            a[k] = off2[pr];
+            d[k] = t * NI + k < n ? (uint32_t)(off2[pr + 1] - a[k]) : 0u;
+        }
+#pragma unroll
+        for (int k = 0; k < NI; ++k) sum += d[k];
+        uint32_t tot;
+        uint32_t c = wg_exclusive_scan_dpp(sum, &tot, s_wave);
+        if (t == 0)
+            s_base = atomicAdd(reinterpret_cast<unsigned long long*>(&ctl->pack[pos]),
+                               ((unsigned long long)tot << kPackBits) | (unsigned long long)n);
+        __syncthreads();
+        const int64_t p0 = pl.eb[pos] + (int64_t)(s_base & kPackMask);
+        const int64_t c0 = (int64_t)ctl->tstart[pos] * kTile + (int64_t)(s_base >> kPackBits);
+        if (p0 + n > pl.eb[pos + 1] || c0 + tot > (int64_t)ctl->tstart[pos + 1] * kTile) {
+            ctl->err = 1;  // more than the processor holds: refuse
+        } else {
+#pragma unroll
+            for (int k = 0; k < NI; ++k) {
+                const int32_t x = t * NI + k;
+                if (x < n) {
+                    s_c[x] = c;
+                    cumul[p0 + x] = c0 + c;
+                    rowstart[p0 + x] = a[k];
+                    uidv[p0 + x] = u[k];
+                }
+                c += d[k];
+            }
+            __syncthreads();
+            write_tile_heads(s_c, n, tot, (int32_t)p0, c0, kTileShift, tile_k);
+        }
+        __syncthreads();  // s_c, s_base are rewritten by the next chunk
+    }
+}
+
+// A position's expansion form and edges (see k2_expand).
+__device__ __forceinline__ int32_t expand_form(const Plan& pl, int64_t rp)
+{
+    const int64_t list_limit = (int64_t)pl.C * pl.WB;  // words of the processor's bitmap
+    const bool list = pl.msg_mode == kMsgList || (pl.msg_mode == kMsgAuto && rp <= list_limit);
+    return list ? kFormList : rp > list_limit ? kFormFlags : kFormBits;
 }
 
 // ---------------------------------------------------------------------------
@@ -339,7 +499,6 @@ __global__ __launch_bounds__(kWG) void k2_scan_top(const Plan* __restrict__ plp,
 {
     __shared__ int64_t s_wave[kWG / 64];
     const Plan& pl = *plp;
-    const int64_t list_limit = (int64_t)pl.C * pl.WB;  // words of the processor's bitmap
     int64_t run = 0;
     for (int32_t t = 0; t < pl.RC; ++t) {
         const int64_t start = run;
@@ -356,12 +515,9 @@ __global__ __launch_bounds__(kWG) void k2_scan_top(const Plan* __restrict__ plp,
         run = start + (rp + kTile - 1) / kTile * kTile;
         if (threadIdx.x == 0) {
             const int32_t p = pl.porder[t];
-            ctl->estart[t] = start;
             ctl->tstart[t] = (int32_t)(start / kTile);
             ctl->rp[p] = rp;
-            const bool list = pl.msg_mode == kMsgList ||
-                              (pl.msg_mode == kMsgAuto && rp <= list_limit);
-            ctl->form[p] = list ? kFormList : rp > list_limit ? kFormFlags : kFormBits;
+            ctl->form[p] = expand_form(pl, rp);
         }
     }
     if (threadIdx.x == 0) {
@@ -370,7 +526,6 @@ __global__ __launch_bounds__(kWG) void k2_scan_top(const Plan* __restrict__ plp,
             ctl->err = 1;
             nt = 0;
         }
-        ctl->estart[pl.RC] = run;
         ctl->tstart[pl.RC] = (int32_t)nt;
         ctl->total_tiles = (int32_t)nt;
         const int64_t ne = pl.eb[pl.RC];
@@ -467,11 +622,10 @@ __global__ __launch_bounds__(kWG) void k2_scan_down(const Plan* __restrict__ plp
 // A processor that keeps no lists and has more edges than its bitmap has
 // words flags the rows it finds instead (a byte per local row, read first,
 // stored plainly; ctl->form): an atomicOr per row bound the heavy level
-// (R-MAT 20, edge factor 16, 2 x 4: 1095 -> 640 us, its
-// k2_expand there 600 -> 157; 4 x 4 at scale 22 3220 -> 1820, 8 x 8 at scale
-// 23 7180 -> 5110).  The flags lie
-// in the processor's list region, idle at such a level (C*B bytes of its
-// C*B ints), and are cleared by k2_scan_down.  k2_update reads a sender's
+// (R-MAT 20, edge factor 16, 2 x 4: 600 -> 157 us, the
+// search 1095 -> 640; 4 x 4 at scale 22 3220 -> 1820).  The flags lie in the
+// processor's list region, idle at such a level (C*B bytes of its C*B ints),
+// and are cleared by the scan.  k2_update reads a sender's
 // and its own flags next to their bitmap words, k2_front folds them into
 // the bitmap.  Concurrent finders of a row store the same flag and level, and
 // any of their columns is a valid predecessor.  Below that edge count the
@@ -489,11 +643,11 @@ __global__ __launch_bounds__(kWG) void k2_expand(const Plan* __restrict__ plp,
                                                  uint32_t* __restrict__ bm,
                                                  int32_t* __restrict__ pred,
                                                  int32_t* __restrict__ dst,
-                                                 int32_t* __restrict__ level)
+                                                 int32_t* __restrict__ level, int one)
 {
     constexpr int EPT = kEPT;
     __shared__ TileLds<EPT> L;
-    __shared__ int32_t s_tstart[kMaxP + 1];
+    __shared__ int32_t s_tile0[kMaxP], s_nt[kMaxP], s_klast[kMaxP];
     __shared__ int64_t s_rend[kMaxP];
     __shared__ uint32_t s_cnt[kMaxP];
     __shared__ uint32_t s_base[kMaxP];
@@ -501,19 +655,43 @@ __global__ __launch_bounds__(kWG) void k2_expand(const Plan* __restrict__ plp,
     const Plan& pl = *plp;
     const int32_t R = pl.R, C = pl.C, B = pl.B, WB = pl.WB, lvl = pl.lvl;
     const SlotWork sw = slot_work(pl);
-    if (threadIdx.x <= pl.RC) s_tstart[threadIdx.x] = ctl->tstart[threadIdx.x];
+    if (ctl->err) return;
     if (threadIdx.x < pl.RC) {
-        const int32_t p = pl.porder[threadIdx.x];
-        s_rend[threadIdx.x] = ctl->estart[threadIdx.x] + ctl->rp[p];
-        s_form[threadIdx.x] = ctl->form[p];
+        const int t = threadIdx.x;
+        const int32_t p = pl.porder[t];
+        const int64_t rp = one ? (int64_t)(ctl->pack[t] >> kPackBits) : ctl->rp[p];
+        const int32_t form = one ? expand_form(pl, rp) : ctl->form[p];
+        s_tile0[t] = ctl->tstart[t];
+        s_nt[t] = (int32_t)((rp + kTile - 1) / kTile);
+        s_rend[t] = (int64_t)s_tile0[t] * kTile + rp;
+        s_klast[t] = (int32_t)(pl.eb[t + 1] - 1);
+        s_form[t] = form;
+        if (one && blockIdx.x == 0) {
+            ctl->rp[p] = rp;
+            ctl->form[p] = form;
+        }
     }
     __syncthreads();
-    const int32_t A = s_tstart[sw.first], E = s_tstart[sw.end];
-    int32_t tile = A + sw.widx;
-    if (tile >= E) return;  // uniform over the workgroup
-    StageRegs<EPT> cur = fetch_stage<EPT>(tile, E, cumul, rowstart, uidv, tile_k);
-    for (; tile < E; tile += sw.nw) {
-        const int32_t t = last_le<int32_t>(s_tstart, sw.first, sw.end, tile);
+    // the slot's tiles, position by position, dealt to its workgroups in turn:
+    // tile x of position t is the (x + tiles of the positions before)-th
+    int32_t t = sw.first, x = sw.widx;
+    auto settle = [&](int32_t& tt, int32_t& xx) {
+        while (tt < sw.end && xx >= s_nt[tt]) xx -= s_nt[tt++];
+    };
+    auto fetch = [&](int32_t tt, int32_t xx) {
+        const bool in = tt < sw.end;
+        const int32_t k = in ? tt : sw.first;
+        return fetch_stage<EPT>(in ? s_tile0[k] + xx : 0, in ? s_tile0[k] + s_nt[k] : 0, cumul,
+                                rowstart, uidv, tile_k, s_klast[k]);
+    };
+    settle(t, x);
+    if (t >= sw.end) return;  // uniform over the workgroup
+    StageRegs<EPT> cur = fetch(t, x);
+    int32_t tn, xn;
+    for (; t < sw.end; t = tn, x = xn) {
+        tn = t;
+        xn = x + sw.nw;
+        settle(tn, xn);
         const int32_t p = pl.porder[t];
         const int32_t i = p % R, j = p / R;
         const bool list = s_form[t] == kFormList;
@@ -527,7 +705,7 @@ __global__ __launch_bounds__(kWG) void k2_expand(const Plan* __restrict__ plp,
         uint32_t wd[EPT];
 #pragma unroll
         for (int q = 0; q < EPT; ++q) wd[q] = ok[q] ? bmp[vv[q] >> 5] : 0xffffffffu;
-        cur = fetch_stage<EPT>(tile + sw.nw, E, cumul, rowstart, uidv, tile_k);
+        cur = fetch(tn, xn);
         if (kFlags && s_form[t] == kFormFlags) {
             uint8_t* flag = reinterpret_cast<uint8_t*>(dst + (int64_t)p * C * B);
             uint8_t fl[EPT];
@@ -629,7 +807,6 @@ __global__ __launch_bounds__(kWG) void k2_update(const Plan* __restrict__ plp,
     const int32_t R = pl.R, C = pl.C, B = pl.B, WB = pl.WB, lvl = pl.lvl;
     const SlotWork sw = slot_work(pl);
     const int64_t pw = (int64_t)C * WB;  // bitmap words per processor
-    const int64_t step = (int64_t)sw.nw * kWG;
     uint32_t accepted = 0, carried = 0;
     for (int32_t t = sw.first; t < sw.end; ++t) {
         const int32_t q = pl.porder[t];
@@ -643,17 +820,26 @@ __global__ __launch_bounds__(kWG) void k2_update(const Plan* __restrict__ plp,
         uint32_t* qcnt = &ctl->dcnt[q * C + m];
         const int64_t vbase = (int64_t)(m * R + i) * B - (int64_t)m * B;  // v = vbase + r
         const int32_t cbase = i * B - m * B;                              // ROW2COL(r) = cbase + r
+        // the messages' units of kWG entries or words, dealt to the workgroups
+        // in turn: a message alone would keep few of them busy
+        int64_t x = sw.widx;
         for (int32_t jj = 0; jj < C; ++jj) {
             if (jj == m) continue;
             const int32_t p = jj * R + i;
+            const int64_t size = fold_is_list(pl, ctl, p, m) ? (int64_t)ctl->dcnt[p * C + m] : WB;
+            const int64_t units = (size + kWG - 1) / kWG;
+            if (x >= units) {
+                x -= units;
+                continue;
+            }
             if (fold_is_list(pl, ctl, p, m)) {
                 // list message: one row per thread, one claim each; the
                 // workgroup walks the list in uniform steps so a wave's
                 // winners append with one reservation
-                const int64_t n = ctl->dcnt[p * C + m];
+                const int64_t n = size;
                 const int32_t* src = dst + ((int64_t)p * C + m) * B;
-                for (int64_t e0 = (int64_t)sw.widx * kWG; e0 < n; e0 += step) {
-                    const int64_t e = e0 + threadIdx.x;
+                for (; x < units; x += sw.nw) {
+                    const int64_t e = x * kWG + threadIdx.x;
                     bool win = false;
                     int32_t r = 0;
                     if (e < n) {
@@ -687,8 +873,8 @@ __global__ __launch_bounds__(kWG) void k2_update(const Plan* __restrict__ plp,
                 const uint32_t* b = bm_old + (int64_t)p * pw + (int64_t)m * WB;
                 uint32_t* rq = bmq + (int64_t)m * WB;
                 const uint4* pflag = flags_of(pl, ctl, dst, p);
-                for (int64_t w0 = (int64_t)sw.widx * kWG; w0 < WB; w0 += step) {
-                    const int64_t w = w0 + threadIdx.x;
+                for (; x < units; x += sw.nw) {
+                    const int64_t w = x * kWG + threadIdx.x;
                     uint32_t got = 0;
                     if (w < WB) {
                         const int64_t rw = (int64_t)m * WB + w;  // word of the local rows
@@ -722,16 +908,24 @@ __global__ __launch_bounds__(kWG) void k2_update(const Plan* __restrict__ plp,
                     }
                 }
             }
+            x -= units;
         }
     }
-    // one counter update per wave
+    // one counter update per workgroup
     for (int d = 32; d >= 1; d >>= 1) {
         accepted += __shfl_xor(accepted, d, 64);
         carried += __shfl_xor(carried, d, 64);
     }
+    __shared__ uint32_t s_sum[2][kWG / 64];
     if (__lane_id() == 0) {
-        if (accepted) atomicAdd(&ctl->updated, (unsigned long long)accepted);
-        if (carried) atomicAdd(&ctl->fold_vertices, (unsigned long long)carried);
+        s_sum[0][threadIdx.x >> 6] = accepted;
+        s_sum[1][threadIdx.x >> 6] = carried;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        unsigned long long x = 0;
+        for (int k = 0; k < kWG / 64; ++k) x += s_sum[threadIdx.x][k];
+        if (x) atomicAdd(threadIdx.x ? &ctl->fold_vertices : &ctl->updated, x);
     }
 }
 
@@ -780,6 +974,7 @@ __global__ __launch_bounds__(kWG) void k2_front(const Plan* __restrict__ plp,
         for (int d = 32; d >= 1; d >>= 1) cnt += __shfl_xor(cnt, d, 64);
         if (__lane_id() == 0 && cnt) atomicAdd(&ctl->nfront[q], cnt);
     }
+    if (blockIdx.x == 0 && threadIdx.x <= kMaxP) ctl->pack[threadIdx.x] = 0;  // spent
     if (blockIdx.x == 0 && C > 1) {
         unsigned long long nl = 0, nb = 0, bytes = 0;
         for (int32_t x = threadIdx.x; x < pl.RC * C; x += kWG) {
@@ -849,6 +1044,8 @@ using namespace bfsmi;
 using namespace bfsmi::g2;
 
 struct bfs_grid2d {
+    int64_t nnzp[kMaxP] = {};  // edges by processor
+    int64_t maxseg = 0;        // most edges of one column in one processor
     int32_t V = 0, R = 1, C = 1, RC = 1, B = 32, WB = 1;
     int64_t nnz = 0;
     int device = 0;
@@ -1000,6 +1197,7 @@ int run2d(bfs_grid2d* g, int32_t root, int32_t msg_mode, int32_t* levels, int32_
     int32_t nlevels = 1;
     int32_t lvl = 1;
     const int cap = g->num_cus * 8;
+    const bool one = g->nnz < kPackMaxEdges;  // one-launch scan
     while (true) {
         // column lists and the scan's entry / block / gather-unit tables
         int64_t ncol[kMaxP] = {0};
@@ -1018,12 +1216,15 @@ int run2d(bfs_grid2d* g, int32_t root, int32_t msg_mode, int32_t* levels, int32_
                 at += P.nfront[j * R + i];
             }
         }
+        // short columns one entry per thread, so that they spread over the chip
+        const bool wide = !one || total > kFewEntries;
+        const int32_t chunk = wide ? kChunk : kWG;
         P.eb[0] = 0;
         P.cb[0] = 0;
         for (int t = 0; t < RC; ++t) {
             const int64_t n = ncol[P.porder[t] / R];
             P.eb[t + 1] = P.eb[t] + n;
-            P.cb[t + 1] = P.cb[t] + (int32_t)((n + kChunk - 1) / kChunk);
+            P.cb[t + 1] = P.cb[t] + (int32_t)((n + chunk - 1) / chunk);
         }
         P.ub[0] = 0;
         for (int p = 0; p < RC; ++p) {
@@ -1039,24 +1240,39 @@ int run2d(bfs_grid2d* g, int32_t root, int32_t msg_mode, int32_t* levels, int32_
             }
         }
         P.lvl = lvl;
-        hipLaunchKernelGGL(k2_plan, dim3(1), dim3(kWG), 0, s, P, g->plan);
-        if (P.ub[RC] > 0)
+        const int32_t nch = P.cb[RC];
+        if (P.ub[RC] <= kFewUnits) {
+            hipLaunchKernelGGL(k2_plan_gather, dim3(std::max(1, P.ub[RC])), dim3(kWG), 0, s, P,
+                               g->plan, g->dst, g->fbm, g->af, g->ctl);
+        } else {
+            hipLaunchKernelGGL(k2_plan, dim3(1), dim3(kWG), 0, s, P, g->plan);
             hipLaunchKernelGGL(k2_gather, dim3(std::min(P.ub[RC], cap)), dim3(kWG), 0, s, g->plan,
                                g->dst, g->fbm, g->af, g->ctl);
-        const int32_t nch = P.cb[RC];
-        if (nch > 0)
-            hipLaunchKernelGGL(k2_scan_reduce, dim3(std::min(nch, cap)), dim3(kWG), 0, s, g->plan,
-                               g->af, g->off2, g->deg, g->rowstart, g->uidv, g->bsum);
-        hipLaunchKernelGGL(k2_scan_top, dim3(1), dim3(kWG), 0, s, g->plan, g->bsum, g->cumul,
-                           g->tile_k, g->tile_cap, g->ctl);
-        if (nch > 0)
-            hipLaunchKernelGGL(k2_scan_down, dim3(std::min(nch, cap)), dim3(kWG), 0, s, g->plan,
-                               g->deg, g->bsum, g->tile_cap, g->cumul, g->tile_k, g->dst, g->ctl);
+        }
+        if (one) {
+            uint64_t flagging = 0;  // processors that may flag
+            for (int p = 0; p < RC && msg_mode != kMsgList; ++p)
+                if (std::min(ncol[p / R] * g->maxseg, g->nnzp[p]) > pw) flagging |= 1ull << p;
+            const int grid = std::min(cap, std::max(nch, flagging ? g->num_cus : 1));
+            hipLaunchKernelGGL(wide ? k2_scan<kScanItems> : k2_scan<1>, dim3(grid), dim3(kWG), 0, s,
+                               g->plan, g->af, g->off2, g->rowstart, g->uidv, g->cumul, g->tile_k,
+                               g->dst, flagging, g->ctl);
+        } else {
+            if (nch > 0)
+                hipLaunchKernelGGL(k2_scan_reduce, dim3(std::min(nch, cap)), dim3(kWG), 0, s,
+                                   g->plan, g->af, g->off2, g->deg, g->rowstart, g->uidv, g->bsum);
+            hipLaunchKernelGGL(k2_scan_top, dim3(1), dim3(kWG), 0, s, g->plan, g->bsum, g->cumul,
+                               g->tile_k, g->tile_cap, g->ctl);
+            if (nch > 0)
+                hipLaunchKernelGGL(k2_scan_down, dim3(std::min(nch, cap)), dim3(kWG), 0, s, g->plan,
+                                   g->deg, g->bsum, g->tile_cap, g->cumul, g->tile_k, g->dst,
+                                   g->ctl);
+        }
         const bool may_flag = msg_mode != kMsgList;
         const auto expand = may_flag ? k2_expand<true> : k2_expand<false>;
         hipLaunchKernelGGL(expand, dim3(g->expand_grid[may_flag]), dim3(kWG), 0, s, g->plan, g->ctl,
                            g->rowstart, g->uidv, g->cumul, g->tile_k, g->lrow, g->bm, g->pred,
-                           g->dst, levels);
+                           g->dst, levels, one ? 1 : 0);
         if (C > 1)
             hipLaunchKernelGGL(k2_update, dim3(g->slot_grid), dim3(kWG), 0, s, g->plan, g->ctl,
                                g->bm, g->bm_old, g->pred, g->dst, levels);
@@ -1248,6 +1464,24 @@ int bfs_grid2d_create(bfs_grid2d** out, int32_t V, int64_t nnz, const int64_t* d
     hipLaunchKernelGGL(k2_part_scatter, dim3(pgrid), dim3(kWG), 0, s, V, R, g->B, d_row_offsets,
                        d_col, g->off2, g->lrow);
     e = hipGetLastError();
+    // the processors' edges, and where their tiles start (one-launch scan)
+    uint64_t sums[kMaxP + 1] = {};
+    if (e == hipSuccess) e = hipMemcpyAsync(g->ctl->pack, sums, sizeof(sums), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(k2_part_sums, dim3(cus), dim3(kWG), 0, s, V, R, g->B, g->off2,
+                           g->ctl->pack);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipMemcpyAsync(sums, g->ctl->pack, sizeof(sums), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return bail(hip_fail(e, "2D partition"));
+    int32_t tstart[kMaxP + 1] = {};
+    for (int t = 0; t < g->RC; ++t) {
+        g->nnzp[t] = (int64_t)sums[t];
+        tstart[t + 1] = tstart[t] + (int32_t)((sums[P.porder[t]] + kTile - 1) / kTile);
+    }
+    g->maxseg = (int64_t)sums[kMaxP];
+    e = hipMemcpyAsync(g->ctl->tstart, tstart, sizeof(tstart), hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return bail(hip_fail(e, "2D partition"));
     *out = g;

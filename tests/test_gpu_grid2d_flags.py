@@ -67,3 +67,18 @@ def test_lists_beside_flags(bfsmi, R, C):
     g = graphgen.from_edges(n, src, dst)
     g.name = "heavy%dx%d" % (R, C)
     _search(bfsmi, g, R, C, [1, n - 1, int(dst[-1])])
+
+
+@pytest.mark.parametrize("leaves", [255, 257, 32_767, 32_769, 65_535, 65_536, 65_537])
+@pytest.mark.parametrize("R,C", [(1, 1), (2, 4), (8, 8)])
+def test_scan_widths(bfsmi, leaves, R, C):
+    # the leaves' level: columns around a workgroup's 256 entries and levels
+    # around the 65536 entries where a thread takes eight; 16 list units of
+    # 2048 entries, above which plan and gather are two launches
+    rng = np.random.default_rng(leaves)
+    n = leaves + leaves // 2 + 7
+    src = np.concatenate([np.zeros(leaves, np.int64), rng.integers(1, leaves + 1, leaves)])
+    dst = np.concatenate([np.arange(1, leaves + 1), rng.integers(1, n, leaves)])
+    g = graphgen.from_edges(n, src, dst)
+    g.name = "leaves%d" % leaves
+    _search(bfsmi, g, R, C, [0, 1])
