@@ -532,7 +532,8 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
                            : fuse             ? reinterpret_cast<uint8_t*>(g->deg)
                                               : nullptr;
     BFS_HIP_TRY(launch_init(s, g->V, g->W, root, g->rank, lv_s, pa_s, g->vis, g->vis_old,
-                            g->q[0], g->ctrl, g->small_sync, grid_cap, g->rank ? 0 : 1, flags));
+                            g->q[0], g->ctrl, g->small_sync, grid_cap, g->rank ? 0 : 1, flags,
+                            g->csr, g->n_csr));
     const int32_t sum_words = g->summary_words;
     const int xgrid_full = g->num_cus * std::min(g->grid_wgs, expand_blocks_per_cu(g->ept, 0));
     const int xgrid_sum = g->num_cus * std::min(g->grid_wgs, expand_blocks_per_cu(g->ept, sum_words));
@@ -559,6 +560,13 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
             const int rc = wait_published(&mirror->seq, g->seq, s);
             if (rc != BFS_OK) return rc;
         }
+        if (g->h_ctrl->err & kErrCsr) {
+            const int32_t code = g->h_ctrl->err & ~kErrCsr;
+            if (code & 3)
+                return fail(BFS_ERR_INVALID, "row offsets are not a valid CSR (code %d)", code);
+            return fail(BFS_ERR_INVALID, "a column id is outside [0, V)");
+        }
+        if (g->maxdeg < 0) g->maxdeg = g->h_ctrl->maxdeg;
         if (g->h_ctrl->err)
             return fail(BFS_ERR_HIP, "internal guard tripped (code %d)", g->h_ctrl->err);
         return BFS_OK;
@@ -579,6 +587,7 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
     const int nb_grid = (int)std::max<int64_t>(
         1, std::min<int64_t>(((int64_t)g->W + kBitmapWordsPerWG - 1) / kBitmapWordsPerWG, grid_cap));
     const int sum_grid = std::max(1, std::min(grid_cap, (g->summary_blocks + 31) / 32));
+    if (g->maxdeg < 0 && !dev_ok && (rc = read_back(false)) != BFS_OK) return rc;
     while (true) {
         if (bottom_up) {
             // one bottom-up step discovering depth lvl

@@ -58,7 +58,7 @@ struct alignas(64) Ctrl {
     int8_t* out8;        // batch: output rows (read by the device each launch)
     // single-root persistent loop (smallloop.hip)
     int32_t steps;       // levels completed in the loop
-    int32_t pad3;
+    int32_t maxdeg;      // searches that check their CSR: its largest degree
     int64_t skipped;     // edges the degree scan dropped (row prefix skip)
     int32_t fp_cand;     // batch: first id some live lane has not seen (prefix search)
     int32_t pad4;
@@ -85,15 +85,21 @@ static_assert(offsetof(Ctrl, pack) / 128 != offsetof(Ctrl, dropped) / 128, "two 
 
 
 struct SmallSync;  // below
+constexpr int32_t kErrCsr = 0x100;  // ctrl->err: an invalid CSR
 
 // ---- single-root kernels (frontier.hip) ----
 // Also clears the persistent loop's sync block.
+// csr non-null: what the CSR check's n_csr workgroups found
+// (launch_check_csr); when one found a fault, nothing is initialised, ctrl->err
+// becomes kErrCsr | the check's code and the persistent loop runs nothing.
+// Otherwise ctrl->maxdeg is the largest degree.
 // fill == 0: only the root's level / parent entries (degree order; the
 // finish pass masks unvisited vertices).
 hipError_t launch_init(hipStream_t s, int32_t V, int32_t W, int32_t root,
                        const int32_t* rank, int32_t* level, int32_t* parent,
                        uint32_t* vis, uint32_t* vis_old, int32_t* Q, Ctrl* ctrl, SmallSync* sy,
-                       int grid_cap, int fill, uint8_t* found = nullptr);
+                       int grid_cap, int fill, uint8_t* found = nullptr,
+                       const int2* csr = nullptr, int n_csr = 0);
 
 // Degree scan of the frontier Q (three launches, entries in Q's order): deg, cumul (exclusive, cumul[qlen] = r),
 // rowstart[k] = off[Q[k]], uidv[k] = uid_map ? uid_map[Q[k]] : Q[k], and
@@ -194,7 +200,7 @@ int small_loop_blocks();
 // level's output, ctrl->qn_count + the entries in ctrl->pack[-1 - qlen] (one of
 // them is 0), also stored to ctrl->front_n; the loop then runs no level when it
 // is 0 or above qlimit.  Levels run here leave both packs zero.  h_ctrl non-null: pinned host mirror of ctrl, published
-// at the end with sequence number seq.  The loop does not keep vis_old.  rlimit is at most 8192 * wgs; maxdeg: the graph's
+// at the end with sequence number seq.  The loop does not keep vis_old.  rlimit is at most 8192 * wgs; maxdeg (negative: in ctrl->maxdeg): the graph's
 // largest degree.
 hipError_t launch_small_levels(hipStream_t s, int wgs, int cls, int32_t V, const int64_t* off,
                                const int32_t* col, const int32_t* orig, uint32_t* vis,
@@ -356,6 +362,11 @@ hipError_t build_degree_order(hipStream_t s, int32_t V, int64_t nnz, const int64
                               int64_t* bsum_tmp, int32_t* tile_k, int64_t tile_cap,
                               uint32_t* hist_tmp, Ctrl* ctrl, int grid_cap);
 
+// The same check without memory to clear first: workgroup i of the launch stores
+// its {code, largest degree} in out[i]; returns their number in n_out (at most
+// 1024, one per 1024 of max(V, nnz) entries).
+hipError_t launch_check_csr(hipStream_t s, int32_t V, int64_t nnz, const int64_t* off,
+                            const int32_t* col, int2* out, int* n_out);
 hipError_t launch_validate_csr(hipStream_t s, int32_t V, int64_t nnz,
                                const int64_t* off, const int32_t* col,
                                int32_t* bad_flag, int32_t* maxdeg, int check_col);

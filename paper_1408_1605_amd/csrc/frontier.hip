@@ -35,8 +35,28 @@ __global__ __launch_bounds__(kWG) void k_init(int32_t V, int32_t W, int32_t root
                                               uint32_t* __restrict__ vis_old,
                                               int32_t* __restrict__ Q, Ctrl* __restrict__ ctrl,
                                               SmallSync* __restrict__ sy, int vec, int fill, uint4* __restrict__ found16,
-                                              int64_t n_found16)
+                                              int64_t n_found16,
+                                              const int2* __restrict__ csr, int n_csr)
 {
+    int32_t maxdeg = 0;
+    if (csr) {
+        __shared__ int32_t s_bad, s_max;
+        if (threadIdx.x == 0) s_bad = s_max = 0;
+        __syncthreads();
+        for (int i = threadIdx.x; i < n_csr; i += kWG) {
+            if (csr[i].x) atomicOr(&s_bad, csr[i].x);
+            atomicMax(&s_max, csr[i].y);
+        }
+        __syncthreads();
+        maxdeg = s_max;
+        if (s_bad) {  // uniform, in every workgroup
+            if (blockIdx.x == 0 && threadIdx.x == 0) {
+                *sy = SmallSync{};
+                ctrl->err = kErrCsr | s_bad;
+            }
+            return;
+        }
+    }
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int32_t rin = rank ? rank[root] : root;  // the root's search id
@@ -95,6 +115,7 @@ __global__ __launch_bounds__(kWG) void k_init(int32_t V, int32_t W, int32_t root
         ctrl->levels = 1;
         ctrl->bitmap_levels = 0;
         ctrl->err = 0;
+        ctrl->maxdeg = maxdeg;
         ctrl->skipped = 0;
         ctrl->pack[0] = ctrl->pack[1] = 0;
         ctrl->dropped[0] = ctrl->dropped[1] = 0;
@@ -105,7 +126,7 @@ __global__ __launch_bounds__(kWG) void k_init(int32_t V, int32_t W, int32_t root
 hipError_t launch_init(hipStream_t s, int32_t V, int32_t W, int32_t root, const int32_t* rank,
                        int32_t* level, int32_t* parent, uint32_t* vis, uint32_t* vis_old,
                        int32_t* Q, Ctrl* ctrl, SmallSync* sy, int grid_cap, int fill,
-                       uint8_t* found)
+                       uint8_t* found, const int2* csr, int n_csr)
 {
     const bool vec = ((uintptr_t)level % 16 == 0) &&
                      (parent == nullptr || (uintptr_t)parent % 16 == 0);
@@ -119,7 +140,7 @@ hipError_t launch_init(hipStream_t s, int32_t V, int32_t W, int32_t root, const 
     if (grid < 1) grid = 1;
     hipLaunchKernelGGL(k_init, dim3((unsigned)grid), dim3(kWG), 0, s, V, W, root, rank, level,
                        parent, vis, vis_old, Q, ctrl, sy, vec ? 1 : 0, fill,
-                       reinterpret_cast<uint4*>(found), n_found16);
+                       reinterpret_cast<uint4*>(found), n_found16, csr, n_csr);
     return hipGetLastError();
 }
 
@@ -1317,7 +1338,8 @@ __global__ __launch_bounds__(kWG) void k_validate_csr(int32_t V, int64_t nnz,
                                                       const int64_t* __restrict__ off,
                                                       const int32_t* __restrict__ col,
                                                       int32_t* __restrict__ bad,
-                                                      int32_t* __restrict__ maxdeg, int check_col)
+                                                      int32_t* __restrict__ maxdeg, int check_col,
+                                                      int2* __restrict__ out)
 {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1344,12 +1366,36 @@ __global__ __launch_bounds__(kWG) void k_validate_csr(int32_t V, int64_t nnz,
         mx = m2 > mx ? m2 : mx;
     }
     if (__lane_id() == 0) s_max[threadIdx.x >> 6] = mx;
-    if (mybad) atomicOr(bad, mybad);
+    __shared__ int32_t s_bad;
+    if (threadIdx.x == 0) s_bad = 0;
+    __syncthreads();
+    if (mybad) atomicOr(&s_bad, mybad);
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int w = 1; w < kWG / 64; ++w) mx = s_max[w] > mx ? s_max[w] : mx;
-        if (mx > 0) atomicMax(maxdeg, mx);
+        if (out) {
+            out[blockIdx.x] = make_int2(s_bad, mx);
+        } else {
+            if (s_bad) atomicOr(bad, s_bad);
+            if (mx > 0) atomicMax(maxdeg, mx);
+        }
     }
+}
+
+static unsigned check_grid(int64_t work)
+{
+    const int64_t grid = (work + 4 * kWG - 1) / (4 * kWG);  // a few items per thread
+    return (unsigned)(grid < 1 ? 1 : grid > 1024 ? 1024 : grid);
+}
+
+hipError_t launch_check_csr(hipStream_t s, int32_t V, int64_t nnz, const int64_t* off,
+                            const int32_t* col, int2* out, int* n_out)
+{
+    const unsigned grid = check_grid(nnz > V ? nnz : V);
+    *n_out = (int)grid;
+    hipLaunchKernelGGL(k_validate_csr, dim3(grid), dim3(kWG), 0, s, V, nnz, off, col, nullptr,
+                       nullptr, 1, out);
+    return hipGetLastError();
 }
 
 hipError_t launch_validate_csr(hipStream_t s, int32_t V, int64_t nnz, const int64_t* off,
@@ -1357,9 +1403,8 @@ hipError_t launch_validate_csr(hipStream_t s, int32_t V, int64_t nnz, const int6
                                int check_col)
 {
     const int64_t work = check_col && nnz > V ? nnz : V;
-    const int64_t grid = (work + 4 * kWG - 1) / (4 * kWG);  // a few items per thread
-    hipLaunchKernelGGL(k_validate_csr, dim3((unsigned)(grid < 1 ? 1 : grid > 1024 ? 1024 : grid)),
-                       dim3(kWG), 0, s, V, nnz, off, col, bad_flag, maxdeg, check_col);
+    hipLaunchKernelGGL(k_validate_csr, dim3(check_grid(work)), dim3(kWG), 0, s, V, nnz, off, col,
+                       bad_flag, maxdeg, check_col, nullptr);
     return hipGetLastError();
 }
 

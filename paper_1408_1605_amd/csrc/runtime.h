@@ -43,7 +43,9 @@ struct bfs_graph {
     uint32_t flags = 0;
     int device = 0;
     int num_cus = 0;
-    int32_t maxdeg = 0;
+    int32_t maxdeg = 0;         // negative: the CSR check of the search's own finds it
+    const int2* csr = nullptr;  // ... where its n_csr workgroups leave it
+    int n_csr = 0;
     bfsmi::WsLayout L{};
 
     uint32_t* vis = nullptr;

@@ -736,7 +736,8 @@ __global__ __launch_bounds__(kSW) void k_small_levels(
     // qlen0 < 0: launched right behind a host-driven level, whose next
     // frontier size is in ctrl; an empty frontier ends the search and one
     // above the limit goes back to the host, both before any level
-    bool run = true;
+    bool run = !(ctrl->err & kErrCsr);
+    if (maxdeg < 0) maxdeg = ctrl->maxdeg;
     if (qlen0 < 0) {
         qlen0 = (int32_t)(ctrl->qn_count + (uint32_t)(ctrl->pack[-1 - qlen0] & kPackMask));
         if (w == 0 && t == 0) scoped_store<false>(&ctrl->front_n, (uint32_t)qlen0);
