@@ -583,7 +583,14 @@ hipError_t launch_sync_old(hipStream_t s, int grid, int32_t W, const uint32_t* v
 // summary_words > 0, the visited summary of this level is copied into LDS
 // and answers the early test before any bitmap load.
 
-template <int EPT>
+// Parents are written once per search and read back only at its end: past the
+// caches where they are larger than these can keep, else into them, for the
+// finish pass and the other parents of the line (R-MAT 16 152 -> 140 us, 20
+// 336 -> 310, 23 1,240 -> 1,218; 24 the same; 25 and 26, if cached, 2 and 4
+// percent slower).
+constexpr int32_t kStreamParentsV = 1 << 24;
+
+template <int EPT, bool NT>
 __global__ __launch_bounds__(kWG) void k_expand(int32_t V, const int64_t* __restrict__ rowstart,
                                                 const int32_t* __restrict__ uidv,
                                                 const int64_t* __restrict__ cumul,
@@ -681,8 +688,11 @@ __global__ __launch_bounds__(kWG) void k_expand(int32_t V, const int64_t* __rest
                 const uint32_t b = (uint32_t)v >> shift;
                 known[j] = (s_sum[b >> 5] >> (b & 31)) & 1u;
             }
-            if (!known[j]) wd[j] = vis[v >> 5];
         }
+        // (unconditional, of a valid word: behind a branch the compiler waits
+        // for each load before it issues the next)
+#pragma unroll
+        for (int j = 0; j < EPT; ++j) wd[j] = vis[known[j] ? 0 : vv[j] >> 5];
         // the next tile's staging loads overlap this tile's probes and claims
         cur = fetch_stage<EPT>(tile + t_step, t_end, cumul, rowstart, uidv, tile_k, k_last);
         bool need[EPT];
@@ -714,7 +724,10 @@ __global__ __launch_bounds__(kWG) void k_expand(int32_t V, const int64_t* __rest
             for (int j = 0; j < EPT; ++j) {
                 if (!fl[j]) {
                     found[vv[j]] = 1;
-                    if (parent) __builtin_nontemporal_store(uu[j], parent + vv[j]);
+                    if (parent) {
+                        if constexpr (NT) __builtin_nontemporal_store(uu[j], parent + vv[j]);
+                        else parent[vv[j]] = uu[j];
+                    }
                 }
             }
             __syncthreads();
@@ -734,8 +747,10 @@ __global__ __launch_bounds__(kWG) void k_expand(int32_t V, const int64_t* __rest
         for (int j = 0; j < EPT; ++j) {
             if (win[j]) {
                 if (list_out) level[vv[j]] = lvl;
-                // written once per search, read back only at its end
-                if (parent) __builtin_nontemporal_store(uu[j], parent + vv[j]);
+                if (parent) {
+                    if constexpr (NT) __builtin_nontemporal_store(uu[j], parent + vv[j]);
+                    else parent[vv[j]] = uu[j];
+                }
             }
         }
         if (list_out) {
@@ -780,7 +795,7 @@ hipError_t launch_expand(hipStream_t s, int ept, int grid, int32_t V, const int6
     const size_t dyn = (size_t)summary_words * 4;
 #define BFS_EXPAND_CASE(E)                                                                        \
     case E:                                                                                      \
-        hipLaunchKernelGGL(k_expand<E>, dim3(grid), dim3(kWG), dyn, s, V, rowstart, uidv, cumul,  \
+        hipLaunchKernelGGL((V > kStreamParentsV ? k_expand<E, true> : k_expand<E, false>), dim3(grid), dim3(kWG), dyn, s, V, rowstart, uidv, cumul,  \
                            tile_k, col, summary, summary_words, shift, use_prefix, vis,           \
                            vis_old,                                                              \
                            level, parent,                                                        \
@@ -804,10 +819,10 @@ int expand_blocks_per_cu(int ept, int summary_words)
     const size_t dyn = (size_t)(summary_words > 0 ? summary_words : 0) * 4;
     hipError_t e = hipErrorInvalidValue;
     switch (ept) {
-    case 1: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_expand<1>, kWG, dyn); break;
-    case 2: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_expand<2>, kWG, dyn); break;
-    case 4: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_expand<4>, kWG, dyn); break;
-    case 8: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_expand<8>, kWG, dyn); break;
+    case 1: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_expand<1, true>, kWG, dyn); break;
+    case 2: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_expand<2, true>, kWG, dyn); break;
+    case 4: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_expand<4, true>, kWG, dyn); break;
+    case 8: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_expand<8, true>, kWG, dyn); break;
     default: break;
     }
     if (e != hipSuccess || n < 1) n = 1;
