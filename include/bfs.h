@@ -137,7 +137,7 @@ extern "C" {
                                       valid parents                          */
 #define BFS_OPT_XCD_SLICES      15 /* degree-ordered graphs: 1 (default) runs the
                                       early host-driven levels of graphs with
-                                      at least 2^23 vertices (frontier and
+                                      at least 2^20 vertices (frontier and
                                       visited set both at most V/64) as XCD-
                                       sliced levels: the ids are dealt to 8
                                       slices by 1024-id blocks (one line of

@@ -320,9 +320,14 @@ int bfs_graph_create(bfs_graph** out, int32_t V, int64_t nnz, const int64_t* d_r
         // of two), so the vertices of at least each degree are exactly the
         // ids below their count
         uint32_t* d_cnt = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(g->scratch) + 128);
+        unsigned long long* d_sl = reinterpret_cast<unsigned long long*>(d_cnt + 16);
         uint32_t h_cnt[4] = {0, 0, 0, 0};
+        unsigned long long h_sl[kXcdSlices] = {};
         if (e == hipSuccess) e = hipMemcpyAsync(d_cnt, h_cnt, sizeof(h_cnt), hipMemcpyHostToDevice, s);
-        if (e == hipSuccess) e = launch_count_degrees(s, g->num_cus * 8, V, g->s_off, d_cnt);
+        if (e == hipSuccess) e = hipMemcpyAsync(d_sl, h_sl, sizeof(h_sl), hipMemcpyHostToDevice, s);
+        if (e == hipSuccess)
+            e = launch_count_degrees(s, g->num_cus * 8, V, g->s_off, g->xo, d_cnt, d_sl);
+        if (e == hipSuccess) e = hipMemcpyAsync(h_sl, d_sl, sizeof(h_sl), hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipMemcpyAsync(h_cnt, d_cnt, sizeof(h_cnt), hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) {
@@ -330,6 +335,7 @@ int bfs_graph_create(bfs_graph** out, int32_t V, int64_t nnz, const int64_t* d_r
             return cleanup(hip_fail(e, "degree ordering"));
         }
         g->v_active = (int32_t)h_cnt[0];
+        for (int k = 0; k < kXcdSlices; ++k) g->slice_nnz[k] = (int64_t)h_sl[k];
         // a pull level reads the rows as in-edges
         if (g->symmetric)
             g->pull = PullRows{(int32_t)h_cnt[3], (int32_t)h_cnt[2], (int32_t)h_cnt[1],
@@ -581,6 +587,7 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
     int64_t bu_front_deg = 0, bu_prev = 0, examined = 0;
     int32_t bu_levels = 0;
     int pk = 0;             // ctrl->pack[pk]: this host-driven level's size
+    int slice_set = 0;      // small_sync->slice[slice_set]: the next sliced level's
     bool scanned = false;   // the current frontier's scan is there
     bool prefixed = false;  // ... and ctrl->full_prefix is its level's prefix
     int64_t r_next = 0;     // its edges
@@ -654,6 +661,14 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
             g->xo && g->xcd_slices != 0 && !dir_opt && (int64_t)qlen * kXcdSlices <= g->V &&
             (g->xcd_slices == 2 ||
              (g->V >= kSliceMinV && reached * kXcdSlices <= (int64_t)g->V));
+        // ... its scan in one launch where every slice finds room for its tiles
+        SliceTiles st8{};
+        bool slice_one = sliced && fuse;
+        for (int k = 0; slice_one && k < kXcdSlices; ++k) {
+            st8.t[k + 1] = st8.t[k] + (int32_t)((g->slice_nnz[k] + tile - 1) / tile);
+            slice_one = st8.t[k + 1] <= tile_cap;
+        }
+        uint64_t* const slice_pack = slice_one ? g->small_sync->slice[slice_set] : nullptr;
         const bool have = scanned && !sliced;  // the level before left the scan
         int64_t rmax = (int64_t)qlen * (int64_t)g->maxdeg;
         if (rmax > g->nnz) rmax = g->nnz;
@@ -670,7 +685,9 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
         // one-launch scan)
         const bool decide = dir_opt && !bu_done;
         const bool quick = decide && g->nnz < kPackMaxEdges;
-        const bool use_sum = g->use_summary > 0 && rmax > T && !quick &&
+        // a sliced level after a bitmap level has that level's prefix
+        const bool known = sliced && scanned && prefixed && g->V < kLdsSummaryMinV;
+        const bool use_sum = g->use_summary > 0 && rmax > T && !quick && !known &&
                              (!fuse || (g->rank && reached >= (1 << kSkipLow)));
         const bool lds_sum = use_sum && g->use_summary == 2 && (!have || g->V >= kLdsSummaryMinV);
         const bool skip_rows =
@@ -693,7 +710,7 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
             old_left = false;
         }
         const bool packed = have || quick || (fuse && !sliced && !skip_rows);
-        if (old_left && (sliced || !packed))
+        if (old_left && !slice_one && (sliced || !packed))
             BFS_HIP_TRY(launch_sync_old(s, grid_cap, g->W, g->vis, g->vis_old));
         if (have) {
             // the compaction has scanned this frontier
@@ -701,7 +718,13 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
             BFS_HIP_TRY(launch_list_scan(s, Q, qlen, g->s_off, g->orig, g->rowstart, g->suid,
                                          g->cumul, g->tile_k, tile, g->ctrl, pk, g->W, g->vis,
                                          old_left ? g->vis_old : nullptr));
-        else if (sliced)
+        else if (slice_one) {
+            BFS_HIP_TRY(launch_slice_scan_one(s, Q, qlen, g->s_off, g->xo, g->orig, g->rowstart,
+                                              g->suid, g->cumul, g->tile_k, tile, st8, slice_pack,
+                                              g->small_sync->slice[slice_set ^ 1], g->ctrl, g->W,
+                                              g->vis, old_left ? g->vis_old : nullptr));
+            slice_set ^= 1;
+        } else if (sliced)
             BFS_HIP_TRY(launch_slice_scan(s, std::max(1, std::min(grid_cap, (qlen + kWG - 1) / kWG)),
                                           Q, qlen, g->s_off, g->xo, g->orig, g->deg, g->rowstart,
                                           g->suid, g->bsum, g->cumul, g->tile_k, tile_cap, tile, T,
@@ -747,10 +770,10 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
         BFS_HIP_TRY(launch_expand(s, g->ept, grid, g->V, g->rowstart, g->suid, g->cumul,
                                   g->tile_k, sliced ? g->col_x : g->s_col, g->summary,
                                   lds_sum ? sum_words : 0, g->summary_shift,
-                                  (have ? prefixed : use_sum) ? 1 : 0, g->vis, g->vis_old, lv_s,
+                                  (have ? prefixed : use_sum || known) ? 1 : 0, g->vis, g->vis_old, lv_s,
                                   pa_s, lvl, Qn, g->ctrl,
                                   LevelSize{packed ? pk : -1, allow_bitmap, T}, lflags,
-                                  sliced ? qlen : 0));
+                                  sliced ? qlen : 0, slice_pack, st8));
         xlaunches++;
         if (prof) BFS_HIP_TRY(hipEventRecord(g->pev[2], s));
         const bool maybe_bitmap = (allow_bitmap == 2 && rmax > 0) || (allow_bitmap == 1 && rmax > T);

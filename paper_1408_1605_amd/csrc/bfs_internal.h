@@ -23,7 +23,10 @@ constexpr int kBigTileList = 256;     // ... is queued (up to this many per bloc
 // XCD b mod 8, so an expansion whose workgroups b only probe slice b mod 8
 // keeps each XCD's probes within one eighth of the bitmap (its own L2).
 constexpr int kXcdSlices = 8;
-constexpr int32_t kSliceMinV = 1 << 17;  // automatic sliced levels from this many vertices
+// Automatic sliced levels from this many vertices (R-MAT without and with them:
+// 2^17 150 / 157 us, 2^18 194 / 205, 2^19 238 / 244, 2^20 306 / 294, 2^21 494 / 472,
+// 2^22 782 / 625, 2^25 3,670 / 3,200).
+constexpr int32_t kSliceMinV = 1 << 20;
 constexpr int32_t kSliceHot = 1 << 13;   // ids below: dealt to slices by row, not by id
 __host__ __device__ __forceinline__ int xcd_slice(int32_t v) { return (v >> 10) & (kXcdSlices - 1); }
 
@@ -162,6 +165,12 @@ struct LevelSize {
     int64_t bitmap_threshold;
 };
 
+// Where the tiles of each XCD slice start (one-launch slice scan): slice s of
+// the graph's rows has fewer edges than its tiles hold.
+struct SliceTiles {
+    int32_t t[kXcdSlices + 1];
+};
+
 // Expansion of one level (Algorithm 3); level / parent by search id, the
 // level only in list mode (bitmap mode: launch_bitmap_to_queue writes it).
 hipError_t launch_expand(hipStream_t s, int ept, int grid, int32_t V, const int64_t* rowstart,
@@ -170,8 +179,21 @@ hipError_t launch_expand(hipStream_t s, int ept, int grid, int32_t V, const int6
                          const uint32_t* summary, int32_t summary_words, int32_t shift,
                          int use_prefix, uint32_t* vis, uint32_t* vis_old, int32_t* level,
                          int32_t* parent, int32_t lvl, int32_t* Qn, Ctrl* ctrl, LevelSize size,
-                         uint8_t* found = nullptr, int32_t slice_q = 0);
-// XCD-sliced level: the scan of launch_scan over 8 * qlen entries, entry
+                         uint8_t* found = nullptr, int32_t slice_q = 0,
+                         const uint64_t* slice_pack = nullptr, SliceTiles slices = {});
+// XCD-sliced level: frontier entry k becomes an entry of every slice s, its
+// slice group in the slice-grouped rows (offsets xo), at a place in
+// [s * qlen, (s + 1) * qlen); then launch_expand with slice_q = qlen on those
+// rows.  Needs 8 * qlen <= V.  One launch, with the sizes in pack[0..7] and
+// each slice's tiles from slices.t[s] on (launch_expand: slice_pack = pack);
+// clears pack_next[0..7]; vis_old non-null: also brought up to vis.
+hipError_t launch_slice_scan_one(hipStream_t s, const int32_t* Q, int32_t qlen, const int64_t* off,
+                                 const uint32_t* xo, const int32_t* uid_map, int64_t* rowstart,
+                                 int32_t* uidv, int64_t* cumul, int32_t* tile_k, int tile,
+                                 const SliceTiles& slices, uint64_t* pack, uint64_t* pack_next,
+                                 Ctrl* ctrl, int32_t W, const uint32_t* vis, uint32_t* vis_old);
+// The same in four launches (graphs of 2^32 edges and more), the edges numbered
+// slice by slice: the scan of launch_scan over 8 * qlen entries, entry
 // s * qlen + k being slice s's group of frontier entry k's row in the
 // slice-grouped rows (offsets xo); then launch_expand with slice_q = qlen on
 // those rows.  Needs 8 * qlen <= V.
@@ -191,7 +213,10 @@ struct SmallSync {
     uint32_t spill;    // queue positions reserved by shares that overflowed
     uint32_t pad1[31];
     int64_t edges;     // edges the launch expanded (to ctrl->r_total at the end)
-    int64_t pad2[31];
+    // one-launch slice scans: slice s's edges << kPackBits | entries, two sets
+    // used in turn
+    uint64_t slice[2][8];
+    int64_t pad2[15];
 };
 int small_loop_blocks();
 // wgs workgroups (at most kSmallMaxWGs) on the XCD that workgroups cls, cls + 8,
@@ -250,9 +275,10 @@ hipError_t launch_bottom_up(hipStream_t s, int grid, int num_cus, int32_t V, int
                             uint32_t* vis, uint32_t* vis_old, int32_t* level, int32_t* parent,
                             int32_t lvl, Ctrl* ctrl);
 // Adds the number of vertices of degree >= 1, kPullLow, kPullMid and kPullHub to
-// out[0..3] (the caller zeroes them).
+// out[0..3], and the edges of each XCD slice of the rows (offsets xo) to
+// slices[0..7] (the caller zeroes them).
 hipError_t launch_count_degrees(hipStream_t s, int grid, int32_t V, const int64_t* off,
-                                uint32_t* out);
+                                const uint32_t* xo, uint32_t* out, unsigned long long* slices);
 // Wrapping sums of two hashes of every (u, v) and of every (v, u) into
 // sums[0..1] and sums[2..3] (the caller zeroes them).
 hipError_t launch_symmetry_sums(hipStream_t s, int grid, int32_t V, const int64_t* off,

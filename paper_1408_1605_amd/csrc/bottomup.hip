@@ -199,9 +199,15 @@ __global__ __launch_bounds__(kBuWG, 8) void k_bottom_up(int32_t V, int32_t V_sca
 // order they are exactly the internal ids below each count; a bottom-up step
 // need not look at ids without a neighbour, which no search can reach).
 __global__ __launch_bounds__(kWG) void k_count_degrees(int32_t V, const int64_t* __restrict__ off,
-                                                       uint32_t* __restrict__ out)
+                                                       const uint32_t* __restrict__ xo,
+                                                       uint32_t* __restrict__ out,
+                                                       unsigned long long* __restrict__ slices)
 {
+    __shared__ unsigned long long s_n[4 + kXcdSlices];
+    if (threadIdx.x < 4 + kXcdSlices) s_n[threadIdx.x] = 0;
+    __syncthreads();
     uint32_t n[4] = {0, 0, 0, 0};
+    int64_t x[kXcdSlices] = {};
     const int64_t stride = (int64_t)gridDim.x * kWG;
     for (int64_t v = (int64_t)blockIdx.x * kWG + threadIdx.x; v < V; v += stride) {
         const int64_t d = off[v + 1] - off[v];
@@ -209,19 +215,29 @@ __global__ __launch_bounds__(kWG) void k_count_degrees(int32_t V, const int64_t*
         n[1] += d >= kPullLow ? 1u : 0u;
         n[2] += d >= kPullMid ? 1u : 0u;
         n[3] += d >= kPullHub ? 1u : 0u;
+        const uint32_t* st = xo + v * kXcdSlices;
+#pragma unroll
+        for (int s = 0; s < kXcdSlices; ++s)
+            x[s] += (s + 1 < kXcdSlices ? (int64_t)st[s + 1] : d) - (int64_t)st[s];
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        for (int d = 32; d >= 1; d >>= 1) n[i] += __shfl_xor(n[i], d, 64);
-        if (__lane_id() == 0 && n[i]) atomicAdd(&out[i], n[i]);
-    }
+    for (int i = 0; i < 4; ++i)
+        if (n[i]) atomicAdd(&s_n[i], (unsigned long long)n[i]);
+#pragma unroll
+    for (int s = 0; s < kXcdSlices; ++s)
+        if (x[s]) atomicAdd(&s_n[4 + s], (unsigned long long)x[s]);
+    __syncthreads();
+    const int t = threadIdx.x;
+    if (t < 4 && s_n[t]) atomicAdd(&out[t], (uint32_t)s_n[t]);
+    if (t >= 4 && t < 4 + kXcdSlices && s_n[t]) atomicAdd(&slices[t - 4], s_n[t]);
 }
 
 hipError_t launch_count_degrees(hipStream_t s, int grid, int32_t V, const int64_t* off,
-                                uint32_t* out)
+                                const uint32_t* xo, uint32_t* out, unsigned long long* slices)
 {
     if (grid < 1) grid = 1;
-    hipLaunchKernelGGL(k_count_degrees, dim3(grid), dim3(kWG), 0, s, V, off, out);
+    hipLaunchKernelGGL(k_count_degrees, dim3(grid), dim3(kWG), 0, s, V, off, xo, out,
+                       slices);
     return hipGetLastError();
 }
 

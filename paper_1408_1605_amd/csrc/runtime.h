@@ -109,6 +109,7 @@ struct bfs_graph {
     int do_alpha = 14;      // top-down -> bottom-up when frontier edges * alpha > unvisited edges
     int do_beta = 24;       // bottom-up -> top-down when frontier * beta < V and shrinking
     int symmetric = 0;      // the CSR equals its transpose (checked at creation)
+    int64_t slice_nnz[bfsmi::kXcdSlices] = {};  // edges of each XCD slice (degree order)
     int32_t v_active = 0;   // degree order: internal ids below it have a neighbour (else V)
     bfsmi::PullRows pull{};  // batch levels searched from the unseen side (degree order,
                              // symmetric CSR; n_act = 0: none)
