@@ -14,8 +14,8 @@
 // compacts the union frontier.  Lanes never interact, so each row equals the
 // single-root search from its root.
 //
-// When the union frontier is small (at most V/64 vertices: deep, narrow
-// searches such as grids), the expansion also marks each vertex it finds in
+// When the union frontier is small (at most V/64 vertices of a graph above
+// 2^18: deep, narrow searches such as grids), the expansion also marks each vertex it finds in
 // a touched bitmap, the old frontier's masks are cleared through the queue,
 // and the finalize pass only does work for touched vertices, so a level
 // costs O(frontier + V/32) instead of O(V).
@@ -28,6 +28,17 @@
 #include "wave_ops.h"
 
 namespace bfsmi {
+
+// Largest union frontier of a sparse level (see the file comment).  On small
+// graphs no level is: a finalize that writes every vertex's frontier mask costs
+// less there than the launch that clears the old ones and the atomics that
+// mark what was found (5 roots, plain graph of 50,021 vertices, with the
+// finalize's smaller chunks 280 -> 219 us; 64 roots, R-MAT 16 352 -> 322).
+constexpr int32_t kMsDenseV = 1 << 18;
+__host__ __device__ constexpr int32_t ms_sparse_limit(int32_t V)
+{
+    return V <= kMsDenseV ? -1 : V / 64;
+}
 
 __global__ __launch_bounds__(kWG) void k_ms_clear(int32_t V, int32_t n_roots,
                                                   SeenNext* __restrict__ sn,
@@ -114,8 +125,8 @@ __global__ __launch_bounds__(kWG) void k_ms_roots(int32_t V, int32_t n_roots,
         ctrl->no_push = 0;
         ctrl->pack[0] = ctrl->pack[1] = 0;
         ctrl->dropped[0] = ctrl->dropped[1] = 0;
-        ctrl->sparse_limit = V / 64;
-        ctrl->sparse = s_n <= V / 64;
+        ctrl->sparse_limit = ms_sparse_limit(V);
+        ctrl->sparse = s_n <= ctrl->sparse_limit;
     }
 }
 
@@ -465,7 +476,10 @@ __global__ __launch_bounds__(kWG) void k_ms_expand(const int64_t* __restrict__ r
     }
 }
 
-constexpr int kFinItems = 8;  // vertices per thread and chunk in the finalize
+// Vertices per thread and chunk in the finalize: two on small graphs, whose
+// chunks would else keep a tenth of the chip busy.
+constexpr int kFinItems = 8, kFinItemsSmall = 2;
+constexpr int32_t kFinSmallV = 1 << 17;
 
 __device__ __forceinline__ uint64_t wave_or64(uint64_t x)
 {
@@ -477,7 +491,7 @@ __device__ __forceinline__ uint64_t wave_or64(uint64_t x)
 //                them int8 rows ctrl->out8[b][v] = level.
 // OUT16 = true : serving output, lane b writes level - lane_start[b] into
 //                its own int16 buffer lane_out[b] (caller ids).
-template <bool OUT16, bool FUSE>
+template <bool OUT16, bool FUSE, int IT>
 __global__ __launch_bounds__(kWG) void k_ms_finalize(int32_t V, const int32_t* __restrict__ orig,
                                                      SeenNext* __restrict__ sn,
                                                      uint64_t* __restrict__ front,
@@ -489,7 +503,6 @@ __global__ __launch_bounds__(kWG) void k_ms_finalize(int32_t V, const int32_t* _
                                                      const int64_t* __restrict__ deg_off,
                                                      uint64_t* __restrict__ planes, MsScan next)
 {
-    constexpr int IT = kFinItems;
     __shared__ uint32_t s_c[FUSE ? kWG * IT : 1];
     __shared__ uint64_t s_wave2[kWG / 64], s_pack;
     __shared__ int16_t* s_out[64];
@@ -967,10 +980,20 @@ hipError_t launch_ms_level(hipStream_t s, int scan_grid, int expand_grid, int fi
     default: return hipErrorInvalidValue;
     }
     if (fin_grid < 1) fin_grid = 1;
-    hipLaunchKernelGGL(k_ms_pull, dim3(pull_nnz > 0 ? expand_grid : scan_grid), dim3(kWG), 0, s, Q,
-                       pull, off, col, front, sn, ctrl);
-    const auto finalize = lane_out ? (fuse ? k_ms_finalize<true, true> : k_ms_finalize<true, false>)
-                                   : (fuse ? k_ms_finalize<false, true> : k_ms_finalize<false, false>);
+    if (pull_nnz > 0 || V > kMsDenseV)  // else it has no lanes to search and nothing to clear
+        hipLaunchKernelGGL(k_ms_pull, dim3(pull_nnz > 0 ? expand_grid : scan_grid), dim3(kWG), 0,
+                           s, Q, pull, off, col, front, sn, ctrl);
+    constexpr int L8 = kFinItems, L2 = kFinItemsSmall;
+    const bool small = V <= kFinSmallV;
+    const auto finalize =
+        lane_out ? (fuse ? (small ? k_ms_finalize<true, true, L2> : k_ms_finalize<true, true, L8>)
+                         : (small ? k_ms_finalize<true, false, L2> : k_ms_finalize<true, false, L8>))
+                 : (fuse ? (small ? k_ms_finalize<false, true, L2> : k_ms_finalize<false, true, L8>)
+                         : (small ? k_ms_finalize<false, false, L2> : k_ms_finalize<false, false, L8>));
+    if (small) {  // a chunk per workgroup
+        const int64_t chunks = ((int64_t)V + kWG * L2 - 1) / (kWG * L2);
+        if (fin_grid < chunks) fin_grid = (int)chunks;
+    }
     hipLaunchKernelGGL(finalize, dim3(fin_grid), dim3(kWG), 0, s, V, orig, sn, front, touched, Qn,
                        lane_out, lane_start, ctrl, fuse || pull_nnz > 0 ? off : nullptr, planes, out);
     if (prefix)
@@ -1016,8 +1039,8 @@ __global__ __launch_bounds__(kWG) void k_srv_reset(int32_t V, SeenNext* __restri
         ctrl->no_push = 0;
         ctrl->pack[0] = ctrl->pack[1] = 0;
         ctrl->dropped[0] = ctrl->dropped[1] = 0;
-        ctrl->sparse_limit = V / 64;
-        ctrl->sparse = 1;
+        ctrl->sparse_limit = ms_sparse_limit(V);
+        ctrl->sparse = 0 <= ctrl->sparse_limit;
     }
 }
 

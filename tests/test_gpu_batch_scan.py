@@ -1,7 +1,9 @@
 """The batch's one-launch degree scans against the oracle: queues on both sides
 of one workgroup's 256 entries, of a chunk of 2048 vertices and of the 131072
 entries above which a workgroup takes 2048, scanned from the queue (degree
-order; single levels) and by the finalize of the level before."""
+order; single levels) and by the finalize of the level before; graphs on both
+sides of the 2^17 and 2^18 vertices where the finalize changes its chunks and
+levels may be sparse."""
 import numpy as np
 import pytest
 
@@ -33,7 +35,8 @@ def _union_counts(g, rows):
 
 # a hub with n leaves, a third of them with a few edges more: its level is a
 # queue of n entries, many of degree 1
-@pytest.mark.parametrize("leaves", [1, 255, 256, 257, 2_047, 2_048, 2_049, 131_071, 131_073, 300_007])
+@pytest.mark.parametrize("leaves", [1, 255, 256, 257, 2_047, 2_048, 2_049, 65_533, 65_535, 90_001, 131_067,
+                                    131_071, 131_073, 300_007])
 @pytest.mark.parametrize("dord", [0, 1])
 @pytest.mark.parametrize("symmetric", [True, False])
 def test_queue_lengths(bfsmi, leaves, dord, symmetric):
