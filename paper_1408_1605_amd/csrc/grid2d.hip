@@ -432,12 +432,17 @@ __global__ __launch_bounds__(kWG) void k2_scan(const Plan* __restrict__ plp,
     }
 }
 
-// A position's expansion form and edges (see k2_expand).
+// A position's expansion form (see k2_expand).  Flags of more rows than this
+// miss the caches more often than the claims cost (claims against flags, 2 x 4:
+// 2^24 rows at scale 25 13.8 / 12.9 ms, 2^25 rows at scale 26 25.4 / 28.0; 8 x 1 at
+// scale 26, 2^23 rows, 31.0 / 27.5).
+constexpr int64_t kFlagMaxRows = 1 << 24;
 __device__ __forceinline__ int32_t expand_form(const Plan& pl, int64_t rp)
 {
     const int64_t list_limit = (int64_t)pl.C * pl.WB;  // words of the processor's bitmap
     const bool list = pl.msg_mode == kMsgList || (pl.msg_mode == kMsgAuto && rp <= list_limit);
-    return list ? kFormList : rp > list_limit ? kFormFlags : kFormBits;
+    const bool flags = rp > list_limit && (int64_t)pl.C * pl.B <= kFlagMaxRows;
+    return list ? kFormList : flags ? kFormFlags : kFormBits;
 }
 
 // ---------------------------------------------------------------------------
@@ -1251,7 +1256,8 @@ int run2d(bfs_grid2d* g, int32_t root, int32_t msg_mode, int32_t* levels, int32_
         }
         if (one) {
             uint64_t flagging = 0;  // processors that may flag
-            for (int p = 0; p < RC && msg_mode != kMsgList; ++p)
+            const bool may = msg_mode != kMsgList && (int64_t)C * B <= kFlagMaxRows;
+            for (int p = 0; p < RC && may; ++p)
                 if (std::min(ncol[p / R] * g->maxseg, g->nnzp[p]) > pw) flagging |= 1ull << p;
             const int grid = std::min(cap, std::max(nch, flagging ? g->num_cus : 1));
             hipLaunchKernelGGL(wide ? k2_scan<kScanItems> : k2_scan<1>, dim3(grid), dim3(kWG), 0, s,

@@ -82,3 +82,34 @@ def test_scan_widths(bfsmi, leaves, R, C):
     g = graphgen.from_edges(n, src, dst)
     g.name = "leaves%d" % leaves
     _search(bfsmi, g, R, C, [0, 1])
+
+
+@pytest.mark.parametrize("n", [1 << 24, (1 << 24) + 1])
+def test_rows_at_the_rule(bfsmi, n):
+    # 1 x 1: a level of more edges than bitmap words on both sides of the most
+    # rows that are flagged
+    leaves = n // 32 + 5
+    rng = np.random.default_rng(3)
+    leaf = rng.choice(n - 1, size=leaves, replace=False) + 1
+    off = np.full(n + 1, 2 * leaves, np.int64)
+    deg = np.zeros(n, np.int64)
+    deg[0], deg[leaf] = leaves, 1
+    off[0] = 0
+    np.cumsum(deg, out=off[1:])
+    col = np.zeros(2 * leaves, np.int32)
+    col[:leaves] = np.sort(leaf)
+    G = bfsmi.Grid2D.from_csr(off, col, 1, 1)
+    try:
+        for mode in (0, 2):
+            print("case", n, mode, flush=True)
+            lv, pa, st = G.run(0, msg_mode=mode)
+            torch.cuda.synchronize()
+            lv, pa = lv.cpu().numpy(), pa.cpu().numpy()
+            exp = np.full(n, -1, np.int32)
+            exp[0], exp[leaf] = 0, 1
+            assert np.array_equal(lv, exp)
+            exp[leaf] = 0
+            assert np.array_equal(pa, exp)
+            assert (st.levels, st.reached, st.edges_scanned) == (2, leaves + 1, 2 * leaves)
+    finally:
+        G.close()
