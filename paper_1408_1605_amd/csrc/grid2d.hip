@@ -347,8 +347,9 @@ __global__ __launch_bounds__(kWG) void k2_plan_gather(Plan p, Plan* __restrict__
 // (those whose columns could reach more edges than their bitmap has words), the
 // flags k2_expand may set.  A level of a small front is a chain of launches:
 // with this, k2_plan_gather and the fold's messages spread over all
-// workgroups, R-MAT 14 on 2 x 4 299 -> 215 us, R-MAT 20 on 2 x 4 640 -> 532, on
-// 8 x 8 1,431 -> 877.
+// workgroups, R-MAT 14 on 2 x 4 299 -> 215 us, R-MAT 20 on 2 x 4 640 -> 522, on
+// 8 x 8 1,431 -> 817.  (Entries eight in a row to a thread, which stores strided
+// by 64 bytes: 532, 877; 8 x 1 at scale 26 27.8 ms instead of 25.3.)
 
 template <int NI>
 __global__ __launch_bounds__(kWG) void k2_scan(const Plan* __restrict__ plp,
@@ -363,6 +364,7 @@ __global__ __launch_bounds__(kWG) void k2_scan(const Plan* __restrict__ plp,
 {
     __shared__ uint32_t s_wave[kWG / 64];
     __shared__ uint32_t s_c[kWG * NI];
+    __shared__ uint32_t s_d[kWG * NI + kWG];  // degrees, a word between the threads' runs
     __shared__ uint64_t s_base;
     const Plan& pl = *plp;
     const int t = threadIdx.x;
@@ -392,17 +394,27 @@ __global__ __launch_bounds__(kWG) void k2_scan(const Plan* __restrict__ plp,
         uint32_t d[NI], sum = 0;
 #pragma unroll
         for (int k = 0; k < NI; ++k) {
-            const int32_t x = t * NI + k;
+            const int32_t x = k * kWG + t;
             u[k] = j * pl.R * pl.B + af[colbase + l0 + (x < n ? x : n - 1)];
         }
 #pragma unroll
         for (int k = 0; k < NI; ++k) {
             const int64_t pr = (int64_t)u[k] * pl.R + i;
             a[k] = off2[pr];
-            d[k] = t * NI + k < n ? (uint32_t)(off2[pr + 1] - a[k]) : 0u;
+            d[k] = k * kWG + t < n ? (uint32_t)(off2[pr + 1] - a[k]) : 0u;
         }
+        // loads and stores by entry, the prefix sum over runs of NI entries
 #pragma unroll
-        for (int k = 0; k < NI; ++k) sum += d[k];
+        for (int k = 0; k < NI; ++k) {
+            const int32_t x = k * kWG + t;
+            s_d[x + x / NI] = d[k];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < NI; ++k) {
+            d[k] = s_d[t * (NI + 1) + k];
+            sum += d[k];
+        }
         uint32_t tot;
         uint32_t c = wg_exclusive_scan_dpp(sum, &tot, s_wave);
         if (t == 0)
@@ -416,16 +428,19 @@ __global__ __launch_bounds__(kWG) void k2_scan(const Plan* __restrict__ plp,
         } else {
 #pragma unroll
             for (int k = 0; k < NI; ++k) {
-                const int32_t x = t * NI + k;
-                if (x < n) {
-                    s_c[x] = c;
-                    cumul[p0 + x] = c0 + c;
-                    rowstart[p0 + x] = a[k];
-                    uidv[p0 + x] = u[k];
-                }
+                s_c[t * NI + k] = c;
                 c += d[k];
             }
             __syncthreads();
+#pragma unroll
+            for (int k = 0; k < NI; ++k) {
+                const int32_t x = k * kWG + t;
+                if (x < n) {
+                    cumul[p0 + x] = c0 + s_c[x];
+                    rowstart[p0 + x] = a[k];
+                    uidv[p0 + x] = u[k];
+                }
+            }
             write_tile_heads(s_c, n, tot, (int32_t)p0, c0, kTileShift, tile_k);
         }
         __syncthreads();  // s_c, s_base are rewritten by the next chunk
