@@ -2,17 +2,19 @@
 // workgroups).
 //
 // One BFS level is (Section 3.4 of the paper, one GPU over the whole graph):
-//   scan   : d_k = deg(Q[k]); cumul = exclusive_scan(d)      (k_scan_*)
+//   scan   : d_k = deg(Q[k]); cumul = exclusive_scan(d)      (k_list_scan,
+//            k_slice_scan, k_front_scan; k_scan_* for graphs of 2^32 edges)
 //   expand : every frontier edge e is mapped to the frontier entry
 //            k = max{l : cumul[l] <= e} and its neighbour
 //            v = col[off[Q[k]] + e - cumul[k]]; v's bit in the visited bitmap
 //            is probed with a plain load and claimed with atomicOr; the
 //            thread whose returned word lacked the bit is the only winner
-//            and sets level[v] and parent[v] = Q[k]  (Algorithm 3)  (k_expand)
+//            and sets level[v] and parent[v] = Q[k]  (Algorithm 3); bitmap
+//            mode sets a byte flag instead of claiming        (k_expand)
 //   next   : list mode: winners append to the next queue (one atomicAdd per
-//            wave); bitmap mode: the next frontier is the set of bits that
-//            turned on during the level, compacted to an id-ordered list
-//            (Section 5)                                      (k_bitmap_to_queue)
+//            wave); bitmap mode: the next frontier is the set of flags and
+//            bits that turned on during the level, compacted to a list and
+//            scanned (Section 5)         (k_front_scan, k_bitmap_to_queue)
 #include "bfs_internal.h"
 #include "tile_map.h"
 #include "wave_ops.h"
@@ -1121,7 +1123,7 @@ __global__ __launch_bounds__(kWG) void k_list_scan(const int32_t* __restrict__ Q
     write_tile_heads(s_c, n, tot, p0, c0, tile_sh, tile_k);
 }
 
-constexpr int32_t kFrontWideV = 1 << 24;
+constexpr int32_t kFrontWideV = 1 << 19;
 
 hipError_t launch_list_scan(hipStream_t s, const int32_t* Q, int32_t qlen, const int64_t* off,
                             const int32_t* uid_map, int64_t* rowstart, int32_t* uidv,
@@ -1153,7 +1155,9 @@ hipError_t launch_list_scan(hipStream_t s, const int32_t* Q, int32_t qlen, const
 // numbers are listed in LDS and written out from there, so that the entry
 // arrays' stores are contiguous.  A workgroup of NT threads reserves its
 // places with one atomic; these take 12 ns each, one after the other, so
-// graphs above kFrontWideV take NT = 1024.
+// graphs above kFrontWideV take NT = 1024 (256 / 1024: 2^19 vertices the same,
+// 777,777 without order 272 / 265 us, 2^21 470 / 446, 2^22 631 / 611, 2^23 1,198 / 1,145,
+// 2^24 2,360 / 2,255).
 template <int NT>
 __global__ __launch_bounds__(NT) void k_front_scan(
     int32_t V, uint8_t* __restrict__ vis8, uint8_t* __restrict__ old8, int32_t* __restrict__ Qn,

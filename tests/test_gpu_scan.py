@@ -1,6 +1,6 @@
 """One-launch level scans (k_list_scan, k_front_scan) against the oracle where
 they change their way: vertex counts around the groups of 8 ids, the blocks of
-2048 and (above 2^24 vertices) 8192 ids, lists on both sides of 65536 entries,
+2048 and (above 2^19 vertices) 8192 ids, lists on both sides of 65536 entries,
 rows of no, few and very many edges, every tile size, with and without the
 row prefix skip, and row offsets that allow no 16-byte loads."""
 import numpy as np
@@ -60,6 +60,21 @@ def test_sizes(bfsmi, n, dord):
         G.set_option(bfsmi.BFS_OPT_EDGES_PER_THREAD, ept)
         for r in (root, 0, n - 1):
             _check(g, G, r)
+    G.close()
+
+
+@pytest.mark.parametrize("n", [524_287, 524_288, 524_289, 532_481, 600_003])
+@pytest.mark.parametrize("dord", [0, 1])
+def test_block_widths(bfsmi, n, dord):
+    # bitmap levels on both sides of the wide blocks' line, last blocks of one
+    # and of many ids
+    g = _random(n, 3 * n, n, hub=n // 2)
+    print("case", g.name, dord, flush=True)
+    G = bfsmi.Graph.from_csr(g.off, g.col, flags=bfsmi.BFS_DEGREE_ORDER if dord else 0)
+    G.set_option(bfsmi.BFS_OPT_LOOP_DRIVER, 1)
+    for mode in (0, 2):
+        G.set_option(bfsmi.BFS_OPT_FRONTIER_MODE, mode)
+        _check(g, G, int(np.argmax(np.diff(g.off))))
     G.close()
 
 
