@@ -791,11 +791,12 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
                                               prefixed ? g->skip : nullptr, g->rowstart, g->suid,
                                               g->cumul, g->tile_k, tile, g->ctrl, pk ^ 1));
             } else {
-                // the direction-optimizing mode also sums the next frontier's
-                // degrees, so the next level's direction is known without a scan
+                // until it has been bottom-up, the direction-optimizing mode also
+                // sums the next frontier's degrees (from the zero the expansion
+                // leaves), so the next level's direction is known without a scan
                 BFS_HIP_TRY(launch_bitmap_to_queue(s, grid2, g->V, g->W, g->vis, g->vis_old, Qn,
                                                    lv_s, lvl, g->ctrl,
-                                                   dir_opt ? g->s_off : nullptr, lflags));
+                                                   decide ? g->s_off : nullptr, lflags));
             }
         }
         if (prof) BFS_HIP_TRY(hipEventRecord(g->pev[3], s));

@@ -71,6 +71,7 @@ struct alignas(64) Ctrl {
     int64_t bu_deg;      // their degree sum
     int64_t bu_edges;    // neighbours the step probed
     int64_t next_deg;    // degree sum of the next frontier, when the compaction is asked for it
+                         // (the expansion clears it)
     // batch: lanes this level searches from the unseen side (k_ms_pull)
     uint64_t pull;
     // single-root levels scanned in one launch (launch_list_scan,
@@ -158,7 +159,7 @@ hipError_t launch_summary_bits(hipStream_t s, int grid, int32_t V, int32_t W, co
 // Where the expansion finds the level's size: par >= 0: ctrl->pack[par] (the
 // other pack is cleared, and ctrl->r, skipped and bitmap_out are set);
 // par < 0: ctrl->r and bitmap_out as launch_scan leaves them (both packs are
-// cleared).
+// cleared).  Both ways next_deg is cleared too.
 struct LevelSize {
     int par;
     int allow_bitmap;
@@ -250,7 +251,7 @@ hipError_t launch_sync_old(hipStream_t s, int grid, int32_t W, const uint32_t* v
 int expand_blocks_per_cu(int ept, int summary_words);
 
 // deg_off non-null: also adds the degrees of the new frontier's vertices
-// (from these row offsets) to ctrl->next_deg.
+// (from these row offsets) to ctrl->next_deg, which launch_expand cleared.
 hipError_t launch_bitmap_to_queue(hipStream_t s, int grid, int32_t V, int32_t W, uint32_t* vis,
                                   uint32_t* vis_old, int32_t* Qn, int32_t* level, int32_t lvl,
                                   Ctrl* ctrl, const int64_t* deg_off = nullptr,

@@ -728,6 +728,7 @@ __global__ __launch_bounds__(kWG) void k_expand(int32_t V, const int64_t* __rest
             ctrl->pack[size.par ^ 1] = 0;
             ctrl->dropped[size.par ^ 1] = 0;
             ctrl->fp_cand = 0x7fffffff;
+            ctrl->next_deg = 0;
         }
     } else {
         if (slice_pack) {
@@ -751,6 +752,7 @@ __global__ __launch_bounds__(kWG) void k_expand(int32_t V, const int64_t* __rest
             ctrl->pack[0] = ctrl->pack[1] = 0;
             ctrl->dropped[0] = ctrl->dropped[1] = 0;
             ctrl->fp_cand = 0x7fffffff;
+            ctrl->next_deg = 0;
         }
     }
     // flag claims: a bitmap level marks its vertices with byte stores
