@@ -111,6 +111,13 @@ __device__ __forceinline__ void ms_store_agent(T* p, T x)
     __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Words that other workgroups of the XCD read behind a barrier.
+template <typename T>
+__device__ __forceinline__ void ms_store(T* p, T x)
+{
+    __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 __device__ __forceinline__ void ms_bad(MsLds& S, int32_t* flag, int32_t x)
 {
     ms_store_agent(flag, x);
@@ -202,7 +209,7 @@ __device__ __forceinline__ void ms_append(MsLds& S, const int32_t (&vv)[NE], con
                 S.nv[par][pos] = vv[j];
             } else {
                 const uint32_t q = q0 + (pos - over0);
-                if (q < (uint32_t)V) list[q] = vv[j];
+                if (q < (uint32_t)V) ms_store(list + q, vv[j]);
                 else ms_bad(S, &ctrl->err, 7);
                 if (!ROWS) {
                     const int64_t dd = off[vv[j] + 1] - off[vv[j]];
@@ -357,15 +364,12 @@ __device__ __forceinline__ void ms_levels_body(
         ++epoch;
         if (t == 0) {
             uint64_t* p = ms_slots(slots, epoch, N) + w;
-            __hip_atomic_store(p, (uint64_t)epoch << 32 | w0, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (!ROWS)
-                __hip_atomic_store(p + N, (uint64_t)epoch << 32 | w1, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+            ms_store(p, (uint64_t)epoch << 32 | w0);
+            if (!ROWS) ms_store(p + N, (uint64_t)epoch << 32 | w1);
         }
     };
     auto settle = [&]() {
-        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's stores and atomics
+        wait_stores();
         __syncthreads();
     };
     auto limits = [&]() {
@@ -461,7 +465,7 @@ __device__ __forceinline__ void ms_levels_body(
         uint64_t nw = 0, seen[kMsRowEdges];
         if (v >= 0) {
             nw = ms_load(front + v);
-            front[v] = 0;  // this workgroup is the only reader of v's mask
+            ms_store(front + v, (uint64_t)0);  // this workgroup is the only reader of v's mask
         }
         if (ROWS)
 #pragma unroll
@@ -489,8 +493,7 @@ __device__ __forceinline__ void ms_levels_body(
                           (!ROWS && (S.esum > rlimit || (S.bits & kMsOver)));
         const bool deal = (S.bits & kMsDeal) != 0;
         if (w == 0 && t == 0)  // last read before the previous barrier
-            __hip_atomic_store(&sy->fn[(j + 1) % 3], 0u, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_WORKGROUP);
+            ms_store(&sy->fn[(j + 1) % 3], 0u);
         int64_t f0 = 0, f1 = n;
         if (deal) {
             // the share behind what has spilled, then equal slices for all
@@ -500,7 +503,7 @@ __device__ __forceinline__ void ms_levels_body(
             __syncthreads();
             for (int32_t i = t; i < n; i += kMsW) {
                 const uint32_t q = S.q0 + (uint32_t)i;
-                if (q < (uint32_t)V) Lin[q] = S.nv[sp][i];
+                if (q < (uint32_t)V) ms_store(Lin + q, S.nv[sp][i]);
                 else ms_bad(S, &ctrl->err, 8);
             }
             settle();
@@ -528,11 +531,11 @@ __device__ __forceinline__ void ms_levels_body(
                     // v's own slot only: other threads OR into the marks of
                     // the other parity meanwhile
                     if (sp) {
-                        if (nw) sn[v].seen = had | nw;
-                        front[v] = last ? nw : 0ull;
+                        if (nw) ms_store(&sn[v].seen, had | nw);
+                        ms_store(front + v, last ? nw : (uint64_t)0);
                     } else {
-                        sn[v] = SeenNext{had | nw, 0ull};
-                        if (last) front[v] = nw;
+                        sn[v] = SeenNext{had | nw, 0ull};  // (one 16-byte store)
+                        if (last) ms_store(front + v, nw);
                     }
                 }
                 if (nw) S.found = 1;
@@ -619,7 +622,7 @@ __global__ __launch_bounds__(kMsW) void k_ms_small_levels(
             S.mdeg = 0;
             for (int k = 0; k < 4; ++k) ms_store_agent(slots + k * N + w, (uint64_t)0);
             // the slots have reached the other XCDs before this arrival does
-            __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+            wait_stores();
             // one 7-bit count of arrivals per XCC; the sign bit calls off
             const uint32_t xcc = __builtin_amdgcn_s_getreg((2 << 11) | 20);  // XCC_ID[2:0]
             const uint64_t one = 1ull << (7 * xcc);
@@ -643,7 +646,7 @@ __global__ __launch_bounds__(kMsW) void k_ms_small_levels(
             ms_levels_body<ROWS>(S, V, off, col, orig, sn, front, Qa, Qb, found, slots, sy, ctrl,
                                  N, w, qlen0, lvl0, max_levels, qlimit, rlimit, dlimit);
     }
-    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): what this wave reports is stored
+    wait_stores();  // what this wave reports
     __syncthreads();
     if (t >= 64) return;
     uint32_t k = 0;
@@ -672,7 +675,7 @@ __global__ __launch_bounds__(kMsW) void k_ms_small_levels(
         *sy = MsSync{};
     }
     if (h_ctrl) {
-        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+        wait_stores();
         if (t < (int)(sizeof(Ctrl) / 8))
             reinterpret_cast<uint64_t*>(h_ctrl)[t] =
                 ms_load(reinterpret_cast<const uint64_t*>(ctrl) + t);

@@ -664,7 +664,7 @@ __device__ __forceinline__ void small_levels_body(
             }
             // the stores (the spilled entries' too) have reached the L2, or
             // with device scope the other XCDs: no cache is written back
-            __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+            wait_stores();
             __syncthreads();
             ++ep_cnt;
             if (t == 0) scoped_store<L>(&slots->cnt[ep_cnt & 1][w], (uint64_t)ep_cnt << 32);
@@ -753,7 +753,7 @@ __global__ __launch_bounds__(kSW) void k_small_levels(
             scoped_store<false>(&slots->deg[0][w], (uint64_t)0);
             scoped_store<false>(&slots->deg[1][w], ((uint64_t)1 << 32) | lim);
             // the slots have reached the other XCDs before this arrival does
-            __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+            wait_stores();
             // one 7-bit count of arrivals per XCC; the sign bit calls off
             const uint32_t xcc = __builtin_amdgcn_s_getreg((2 << 11) | 20);  // XCC_ID[2:0]
             const uint64_t one = 1ull << (7 * xcc);
@@ -782,7 +782,7 @@ __global__ __launch_bounds__(kSW) void k_small_levels(
     } else if (w == 0 && t == 0) {
         not_run();
     }
-    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): edge counts and result are stored
+    wait_stores();  // edge counts and result
     __syncthreads();
     if (t < 64) {
         uint32_t k = 0;

@@ -12,6 +12,16 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask)
                                      __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
+// Waits until this wave's stores and atomics have reached the L2 (or with
+// device scope the other XCDs).  The signal fences, no instructions
+// themselves, keep the compiler from moving a store across the wait.
+__device__ __forceinline__ void wait_stores()
+{
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+
 template <typename T>
 __device__ __forceinline__ T wave_inclusive_scan(T x)
 {
