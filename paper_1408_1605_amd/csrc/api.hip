@@ -455,6 +455,15 @@ int bfs_get_option(bfs_graph* g, int key, int64_t* value)
     return ok();
 }
 
+int bfs_test_pack_limit(bfs_graph* g, int64_t edges)
+{
+    if (!g || edges < 0 || edges > g->pack_edges) return fail(BFS_ERR_INVALID, "bad pack limit");
+    if (g->ms_graph) (void)hipGraphExecDestroy(g->ms_graph);  // captured with the old limit
+    g->ms_graph = nullptr;
+    g->pack_edges = edges;
+    return ok();
+}
+
 }  // extern "C"
 
 namespace {
@@ -532,7 +541,7 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
     const bool dir_opt = g->direction != 0 && g->symmetric;
     // one-launch scans (not with the direction-optimizing mode, which looks at
     // a level's edges before it decides how to search it)
-    const bool fuse = !dir_opt && g->nnz < kPackMaxEdges;
+    const bool fuse = !dir_opt && g->nnz < g->pack_edges;
     uint8_t* const flags = g->claim_mode == 0 ? nullptr
                            : g->found         ? g->found
                            : fuse             ? reinterpret_cast<uint8_t*>(g->deg)
@@ -684,7 +693,7 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
         // top-down levels are light: it needs the frontier's edge count, from the
         // one-launch scan)
         const bool decide = dir_opt && !bu_done;
-        const bool quick = decide && g->nnz < kPackMaxEdges;
+        const bool quick = decide && g->nnz < g->pack_edges;
         // a sliced level after a bitmap level has that level's prefix
         const bool known = sliced && scanned && prefixed && g->V < kLdsSummaryMinV;
         const bool use_sum = g->use_summary > 0 && rmax > T && !quick && !known &&

@@ -59,8 +59,9 @@ static hipError_t enqueue_level(bfs_graph* g, hipStream_t s, const BatchGrids& b
                            nullptr, g->q[parity], g->q[parity ^ 1], g->deg, g->rowstart, g->suid,
                            g->bsum, g->cumul,
                            g->tile_k, g->ms_sn, g->ms_front, g->ms_touched, nullptr,
-                           nullptr, g->ms_ctrl, g->pull, level, last, g->ms_planes, skip ? g->skip : nullptr,
-                           skip ? g->num_cus * 2 : 0);
+                           nullptr, g->ms_ctrl, g->pull,
+                           (b.tile_cap - 1) * kMinTile < g->pack_edges, level, last, g->ms_planes,
+                           skip ? g->skip : nullptr, skip ? g->num_cus * 2 : 0);
 }
 
 static int capture_batch_graph(bfs_graph* g, const BatchGrids& b)

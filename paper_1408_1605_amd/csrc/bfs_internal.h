@@ -318,6 +318,8 @@ struct PullRows {
 // and the next level's scan drops each row's block below the largest cut
 // 2^(16 + i) inside it (the row prefix skip); the dropped edges go to
 // ctrl->skipped.
+// one: scanned in one launch or by the finalize before (graphs of fewer than
+// kPackMaxEdges edges, rounded up to tiles).
 // level: 0 for the first of the levels queued together, whose frontier is
 // scanned from Q; last: the last of them (its next frontier is not scanned
 // here).
@@ -329,7 +331,7 @@ hipError_t launch_ms_level(hipStream_t s, int scan_grid, int expand_grid, int fi
                            int32_t* tile_k, SeenNext* sn, uint64_t* front,
                            uint32_t* touched, int16_t* const* lane_out,
                            const int32_t* lane_start, Ctrl* ctrl, const PullRows& pull,
-                           int level, bool last,
+                           bool one, int level, bool last,
                            uint64_t* planes = nullptr, const int32_t* skip = nullptr, int prefix_grid = 0);
 int ms_expand_blocks_per_cu(int ept);
 

@@ -1094,6 +1094,7 @@ struct bfs_grid2d {
     Ctl* h_ctl = nullptr;    // pinned host (head only is read back)
     uint64_t* h_seq = nullptr;  // pinned host: number of the last read-back
     uint64_t seq = 0;
+    int64_t pack_edges = kPackMaxEdges;  // graphs of fewer edges: one-launch scan
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     std::atomic<int> busy{0};
 };
@@ -1217,7 +1218,7 @@ int run2d(bfs_grid2d* g, int32_t root, int32_t msg_mode, int32_t* levels, int32_
     int32_t nlevels = 1;
     int32_t lvl = 1;
     const int cap = g->num_cus * 8;
-    const bool one = g->nnz < kPackMaxEdges;  // one-launch scan
+    const bool one = g->nnz < g->pack_edges;  // one-launch scan
     while (true) {
         // column lists and the scan's entry / block / gather-unit tables
         int64_t ncol[kMaxP] = {0};
@@ -1506,6 +1507,14 @@ int bfs_grid2d_create(bfs_grid2d** out, int32_t V, int64_t nnz, const int64_t* d
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return bail(hip_fail(e, "2D partition"));
     *out = g;
+    return ok();
+}
+
+int bfs_test_grid2d_pack_limit(bfs_grid2d* g, int64_t edges)
+{
+    // never raised: the scan of larger graphs moves the tiles' starts
+    if (!g || edges < 0 || edges > g->pack_edges) return fail(BFS_ERR_INVALID, "bad pack limit");
+    g->pack_edges = edges;
     return ok();
 }
 

@@ -948,14 +948,12 @@ hipError_t launch_ms_level(hipStream_t s, int scan_grid, int expand_grid, int fi
                            int64_t* rowstart, int32_t* uidv, int64_t* bsum, int64_t* cumul,
                            int32_t* tile_k, SeenNext* sn, uint64_t* front, uint32_t* touched,
                            int16_t* const* lane_out, const int32_t* lane_start, Ctrl* ctrl,
-                           const PullRows& pull, int level, bool last, uint64_t* planes,
-                           const int32_t* skip, int prefix_grid)
+                           const PullRows& pull, bool one, int level, bool last,
+                           uint64_t* planes, const int32_t* skip, int prefix_grid)
 {
     const bool prefix = skip != nullptr && prefix_grid > 0;
     const int64_t pull_nnz = pull.n_act > 0 ? pull.nnz : 0;
-    // scanned in one launch, or by the finalize of the level before
     const int64_t max_edges = (tile_cap - 1) * kMinTile;
-    const bool one = max_edges < kPackMaxEdges;
     const bool can_fuse = one && !prefix && pull_nnz == 0;
     const int par = one ? level & 1 : -1;
     MsScan out{rowstart, uidv, cumul, tile_k, log2_tile(kWG * ept), par, max_edges};

@@ -116,6 +116,9 @@ struct bfs_graph {
     int xcd_slices = 1;     // 0 off, 1 auto, 2 whenever the frontier fits (8 * qlen <= V)
     int claim_mode = 1;     // bitmap levels: 0 atomic claims, 1 flag claims up to
                             // kFlagAutoMaxV vertices, 2 flag claims
+    // graphs of fewer edges have their levels scanned in one launch (only
+    // bfs_test_pack_limit changes it)
+    int64_t pack_edges = bfsmi::kPackMaxEdges;
     std::atomic<int> busy{0};
 };
 
@@ -142,3 +145,9 @@ int wait_published(const uint64_t* flag, uint64_t seq, hipStream_t s);
 int small_loop_grid(int num_cus);
 
 }  // namespace bfsmi
+
+// Test hooks, not part of the ABI of bfs.h: from this many edges on (at most
+// the limit there is) the handle's searches scan their levels as those of graphs
+// of 2^32 edges and more do.  A server is to be given the graph afterwards.
+extern "C" int bfs_test_pack_limit(bfs_graph* g, int64_t edges);
+extern "C" int bfs_test_grid2d_pack_limit(struct bfs_grid2d* g, int64_t edges);

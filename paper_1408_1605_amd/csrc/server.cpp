@@ -289,7 +289,8 @@ hipError_t enqueue_srv_level(const bfs_graph* g, SrvBatch* B, hipStream_t s, int
     return launch_ms_level(s, scan, expand, fin, ept, g->V, tile_cap, g->s_off, g->s_col, g->orig,
                            B->q[parity], B->q[parity ^ 1], B->deg, B->rowstart, B->suid, B->bsum,
                            B->cumul, B->tile_k, B->sn, B->front, B->touched,
-                           B->lane_out, B->lane_start, B->ctrl, g->pull, level, last);
+                           B->lane_out, B->lane_start, B->ctrl, g->pull,
+                           (tile_cap - 1) * kMinTile < g->pack_edges, level, last);
 }
 
 // Capture kRoundLevels[i] levels of this batch into round[i].
