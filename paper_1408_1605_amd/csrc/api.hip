@@ -15,6 +15,10 @@ namespace bfsmi {
 
 constexpr int32_t kSmallQ = 1 << 16;  // frontiers up to this size may run in the persistent loop
 constexpr int32_t kSmallDeg = 8192;   // ... if no frontier vertex has a larger degree
+// a longer row than this many times the mean is a hub's (2^18 ids of mean degree 8,
+// 2.9 times: claims merged 239 us, not merged 211; 512 vertices with 8 children each,
+// degree ordered, 4.5 times: 97 / 188)
+constexpr double kHubRatio = 4.0;
 constexpr int kSmallWGs = 32;         // workgroups of the persistent loop
 // levels whose scan came with the compaction take the summary's block bits from
 // this size on (R-MAT 26 4% faster with them, R-MAT 22 and 24 unchanged)
@@ -564,6 +568,9 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
     // read-backs of the control block: the persistent loop publishes it itself
     // at its end, other points have a launch of their own for it
     Ctrl* const mirror = g->pinned ? g->h_ctrl : nullptr;
+    // (the vertices that have a neighbour, where the handle has counted them)
+    const double mean = (double)g->nnz / std::max(1, g->rank ? g->v_active : g->V);
+    const HubRule hub{(int32_t)std::min(mean * kHubRatio, 2147483647.0), g->symmetric};
     auto read_back = [&](bool published) -> int {
         if (!mirror) {
             BFS_HIP_TRY(hipMemcpyAsync(g->h_ctrl, g->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
@@ -644,7 +651,7 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
                                             mirror ? ++g->seq : 0, qlen,
                                             lvl, g->small_limit,
                                             (int64_t)g->small_grid * kSmallDeg, kSmallDeg,
-                                            g->maxdeg));
+                                            g->maxdeg, hub));
             if ((rc = read_back(true)) != BFS_OK) return rc;
             const Ctrl& c = *g->h_ctrl;
             reached += c.reached;
@@ -820,7 +827,7 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
                                             g->small_sync, g->summary, g->ctrl, mirror,
                                             mirror ? ++g->seq : 0, -1 - (pk ^ 1), lvl + 1,
                                             g->small_limit, (int64_t)g->small_grid * kSmallDeg,
-                                            kSmallDeg, g->maxdeg));
+                                            kSmallDeg, g->maxdeg, hub));
         }
         if ((rc = read_back(spec)) != BFS_OK) return rc;
         if (prof) {

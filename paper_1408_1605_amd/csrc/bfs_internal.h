@@ -220,6 +220,12 @@ struct SmallSync {
     int64_t pad2[15];
 };
 int small_loop_blocks();
+// Whether edges meet at hubs: the graph has rows longer than degree (four times
+// the mean), or, not being symmetric, may have many rows that name one vertex.
+struct HubRule {
+    int32_t degree;
+    int32_t symmetric;
+};
 // wgs workgroups (at most kSmallMaxWGs) on the XCD that workgroups cls, cls + 8,
 // .. of a launch run on; slot_words: kSummaryMaxWords words of scratch, any
 // contents.  qlen < 0: the frontier size is that of the previous host-driven
@@ -234,7 +240,7 @@ hipError_t launch_small_levels(hipStream_t s, int wgs, int cls, int32_t V, const
                                int32_t* parent, SmallSync* sy, uint32_t* slot_words, Ctrl* ctrl,
                                Ctrl* h_ctrl, uint64_t seq,
                                int32_t qlen, int32_t lvl, int32_t qlimit, int64_t rlimit,
-                               int32_t dlimit, int32_t maxdeg);
+                               int32_t dlimit, int32_t maxdeg, HubRule hub);
 
 // Visited summary before a heavy level: ctrl->full_prefix and one bit per
 // block of 2^shift ids (set when the whole block is visited); clears

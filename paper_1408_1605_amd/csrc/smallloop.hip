@@ -37,8 +37,10 @@
 // On levels of few edges claims go straight to the atomicOr of Algorithm 3
 // (a plain-read probe would add one dependent round trip).  Levels with more
 // probe first, and collect the ids below kHotIds (under degree order the ones
-// most edges point at) in LDS, to be claimed a bitmap word at a time.  Winners
-// write level and parent; the bitmap of the level before (vis_old) is left
+// most edges point at) in LDS, to be claimed a bitmap word at a time.  Where
+// edges do not meet, on symmetric graphs without hubs and with more ids than
+// those, they claim directly at any size.  Winners write level and parent; the
+// bitmap of the level before (vis_old) is left
 // behind, the host brings it up to date before it next drives a level itself.
 //
 // The kernel hands the search back to the host when the next frontier, its
@@ -56,17 +58,29 @@ namespace bfsmi {
 constexpr int kSW = 512;           // threads per workgroup (8 waves)
 constexpr int kSmallEPT = 2;
 constexpr int kSmallTile = kSW * kSmallEPT;
-constexpr int kSmallStage = 1024;  // frontier entries per workgroup and pass
-constexpr int kStagePer = kSmallStage / kSW;
+// Frontier entries per workgroup and pass: 32 workgroups hold the largest
+// frontier there is (with 1024, frontiers from 32K vertices on were dealt out
+// again: 4,096 hubs of 15 leaves 178 -> 156 us, 64 of 1,000 126 -> 105).  A
+// thread takes two of up to kStageFew, else four (with four always, R-MAT 12
+// 75 -> 80 us, 30 x 30 x 30 lattice 252 -> 284).
+constexpr int kSmallStage = 2048;
+constexpr int kStageFew = 1024;
 constexpr int kRowEdges = 4;       // rows of at most this many edges: one lane per edge
 constexpr int kRowStep = kSmallTile / kRowEdges;  // such rows per step
 constexpr uint32_t kStartCap = 1u << 14;  // polls before a launch is called off
 constexpr uint32_t kSpinCap = 1u << 23;
-constexpr int64_t kMergeEdges = 1 << 11;   // levels with more edges merge the hot ids' claims
-constexpr int kHotIds = 1 << 16;           // ... those below this
+// Levels with more edges merge the hot ids' claims (at 2^9, 2^11, 2^13 and never:
+// R-MAT 2^9 65, 65, 115, 115 us, 2^14 of edge factor 4 111, 112, 134, 607, 30 x 30
+// x 30 lattice 267, 262, 276, 279).
+constexpr int64_t kMergeEdges = 1 << 11;
+// Lattices (their rows point at few ids a line: 512 x 512 from 2^11 edges on 1,475
+// us, from 2^16 on 1,245) do from here on, or where a level points at half of
+// the ids (ternary tree of 9,841 ids 152 -> 90 us).
+constexpr int64_t kRowMergeEdges = 1 << 16;
+constexpr int kHotIds = 1 << 16;  // ids below this are merged
 // Edge counts saturate, per thread and per share, above every limit the host
 // passes (at most 8192 edges per workgroup).
-constexpr int64_t kDegSat = 1 << 22, kEdgeSat = 1 << 24;
+constexpr int64_t kDegSat = 1 << 20, kEdgeSat = 1 << 24;
 static_assert((int64_t)kSmallMaxWGs * 8192 < kDegSat, "a saturated count is over the limit");
 
 // Barrier words, one per workgroup, in two sets used in turn: a workgroup
@@ -211,6 +225,17 @@ __device__ __forceinline__ void keep_winners(const int32_t (&vv)[NE], const bool
     }
 }
 
+// Where few probes meet (rows that may meet at a vertex, but no hubs seen), they
+// read the bitmap through the L1: past it, a level of 250K edges took 60 us more
+// (directed, 2^18 ids of mean degree 8: 350 -> 309 us; graphs with hubs lose 2 to 4 us
+// by it).  Its words are dropped from the L1 at a merge level's end, by the wave
+// that has the least to do while the others arrive: a later level must not take
+// an id for unvisited, since it stores the parents of those.
+__device__ __forceinline__ void drop_l1()
+{
+    if (threadIdx.x >= kSW - 64) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+}
+
 // Claims of one step: the atomicOr on every edge.  At a merge level an edge
 // first reads the bitmap; one to an unvisited hot id is noted in hot (the
 // first of the workgroup stores the parent: whichever store remains, it names
@@ -219,7 +244,7 @@ __device__ __forceinline__ void keep_winners(const int32_t (&vv)[NE], const bool
 // the compiler waits for each before it issues the next.)
 template <bool L, int NE>
 __device__ __forceinline__ void claim_edges(const int32_t (&vv)[NE], const int32_t (&uu)[NE],
-                                            const bool (&ok)[NE], bool merge,
+                                            const bool (&ok)[NE], bool merge, bool l1,
                                             uint32_t* __restrict__ vis,
                                             int32_t* __restrict__ parent, uint32_t* hot,
                                             bool (&win)[NE])
@@ -228,10 +253,17 @@ __device__ __forceinline__ void claim_edges(const int32_t (&vv)[NE], const int32
 #pragma unroll
     for (int j = 0; j < NE; ++j) old[j] = ok[j] ? 0u : ~0u;
     if (merge) {
+        if (l1) {  // (uniform)
 #pragma unroll
-        for (int j = 0; j < NE; ++j)  // past the L1, which no barrier here invalidates
-            old[j] |= __hip_atomic_load(vis + (vv[j] >> 5), __ATOMIC_RELAXED,
-                                        __HIP_MEMORY_SCOPE_AGENT);
+            for (int j = 0; j < NE; ++j)
+                old[j] |= __hip_atomic_load(vis + (vv[j] >> 5), __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_WAVEFRONT);
+        } else {
+#pragma unroll
+            for (int j = 0; j < NE; ++j)
+                old[j] |= __hip_atomic_load(vis + (vv[j] >> 5), __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_AGENT);
+        }
 #pragma unroll
         for (int j = 0; j < NE; ++j) {
             const uint32_t bit = 1u << (vv[j] & 31);
@@ -338,13 +370,14 @@ __device__ __forceinline__ void map_small_tile(SmallLds& S, int32_t n, int32_t R
     }
 }
 
-// Stages entries ids[0..n), n <= kSmallStage, kStagePer consecutive ones per thread:
+// Stages entries ids[0..n), n <= PER * kSW, PER consecutive ones per thread:
 // row starts, caller ids and the prefix sum of the degrees.  Returns the
 // share's edges (saturated: over the limits the prefix sums mean nothing);
 // S.dmax gets the largest degree of each wave.
-__device__ __forceinline__ int32_t stage_share(SmallLds& S, const int32_t* __restrict__ ids, int32_t n,
-                                               const int64_t* __restrict__ off,
-                                               const int32_t* __restrict__ orig)
+template <int PER>
+__device__ __forceinline__ int32_t stage_entries(SmallLds& S, const int32_t* __restrict__ ids,
+                                                 int32_t n, const int64_t* __restrict__ off,
+                                                 const int32_t* __restrict__ orig)
 {
     const int t = threadIdx.x;
     if (n == 0) {  // uniform
@@ -352,12 +385,12 @@ __device__ __forceinline__ int32_t stage_share(SmallLds& S, const int32_t* __res
         __syncthreads();
         return 0;
     }
-    int64_t a[kStagePer], sum = 0;
-    int32_t d[kStagePer], id[kStagePer];
+    int64_t a[PER], sum = 0;
+    int32_t d[PER], id[PER];
     int32_t mx = 0;
 #pragma unroll
-    for (int m = 0; m < kStagePer; ++m) {
-        const int32_t i = t * kStagePer + m;
+    for (int m = 0; m < PER; ++m) {
+        const int32_t i = t * PER + m;
         const int32_t u = queue_load(ids + (i < n ? i : n - 1));
         a[m] = off[u];
         const int64_t dd = off[u + 1] - a[m];
@@ -365,7 +398,7 @@ __device__ __forceinline__ int32_t stage_share(SmallLds& S, const int32_t* __res
         id[m] = orig ? orig[u] : u;
     }
 #pragma unroll
-    for (int m = 0; m < kStagePer; ++m) {
+    for (int m = 0; m < PER; ++m) {
         sum += d[m];
         mx = d[m] > mx ? d[m] : mx;
     }
@@ -388,8 +421,8 @@ __device__ __forceinline__ int32_t stage_share(SmallLds& S, const int32_t* __res
         R += x;
     }
 #pragma unroll
-    for (int m = 0; m < kStagePer; ++m) {
-        const int32_t i = t * kStagePer + m;
+    for (int m = 0; m < PER; ++m) {
+        const int32_t i = t * PER + m;
         if (i < n) {
             S.cum[i] = c;
             S.uid[i] = id[m];
@@ -400,6 +433,16 @@ __device__ __forceinline__ int32_t stage_share(SmallLds& S, const int32_t* __res
     if (t == 0) S.cum[n] = R;
     __syncthreads();
     return R;
+}
+
+// (two entries a thread where that holds them all: a level's loads are the
+// longer the more there are)
+__device__ __forceinline__ int32_t stage_share(SmallLds& S, const int32_t* __restrict__ ids, int32_t n,
+                                               const int64_t* __restrict__ off,
+                                               const int32_t* __restrict__ orig)
+{
+    return n <= kStageFew ? stage_entries<kStageFew / kSW>(S, ids, n, off, orig)
+                          : stage_entries<kSmallStage / kSW>(S, ids, n, off, orig);
 }
 
 // Edges and largest degree of this workgroup's slice of Q, as a deg slot's
@@ -437,21 +480,20 @@ __device__ __forceinline__ uint32_t slice_limits(SmallLds& S, const int32_t* __r
 }
 
 // The levels; every workgroup returns from it exactly once.  deg slot set 1
-// holds epoch 1, the limits of the first frontier (Qa[0 .. qlen0)).
-template <bool L>
+// holds epoch 1, the limits of the first frontier (Qa[0 .. qlen0)).  ROWS: one
+// lane per edge, in a body of its own (what the other form does between two
+// levels cost the 256 x 256 grid 3% as branches of one body: 620 -> 641 us, apart
+// 609).
+template <bool L, bool ROWS>
 __device__ __forceinline__ void small_levels_body(
     SmallLds& S, int32_t V, const int64_t* __restrict__ off, const int32_t* __restrict__ col,
     const int32_t* __restrict__ orig, uint32_t* __restrict__ vis,
     int32_t* __restrict__ Qa, int32_t* __restrict__ Qb, int32_t* __restrict__ level,
     int32_t* __restrict__ parent, SmallSync* __restrict__ sy, SmallSlots* __restrict__ slots,
     Ctrl* __restrict__ ctrl, int N, int w, int32_t qlen0, int32_t lvl0, int32_t qlimit,
-    int64_t rlimit, int32_t dlimit, int32_t maxdeg)
+    int64_t rlimit, int32_t dlimit, int32_t maxdeg, HubRule hub)
 {
     const int t = threadIdx.x;
-    // one lane per edge: the limits on edges and degrees cannot be exceeded
-    // by a frontier that fits the workgroups' shares
-    const bool rows = maxdeg <= kRowEdges && maxdeg <= dlimit &&
-                      (int64_t)N * kSmallStage * maxdeg <= rlimit;
     uint32_t ep_cnt = 0, ep_deg = 1;
     int32_t qlen = qlen0, lvl = lvl0, step = 0, par = 0, code = 0;
     int64_t my_edges = 0, reached = 0;
@@ -465,7 +507,14 @@ __device__ __forceinline__ void small_levels_body(
         if (w == 0 && t == 0) report(ctrl, 2, qlen0, lvl0, 0, 0, 0);
         return;
     }
-    bool merge = bar.x > kMergeEdges;
+    // No hubs, and ids outside the hot ones: if the graph is symmetric, no id is
+    // pointed at much more often than others either, and claims do not queue
+    // (2^18 ids of mean degree 64 497 -> 269 us, 2^20 810 -> 629, 128 x 128 x 128
+    // lattice 3.37 -> 2.79 ms; 40 x 40 x 40 lattice, all ids hot, merged 8% faster).
+    const bool plain = !ROWS && V > kHotIds && maxdeg <= hub.degree;
+    const int64_t merge_edges = plain && hub.symmetric ? INT64_MAX : kMergeEdges;
+    const bool l1 = L && plain;
+    bool merge = bar.x > merge_edges;
     if (t < 2) S.cnt[t] = 0;
     __syncthreads();
     uint32_t spill0 = 0; // sy->spill before this level: it only grows within a launch
@@ -531,7 +580,7 @@ __device__ __forceinline__ void small_levels_body(
         int32_t* nv_out = S.nv[buf ^ 1];
         auto tile_step = [&]() {
             store_outputs(lvl);
-            claim_edges<L, kSmallEPT>(tv, tu, tok, merge, vis, parent, S.hot, own);
+            claim_edges<L, kSmallEPT>(tv, tu, tok, merge, l1, vis, parent, S.hot, own);
             keep_winners<L, kSmallEPT>(tv, own, V, nv_out, cnt, Qn, &sy->spill, spill0, ctrl);
 #pragma unroll
             for (int j = 0; j < kSmallEPT; ++j) {
@@ -539,7 +588,7 @@ __device__ __forceinline__ void small_levels_body(
                 ou[j] = tu[j];
             }
         };
-        if (local && rows) {
+        if (ROWS && local) {
             for (int32_t i0 = 0; i0 < n; i0 += kRowStep) {
                 if (i0 > 0) load_rows(nv_in, i0);
 #pragma unroll
@@ -559,7 +608,7 @@ __device__ __forceinline__ void small_levels_body(
             const int32_t* __restrict__ Q = par ? Qb : Qa;
             // a frontier that one stage holds is split by edges (every
             // workgroup stages all of it), a larger one by entries
-            const bool split = qlen <= kSmallStage;
+            const bool split = qlen <= kStageFew;
             const int64_t k0 = split ? 0 : (int64_t)qlen * w / N;
             const int64_t k1 = split ? qlen : (int64_t)qlen * (w + 1) / N;
             for (int64_t s0 = k0; s0 < k1; s0 += kSmallStage) {
@@ -591,7 +640,7 @@ __device__ __forceinline__ void small_levels_body(
                           ((uint64_t)ep_cnt << 32) | (flag << 31) | (uint32_t)n);
         if (t == kSW - 1) S.cnt[(step & 1) ^ 1] = 0;  // the next level's, behind a barrier
         // the share's rows and first neighbours, while the others arrive
-        if (rows) {
+        if (ROWS) {
             load_rows(S.nv[buf], 0);
         } else {
             R = stage_share(S, S.nv[buf], n, off, orig);
@@ -605,6 +654,7 @@ __device__ __forceinline__ void small_levels_body(
             }
             if (R > 0 && R <= rlimit) map_small_tile(S, n, R, 0, col, tv, tu, tok);
         }
+        if (merge && l1) drop_l1();
         store_outputs(lvl);
         bar = wait_slots(slots->cnt[ep_cnt & 1], ep_cnt, N, w, kRowStep, S);
         if (!(bar.y & kBarOk)) {
@@ -612,7 +662,7 @@ __device__ __forceinline__ void small_levels_body(
             break;
         }
         const bool over = (bar.y & kBarAny) != 0;
-        bool deal = over || (rows && (bar.y & kBarSkew));
+        bool deal = over || (ROWS && (bar.y & kBarSkew));
         int32_t qn = bar.x, spilled = 0;
         if (over) {
             // (the next spill is behind the barrier of the dealing below)
@@ -634,8 +684,9 @@ __device__ __forceinline__ void small_levels_body(
         bool back = qn > qlimit;
         int32_t pre = -1;
         if (!back && !over) {
-            if (rows) {
-                merge = (int64_t)qn * maxdeg > kMergeEdges * 32;
+            if (ROWS) {
+                const int64_t r = (int64_t)qn * maxdeg;  // at least the level's edges
+                merge = r > kRowMergeEdges || (r > kMergeEdges && 2 * r > V);
             } else {
                 pre = S.pre;
                 __syncthreads();  // S.pre has been read
@@ -646,7 +697,7 @@ __device__ __forceinline__ void small_levels_body(
                 }
                 back = bar.x > rlimit || (bar.y & kBarAny);
                 deal = (bar.y & kBarSkew) != 0;
-                merge = bar.x > kMergeEdges;
+                merge = bar.x > merge_edges;
             }
         }
         if (back || deal) {
@@ -689,7 +740,7 @@ __device__ __forceinline__ void small_levels_body(
                     code = 2;
                     break;
                 }
-                merge = bar.x > kMergeEdges;
+                merge = bar.x > merge_edges;
             }
             local = false;
         } else {
@@ -725,7 +776,7 @@ __global__ __launch_bounds__(kSW) void k_small_levels(
     int32_t* __restrict__ Qa, int32_t* __restrict__ Qb, int32_t* __restrict__ level,
     int32_t* __restrict__ parent, SmallSync* __restrict__ sy, SmallSlots* __restrict__ slots,
     Ctrl* __restrict__ ctrl, Ctrl* __restrict__ h_ctrl, uint64_t seq, int32_t cls, int32_t qlen0, int32_t lvl0, int32_t qlimit,
-    int64_t rlimit, int32_t dlimit, int32_t maxdeg)
+    int64_t rlimit, int32_t dlimit, int32_t maxdeg, HubRule hub)
 {
     if ((int)(blockIdx.x & (kXcdSlices - 1)) != cls) return;
     __shared__ SmallLds S;
@@ -773,12 +824,21 @@ __global__ __launch_bounds__(kSW) void k_small_levels(
             s_go = (a >> 63) ? 0 : (a == one * (uint64_t)N ? 2 : 1);
         }
         __syncthreads();
-        if (s_go == 2)
-            small_levels_body<true>(S, V, off, col, orig, vis, Qa, Qb, level, parent, sy,
-                                    slots, ctrl, N, w, qlen0, lvl0, qlimit, rlimit, dlimit, maxdeg);
-        else if (s_go == 1)
-            small_levels_body<false>(S, V, off, col, orig, vis, Qa, Qb, level, parent, sy,
-                                     slots, ctrl, N, w, qlen0, lvl0, qlimit, rlimit, dlimit, maxdeg);
+        // rows that take one lane per edge: the limits on edges and degrees cannot
+        // be exceeded by a frontier that fits the workgroups' shares
+        const bool rows = maxdeg <= kRowEdges && maxdeg <= dlimit &&
+                          (int64_t)N * kSmallStage * maxdeg <= rlimit;
+#define BFS_SMALL_BODY(L, ROWS)                                                                   \
+    small_levels_body<L, ROWS>(S, V, off, col, orig, vis, Qa, Qb, level, parent, sy, slots, ctrl, \
+                               N, w, qlen0, lvl0, qlimit, rlimit, dlimit, maxdeg, hub)
+        if (s_go == 2) {
+            if (rows) BFS_SMALL_BODY(true, true);
+            else BFS_SMALL_BODY(true, false);
+        } else if (s_go == 1) {
+            if (rows) BFS_SMALL_BODY(false, true);
+            else BFS_SMALL_BODY(false, false);
+        }
+#undef BFS_SMALL_BODY
     } else if (w == 0 && t == 0) {
         not_run();
     }
@@ -834,7 +894,7 @@ hipError_t launch_small_levels(hipStream_t s, int wgs, int cls, int32_t V, const
                                int32_t* Qa, int32_t* Qb, int32_t* level,
                                int32_t* parent, SmallSync* sy, uint32_t* slot_words, Ctrl* ctrl,
                                Ctrl* h_ctrl, uint64_t seq, int32_t qlen, int32_t lvl, int32_t qlimit, int64_t rlimit,
-                               int32_t dlimit, int32_t maxdeg)
+                               int32_t dlimit, int32_t maxdeg, HubRule hub)
 {
     // An ordinary launch: the workgroups that take part are few enough to be
     // resident at once, and a cooperative launch would make the runtime stop
@@ -843,7 +903,7 @@ hipError_t launch_small_levels(hipStream_t s, int wgs, int cls, int32_t V, const
     hipLaunchKernelGGL(k_small_levels, dim3(wgs * kXcdSlices), dim3(kSW), 0, s, V, off, col, orig,
                        vis, Qa, Qb, level, parent, sy,
                        reinterpret_cast<SmallSlots*>(slot_words), ctrl, h_ctrl, seq, cls, qlen,
-                       lvl, qlimit, rlimit, dlimit, maxdeg);
+                       lvl, qlimit, rlimit, dlimit, maxdeg, hub);
     return hipGetLastError();
 }
 
