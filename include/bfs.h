@@ -81,12 +81,19 @@ extern "C" {
 #define BFS_OPT_GRID_WGS         5 /* workgroups per CU for grid-stride kernels */
 #define BFS_OPT_PROFILE          6 /* 1: time each kernel class with HIP events
                                       (fills the *_ms fields of bfs_stats)    */
-#define BFS_OPT_VISITED_SUMMARY  7 /* before heavy levels, summarise the visited
-                                      bitmap so the expansion's early visited
-                                      test skips most bitmap loads:
-                                      0 off, 1 fully visited id prefix,
-                                      2 (default) prefix + one LDS bit per
-                                      fully visited block of ids              */
+#define BFS_OPT_VISITED_SUMMARY  7 /* degree-ordered graphs, and graphs of 2^32
+                                      edges and more: before heavy levels,
+                                      summarise the visited bitmap so the
+                                      expansion's early visited test skips
+                                      most bitmap loads: 0 off, 1 fully
+                                      visited id prefix, 2 (default) prefix +
+                                      one LDS bit per fully visited block of
+                                      ids (below 2^25 vertices only at levels
+                                      whose frontier came as a list).  Other
+                                      graphs: only levels after the bottom-up
+                                      steps of BFS_OPT_DIRECTION use it; on
+                                      the rest it paid for no launch of its
+                                      own                                     */
 #define BFS_OPT_ROW_SKIP         8 /* degree-ordered graphs: 1 (default) lets a
                                       heavy level's degree scan drop each
                                       frontier row's leading block of edges
@@ -133,12 +140,18 @@ extern "C" {
                                       visited and 0 for the others.  Levels
                                       whose next frontier is
                                       a list always claim with atomicOr.
+                                      Graphs without degree order claim with
+                                      atomicOr in every mode where they have
+                                      2^32 edges or more or are searched with
+                                      BFS_OPT_DIRECTION (the flags share an
+                                      array with the degrees, which those
+                                      searches scan).
                                       Every mode gives the same levels and
                                       valid parents                          */
 #define BFS_OPT_XCD_SLICES      15 /* degree-ordered graphs: 1 (default) runs the
                                       early host-driven levels of graphs with
                                       at least 2^20 vertices (frontier and
-                                      visited set both at most V/64) as XCD-
+                                      visited set both at most V/8) as XCD-
                                       sliced levels: the ids are dealt to 8
                                       slices by 1024-id blocks (one line of
                                       the visited bitmap each), every row is

@@ -2,8 +2,10 @@
 
 Spaces:
   single    -- edges per thread (the expansion's tile: 256 * EPT edges), the
-               visited-summary mode, workgroups per CU, and the largest
-               frontier the persistent small-level loop runs;
+               visited-summary mode (without degree order, below 2^32 edges,
+               both modes run the same kernels: pass a space without it),
+               workgroups per CU, and the largest frontier the persistent
+               small-level loop runs;
   direction -- the alpha / beta switch thresholds of the direction-optimizing
                mode;
   batch     -- the multi-source batch's tile (edges per workgroup).

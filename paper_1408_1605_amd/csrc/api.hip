@@ -1,5 +1,5 @@
 // C ABI: errors, workspace layout, graph handles and the single-root search
-// driver (host-driven level loop, one 64-byte control read-back per level).
+// driver (host-driven level loop, one read-back of the control block per level).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -719,8 +719,7 @@ int run_host_loop(bfs_graph* g, int32_t root, int32_t* levels, int32_t* parents,
                 BFS_HIP_TRY(launch_summary_bits(s, sum_grid, g->V, g->W, g->vis, g->summary_shift,
                                                 g->summary_blocks, g->summary));
         } else if (use_sum) {
-            const int gs = std::max(1, std::min(grid_cap, (g->summary_blocks + 31) / 32));
-            BFS_HIP_TRY(launch_visited_summary(s, gs, g->V, g->W, g->vis, g->summary_shift,
+            BFS_HIP_TRY(launch_visited_summary(s, sum_grid, g->V, g->W, g->vis, g->summary_shift,
                                                g->summary_blocks, g->summary, g->ctrl,
                                                old_left ? g->vis_old : nullptr));
             old_left = false;

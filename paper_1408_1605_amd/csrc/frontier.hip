@@ -827,7 +827,7 @@ __global__ __launch_bounds__(kWG) void k_expand(int32_t V, const int64_t* __rest
         for (int j = 0; j < EPT; ++j) need[j] = !known[j] && !(wd[j] & (1u << (vv[j] & 31)));
         if (flags) {
             // A bitmap level needs no exactly-once claim: its next frontier is
-            // the set of flagged vertices, taken by k_bitmap_to_queue.  A
+            // the set of flagged vertices, taken by the compaction.  A
             // vertex not visited before the level gets its flag byte set
             // (byte stores never disturb neighbouring flags, so no atomic is
             // needed) and a parent from the frontier; when several threads
@@ -1133,7 +1133,9 @@ hipError_t launch_list_scan(hipStream_t s, const int32_t* Q, int32_t qlen, const
                             int32_t W, const uint32_t* vis, uint32_t* vis_old)
 {
     if (qlen < 1) return hipErrorInvalidValue;
-    // short lists one entry per thread, so that they spread over the chip
+    // short lists one entry per thread, so that they spread over the chip (one
+    // entry against eight, lists of a plain graph: 2^15 155 / 163 us a search, 2^16
+    // 165 / 168, 98,304 184 / 183, 2^17 193 / 188, 2^20 707 / 614)
     const int items = qlen <= (1 << 16) ? 1 : 8;
     unsigned grid = (unsigned)(((int64_t)qlen + kWG * items - 1) / (kWG * items));
     // a short list of a large graph: workgroups that only copy the bitmap, 8

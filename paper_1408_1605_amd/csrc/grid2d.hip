@@ -316,9 +316,14 @@ __global__ __launch_bounds__(kWG) void k2_gather(const Plan* __restrict__ plp,
     gather_units(*plp, dst, fbm, af, ctl);
 }
 
-// k2_plan and k2_gather in one launch, for levels of few units: every
-// workgroup reads the plan from its kernel argument.
+// k2_plan and k2_gather in one launch: every workgroup reads the plan from its
+// kernel argument.  That saves a launch at any size (2 x 4 R-MAT 14 253 -> 234 us, 16
+// 295 -> 275; 8 x 8 R-MAT 22 2,230 -> 2,212 if every level did), so the line only
+// keeps the plan's 4 KB from being read by hundreds of workgroups.
 constexpr int kFewUnits = 16;
+// Levels of up to so many entries (all processors' together) are scanned one entry
+// a thread (one entry against eight: 2 x 4 stars of 2^14 leaves 200 / 205 us, of 2^16
+// 233 / 225, of 2^18 335 / 281; R-MAT 16 389 / 400, 18 353 / 354, 20 635 / 602).
 constexpr int64_t kFewEntries = 1 << 16;
 __global__ __launch_bounds__(kWG) void k2_plan_gather(Plan p, Plan* __restrict__ out,
                                                       const int32_t* __restrict__ dst,

@@ -33,7 +33,11 @@ namespace bfsmi {
 // graphs no level is: a finalize that writes every vertex's frontier mask costs
 // less there than the launch that clears the old ones and the atomics that
 // mark what was found (5 roots, plain graph of 50,021 vertices, with the
-// finalize's smaller chunks 280 -> 219 us; 64 roots, R-MAT 16 352 -> 322).
+// finalize's smaller chunks 280 -> 219 us; 64 roots, R-MAT 16 352 -> 322).  Sparse
+// against dense at 2^18 vertices: 5 roots of a plain R-MAT 335 / 318 us, a 512 x 512
+// grid by level kernels 19.3 / 18.4 ms; sparse levels pay from 2^21 on, on deep
+// graphs (1448 x 1448 51.7 / 57.9 ms, a binary tree of 2^23 ids 2.21 / 2.29; R-MAT 23
+// 4.40 / 4.33).
 constexpr int32_t kMsDenseV = 1 << 18;
 __host__ __device__ constexpr int32_t ms_sparse_limit(int32_t V)
 {
@@ -477,7 +481,9 @@ __global__ __launch_bounds__(kWG) void k_ms_expand(const int64_t* __restrict__ r
 }
 
 // Vertices per thread and chunk in the finalize: two on small graphs, whose
-// chunks would else keep a tenth of the chip busy.
+// chunks would else keep a tenth of the chip busy (eight against two, 5 and 64
+// roots of a plain R-MAT: 2^14 222 / 181, 343 / 236 us, 2^17 291 / 257, 590 / 476;
+// the curves cross between 2^18, 320 / 301, and 2^19, 471 / 492).
 constexpr int kFinItems = 8, kFinItemsSmall = 2;
 constexpr int32_t kFinSmallV = 1 << 17;
 
