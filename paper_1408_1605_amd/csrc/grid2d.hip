@@ -322,8 +322,8 @@ __global__ __launch_bounds__(kWG) void k2_gather(const Plan* __restrict__ plp,
 // keeps the plan's 4 KB from being read by hundreds of workgroups.
 constexpr int kFewUnits = 16;
 // Levels of up to so many entries (all processors' together) are scanned one entry
-// a thread (one entry against eight: 2 x 4 stars of 2^14 leaves 200 / 205 us, of 2^16
-// 233 / 225, of 2^18 335 / 281; R-MAT 16 389 / 400, 18 353 / 354, 20 635 / 602).
+// a thread (one entry against eight, 2 x 4: a root with 2^14 children 200 / 205 us, 2^16
+// 233 / 225, 2^18 335 / 281; R-MAT 16 389 / 400, 18 353 / 354, 20 635 / 602).
 constexpr int64_t kFewEntries = 1 << 16;
 __global__ __launch_bounds__(kWG) void k2_plan_gather(Plan p, Plan* __restrict__ out,
                                                       const int32_t* __restrict__ dst,
