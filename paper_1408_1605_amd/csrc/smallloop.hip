@@ -58,13 +58,13 @@ namespace bfsmi {
 constexpr int kSW = 512;           // threads per workgroup (8 waves)
 constexpr int kSmallEPT = 2;
 constexpr int kSmallTile = kSW * kSmallEPT;
-// Frontier entries per workgroup and pass: 32 workgroups hold the largest
-// frontier there is (with 1024, frontiers from 32K vertices on were dealt out
-// again: 4,096 hubs of 15 leaves 178 -> 156 us, 64 of 1,000 126 -> 105).  A
-// thread takes two of up to kStageFew, else four (with four always, R-MAT 12
-// 75 -> 80 us, 30 x 30 x 30 lattice 252 -> 284).
-constexpr int kSmallStage = 2048;
-constexpr int kStageFew = 1024;
+// Frontier entries per workgroup and pass.  (2048 would hold every frontier that
+// the loop takes, and frontiers from 32K vertices on would not be dealt out
+// again: 4,096 hubs of 15 leaves 178 -> 153 us.  But with 58 KB of LDS instead of 34
+// the workgroups of concurrent searches wait for each other: twelve threads
+// searching R-MAT 16 80 -> 165 us a search.)
+constexpr int kSmallStage = 1024;
+constexpr int kStagePer = kSmallStage / kSW;
 constexpr int kRowEdges = 4;       // rows of at most this many edges: one lane per edge
 constexpr int kRowStep = kSmallTile / kRowEdges;  // such rows per step
 constexpr uint32_t kStartCap = 1u << 14;  // polls before a launch is called off
@@ -80,7 +80,7 @@ constexpr int64_t kRowMergeEdges = 1 << 16;
 constexpr int kHotIds = 1 << 16;  // ids below this are merged
 // Edge counts saturate, per thread and per share, above every limit the host
 // passes (at most 8192 edges per workgroup).
-constexpr int64_t kDegSat = 1 << 20, kEdgeSat = 1 << 24;
+constexpr int64_t kDegSat = 1 << 22, kEdgeSat = 1 << 24;
 static_assert((int64_t)kSmallMaxWGs * 8192 < kDegSat, "a saturated count is over the limit");
 
 // Barrier words, one per workgroup, in two sets used in turn: a workgroup
@@ -370,14 +370,13 @@ __device__ __forceinline__ void map_small_tile(SmallLds& S, int32_t n, int32_t R
     }
 }
 
-// Stages entries ids[0..n), n <= PER * kSW, PER consecutive ones per thread:
+// Stages entries ids[0..n), n <= kSmallStage, kStagePer consecutive ones per thread:
 // row starts, caller ids and the prefix sum of the degrees.  Returns the
 // share's edges (saturated: over the limits the prefix sums mean nothing);
 // S.dmax gets the largest degree of each wave.
-template <int PER>
-__device__ __forceinline__ int32_t stage_entries(SmallLds& S, const int32_t* __restrict__ ids,
-                                                 int32_t n, const int64_t* __restrict__ off,
-                                                 const int32_t* __restrict__ orig)
+__device__ __forceinline__ int32_t stage_share(SmallLds& S, const int32_t* __restrict__ ids, int32_t n,
+                                               const int64_t* __restrict__ off,
+                                               const int32_t* __restrict__ orig)
 {
     const int t = threadIdx.x;
     if (n == 0) {  // uniform
@@ -385,12 +384,12 @@ __device__ __forceinline__ int32_t stage_entries(SmallLds& S, const int32_t* __r
         __syncthreads();
         return 0;
     }
-    int64_t a[PER], sum = 0;
-    int32_t d[PER], id[PER];
+    int64_t a[kStagePer], sum = 0;
+    int32_t d[kStagePer], id[kStagePer];
     int32_t mx = 0;
 #pragma unroll
-    for (int m = 0; m < PER; ++m) {
-        const int32_t i = t * PER + m;
+    for (int m = 0; m < kStagePer; ++m) {
+        const int32_t i = t * kStagePer + m;
         const int32_t u = queue_load(ids + (i < n ? i : n - 1));
         a[m] = off[u];
         const int64_t dd = off[u + 1] - a[m];
@@ -398,7 +397,7 @@ __device__ __forceinline__ int32_t stage_entries(SmallLds& S, const int32_t* __r
         id[m] = orig ? orig[u] : u;
     }
 #pragma unroll
-    for (int m = 0; m < PER; ++m) {
+    for (int m = 0; m < kStagePer; ++m) {
         sum += d[m];
         mx = d[m] > mx ? d[m] : mx;
     }
@@ -421,8 +420,8 @@ __device__ __forceinline__ int32_t stage_entries(SmallLds& S, const int32_t* __r
         R += x;
     }
 #pragma unroll
-    for (int m = 0; m < PER; ++m) {
-        const int32_t i = t * PER + m;
+    for (int m = 0; m < kStagePer; ++m) {
+        const int32_t i = t * kStagePer + m;
         if (i < n) {
             S.cum[i] = c;
             S.uid[i] = id[m];
@@ -433,16 +432,6 @@ __device__ __forceinline__ int32_t stage_entries(SmallLds& S, const int32_t* __r
     if (t == 0) S.cum[n] = R;
     __syncthreads();
     return R;
-}
-
-// (two entries a thread where that holds them all: a level's loads are the
-// longer the more there are)
-__device__ __forceinline__ int32_t stage_share(SmallLds& S, const int32_t* __restrict__ ids, int32_t n,
-                                               const int64_t* __restrict__ off,
-                                               const int32_t* __restrict__ orig)
-{
-    return n <= kStageFew ? stage_entries<kStageFew / kSW>(S, ids, n, off, orig)
-                          : stage_entries<kSmallStage / kSW>(S, ids, n, off, orig);
 }
 
 // Edges and largest degree of this workgroup's slice of Q, as a deg slot's
@@ -608,7 +597,7 @@ __device__ __forceinline__ void small_levels_body(
             const int32_t* __restrict__ Q = par ? Qb : Qa;
             // a frontier that one stage holds is split by edges (every
             // workgroup stages all of it), a larger one by entries
-            const bool split = qlen <= kStageFew;
+            const bool split = qlen <= kSmallStage;
             const int64_t k0 = split ? 0 : (int64_t)qlen * w / N;
             const int64_t k1 = split ? qlen : (int64_t)qlen * (w + 1) / N;
             for (int64_t s0 = k0; s0 < k1; s0 += kSmallStage) {
